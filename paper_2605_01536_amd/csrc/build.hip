@@ -176,6 +176,7 @@ __global__ void k_karras(const uint64_t* __restrict__ keys, int n, Node* __restr
     int right = (max(i, j) == gamma + 1) ? ~(gamma + 1) : gamma + 1;
     nodes[i].link.x = left;
     nodes[i].link.y = right;
+    nodes[i].link.w = j;   // the other end of the node's leaf range (i is one)
     if (left >= 0) nodes[left].link.z = i;
     else leaf_parent[~left] = i;
     if (right >= 0) nodes[right].link.z = i;
@@ -200,11 +201,17 @@ __device__ __forceinline__ void write_slot(Node* nodes, int parent, int child, c
 }
 
 // Bottom-up refit: each leaf writes its box into its parent's child slot; the
-// second thread to reach a node merges both slots and continues upward.
-__global__ void k_refit(const TriQ* __restrict__ tris, int n, Node* nodes, const int* __restrict__ leaf_parent,
-                        int* flags) {
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n || n < 2) return;
+// second thread to reach a node merges both slots and continues upward.  A node
+// whose leaves all belong to one workgroup (all but about 1 in 200) is settled there:
+// its arrival count is in LDS and its boxes pass through the workgroup's own cache.
+// Only the nodes above cross workgroups and need fences of the whole device, which
+// write back and invalidate an XCD's L2: with those at every node the refit took
+// 2.2 ms for 312,000 triangles (7.7 ms for 1.05M).
+constexpr int kRefitThreads = 1024, kRefitLeaves = 4096;
+
+__device__ __forceinline__ void refit_leaf(const TriQ* __restrict__ tris, int n, Node* nodes,
+                                           const int* __restrict__ leaf_parent, int* flags, int t, int t0, int t1,
+                                           int* inside) {
     TriQ q = tris[t];
     int b[6] = {min(q.a.x, min(q.b.x, q.c.x)), max(q.a.x, max(q.b.x, q.c.x)),
                 min(q.a.y, min(q.b.y, q.c.y)), max(q.a.y, max(q.b.y, q.c.y)),
@@ -217,21 +224,51 @@ __global__ void k_refit(const TriQ* __restrict__ tris, int n, Node* nodes, const
             return;
         }
         write_slot(nodes, parent, child, b);
-        __threadfence();
-        if (atomicAdd(flags + parent, 1) == 0) return;
-        __threadfence();
+        const int other = nodes[parent].link.w;   // written before this kernel
+        const bool local = min(parent, other) >= t0 && max(parent, other) < t1;
+        if (local) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            const int before = __hip_atomic_fetch_add(&inside[parent - t0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (before == 0) return;
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        } else {
+            __threadfence();
+            if (atomicAdd(flags + parent, 1) == 0) return;
+            __threadfence();
+        }
         const int* L = &nodes[parent].lxy.x;
         const int* R = &nodes[parent].rxy.x;
         const int* Z = &nodes[parent].z.x;
-        b[0] = min(ld_acq(L + 0), ld_acq(R + 0));
-        b[1] = max(ld_acq(L + 1), ld_acq(R + 1));
-        b[2] = min(ld_acq(L + 2), ld_acq(R + 2));
-        b[3] = max(ld_acq(L + 3), ld_acq(R + 3));
-        b[4] = min(ld_acq(Z + 0), ld_acq(Z + 2));
-        b[5] = max(ld_acq(Z + 1), ld_acq(Z + 3));
+        if (local) {
+            const int4 l = *(const int4*)L, r = *(const int4*)R, z = *(const int4*)Z;
+            b[0] = min(l.x, r.x);
+            b[1] = max(l.y, r.y);
+            b[2] = min(l.z, r.z);
+            b[3] = max(l.w, r.w);
+            b[4] = min(z.x, z.z);
+            b[5] = max(z.y, z.w);
+        } else {
+            b[0] = min(ld_acq(L + 0), ld_acq(R + 0));
+            b[1] = max(ld_acq(L + 1), ld_acq(R + 1));
+            b[2] = min(ld_acq(L + 2), ld_acq(R + 2));
+            b[3] = max(ld_acq(L + 3), ld_acq(R + 3));
+            b[4] = min(ld_acq(Z + 0), ld_acq(Z + 2));
+            b[5] = max(ld_acq(Z + 1), ld_acq(Z + 3));
+        }
         child = parent;
         parent = ld_acq(&nodes[parent].link.z);
     }
+}
+
+__global__ __launch_bounds__(kRefitThreads) void k_refit(const TriQ* __restrict__ tris, int n, Node* nodes,
+                                                        const int* __restrict__ leaf_parent, int* flags) {
+    __shared__ int inside[kRefitLeaves];   // arrivals at node t0 + k, for nodes within the workgroup's leaves
+    if (n < 2) return;
+    const int t0 = blockIdx.x * kRefitLeaves, t1 = min(t0 + kRefitLeaves, n);
+    for (int k = threadIdx.x; k < kRefitLeaves; k += kRefitThreads) inside[k] = 0;
+    __syncthreads();
+    for (int t = t0 + (int)threadIdx.x; t < t1; t += kRefitThreads)
+        refit_leaf(tris, n, nodes, leaf_parent, flags, t, t0, t1, inside);
 }
 
 __global__ void k_depth(int n, const Node* __restrict__ nodes, const int* __restrict__ leaf_parent, int* depth) {
@@ -436,13 +473,16 @@ __global__ void k_weld_heads(const float* __restrict__ vz, int64_t vs, int64_t n
     head[j] = h ? (int)j : 0;
 }
 
-__global__ void k_weld_map(const int* __restrict__ idx, const int* __restrict__ start, int64_t nv,
-                           int* __restrict__ remap, int* __restrict__ nunique) {
-    const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (j >= nv) return;
-    const int s = start[j];
-    remap[idx[j]] = idx[s];   // the stable sort keeps the smallest index first in a run
-    if (s == (int)j) atomicAdd(nunique, 1);
+__global__ __launch_bounds__(kThreads) void k_weld_map(const int* __restrict__ idx, const int* __restrict__ start,
+                                                      int64_t nv, int* __restrict__ remap, int* __restrict__ nunique) {
+    int heads = 0;
+    for (int64_t j0 = blockIdx.x * (int64_t)kThreads; j0 < nv; j0 += (int64_t)gridDim.x * kThreads) {
+        const int64_t j = j0 + threadIdx.x;
+        const int s = j < nv ? start[j] : -1;
+        if (j < nv) remap[idx[j]] = idx[s];   // the stable sort keeps the smallest index first in a run
+        heads += __syncthreads_count(j < nv && s == (int)j);
+    }
+    if (threadIdx.x == 0) atomicAdd(nunique, heads);   // one per workgroup: they all meet at one address
 }
 
 __global__ void k_weld_tris(const int32_t* __restrict__ tri, int64_t n3, const int* __restrict__ remap,
@@ -589,7 +629,7 @@ gwn_status build_mesh(const float* vx, const float* vy, const float* vz, int64_t
         GWN_HIP_TRY(with_temp(S, scan_temp_bytes(nv), [&](void* tmp) {
             return scan_inclusive_max(head, start, nv, tmp, st);
         }));
-        k_weld_map<<<nblocks(nv), kThreads, 0, st>>>(idx3, start, nv, remap, nuq);
+        k_weld_map<<<std::min(nblocks(nv), 1024), kThreads, 0, st>>>(idx3, start, nv, remap, nuq);
         GWN_HIP_TRY(hipGetLastError());
         k_weld_tris<<<nblocks(3 * nf), kThreads, 0, st>>>(tri, 3 * nf, remap, triw);
         GWN_HIP_TRY(hipGetLastError());
@@ -665,7 +705,7 @@ gwn_status build_mesh(const float* vx, const float* vy, const float* vz, int64_t
             GWN_HIP_TRY(hipMemsetAsync(depth, 0, sizeof(int), st));
             k_karras<<<nblocks(nf - 1), kThreads, 0, st>>>(keys2, (int)nf, m->nodes, leaf_parent);
             GWN_HIP_TRY(hipGetLastError());
-            k_refit<<<nblocks(nf), kThreads, 0, st>>>(m->tris, (int)nf, m->nodes, leaf_parent, rflags);
+            k_refit<<<(unsigned)((nf + kRefitLeaves - 1) / kRefitLeaves), kRefitThreads, 0, st>>>(m->tris, (int)nf, m->nodes, leaf_parent, rflags);
             GWN_HIP_TRY(hipGetLastError());
             k_depth<<<nblocks(nf), kThreads, 0, st>>>((int)nf, m->nodes, leaf_parent, depth);
             GWN_HIP_TRY(hipGetLastError());
