@@ -68,6 +68,8 @@ void release(gwn_mesh_s* m) {
     (void)hipFree(m->trif);
     (void)hipFree(m->bverts);
     (void)hipFree(m->loop_off);
+    (void)hipFree(m->chain);
+    (void)hipFree(m->cbox);
     delete m;
 }
 

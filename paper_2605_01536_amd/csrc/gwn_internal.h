@@ -37,6 +37,14 @@ struct alignas(32) BVert {
     int loop;
 };
 
+// The boundary again as chunks of kChunk chained vertices (see k_emit_chain in
+// build.hip): entry e of a chunk leads to entry e + 1 where pad1 & kChainEdge.
+// A long loop is cut every kChunk - 1 edges, loops (or their ends) of at most
+// three edges share a chunk in pairs; loops follow each other in Morton order, so
+// a chunk is small.  Entries past a piece's end repeat a vertex, without an edge.
+constexpr int kChunk = 8;
+constexpr int kChainEdge = 1, kChainValid = 2, kChainTri = 4;   // kChainTri: first vertex of a loop of three edges
+
 // Fixed-point grid parameters: q = rint((x - lo) * scale), scale = 2^k.
 struct QGrid {
     double lo[3];
@@ -51,6 +59,9 @@ struct MeshView {
     const TriQ* tris;
     const BVert* bverts;
     const int* loop_off;   // nloops + 1 offsets into bverts
+    const BVert* chain;    // kChunk vertices per chunk
+    const int4* cbox;      // per chunk: quantised xlo, xhi, ylo, yhi
+    int nchunk;
     int nloops;
     int nf;
     int root;              // >= 0 internal node, < 0 leaf ~t, INT_MIN when nf == 0
@@ -59,6 +70,16 @@ struct MeshView {
 };
 
 constexpr int kNoRoot = (int)0x80000000;
+
+// A cell-centred grid in the mesh frame; one wave per (column, z-chunk).
+struct GridArgs {
+    double o[3], s[3];
+    long long nx, ny, nz;
+    long long nchunks;   // z-chunks per column
+    long long nwaves;    // columns * nchunks
+    long long wave0;     // first wave of this launch (large grids take several)
+    long long st[3];     // output strides of the frame's x, y, z indices (world z fastest)
+};
 
 // A mesh built along axis a works in the frame (X, Y, Z) = (x, y, z), (y, z, x)
 // or (z, x, y) for a = 0 (z), 1 (x), 2 (y): a cyclic permutation, i.e. a

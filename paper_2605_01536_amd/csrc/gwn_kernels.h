@@ -182,16 +182,25 @@ __device__ __forceinline__ T wave_lane(T x, int l) {
 // fix-up and only the short-range polynomial.  Where ZB samples share one
 // column's x/y (grids), N1 N2 is the column's and the product costs three
 // operations per sample instead of a second reciprocal and arctangent.  FP32
-// offsets are in units of 2^16 cells (an exact scale that keeps products of two
-// D below 2^68), and D <= 2^-50 of those units takes the single-edge path
-// (products stay normal).
+// offsets are in units of 2^18 cells (an exact scale), and D <= 2^-50 of those
+// units takes the single-edge path (products stay normal).
+//
+// On grids four edges with |N| < tan(pi/32) D each, decided by the column's x/y
+// terms alone, take one arctangent likewise: the product of two pairs costs four
+// more operations per sample and saves a reciprocal and a polynomial (ten).  That
+// needs D^4 in FP32's range: with the samples within 2^32 cells of the box in z
+// (quad_z) an offset is below 2^15 units and D below 2^30, and the x/y bound
+// D > dot > kQuadDot = 2^-20 keeps the product above 2^-80.
 template <class T, int ZB, bool FAR>
 struct EdgePairs {
     static constexpr bool on = !FAR;
     static constexpr bool f32 = std::is_same<T, float>::value;
-    static constexpr float kUnit = on && f32 ? 0x1p-16f : 1.0f;   // cell units per offset unit
+    static constexpr float kUnit = on && f32 ? 0x1p-18f : 1.0f;   // cell units per offset unit
     static constexpr float kInvTan = 5.02734f;                     // 1 / tan(pi/16), rounded up
+    static constexpr float kInvTan4 = 10.15318f;                   // 1 / tan(pi/32), rounded up
     static constexpr float kMinD = 0x1p-50f;
+    static constexpr float kQuadDot = 0x1p-20f;
+    static constexpr float kTan8 = 0.41421354f;                    // just below tan(pi/8)
 };
 
 template <class T, int ZB, bool FAR>
@@ -285,6 +294,10 @@ __device__ __forceinline__ void edge_step(const ColV<T>& a, const ColV<T>& b, co
 // in its units.
 __device__ __forceinline__ bool near_z(float pz, const QGrid& g) {
     return fabs(((double)pz - g.lo[2]) * g.scale) <= 0x1p40;
+}
+
+__device__ __forceinline__ bool quad_z(float pz, const QGrid& g) {
+    return fabs(((double)pz - g.lo[2]) * g.scale) <= 0x1p32;
 }
 
 // Edges a -> b -> c for ZB samples: as one pair where allowed, else one by one.
@@ -475,17 +488,22 @@ __device__ __forceinline__ void boundary_loops(const MeshView& mv, int qqx, int 
 // ---------------------------------------------------------------- grid columns
 // In a grid column every sample shares x and y, so a boundary vertex's x/y
 // terms (rho^2, and N, the x/y dot and the pair bound of its outgoing edge) are
-// the same for the whole wave.  They are computed for 64 boundary vertices at a
-// time, one vertex per lane, into a ring of records in LDS that every lane then
-// reads at the same address (a broadcast): a wave instruction's worth of x/y
-// work per vertex becomes one lane's.  The same pass counts each vertex's
-// blocks with a sample below it (R, see the sample blocks note), and whether its outgoing
-// edge pairs on its x/y terms alone becomes a bit of a wave mask.
+// the same for the whole wave.  They are computed for 64 chained vertices (8
+// chunks of the boundary) at a time, one vertex per lane, into records in LDS
+// that every lane then reads at the same address (a broadcast): a wave
+// instruction's worth of x/y work per vertex becomes one lane's.  What the x/y terms
+// settle for all samples at once becomes bits of wave masks: whether the outgoing
+// edge can share an arctangent, and whether the vertex is in the FARV case:
+// every sample below it has r_z^2 <= 3 rho^2, where s = l - r_z = t - 2 max(r_z, 0)
+// loses at most ~16 ulps to cancellation (its rounding error is ~2 u l, and
+// s = rho^2 / (l + r_z) >= l / 8 there) and needs no reciprocal.  Between two chunks, and past a piece's end, stands an edge
+// with N = 0 and x/y dot 1 (offset units squared): its D is positive whatever its
+// vertices, so it adds an angle of 0 through the same instructions as any edge.
 template <class T>
 struct alignas(4 * sizeof(T)) ColRec {
     T zu;     // vertex z in offset units
     T rho2;   // r_x^2 + r_y^2 from the column
-    T N;      // N of the outgoing edge (to the next vertex of the loop)
+    T N;      // N of the outgoing edge (to the next vertex of the chunk)
     T dot;    // r_a,x r_b,x + r_a,y r_b,y of the outgoing edge
 };
 
@@ -496,107 +514,117 @@ struct ColAux {   // read on the rare paths only
     int dx, dy;
 };
 
-constexpr int kColRing = 128;   // slots per wave; slot kColRing holds the loop's first vertex
+constexpr int kColRing = 128;   // slots of the gradient's ring per wave
+constexpr int kColChunks = 8;   // chunks per fill
+constexpr int kColRecs = kColChunks * kChunk;
+static_assert(kColRecs == 64, "one lane per record");
 
 template <class T>
-struct ColRing {
-    ColRec<T> rec[kColRing + 1];
-    ColAux<T> aux[kColRing + 1];
-    int R[kColRing + 1];   // block count R of the vertex, plus 256 in the FARV case (see the sample blocks note, s_blocks)
+struct ColBuf {
+    ColRec<T> rec[kColRecs];
+    ColAux<T> aux[kColRecs];
+    int queue[64 + kColChunks];   // chunks waiting for a fill
 };
 
-// Records of vertices v0 .. v0 + n - 1 (n <= 64) of the loop [b0, b1), into the
-// ring slots (v0 - b0) mod kColRing; v0 - b0 is a multiple of 64, so they fill
-// one half.  The first call of a loop (v0 == b0) also keeps its first vertex in
-// slot kColRing.  bminr[r]: block r's smallest z in offset units (see the sample blocks note).
-// Bit k of mk: the edge leaving the half's slot k pairs on its x/y terms alone.
+// Which chunks a column sums (see gwn_far.h): all of them, those near its block
+// of columns, or those far from the block but not from the block's parent.  Far
+// from a block: the chunk's box and the block are at least thr cells apart in x
+// or in y.
+struct ChunkFilter {
+    enum Mode { kAll, kNear, kRing } mode;
+    int2 x, y;        // the block's quantised x and y ranges
+    int thr;
+    int2 px, py;      // its parent's (kRing; pthr < 0: no parent)
+    int pthr;
+};
+
+__device__ __forceinline__ bool chunk_far(const int4& b, const int2& x, const int2& y, int thr) {
+    return max(max(b.x - x.y, x.x - b.y), max(b.z - y.y, y.x - b.w)) >= thr;
+}
+
+__device__ __forceinline__ bool chunk_kept(const int4& b, const ChunkFilter& f) {
+    const bool far = chunk_far(b, f.x, f.y, f.thr);
+    if (f.mode == ChunkFilter::kNear) return !far;
+    return far && !(f.pthr >= 0 && chunk_far(b, f.px, f.py, f.pthr));
+}
+
+// the wave reads what its own lanes wrote; LDS operations of a wave complete in order
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Records of the chunks queue[0 .. n) (n <= 8), record k = 8 c + e for entry e of
+// chunk c.  zmin: the samples' smallest z in offset units.  Bit k of m2 (m4): the edge
+// leaving record k can be one of a pair (of four) on its x/y terms alone; of mf: its
+// vertex is in the FARV case; of mt: it starts a loop of three edges.
 template <class T, int ZB>
-__device__ __forceinline__ void col_fill(const MeshView& mv, int v0, int n, int b0, int b1, int qqx, int qqy,
-                                         const T* bminr, bool asc, bool pairs, ColRing<T>& ring,
-                                         unsigned long long& mk) {
+__device__ __forceinline__ void col_fill(const MeshView& mv, const int* queue, int n, int qqx, int qqy, T zmin,
+                                         bool pairs, bool quads, ColBuf<T>& buf, unsigned long long& m2,
+                                         unsigned long long& m4, unsigned long long& mf, unsigned long long& mt) {
     using P = EdgePairs<T, ZB, false>;
     constexpr T u = (T)P::kUnit;
     int lane = (int)(threadIdx.x & 63);
-    // Opaque to the optimiser (no instruction is emitted): the ring addresses
+    // Opaque to the optimiser (no instruction is emitted): the record addresses
     // derived from the lane are then formed here, once per fill, instead of
     // being hoisted out of the boundary loops and held (or spilled) throughout.
     asm volatile("" : "+v"(lane));
-    bool e = false;
-    int R = 0;
-    if (lane < n) {
-        const int v = v0 + lane;
-        const int vn = v + 1 < b1 ? v + 1 : b0;
-        const BVert a = mv.bverts[v], b = mv.bverts[vn];
+    const int c = lane >> 3, en = lane & 7;
+    bool e = false, e4 = false, ef = false, et = false;
+    if (c < n) {
+        const BVert* v = mv.chain + (size_t)queue[c] * kChunk;
+        const BVert a = v[en], b = v[min(en + 1, kChunk - 1)];
         const ColV<T> ca = col_vtx<T, ZB, false>(a, qqx, qqy, (T)0, (T)0, (T)1);
         const ColV<T> cb = col_vtx<T, ZB, false>(b, qqx, qqy, (T)0, (T)0, (T)1);
+        const bool edge = (a.pad1 & kChainEdge) != 0;
+        et = (a.pad1 & kChainTri) != 0;
         ColRec<T> rc;
         rc.zu = u == (T)1 ? (T)a.z : (T)a.z * u;   // exact (u is a power of two)
         rc.rho2 = ca.rho2;
-        rc.N = ca.ry * cb.rx - ca.rx * cb.ry;
-        rc.dot = ca.rx * cb.rx + ca.ry * cb.ry;
+        // N = r_a,y r_b,x - r_a,x r_b,y through the edge's own x and y (exact integers), so
+        // that its error goes with the edge's length and not with the distance
+        const T ex = (T)(b.qx - a.qx) * u, ey = (T)(b.qy - a.qy) * u;
+        rc.N = edge ? ca.ry * ex - ca.rx * ey : (T)0;
+        rc.dot = edge ? ca.rx * cb.rx + ca.ry * cb.ry : (T)1;
         ColAux<T> ax;
         ax.m = fmax(fabs(rc.N) * (T)P::kInvTan, (T)P::kMinD);
         ax.rx = ca.rx;
         ax.ry = ca.ry;
         ax.dx = ca.dx;
         ax.dy = ca.dy;
-        if (asc) {
-            bool farv = true;   // every sample below the vertex has r_z^2 <= 3 rho^2
-#pragma unroll
-            for (int r = 0; r < ZB; ++r) {
-                const T zr = u == (T)1 ? (T)a.z - bminr[r] : fma((T)a.z, u, -bminr[r]);
-                R += zr > (T)0;
-                farv &= !((zr > (T)0) & (zr * zr > (T)3 * rc.rho2));   // zr: the block's largest r_z
-            }
-            R |= farv ? 256 : 0;
-        } else {
-            R = ZB + 1;
-        }
         e = ax.m < rc.dot;
-        const int s = (v - b0) & (kColRing - 1);
-        ring.rec[s] = rc;
-        ring.aux[s] = ax;
-        ring.R[s] = R;
-        if (v == b0) {
-            ring.rec[kColRing] = rc;
-            ring.aux[kColRing] = ax;
-            ring.R[kColRing] = R;
-        }
+        e4 = fmax(fabs(rc.N) * (T)P::kInvTan4, (T)P::kQuadDot) < rc.dot;
+        buf.rec[lane] = rc;
+        buf.aux[lane] = ax;
+        const T zr = u == (T)1 ? (T)a.z - zmin : fma((T)a.z, u, -zmin);   // the largest r_z
+        ef = !((zr > (T)0) & (zr * zr > (T)3 * rc.rho2));
     }
-    mk = __builtin_amdgcn_ballot_w64(e && pairs);
-    // the wave reads what its own lanes wrote; LDS operations of a wave complete in order
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    m2 = __builtin_amdgcn_ballot_w64(e && pairs);
+    m4 = __builtin_amdgcn_ballot_w64(e4 && quads);
+    mf = __builtin_amdgcn_ballot_w64(ef);
+    mt = __builtin_amdgcn_ballot_w64(et);
+    wave_lds_sync();
 }
 
-__device__ __forceinline__ bool col_e(unsigned long long m0, unsigned long long m1, int k) {
-    return (((k & 64) ? m1 : m0) >> (k & 63)) & 1ull;
-}
-
-template <class T>
-__device__ __forceinline__ int ring_R(const ColRing<T>& ring, int k) {
-    return __builtin_amdgcn_readfirstlane(ring.R[k]);
-}
-
-// s of the vertex in slot k for the lane's ZB samples (pz in offset units),
-// and its outgoing edge's N and x/y dot
-template <class T, int ZB>
-__device__ __forceinline__ void col_vertex(const ColRec<T>& c, int R, const T* pz, T* sv, T& N, T& dot) {
-    T rz[ZB];
+// s of a vertex for the lane's ZB samples (pz in offset units), and its
+// outgoing edge's N and x/y dot
+template <class T, int ZB, bool FARV = false>
+__device__ __forceinline__ void col_vertex(const ColRec<T>& c, const T* pz, T* sv, T& N, T& dot) {
 #pragma unroll
     for (int r = 0; r < ZB; ++r) {
-        rz[r] = c.zu - pz[r];
-        sv[r] = Arith<T>::sqrt(rz[r] * rz[r] + c.rho2) + fabs(rz[r]);   // t, made s in place
+        const T rz = c.zu - pz[r];
+        const T t = Arith<T>::sqrt(rz * rz + c.rho2) + fabs(rz);
+        if constexpr (FARV) sv[r] = fma((T)-2, fmax(rz, (T)0), t);
+        else sv[r] = rz > (T)0 ? c.rho2 * Arith<T>::rcp(t) : t;
     }
-    s_prefix<T, ZB>(R & 0xff, rz, c.rho2, sv, R >= 256);
     N = c.N;
     dot = c.dot;
 }
 
 template <class T>
-__device__ __forceinline__ ColV<T> col_aux(const ColRing<T>& ring, int k) {
-    const ColAux<T> a = ring.aux[k];
+__device__ __forceinline__ ColV<T> col_aux(const ColBuf<T>& buf, int k) {
+    const ColAux<T> a = buf.aux[k];
     ColV<T> c;
     c.dx = a.dx;
     c.dy = a.dy;
@@ -606,10 +634,10 @@ __device__ __forceinline__ ColV<T> col_aux(const ColRing<T>& ring, int k) {
     return c;
 }
 
-// One edge (slot ka to slot kb) given its D per sample: the fast form where
+// One edge (record ka to record kb) given its D per sample: the fast form where
 // every sample allows it, else the exact and full-range forms (edge_slow).
 template <class T, int ZB>
-__device__ __forceinline__ void col_finish(const ColRing<T>& ring, int ka, int kb, const T* sa, const T* sb, T N,
+__device__ __forceinline__ void col_finish(const ColBuf<T>& buf, int ka, int kb, const T* sa, const T* sb, T N,
                                            const T* D, T* acc) {
     const T aN = fabs(N);
     bool slow = false;
@@ -619,29 +647,22 @@ __device__ __forceinline__ void col_finish(const ColRing<T>& ring, int ka, int k
 #pragma unroll
         for (int r = 0; r < ZB; ++r) acc[r] += Arith<T>::atan_small(N * Arith<T>::rcp(D[r]));
     } else {
-        const ColV<T> a = col_aux<T>(ring, ka), b = col_aux<T>(ring, kb);
+        const ColV<T> a = col_aux<T>(buf, ka), b = col_aux<T>(buf, kb);
 #pragma unroll
         for (int r = 0; r < ZB; ++r) acc[r] += edge_slow<T>(a, b, sa[r], sb[r], N, D[r], true);
     }
 }
 
-// Edges slot ka -> kb -> kc: one arctangent for the pair where every sample of
-// the wave allows it (decided by the x/y terms alone when ok, else per sample),
-// else one by one.
+// Two edges, record ka -> kb -> kc, given their D per sample: one arctangent for the
+// pair where every sample of the wave allows it (known when ok), else one by one.
 template <class T, int ZB>
-__device__ __forceinline__ void col_pair(const ColRing<T>& ring, int ka, int kb, int kc, T N1, T dot1, T N2,
-                                         T dot2, bool ok, bool pairs, const T* sa, const T* sb, const T* sc,
+__device__ __forceinline__ void col_pair(const ColBuf<T>& buf, int ka, int kb, int kc, T N1, T N2, T m1, bool ok,
+                                         bool pairs, const T* sa, const T* sb, const T* sc, const T* D1, const T* D2,
                                          T* acc) {
     using P = EdgePairs<T, ZB, false>;
-    T D1[ZB], D2[ZB];
-#pragma unroll
-    for (int r = 0; r < ZB; ++r) {
-        D1[r] = fma(sa[r], sb[r], dot1);
-        D2[r] = fma(sb[r], sc[r], dot2);
-    }
     bool pair = ok;
     if (!ok && pairs) {
-        const T m1 = ring.aux[ka].m, m2 = ring.aux[kb].m;
+        const T m2 = buf.aux[kb].m;
         bool slow = false;
 #pragma unroll
         for (int r = 0; r < ZB; ++r) slow |= !(m1 < D1[r]) | !(m2 < D2[r]);
@@ -658,172 +679,202 @@ __device__ __forceinline__ void col_pair(const ColRing<T>& ring, int ka, int kb,
             else acc[r] += Arith<T>::atan_small(t);   // |t| < tan(pi/8)
         }
     } else {
-        col_finish<T, ZB>(ring, ka, kb, sa, sb, N1, D1, acc);
-        col_finish<T, ZB>(ring, kb, kc, sb, sc, N2, D2, acc);
+        col_finish<T, ZB>(buf, ka, kb, sa, sb, N1, D1, acc);
+        col_finish<T, ZB>(buf, kb, kc, sb, sc, N2, D2, acc);
     }
 }
 
-// Edges a -> b -> c known to pair on their x/y terms: one arctangent, no test.
+// Edges a -> b -> c -> d -> e known to take one arctangent on their x/y terms.
+template <class T>
+struct Pair {
+    T re, im;
+};
+
+template <class T>
+__device__ __forceinline__ Pair<T> edge_product(T N1, T D1, T N2, T D2) {
+    return {fma(D1, D2, -(N1 * N2)), fma(D1, N2, N1 * D2)};
+}
+
+template <class T>
+__device__ __forceinline__ Pair<T> edge_product(const Pair<T>& a, const Pair<T>& b) {
+    return {fma(a.re, b.re, -(a.im * b.im)), fma(a.re, b.im, a.im * b.re)};
+}
+
+template <class T>
+__device__ __forceinline__ T pair_acc(const Pair<T>& a, T acc) {
+    const T t = a.im * Arith<T>::rcp(a.re);   // |t| < tan(pi/8)
+    if constexpr (std::is_same<T, float>::value) return atan_pair_acc(t, acc);
+    else return acc + Arith<T>::atan_small(t);
+}
+
+// Edges p -> k -> k + 1 -> k + 2 -> k + 3 (records), p's s, N and dot in sp, Np,
+// dotp and replaced by record k + 3's.  FARV: all four vertices are in that case.
+// TRI: the records are a loop of three edges (entered by an edge of no angle),
+// whose last vertex, its first again, is not computed twice.
+template <class T, int ZB, bool FARV, bool TRI>
+__device__ __forceinline__ void col_quad(const ColBuf<T>& buf, int k, const T* pz, T* sp, T& Np, T& dotp, T* acc) {
+    const ColRec<T> c0 = buf.rec[k], c1 = buf.rec[k + 1], c2 = buf.rec[k + 2];
+    T sq[ZB], sr[ZB], N0, dot0, N1, dot1;
+    Pair<T> g[ZB];
+    if constexpr (TRI) {
+        T N2, dot2;
+        col_vertex<T, ZB, FARV>(c0, pz, sp, N0, dot0);
+        col_vertex<T, ZB, FARV>(c1, pz, sq, N1, dot1);
+        col_vertex<T, ZB, FARV>(c2, pz, sr, N2, dot2);
+#pragma unroll
+        for (int r = 0; r < ZB; ++r) {
+            g[r] = edge_product<T>(N0, fma(sp[r], sq[r], dot0), N1, fma(sq[r], sr[r], dot1));
+            acc[r] = pair_acc<T>(edge_product<T>(g[r], {fma(sr[r], sp[r], dot2), N2}), acc[r]);
+        }
+        Np = (T)0;
+        dotp = (T)1;
+    } else {
+        const ColRec<T> c3 = buf.rec[k + 3];
+        col_vertex<T, ZB, FARV>(c0, pz, sq, N0, dot0);
+        col_vertex<T, ZB, FARV>(c1, pz, sr, N1, dot1);
+#pragma unroll
+        for (int r = 0; r < ZB; ++r)
+            g[r] = edge_product<T>(Np, fma(sp[r], sq[r], dotp), N0, fma(sq[r], sr[r], dot0));
+        col_vertex<T, ZB, FARV>(c2, pz, sq, N0, dot0);
+        col_vertex<T, ZB, FARV>(c3, pz, sp, Np, dotp);
+#pragma unroll
+        for (int r = 0; r < ZB; ++r)
+            acc[r] = pair_acc<T>(
+                edge_product<T>(g[r], edge_product<T>(N1, fma(sr[r], sq[r], dot1), N0, fma(sq[r], sp[r], dot0))), acc[r]);
+    }
+}
+
+// The same four edges where their x/y terms alone do not settle it: one arctangent
+// where for every sample each angle is below pi/4 (|N| < D), so that the sum is the
+// product's argument without a turn, and the sum below pi/8 (a missing triangle's
+// loop, one trip, turns by half its solid angle however wide its edges look); else
+// pair by pair, else edge by edge.  Bit i of b: the i-th edge pairs on its x/y terms.
 template <class T, int ZB>
-__device__ __forceinline__ void col_pair_xy(T N1, T dot1, T N2, T dot2, const T* sa, const T* sb, const T* sc,
-                                            T* acc) {
-    const T N12 = N1 * N2;
+__device__ __forceinline__ void col_trip(const ColBuf<T>& buf, int k, unsigned b, bool pairs, bool quads, const T* pz,
+                                         T* sp, T& Np, T& dotp, T* acc) {
+    using P = EdgePairs<T, ZB, false>;
+    const ColRec<T> c0 = buf.rec[k], c1 = buf.rec[k + 1], c2 = buf.rec[k + 2], c3 = buf.rec[k + 3];
+    T s0[ZB], s1[ZB], s2[ZB], s3[ZB], D0[ZB], D1[ZB], D2[ZB], D3[ZB], N0, N1, N2, N3, dot0, dot1, dot2, dot3;
+    col_vertex<T, ZB>(c0, pz, s0, N0, dot0);
+    col_vertex<T, ZB>(c1, pz, s1, N1, dot1);
+    col_vertex<T, ZB>(c2, pz, s2, N2, dot2);
+    col_vertex<T, ZB>(c3, pz, s3, N3, dot3);
+    const T b0 = fmax(fabs(Np), (T)P::kQuadDot), b1 = fmax(fabs(N0), (T)P::kQuadDot);
+    const T b2 = fmax(fabs(N1), (T)P::kQuadDot), b3 = fmax(fabs(N2), (T)P::kQuadDot);
+    Pair<T> g[ZB];
+    bool slow = !quads;
 #pragma unroll
     for (int r = 0; r < ZB; ++r) {
-        const T D1 = fma(sa[r], sb[r], dot1), D2 = fma(sb[r], sc[r], dot2);
-        const T re = fma(D1, D2, -N12);
-        const T im = fma(D1, N2, N1 * D2);
-        const T t = im * Arith<T>::rcp(re);
-        if constexpr (EdgePairs<T, ZB, false>::f32) acc[r] = atan_pair_acc(t, acc[r]);
-        else acc[r] += Arith<T>::atan_small(t);
+        D0[r] = fma(sp[r], s0[r], dotp);
+        D1[r] = fma(s0[r], s1[r], dot0);
+        D2[r] = fma(s1[r], s2[r], dot1);
+        D3[r] = fma(s2[r], s3[r], dot2);
+        g[r] = edge_product<T>(edge_product<T>(Np, D0[r], N0, D1[r]), edge_product<T>(N1, D2[r], N2, D3[r]));
+        slow |= !(b0 < D0[r]) | !(b1 < D1[r]) | !(b2 < D2[r]) | !(b3 < D3[r]) | !(fabs(g[r].im) < (T)P::kTan8 * g[r].re);
     }
-}
-
-// single edge slot ka -> kb
-template <class T, int ZB>
-__device__ __forceinline__ void col_edge(const ColRing<T>& ring, int ka, int kb, T N, T dot, const T* sa,
-                                         const T* sb, T* acc) {
-    T D[ZB];
+    if (__builtin_amdgcn_ballot_w64(slow) == 0ull) {
 #pragma unroll
-    for (int r = 0; r < ZB; ++r) D[r] = fma(sa[r], sb[r], dot);
-    col_finish<T, ZB>(ring, ka, kb, sa, sb, N, D, acc);
+        for (int r = 0; r < ZB; ++r) acc[r] = pair_acc<T>(g[r], acc[r]);
+    } else {
+        // record 0 is entered by an edge of no angle, which takes no rare path
+        const int kp = k > 0 ? k - 1 : 0;
+        const T mp = k > 0 ? buf.aux[kp].m : (T)P::kMinD;
+        col_pair<T, ZB>(buf, kp, k, k + 1, Np, N0, mp, (b & 3u) == 3u, pairs, sp, s0, s1, D0, D1, acc);
+        col_pair<T, ZB>(buf, k + 1, k + 2, k + 3, N1, N2, buf.aux[k + 1].m, (b >> 2) == 3u, pairs, s1, s2, s3, D2, D3,
+                        acc);
+    }
+#pragma unroll
+    for (int r = 0; r < ZB; ++r) sp[r] = s3[r];
+    Np = N3;
+    dotp = dot3;
 }
 
-// Boundary sum S for the ZB samples of each lane of a grid column inside the
-// fixed-point box (qqx, qqy: the column's quantised x, y; pzs: the samples' z in
-// cells).  Register r of the wave is a block of 64 consecutive samples, z
-// monotone in the lane.  pairs: edge pairs allowed (see near_z).  Same sums as
-// boundary_loops, in the same order: FP32 partials flushed to FP64 every 32 edges.
+// Boundary sum over the chunks that `flt` keeps, added to S, for the ZB samples of
+// each lane of a column inside the fixed-point box (qqx, qqy: the column's
+// quantised x, y; pzs: the samples' z in cells).  z is monotone in the lane.  pairs: edge pairs allowed
+// (see near_z); quads: products of four too (see quad_z).  FP32 partials are
+// flushed to FP64 every 32 edges.  parts > 1: only the part-th of `parts` shares of
+// the chunks, dealt out in eights.
 template <class T, int ZB>
-__device__ __forceinline__ void column_loops(const MeshView& mv, int qqx, int qqy, const T* pzs, double* S,
-                                             bool pairs, ColRing<T>& ring) {
+__device__ __forceinline__ void column_chunks(const MeshView& mv, const ChunkFilter& flt, int qqx, int qqy,
+                                              const T* pzs, double* S, bool pairs, bool quads, int part, int parts,
+                                              ColBuf<T>& buf) {
     constexpr T u = (T)EdgePairs<T, ZB, false>::kUnit;
     T pz[ZB];
 #pragma unroll
     for (int r = 0; r < ZB; ++r) pz[r] = pzs[r] * u;
-    // the samples of a block are monotone in the lane, so its smallest z is in
-    // lane 0 or lane 63.  The column ascends (asc) when every block ascends and
-    // the blocks' smallest z do not fall: the minima alone do not show it, as a
-    // descending column's last block and the blocks of clamped copies of its
-    // last sample after it share their smallest z.
-    T bminr[ZB];
-    bool asc = true;
-    T prev = -(T)INFINITY;
+    // the samples are monotone in the lane, so each register's smallest z is in lane 0 or 63
+    T zmin = (T)INFINITY;
 #pragma unroll
-    for (int r = 0; r < ZB; ++r) {
-        const T z0 = wave_lane<T>(pz[r], 0), z63 = wave_lane<T>(pz[r], 63);
-        bminr[r] = fmin(z0, z63);
-        asc &= !(bminr[r] < prev) & !(z63 < z0);
-        prev = bminr[r];
-    }
-    for (int l = 0; l < mv.nloops; ++l) {
-        const int b0 = mv.loop_off[l], nv = mv.loop_off[l + 1] - b0;
-        unsigned long long m0, m1;   // pair bits of the ring's two halves
-        int done = min(64, nv);
-        col_fill<T, ZB>(mv, b0, done, b0, b0 + nv, qqx, qqy, bminr, asc, pairs, ring, m0);
-        m1 = m0;
-        T sp[ZB], sq[ZB], sr[ZB];
-        T Np, dotp, Nq, dotq, Nr, dotr;
-        // the first vertex's s is computed again for the closing edge (from its
-        // copy in slot kColRing) rather than held in registers through the loop
-        const int R0 = ring_R(ring, 0);
-        col_vertex<T, ZB>(ring.rec[0], R0, pz, sp, Np, dotp);
-        int j = 1;   // vertices are counted from b0; slot of vertex j is j mod kColRing
-        while (j < nv) {
-            const int je = min(nv, j + 32);
-            if (je > done) {   // one fill covers it: j <= done, je <= j + 32
-                const int n = min(64, nv - done);
-                if (done & 64) col_fill<T, ZB>(mv, b0 + done, n, b0, b0 + nv, qqx, qqy, bminr, asc, pairs, ring, m1);
-                else col_fill<T, ZB>(mv, b0 + done, n, b0, b0 + nv, qqx, qqy, bminr, asc, pairs, ring, m0);
-                done += n;
+    for (int r = 0; r < ZB; ++r) zmin = fmin(zmin, fmin(wave_lane<T>(pz[r], 0), wave_lane<T>(pz[r], 63)));
+    // the chained vertex before the current record: none yet, so an edge of no angle
+    T sp[ZB], Np = (T)0, dotp = (T)1;
+#pragma unroll
+    for (int r = 0; r < ZB; ++r) sp[r] = (T)1;
+    const int lane = (int)(threadIdx.x & 63);
+    int base = 0, head = 0, have = 0;   // next of the share to look at; the queue's first and number of chunks
+    const int share = (mv.nchunk + 8 * parts - 1) / (8 * parts) * 8;
+    while (true) {
+        if (have < kColChunks && base < share) {
+            if (head > 0) {   // the rest to the front: fewer than 8 chunks
+                const int t = lane < have ? buf.queue[head + lane] : 0;
+                wave_lds_sync();
+                if (lane < have) buf.queue[lane] = t;
+                head = 0;
             }
+            while (have < kColChunks && base < share) {
+                const int j = base + lane, id = parts == 1 ? j : (j >> 3) * 8 * parts + part * 8 + (j & 7);
+                const bool keep = j < share && id < mv.nchunk && (flt.mode == ChunkFilter::kAll || chunk_kept(mv.cbox[id], flt));
+                const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
+                if (keep)
+                    buf.queue[have + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                               __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = id;
+                have += __builtin_popcountll(m);
+                base += 64;
+            }
+            wave_lds_sync();
+        }
+        if (have == 0) break;
+        const int n = min(have, kColChunks);
+        unsigned long long ms, mq, mf, mt;
+        col_fill<T, ZB>(mv, buf.queue + head, n, qqx, qqy, zmin, pairs, quads, buf, ms, mq, mf, mt);
+        head += n;
+        have -= n;
+        // bit k from here on: the edge entering record k (record 0 is entered by an edge of no angle)
+        ms = (ms << 1) | (pairs ? 1ull : 0ull);
+        mq = (mq << 1) | (quads ? 1ull : 0ull);
+        const int nt = n * (kChunk / 4);   // trips of four vertices (two edge pairs): p-q-r, then r-q-p
+        int t = 0;
+        while (t < nt) {
+            const int te = min(nt, t + 8);
             T acc[ZB];
 #pragma unroll
             for (int r = 0; r < ZB; ++r) acc[r] = (T)0;
-            // four vertices (two edge pairs) per trip: p-q-r, then r-q-p
-            while (j + 3 < je) {
-                // trips whose four edges all pair on their x/y terms alone
-                for (; j + 3 < je && col_e(m0, m1, (j - 1) & (kColRing - 1)) &&
-                       col_e(m0, m1, j & (kColRing - 1)) && col_e(m0, m1, (j + 1) & (kColRing - 1)) &&
-                       col_e(m0, m1, (j + 2) & (kColRing - 1));
-                     j += 4) {
-                    const int kq = j & (kColRing - 1), kr = (j + 1) & (kColRing - 1);
-                    const int kq2 = (j + 2) & (kColRing - 1), kp2 = (j + 3) & (kColRing - 1);
-                    const ColRec<T> cq = ring.rec[kq], cr = ring.rec[kr], cq2 = ring.rec[kq2], cp2 = ring.rec[kp2];
-                    col_vertex<T, ZB>(cq, ring_R(ring, kq), pz, sq, Nq, dotq);
-                    col_vertex<T, ZB>(cr, ring_R(ring, kr), pz, sr, Nr, dotr);
-                    col_pair_xy<T, ZB>(Np, dotp, Nq, dotq, sp, sq, sr, acc);
-                    col_vertex<T, ZB>(cq2, ring_R(ring, kq2), pz, sq, Nq, dotq);
-                    col_vertex<T, ZB>(cp2, ring_R(ring, kp2), pz, sp, Np, dotp);
-                    col_pair_xy<T, ZB>(Nr, dotr, Nq, dotq, sr, sq, sp, acc);
+            while (t < te) {
+                // trips whose four edges take one arctangent on their x/y terms alone
+                for (; t < te && ((unsigned)(mq >> (4 * t)) & 15u) == 15u; ++t) {
+                    const bool f = ((unsigned)(mf >> (4 * t)) & 15u) == 15u;
+                    if ((mt >> (4 * t)) & 1ull) {
+                        if (f) col_quad<T, ZB, true, true>(buf, 4 * t, pz, sp, Np, dotp, acc);
+                        else col_quad<T, ZB, false, true>(buf, 4 * t, pz, sp, Np, dotp, acc);
+                    } else {
+                        if (f) col_quad<T, ZB, true, false>(buf, 4 * t, pz, sp, Np, dotp, acc);
+                        else col_quad<T, ZB, false, false>(buf, 4 * t, pz, sp, Np, dotp, acc);
+                    }
                 }
-                if (j + 3 >= je) break;
-                const int kp = (j - 1) & (kColRing - 1), kq = j & (kColRing - 1);
-                const int kr = (j + 1) & (kColRing - 1), kq2 = (j + 2) & (kColRing - 1);
-                const int kp2 = (j + 3) & (kColRing - 1);
-                // the trip's four records are read up front (LDS latency)
-                const ColRec<T> cq = ring.rec[kq], cr = ring.rec[kr], cq2 = ring.rec[kq2], cp2 = ring.rec[kp2];
-                col_vertex<T, ZB>(cq, ring_R(ring, kq), pz, sq, Nq, dotq);
-                col_vertex<T, ZB>(cr, ring_R(ring, kr), pz, sr, Nr, dotr);
-                col_pair<T, ZB>(ring, kp, kq, kr, Np, dotp, Nq, dotq, col_e(m0, m1, kp) & col_e(m0, m1, kq),
-                                pairs, sp, sq, sr, acc);
-                col_vertex<T, ZB>(cq2, ring_R(ring, kq2), pz, sq, Nq, dotq);
-                col_vertex<T, ZB>(cp2, ring_R(ring, kp2), pz, sp, Np, dotp);
-                col_pair<T, ZB>(ring, kr, kq2, kp2, Nr, dotr, Nq, dotq,
-                                col_e(m0, m1, kr) & col_e(m0, m1, kq2), pairs, sr, sq, sp, acc);
-                j += 4;
-            }
-            if (j + 1 < je) {
-                const int kp = (j - 1) & (kColRing - 1), kq = j & (kColRing - 1);
-                const int kr = (j + 1) & (kColRing - 1);
-                const ColRec<T> cq = ring.rec[kq], cr = ring.rec[kr];
-                col_vertex<T, ZB>(cq, ring_R(ring, kq), pz, sq, Nq, dotq);
-                col_vertex<T, ZB>(cr, ring_R(ring, kr), pz, sr, Nr, dotr);
-                col_pair<T, ZB>(ring, kp, kq, kr, Np, dotp, Nq, dotq, col_e(m0, m1, kp) & col_e(m0, m1, kq),
-                                pairs, sp, sq, sr, acc);
-                Np = Nr;
-                dotp = dotr;
-#pragma unroll
-                for (int r = 0; r < ZB; ++r) sp[r] = sr[r];
-                j += 2;
-            }
-            if (j < je) {
-                const int kp = (j - 1) & (kColRing - 1), kq = j & (kColRing - 1);
-                col_vertex<T, ZB>(ring.rec[kq], ring_R(ring, kq), pz, sq, Nq, dotq);
-                col_edge<T, ZB>(ring, kp, kq, Np, dotp, sp, sq, acc);
-                Np = Nq;
-                dotp = dotq;
-#pragma unroll
-                for (int r = 0; r < ZB; ++r) sp[r] = sq[r];
-                ++j;
+                if (t >= te) break;
+                col_trip<T, ZB>(buf, 4 * t, (unsigned)(ms >> (4 * t)) & 15u, pairs, quads, pz, sp, Np, dotp, acc);
+                ++t;
             }
 #pragma unroll
             for (int r = 0; r < ZB; ++r) S[r] += (double)acc[r];
         }
-        // closing edge, last vertex -> first (kept in slot kColRing)
-        T acc[ZB], sf[ZB], Nf, dotf;
-        col_vertex<T, ZB>(ring.rec[kColRing], R0, pz, sf, Nf, dotf);
-#pragma unroll
-        for (int r = 0; r < ZB; ++r) acc[r] = (T)0;
-        col_edge<T, ZB>(ring, (nv - 1) & (kColRing - 1), kColRing, Np, dotp, sp, sf, acc);
-#pragma unroll
-        for (int r = 0; r < ZB; ++r) S[r] += (double)acc[r];
     }
 }
 
 // ---------------------------------------------------------------- grids
 
 constexpr int kGridWaves = 4;  // waves per block in the wave-per-task kernels
-
-// A cell-centred grid in the mesh frame; one wave per (column, z-chunk).
-struct GridArgs {
-    double o[3], s[3];
-    long long nx, ny, nz;
-    long long nchunks;   // z-chunks per column
-    long long nwaves;    // columns * nchunks
-    long long wave0;     // first wave of this launch (large grids take several)
-    long long st[3];     // output strides of the frame's x, y, z indices (world z fastest)
-};
 
 // The grid in the frame of a mesh built along `axis`: frame axis c is world
 // axis (c + axis) % 3; the output keeps the world layout (x slowest, z fastest).

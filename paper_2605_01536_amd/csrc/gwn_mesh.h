@@ -25,6 +25,10 @@ struct gwn_mesh_s {
     float4* trif = nullptr;        // float corners in Morton order (direct sum)
     gwn::BVert* bverts = nullptr;
     int* loop_off = nullptr;
+    gwn::BVert* chain = nullptr;   // the boundary in chunks (gwn_internal.h)
+    int4* cbox = nullptr;
+    int64_t nchunk = 0;
+    double chunk_w = 0.0;          // mean of the chunks' x and y extents, in cells
     // query tuning (gwn_mesh_set_tuning / gwn_mesh_autotune); 0 = the built-in rule
     int split_max[2] = {0, 0};     // per precision: batches of at most this many points split their edges
     int order_min = 0;             // batches of at least this many points are Morton-ordered
@@ -37,6 +41,9 @@ struct gwn_mesh_s {
         v.tris = tris;
         v.bverts = bverts;
         v.loop_off = loop_off;
+        v.chain = chain;
+        v.cbox = cbox;
+        v.nchunk = (int)nchunk;
         v.nloops = (int)nloops;
         v.nf = (int)nf;
         v.root = root;
