@@ -11,11 +11,11 @@
 namespace gwn {
 namespace {
 
-// sample i of an axis in the mesh frame, as the column kernels place it: quantised
-// x, y; z in cells
-__device__ __forceinline__ double far_sample(const GridArgs& ga, const QGrid& g, bool f32, int axis, long long i) {
+// sample i of an axis in the mesh frame, as the column kernels place it: x, y
+// quantised for w (C = 1), else in cells
+__device__ __forceinline__ double far_sample(const GridArgs& ga, const QGrid& g, bool f32, int C, int axis, long long i) {
     const float p = grid_coord(ga.o[axis], ga.s[axis], i);
-    if (axis < 2) return qround(p, g.lo[axis], g.scale);
+    if (C == 1 && axis < 2) return qround(p, g.lo[axis], g.scale);
     return f32 ? (double)(p * (float)g.scale) : (double)p * g.scale;
 }
 
@@ -28,27 +28,27 @@ __global__ void k_far_nodes(FarPlan p, GridArgs ga, QGrid g, bool f32) {
     // a last block of fewer samples reaches one step past the grid, at every level, so
     // that a single sample has a range too and a block lies inside its parent
     const long long i0 = (long long)c * l.b[axis], i1 = min(i0 + l.b[axis] - 1, (long long)p.ns[axis]);
-    const double a = far_sample(ga, g, f32, axis, i0), b = far_sample(ga, g, f32, axis, i1);
-    if (axis < 2) (axis == 0 ? l.cx : l.cy)[c] = make_int2((int)fmin(a, b), (int)fmax(a, b));
-    else l.cz[c] = make_double2(fmin(a, b), fmax(a, b));
+    const double a = far_sample(ga, g, f32, p.C, axis, i0), b = far_sample(ga, g, f32, p.C, axis, i1);
+    if (axis < 2) {
+        const double qa = far_sample(ga, g, f32, 1, axis, i0), qb = far_sample(ga, g, f32, 1, axis, i1);
+        (axis == 0 ? l.cx : l.cy)[c] = make_int2((int)fmin(qa, qb), (int)fmax(qa, qb));
+    }
     for (int j = 0; j < n; ++j) {
         double x;
-        if (n == p.ns[axis]) x = far_sample(ga, g, f32, axis, j);   // the samples themselves (one block)
-        else x = 0.5 * (a + b) + 0.5 * (b - a) * p.t[j];            // in the samples' direction
-        if (axis == 2) l.pz[c * n + j] = f32 ? (double)(float)x : x;
-        else (axis == 0 ? l.px : l.py)[c * n + j] = (int)rint(x);
+        if (n == p.ns[axis]) x = far_sample(ga, g, f32, p.C, axis, j);   // the samples themselves (one block)
+        else x = 0.5 * (a + b) + 0.5 * (b - a) * p.t[j];                 // in the samples' direction
+        l.pos[axis][c * n + j] = p.C == 1 && axis < 2 ? rint(x) : f32 ? (double)(float)x : x;
     }
 }
 
 // Lagrange weights at x of the n nodes xs
-template <class P>
-__device__ void lagrange(double x, const P* xs, int n, double* w) {
+__device__ void lagrange(double x, const double* xs, int n, double* w) {
     for (int j = 0; j < n; ++j) {
         double num = 1.0, den = 1.0;
         for (int m = 0; m < n; ++m)
             if (m != j) {
-                num *= x - (double)xs[m];
-                den *= (double)xs[j] - (double)xs[m];
+                num *= x - xs[m];
+                den *= xs[j] - xs[m];
             }
         w[j] = num / den;
     }
@@ -66,18 +66,17 @@ __global__ void k_far_weights(FarPlan p, GridArgs ga, QGrid g, bool f32) {
     double* w;
     if (sample) {
         if (i >= p.ns[axis]) return;
-        x = far_sample(ga, g, f32, axis, i);
+        x = far_sample(ga, g, f32, p.C, axis, i);
         c = i / from.b[axis];
         w = p.s[axis];
     } else {
         const FarLevel& l = p.lv[lev];
         if (i >= l.nn[axis]) return;
-        x = axis == 2 ? l.pz[i] : (double)(axis == 0 ? l.px : l.py)[i];
+        x = l.pos[axis][i];
         c = min(i / n / 2, from.nc[axis] - 1);
         w = l.w[axis];
     }
-    if (axis == 2) lagrange(x, from.pz + (size_t)c * n, n, w + (size_t)i * n);
-    else lagrange(x, (axis == 0 ? from.px : from.py) + (size_t)c * n, n, w + (size_t)i * n);
+    lagrange(x, from.pos[axis] + (size_t)c * n, n, w + (size_t)i * n);
 }
 
 // Adds the parent level's sums, interpolated, to a block's nodes: one workgroup per
@@ -163,10 +162,7 @@ size_t far_layout(FarPlan& p, char* base) {
         FarLevel& l = p.lv[i];
         l.cx = (int2*)take(sizeof(int2) * l.nc[0]);
         l.cy = (int2*)take(sizeof(int2) * l.nc[1]);
-        l.cz = (double2*)take(sizeof(double2) * l.nc[2]);
-        l.px = (int*)take(sizeof(int) * l.nn[0]);
-        l.py = (int*)take(sizeof(int) * l.nn[1]);
-        l.pz = (double*)take(sizeof(double) * l.nn[2]);
+        for (int a = 0; a < 3; ++a) l.pos[a] = (double*)take(sizeof(double) * l.nn[a]);
         for (int a = 0; a < 3; ++a) l.w[a] = (double*)take(sizeof(double) * (size_t)l.nn[a] * p.nodes[a]);
         l.T = (double*)take(sizeof(double) * (size_t)p.C * l.nn[0] * l.nn[1] * l.nn[2]);
     }
@@ -200,10 +196,14 @@ FarPlan far_plan(const gwn_mesh_s* m, const GridArgs& ga, int prec, int C) {
         const double lo = a < 2 ? 0x1p20 : -0x1p30, hi = a < 2 ? (double)kQMax - 0x1p20 : 0x1p31;
         if (!(p0 >= lo && p0 <= hi && p1 >= lo && p1 <= hi)) return none;
         if (N[a] > 1 && !(step[a] >= 0x1p14)) return none;
-        // distinct FP32 node heights: a z step of at least 2^8 ulps of the largest z
-        if (a == 2 && N[a] > 1 && !(step[a] >= 0x1p-15 * scale * std::max(std::fabs(ga.o[a]), std::fabs(ga.o[a] + (double)N[a] * ga.s[a]))))
+        // distinct FP32 node positions: a step of at least 2^8 ulps of the largest coordinate
+        if ((a == 2 || C == 3) && N[a] > 1 && !(step[a] >= 0x1p-15 * scale * std::max(std::fabs(ga.o[a]), std::fabs(ga.o[a] + (double)N[a] * ga.s[a]))))
             return none;
     }
+    // the gradient's offsets in units of 2^18 cells, no other scale (far_scale)
+    if (C == 3)
+        for (int a = 0; a < 3; ++a)
+            if (!(scale * std::max(std::fabs(ga.o[a]), std::fabs(ga.o[a] + ((double)N[a] + 1.0) * ga.s[a])) <= 0x1p39)) return none;
     double ext[2];   // the boundary's x and y extent is taken for the mesh's
     for (int a = 0; a < 2; ++a) ext[a] = std::max((m->bbox[3 + a] - m->bbox[a]) * scale, 1.0);
 
@@ -221,8 +221,9 @@ FarPlan far_plan(const gwn_mesh_s* m, const GridArgs& ga, int prec, int C) {
     // Expected time in seconds.  Chained vertices per second, measured: all chunks 3.0e12
     // (FP64 8.3e11), near chunks alone 2.4e12 (8e11; their edges look wider), node columns
     // 2.1e12 (9e11); interpolation per sample and node value; launches.
+    // The gradient's rates likewise, for its three sums together.
     const double rate = f32 ? 3.0e12 : 0.83e12, near_rate = f32 ? 2.4e12 : 0.8e12, node_rate = f32 ? 2.1e12 : 0.9e12;
-    const double B = (double)m->nchunk * kChunk * C, all = (double)N[0] * N[1] * N[2];
+    const double B = (double)m->nchunk * kChunk * (C == 3 ? 1.3 : 1.0), all = (double)N[0] * N[1] * N[2];
     auto padded = [](double z) { return std::ceil(z / 64.0) * 64.0; };
     const double columns = (double)N[0] * N[1] * padded((double)N[2]), direct = columns * B / rate;
     double cost = forced > 0 ? 1e30 : 0.9 * direct;

@@ -1,377 +1,147 @@
-// grad.hip -- gradient of w with respect to the query point (Supp. Sec. 4, Alg. 3).
+// grad.hip -- gradient of w with respect to the query point (Supp. Sec. 4).
 //
-// The crossing count is locally constant, so only the boundary term is
-// differentiated: per boundary edge (a, b), with r0 = a - p, r1 = b - p and the
-// same N, D as the value path (x1 = -z),
-//     grad 2 atan2(N, D) = 2 (D grad N - N grad D) / (N^2 + D^2),
-//     grad N = (r1y - r0y, r0x - r1x, 0),
-//     grad D = -((1 + s1/l0) r0 + (1 + s0/l1) r1) + (l0 + l1) z^,
-// whose z part simplifies to s0 s1 (1/l0 + 1/l1) (no cancellation).  N and D are
-// scaled by 1/(l0 l1) before squaring so nothing overflows in cell units.  No
-// exact predicate is needed: the derivative of atan2 is the same on both sides
-// of its branch cut, so every query uses raw offsets.
+// The crossing count is locally constant, so only the boundary term has a gradient,
+// and the gradient of a loop's solid angle is a line integral along the loop that
+// needs no auxiliary direction (the Biot-Savart field of the loop).  Per directed
+// boundary edge (a, b), with r0 = a - p, r1 = b - p and l = |r|:
 //
-// A boundary vertex exactly above the query (on the +z ray) makes N = D = 0 for
-// its two edges; their divergent terms cancel in the sum but their values are
-// 0/0.  Such a query is summed again with the opposite axis (x0 = -z): the
-// gradient does not depend on the axis, and mirroring z maps that sum onto the
-// same code with r_z negated and the x, y components negated.  A query with
-// boundary vertices both above and below it takes a third pass with a general
-// axis (grad_run_axis, in kernels of its own).  Grids share the x/y quantities (N, grad N, the x/y
-// dot) of a column among its samples.
+//     grad = c (l0 + l1) / (l0 l1 (l0 l1 + r0.r1)),   c = r0 x r1 = r0 x (b - a),
+//
+// 4 pi grad w being the sum.  Alg. 3 sums the derivative of 2 atan2(N, D) for an axis
+// x0 instead: the same total, per edge twice the work (l, s, and two quotients), and
+// 0/0 for a query whose line along x0 meets a boundary vertex, which then has to be
+// summed again for another axis.  The form here is singular on the edge alone.
+//
+// Where r0.r1 < 0 the bracket cancels next to the edge; there it is
+// |c|^2 / (l0 l1 - r0.r1), exactly the same, and c, from the edge's own vector, is
+// rounded once, so the term keeps its digits up to the edge.
+// FP32 offsets are in units of 2^18 cells (times 2^e for far queries, see far_scale):
+// an offset stays below 2^23 and the products below 2^118.
+//
+// Grids share a column's x/y terms among its samples as for w, and sum the chunks far
+// from a block of columns at its nodes (gwn_far.h).
 #include <algorithm>
 
+#include "gwn_alloc.h"
+#include "gwn_far.h"
 #include "gwn_kernels.h"
 #include "gwn_mesh.h"
 
 namespace gwn {
 namespace {
 
-// x/y part of one boundary vertex relative to the query column, shared by all
-// samples of a grid column.  Offsets are in units of 2^e cells (f = 2^-e, see
-// far_scale): each edge term is homogeneous of degree -1 in the offsets, so the
-// sum is rescaled at the end.
+// cells per offset unit
 template <class T>
-struct GCol {
-    T rx, ry, rho2;
+constexpr float kGradUnit = sizeof(T) == 4 ? 0x1p18f : 1.0f;
+
+// x y - z w, correctly rounded to about an ulp however far it cancels
+template <class T>
+__device__ __forceinline__ T diff_of_products(T x, T y, T z, T w) {
+    const T p = z * w;
+    return fma(x, y, -p) + fma(-z, w, p);
+}
+
+// One edge's term added to g, given c, the dot product and the two lengths.  A lane
+// with dot < 0 (the query beside the edge) takes c from exact(), without
+// cancellation; the wave looks for one first, and each lane's result is its own.
+template <class T, class F>
+__device__ __forceinline__ void grad_term(T cx, T cy, T cz, T dot, T la, T lb, F&& exact, bool general, T* g) {
+    const T ll = la * lb;
+    T den = ll * (ll + dot), num = la + lb;
+    if (general) {
+        const bool neg = dot < (T)0;
+        T x, y, z;
+        exact(x, y, z);
+        cx = neg ? x : cx;
+        cy = neg ? y : cy;
+        cz = neg ? z : cz;
+        den = neg ? ll * fma(x, x, fma(y, y, z * z)) : den;
+        num = neg ? num * (ll - dot) : num;
+    }
+    const T f = num * Arith<T>::rcp(den);
+    g[0] = fma(cx, f, g[0]);
+    g[1] = fma(cy, f, g[1]);
+    g[2] = fma(cz, f, g[2]);
+}
+
+// ---------------------------------------------------------------- points
+
+template <class T>
+struct GVert {
+    T x, y, z, l;   // offset and length
 };
 
 template <class T>
-__device__ __forceinline__ GCol<T> gcol(const BVert& b, T pxs, T pys, T f) {
-    GCol<T> c;
-    c.rx = fma((T)b.x, f, -pxs);
-    c.ry = fma((T)b.y, f, -pys);
-    c.rho2 = c.rx * c.rx + c.ry * c.ry;
-    return c;
+__device__ __forceinline__ GVert<T> grad_vert(const BVert& b, T px, T py, T pz, T f) {
+    GVert<T> v;
+    v.x = fma((T)b.x, f, -px);
+    v.y = fma((T)b.y, f, -py);
+    v.z = fma((T)b.z, f, -pz);
+    v.l = Arith<T>::sqrt(fma(v.x, v.x, fma(v.y, v.y, v.z * v.z)));
+    return v;
 }
 
-// per-sample part of one vertex: u = 1/l and s = l - r_z (r_z negated for FLIP)
-template <class T, bool FLIP>
-__device__ __forceinline__ void gsamp(const BVert& b, const GCol<T>& c, T pzs, T f, T& u, T& s) {
-    const T rz0 = fma((T)b.z, f, -pzs);
-    const T rz = FLIP ? -rz0 : rz0;
-    const T l = Arith<T>::sqrt(rz * rz + c.rho2);
-    u = Arith<T>::rcp(l);
-    const T t = l + fabs(rz);
-    s = rz > (T)0 ? c.rho2 * Arith<T>::rcp(t) : t;
-}
-
-// one edge (a -> b) for one sample; N, dot and grad N come from x/y only
+// Sum over chunks c0, c0 + step, ... for one point; FP32 partials are flushed to FP64
+// every 4 chunks.
 template <class T>
-__device__ __forceinline__ void gedge(const GCol<T>& a, const GCol<T>& b, T N, T dot, T gNx, T gNy, T ua, T sa,
-                                      T ub, T sb, T* g) {
-    const T k = ua * ub;
-    const T n = N * k;
-    const T d = fma(sa, sb, dot) * k;
-    const T c0 = (T)1 + sb * ua, c1 = (T)1 + sa * ub;
-    const T dDx = -(c0 * a.rx + c1 * b.rx);
-    const T dDy = -(c0 * a.ry + c1 * b.ry);
-    const T dDz = sa * sb * (ua + ub);
-    const T fr = k * Arith<T>::rcp(n * n + d * d);
-    g[0] += (d * gNx - n * dDx) * fr;
-    g[1] += (d * gNy - n * dDy) * fr;
-    g[2] += (-n * dDz) * fr;
-}
-
-// Sum over all loops of the edge terms for ZB samples on one vertical line, in
-// cell units (FP32 partials flushed into FP64 every 32 edges).  FLIP: the
-// mirrored sum for the axis x0 = -z.
-template <class T, int ZB, bool FLIP>
-__device__ void grad_loops(const MeshView& mv, T pxs, T pys, const T* pzs, T f, double (*G)[3]) {
-    const BVert* __restrict__ bv = mv.bverts;
+__device__ __forceinline__ void grad_chunks_point(const MeshView& mv, int c0, int step, T px, T py, T pz, T f, double* G) {
+    G[0] = G[1] = G[2] = 0.0;
+    T acc[3] = {(T)0, (T)0, (T)0};
+    int left = 4;
+    for (int c = c0; c < mv.nchunk; c += step) {
+        const BVert* __restrict__ v = mv.chain + (size_t)c * kChunk;
+        BVert a = v[0];
+        GVert<T> ra = grad_vert<T>(a, px, py, pz, f);
 #pragma unroll
-    for (int r = 0; r < ZB; ++r) G[r][0] = G[r][1] = G[r][2] = 0.0;
-    for (int lp = 0; lp < mv.nloops; ++lp) {
-        const int b0 = mv.loop_off[lp], b1 = mv.loop_off[lp + 1];
-        const GCol<T> cf = gcol<T>(bv[b0], pxs, pys, f);
-        T uf[ZB], sf[ZB];
-#pragma unroll
-        for (int r = 0; r < ZB; ++r) gsamp<T, FLIP>(bv[b0], cf, pzs[r], f, uf[r], sf[r]);
-        GCol<T> cp = cf;
-        T up[ZB], sp[ZB];
-#pragma unroll
-        for (int r = 0; r < ZB; ++r) {
-            up[r] = uf[r];
-            sp[r] = sf[r];
-        }
-        for (int j = b0 + 1; j <= b1; j += 32) {
-            const int je = min(b1 + 1, j + 32);
-            T acc[ZB][3];
-#pragma unroll
-            for (int r = 0; r < ZB; ++r) acc[r][0] = acc[r][1] = acc[r][2] = (T)0;
-            for (int jj = j; jj < je; ++jj) {
-                // index b1 closes the loop back to its first vertex
-                GCol<T> cc = cf;
-                T uc[ZB], sc[ZB];
-#pragma unroll
-                for (int r = 0; r < ZB; ++r) {
-                    uc[r] = uf[r];
-                    sc[r] = sf[r];
-                }
-                if (jj < b1) {
-                    cc = gcol<T>(bv[jj], pxs, pys, f);
-#pragma unroll
-                    for (int r = 0; r < ZB; ++r) gsamp<T, FLIP>(bv[jj], cc, pzs[r], f, uc[r], sc[r]);
-                }
-                const T N = cp.ry * cc.rx - cp.rx * cc.ry;
-                const T dot = cp.rx * cc.rx + cp.ry * cc.ry;
-                const T gNx = cc.ry - cp.ry, gNy = cp.rx - cc.rx;
-#pragma unroll
-                for (int r = 0; r < ZB; ++r) gedge<T>(cp, cc, N, dot, gNx, gNy, up[r], sp[r], uc[r], sc[r], acc[r]);
-                cp = cc;
-#pragma unroll
-                for (int r = 0; r < ZB; ++r) {
-                    up[r] = uc[r];
-                    sp[r] = sc[r];
-                }
+        for (int e = 1; e < kChunk; ++e) {
+            const BVert b = v[e];
+            const GVert<T> rb = grad_vert<T>(b, px, py, pz, f);
+            if (a.pad1 & kChainEdge) {
+                const T ex = ((T)b.x - (T)a.x) * f, ey = ((T)b.y - (T)a.y) * f, ez = ((T)b.z - (T)a.z) * f;
+                const T dot = fma(ra.x, rb.x, fma(ra.y, rb.y, ra.z * rb.z));
+                grad_term<T>(
+                    fma(ra.y, ez, -(ra.z * ey)), fma(ra.z, ex, -(ra.x * ez)), fma(ra.x, ey, -(ra.y * ex)), dot, ra.l, rb.l,
+                    [&](T& x, T& y, T& z) {
+                        x = diff_of_products(ra.y, ez, ra.z, ey);
+                        y = diff_of_products(ra.z, ex, ra.x, ez);
+                        z = diff_of_products(ra.x, ey, ra.y, ex);
+                    },
+                    __builtin_amdgcn_ballot_w64(dot < (T)0) != 0ull, acc);
             }
-#pragma unroll
-            for (int r = 0; r < ZB; ++r)
-#pragma unroll
-                for (int c = 0; c < 3; ++c) G[r][c] += (double)acc[r][c];
+            a = b;
+            ra = rb;
+        }
+        if (--left == 0) {
+            for (int k = 0; k < 3; ++k) {
+                G[k] += (double)acc[k];
+                acc[k] = (T)0;
+            }
+            left = 4;
         }
     }
-    if (FLIP) {
-#pragma unroll
-        for (int r = 0; r < ZB; ++r) {
-            G[r][0] = -G[r][0];
-            G[r][1] = -G[r][1];
-        }
-    }
+    for (int k = 0; k < 3; ++k) G[k] += (double)acc[k];
 }
 
-// Grid columns: a boundary vertex's x/y terms (its offsets, rho^2, and N, the
-// x/y dot and grad N of its outgoing edge) are the same for every sample of a
-// column's wave, so they are computed for 64 vertices at a time, one per lane,
-// into a ring of records in LDS that the whole wave reads back (as for w; the
-// ring's slots, fills and closing slot follow column_loops).
+// a point's offsets' scale and its coordinates in offset units
 template <class T>
-struct alignas(4 * sizeof(T)) GRec {
-    T z;      // vertex z as stored (offset units once times f)
-    T rho2;
-    T rx, ry;
+struct GPoint {
+    T f, x, y, z;
+    double out;   // the sum's factor: 1 / (4 pi) and the chain rule through the units
 };
 
 template <class T>
-struct alignas(4 * sizeof(T)) GEdge {   // the vertex's outgoing edge
-    T N, dot, gNx, gNy;
-};
-
-template <class T>
-struct GRing {
-    GRec<T> v[kColRing + 1];
-    GEdge<T> e[kColRing + 1];
-    int R[kColRing + 1];   // blocks of the column with a sample below the vertex (see the sample blocks note in gwn_kernels.h), plus 256
-                           // when the vertex is far (s_blocks)
-};
-
-template <class T, int ZB>
-__device__ __forceinline__ void grad_fill(const MeshView& mv, int v0, int n, int b0, int b1, T pxs, T pys, T f,
-                                          const T* bminr, bool asc, GRing<T>& ring) {
-    const int lane = (int)(threadIdx.x & 63);
-    if (lane < n) {
-        const int v = v0 + lane;
-        const int vn = v + 1 < b1 ? v + 1 : b0;
-        const BVert a = mv.bverts[v], b = mv.bverts[vn];
-        const GCol<T> ca = gcol<T>(a, pxs, pys, f), cb = gcol<T>(b, pxs, pys, f);
-        GRec<T> rv;
-        rv.z = (T)a.z;
-        rv.rho2 = ca.rho2;
-        rv.rx = ca.rx;
-        rv.ry = ca.ry;
-        GEdge<T> re;
-        re.N = ca.ry * cb.rx - ca.rx * cb.ry;
-        re.dot = ca.rx * cb.rx + ca.ry * cb.ry;
-        re.gNx = cb.ry - ca.ry;
-        re.gNy = ca.rx - cb.rx;
-        int R = ZB + 1;
-        if (asc) {
-            R = 0;
-            bool farv = true;   // every sample below the vertex has r_z^2 <= 3 rho^2 (see s_blocks)
-#pragma unroll
-            for (int r = 0; r < ZB; ++r) {
-                const T zr = fma((T)a.z, f, -bminr[r]);   // the block's largest r_z
-                R += zr > (T)0;
-                farv &= !((zr > (T)0) & (zr * zr > (T)3 * rv.rho2));
-            }
-            R |= farv ? 256 : 0;
-        }
-        const int k = (v - b0) & (kColRing - 1);
-        ring.v[k] = rv;
-        ring.e[k] = re;
-        ring.R[k] = R;
-        if (v == b0) {
-            ring.v[kColRing] = rv;
-            ring.e[kColRing] = re;
-            ring.R[kColRing] = R;
-        }
-    }
-    // the wave reads what its own lanes wrote; LDS operations of a wave complete in order
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+__device__ __forceinline__ GPoint<T> grad_point(const QGrid& g, float px, float py, float pz, float pzmax) {
+    constexpr T u = (T)1 / (T)kGradUnit<T>;
+    const FarScale<T> fs = far_scale<T>(px, py, pzmax, g.scale);
+    GPoint<T> p;
+    p.f = fs.f * u;
+    const T s = fs.scf * u;
+    p.x = (T)px * s;
+    p.y = (T)py * s;
+    p.z = (T)pz * s;
+    p.out = 0.5 * kInv2Pi * (double)s;
+    return p;
 }
-
-// u = 1/l and s of one ring vertex for the ZB samples: blocks wholly at or above
-// the vertex take s = l + |r_z|, blocks wholly below it s = rho^2 / (l + r_z),
-// the block the vertex's height falls in the two-sided form, and a far vertex
-// l - r_z in every block (the block count and the far test are the w kernel's;
-// r_z is the same fma in both)
-template <class T, int ZB>
-__device__ __forceinline__ void grad_vertex(const GRec<T>& c, int R, const T* pzs, T f, T* u, T* s) {
-    T rz[ZB];
-#pragma unroll
-    for (int r = 0; r < ZB; ++r) {
-        rz[r] = fma(c.z, f, -pzs[r]);
-        const T l = Arith<T>::sqrt(rz[r] * rz[r] + c.rho2);
-        u[r] = Arith<T>::rcp(l);
-        s[r] = l + fabs(rz[r]);   // t, made s in place
-    }
-    s_prefix<T, ZB>(R & 0xff, rz, c.rho2, s, R >= 256);
-}
-
-// grad_loops for a grid column (x0 = +z), register r of the wave a block of 64
-// consecutive samples with z monotone in the lane; same sums in the same order.
-template <class T, int ZB>
-__device__ void grad_column_loops(const MeshView& mv, T pxs, T pys, const T* pzs, T f, double (*G)[3],
-                                  GRing<T>& ring) {
-    T bminr[ZB];
-    bool asc = true;
-    T prev = -(T)INFINITY;
-#pragma unroll
-    for (int r = 0; r < ZB; ++r) {   // ascending blocks with non-falling minima, as for w (column_loops)
-        const T z0 = wave_lane<T>(pzs[r], 0), z63 = wave_lane<T>(pzs[r], 63);
-        bminr[r] = fmin(z0, z63);
-        asc &= !(bminr[r] < prev) & !(z63 < z0);
-        prev = bminr[r];
-    }
-#pragma unroll
-    for (int r = 0; r < ZB; ++r) G[r][0] = G[r][1] = G[r][2] = 0.0;
-    for (int lp = 0; lp < mv.nloops; ++lp) {
-        const int b0 = mv.loop_off[lp], nv = mv.loop_off[lp + 1] - b0;
-        int done = min(64, nv);
-        grad_fill<T, ZB>(mv, b0, done, b0, b0 + nv, pxs, pys, f, bminr, asc, ring);
-        T up[ZB], sp[ZB];
-        grad_vertex<T, ZB>(ring.v[0], __builtin_amdgcn_readfirstlane(ring.R[0]), pzs, f, up, sp);
-        T prx = ring.v[0].rx, pry = ring.v[0].ry;
-        // edge j leads from vertex j - 1 to vertex j; j = nv closes the loop
-        for (int j = 1; j <= nv; j += 32) {
-            const int je = min(nv + 1, j + 32);
-            if (min(je, nv) > done) {   // one fill covers it: j <= done, je <= j + 32
-                const int n = min(64, nv - done);
-                grad_fill<T, ZB>(mv, b0 + done, n, b0, b0 + nv, pxs, pys, f, bminr, asc, ring);
-                done += n;
-            }
-            T acc[ZB][3];
-#pragma unroll
-            for (int r = 0; r < ZB; ++r) acc[r][0] = acc[r][1] = acc[r][2] = (T)0;
-            for (int jj = j; jj < je; ++jj) {
-                const int kp = (jj - 1) & (kColRing - 1), kc = jj < nv ? (jj & (kColRing - 1)) : kColRing;
-                const GRec<T> c = ring.v[kc];
-                const GEdge<T> e = ring.e[kp];
-                T uc[ZB], sc[ZB];
-                grad_vertex<T, ZB>(c, __builtin_amdgcn_readfirstlane(ring.R[kc]), pzs, f, uc, sc);
-                GCol<T> ga, gb;
-                ga.rx = prx;
-                ga.ry = pry;
-                gb.rx = c.rx;
-                gb.ry = c.ry;
-                ga.rho2 = gb.rho2 = (T)0;   // not used by gedge
-#pragma unroll
-                for (int r = 0; r < ZB; ++r) gedge<T>(ga, gb, e.N, e.dot, e.gNx, e.gNy, up[r], sp[r], uc[r], sc[r], acc[r]);
-                prx = c.rx;
-                pry = c.ry;
-#pragma unroll
-                for (int r = 0; r < ZB; ++r) {
-                    up[r] = uc[r];
-                    sp[r] = sc[r];
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < ZB; ++r)
-#pragma unroll
-                for (int cc = 0; cc < 3; ++cc) G[r][cc] += (double)acc[r][cc];
-        }
-    }
-}
-
-// Third pass, for samples whose lines along +z and -z both meet a boundary
-// vertex (vertical stacks of boundary vertices), where both folded forms above
-// are 0/0: the edge term of Alg. 3 for a general axis x0 = u, x1 = -u, in FP64
-// on the same offsets.  u is fixed and in no special relation to the grid or
-// the coordinate axes, so a sample whose line along u also meets a vertex is
-// left as 0/0, as with the paper's random choice of axis.  Per edge, with
-// r0 = a - p, r1 = b - p, l = |r|, v = r / l:
-//     n = x1.(r0 x r1),   d = l0 l1 + l1 x1.r0 + l0 x1.r1 + r0.r1,
-//     grad n = -(r1 x x1 + x1 x r0),
-//     grad d = -(l1 (x1 + v1 + (1 + x1.v1) v0) + l0 (x1 + v0 + (1 + x1.v0) v1)),
-// and the term (d grad n - n grad d) / (n^2 + d^2) is the gradient of
-// atan2(n, d), as the folded forms sum it.
-__device__ __forceinline__ void grad_axis_x1(double* x1) {
-    const double a = 0.5381966011250105, b = 0.4142135623730950, c = 0.7320508075688772;
-    const double k = -1.0 / sqrt(a * a + b * b + c * c);
-    x1[0] = a * k;
-    x1[1] = b * k;
-    x1[2] = c * k;
-}
-
-__device__ __forceinline__ void cross3(const double* u, const double* v, double* w) {
-    w[0] = u[1] * v[2] - u[2] * v[1];
-    w[1] = u[2] * v[0] - u[0] * v[2];
-    w[2] = u[0] * v[1] - u[1] * v[0];
-}
-
-__device__ __forceinline__ double dot3(const double* u, const double* v) {
-    return u[0] * v[0] + u[1] * v[1] + u[2] * v[2];
-}
-
-__device__ __forceinline__ void grad_axis_edge(const double* r0, const double* r1, const double* x1, double* g) {
-    const double l0 = sqrt(dot3(r0, r0)), l1 = sqrt(dot3(r1, r1));
-    double v0[3], v1[3], c[3], c1[3], c0[3];
-    for (int k = 0; k < 3; ++k) {
-        v0[k] = r0[k] / l0;
-        v1[k] = r1[k] / l1;
-    }
-    cross3(r0, r1, c);
-    const double n = dot3(x1, c);
-    const double d = l0 * l1 + l1 * dot3(x1, r0) + l0 * dot3(x1, r1) + dot3(r0, r1);
-    cross3(r1, x1, c1);
-    cross3(x1, r0, c0);
-    const double e1 = 1.0 + dot3(x1, v1), e0 = 1.0 + dot3(x1, v0);
-    const double inv = 1.0 / (n * n + d * d);
-    for (int k = 0; k < 3; ++k) {
-        const double gn = -(c1[k] + c0[k]);
-        const double gd = -(l1 * (x1[k] + v1[k] + e1 * v0[k]) + l0 * (x1[k] + v0[k] + e0 * v1[k]));
-        g[k] += (d * gn - n * gd) * inv;
-    }
-}
-
-// the third pass over boundary vertices [a, e) (edge j leads to the next vertex
-// of its loop) for ZB samples on one vertical line
-template <int ZB>
-__device__ void grad_run_axis(const MeshView& mv, int a, int e, double pxs, double pys, const double* pzs, double f,
-                              double (*G)[3]) {
-    double x1[3];
-    grad_axis_x1(x1);
-#pragma unroll
-    for (int r = 0; r < ZB; ++r) G[r][0] = G[r][1] = G[r][2] = 0.0;
-    const BVert* __restrict__ bv = mv.bverts;
-    for (int j = a; j < e; ++j) {
-        const int lp = min(max(bv[j].loop, 0), mv.nloops - 1);   // in range for any stored value
-        const int nx = j + 1 < mv.loop_off[lp + 1] ? j + 1 : mv.loop_off[lp];
-        const BVert A = bv[j], B = bv[nx];
-        const double ax = fma((double)A.x, f, -pxs), ay = fma((double)A.y, f, -pys);
-        const double bx = fma((double)B.x, f, -pxs), by = fma((double)B.y, f, -pys);
-#pragma unroll
-        for (int r = 0; r < ZB; ++r) {
-            const double r0[3] = {ax, ay, fma((double)A.z, f, -pzs[r])};
-            const double r1[3] = {bx, by, fma((double)B.z, f, -pzs[r])};
-            grad_axis_edge(r0, r1, x1, G[r]);
-        }
-    }
-}
-
-__device__ __forceinline__ bool finite3(const double* g) { return isfinite(g[0]) && isfinite(g[1]) && isfinite(g[2]); }
 
 template <class T>
 __global__ __launch_bounds__(256) void k_grad_batch(MeshView mv, const float* __restrict__ qx,
@@ -380,83 +150,16 @@ __global__ __launch_bounds__(256) void k_grad_batch(MeshView mv, const float* __
     const long long i = blockIdx.x * 256ll + threadIdx.x;
     if (blockIdx.x * 256ll >= nq) return;
     const long long ii = i < nq ? i : nq - 1;
-    const float px = qx[ii * qs], py = qy[ii * qs], pz = qz[ii * qs];
-    const FarScale<T> fs = far_scale<T>(px, py, fabsf(pz), mv.g.scale);
-    const T pxs = (T)px * fs.scf, pys = (T)py * fs.scf, pzs = (T)pz * fs.scf;
-    double G[1][3];
-    grad_loops<T, 1, false>(mv, pxs, pys, &pzs, fs.f, G);
-    if (!finite3(G[0])) grad_loops<T, 1, true>(mv, pxs, pys, &pzs, fs.f, G);
-    if (i < nq) {
-        // sum of 2 atan2 terms over 4 pi, and the chain rule through p * 2^(k-e)
-        const double f = kInv2Pi * (double)fs.scf;
-        // frame component c is world component (c + axis) % 3
-        for (int c = 0; c < 3; ++c) g[3 * i + (c + axis) % 3] = (T)(G[0][c] * f);
-    }
+    const GPoint<T> p = grad_point<T>(mv.g, qx[ii * qs], qy[ii * qs], qz[ii * qs], fabsf(qz[ii * qs]));
+    double G[3];
+    grad_chunks_point<T>(mv, 0, 1, p.x, p.y, p.z, p.f, G);
+    if (i < nq)   // frame component c is world component (c + axis) % 3
+        for (int c = 0; c < 3; ++c) g[3 * i + (c + axis) % 3] = (T)(G[c] * p.out);
 }
 
-// Few points against many boundary edges: one workgroup per point, each lane a
-// contiguous run of boundary vertices (edge j leads to the next vertex of its
-// loop), reduced by wave shuffles and LDS in a fixed order.  FLIP as above.
+// Few points against many boundary edges: one workgroup per point, the chunks dealt
+// out to its lanes, reduced by wave shuffles and LDS in a fixed order.
 constexpr int kSplitThreads = 256;
-
-template <class T, bool FLIP>
-__device__ void grad_run(const MeshView& mv, int a, int e, T pxs, T pys, T pzs, T f, double* G) {
-    G[0] = G[1] = G[2] = 0.0;
-    if (a >= e) return;
-    const BVert* __restrict__ bv = mv.bverts;
-    GCol<T> cp = gcol<T>(bv[a], pxs, pys, f);
-    T up, sp;
-    gsamp<T, FLIP>(bv[a], cp, pzs, f, up, sp);
-    T acc[3] = {(T)0, (T)0, (T)0};
-    int cnt = 0;
-    for (int j = a; j < e; ++j) {
-        const int lp = min(max(bv[j].loop, 0), mv.nloops - 1);   // in range for any stored value
-        const int nx = j + 1 < mv.loop_off[lp + 1] ? j + 1 : mv.loop_off[lp];
-        const GCol<T> cn = gcol<T>(bv[nx], pxs, pys, f);
-        T un, sn;
-        gsamp<T, FLIP>(bv[nx], cn, pzs, f, un, sn);
-        const T N = cp.ry * cn.rx - cp.rx * cn.ry;
-        const T dot = cp.rx * cn.rx + cp.ry * cn.ry;
-        gedge<T>(cp, cn, N, dot, cn.ry - cp.ry, cp.rx - cn.rx, up, sp, un, sn, acc);
-        if (++cnt == 32) {
-            for (int c = 0; c < 3; ++c) {
-                G[c] += (double)acc[c];
-                acc[c] = (T)0;
-            }
-            cnt = 0;
-        }
-        if (j + 1 < e) {
-            if (nx == j + 1) {
-                cp = cn;
-                up = un;
-                sp = sn;
-            } else {   // the next edge starts a new loop
-                cp = gcol<T>(bv[j + 1], pxs, pys, f);
-                gsamp<T, FLIP>(bv[j + 1], cp, pzs, f, up, sp);
-            }
-        }
-    }
-    for (int c = 0; c < 3; ++c) G[c] += (double)acc[c];
-    if (FLIP) {
-        G[0] = -G[0];
-        G[1] = -G[1];
-    }
-}
-
-// sum of the workgroup's per-lane vectors, the same in every lane afterwards
-__device__ void block_sum3(double* G, double (*red)[3]) {
-    for (int c = 0; c < 3; ++c)
-        for (int o = 32; o > 0; o >>= 1) G[c] += __shfl_xor(G[c], o);
-    __syncthreads();   // red may still be read from a previous call
-    if ((threadIdx.x & 63) == 0)
-        for (int c = 0; c < 3; ++c) red[threadIdx.x >> 6][c] = G[c];
-    __syncthreads();
-    for (int c = 0; c < 3; ++c) {
-        double t = 0.0;
-        for (int k = 0; k < kSplitThreads / 64; ++k) t += red[k][c];
-        G[c] = t;
-    }
-}
 
 template <class T>
 __global__ __launch_bounds__(kSplitThreads) void k_grad_split(MeshView mv, const float* __restrict__ qx,
@@ -466,139 +169,294 @@ __global__ __launch_bounds__(kSplitThreads) void k_grad_split(MeshView mv, const
     __shared__ double red[kSplitThreads / 64][3];
     const long long i = blockIdx.x;   // one point per workgroup
     if (i >= nq) return;
-    const float px = qx[i * qs], py = qy[i * qs], pz = qz[i * qs];
-    const FarScale<T> fs = far_scale<T>(px, py, fabsf(pz), mv.g.scale);
-    const T pxs = (T)px * fs.scf, pys = (T)py * fs.scf, pzs = (T)pz * fs.scf;
-    const int nb = mv.loop_off[mv.nloops];
-    const int per = (nb + kSplitThreads - 1) / kSplitThreads;
-    const int a = (int)threadIdx.x * per, e = min(nb, a + per);
+    const GPoint<T> p = grad_point<T>(mv.g, qx[i * qs], qy[i * qs], qz[i * qs], fabsf(qz[i * qs]));
     double G[3];
-    grad_run<T, false>(mv, a, e, pxs, pys, pzs, fs.f, G);
-    block_sum3(G, red);
-    if (!finite3(G)) {   // uniform: every lane holds the same sum
-        grad_run<T, true>(mv, a, e, pxs, pys, pzs, fs.f, G);
-        block_sum3(G, red);
-    }
-    if (threadIdx.x == 0) {
-        const double f = kInv2Pi * (double)fs.scf;
-        for (int c = 0; c < 3; ++c) g[3 * i + (c + axis) % 3] = (T)(G[c] * f);
+    grad_chunks_point<T>(mv, (int)threadIdx.x, kSplitThreads, p.x, p.y, p.z, p.f, G);
+    for (int c = 0; c < 3; ++c)
+        for (int o = 32; o > 0; o >>= 1) G[c] += __shfl_xor(G[c], o);
+    if ((threadIdx.x & 63) == 0)
+        for (int c = 0; c < 3; ++c) red[threadIdx.x >> 6][c] = G[c];
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        const int c = threadIdx.x;
+        double t = 0.0;
+        for (int k = 0; k < kSplitThreads / 64; ++k) t += red[k][c];
+        g[3 * i + (c + axis) % 3] = (T)(t * p.out);
     }
 }
 
-// Gradient on a grid: one wave per (column, z-chunk) as for w, ZB samples per
-// lane (lane l holds samples l + 64 r of the chunk) sharing the column's x/y
-// terms.  A column through a boundary vertex
-// makes the samples below it 0/0 on the +z axis; if any lane has such a sample,
-// the wave sums the mirrored axis too and those samples take that sum.
+// ---------------------------------------------------------------- grid columns
+// Records of 64 chained vertices in LDS, one per lane, as for w: the vertex's z and
+// x/y distance and everything about its outgoing edge that the column's samples share.
+template <class T>
+struct alignas(4 * sizeof(T)) GRec {
+    T zu, rho2, ex, ey;   // vertex z, r_x^2 + r_y^2; the edge's x, y
+};
+
+template <class T>
+struct alignas(4 * sizeof(T)) GEdge {
+    T a, b, cz, dot;      // r_y e_z, r_x e_z, c_z and the x/y dot
+};
+
+template <class T>
+struct GAux {             // beside the edge only
+    T rx, ry, ez;
+};
+
+template <class T>
+struct GBuf {
+    GRec<T> v[kColRecs];
+    GEdge<T> e[kColRecs];
+    GAux<T> x[kColRecs];
+    int queue[64 + kColChunks];
+};
+
+template <class T>
+__device__ __forceinline__ void grad_fill(const MeshView& mv, const int* queue, int n, T px, T py, T f, GBuf<T>& buf) {
+    int lane = (int)(threadIdx.x & 63);
+    asm volatile("" : "+v"(lane));   // addresses formed per fill (see col_fill)
+    const int c = lane >> 3, en = lane & 7;
+    if (c < n) {
+        const BVert* v = mv.chain + (size_t)queue[c] * kChunk;
+        const BVert a = v[en], b = v[min(en + 1, kChunk - 1)];
+        const bool edge = (a.pad1 & kChainEdge) != 0;
+        const T ax = fma((T)a.x, f, -px), ay = fma((T)a.y, f, -py);
+        const T bx = fma((T)b.x, f, -px), by = fma((T)b.y, f, -py);
+        const T ex = edge ? ((T)b.x - (T)a.x) * f : (T)0, ey = edge ? ((T)b.y - (T)a.y) * f : (T)0;
+        const T ez = edge ? ((T)b.z - (T)a.z) * f : (T)0;
+        // between two pieces no edge: c = 0, and a large dot product keeps the bracket positive
+        buf.v[lane] = {(T)a.z * f, ax * ax + ay * ay, ex, ey};
+        buf.x[lane] = {ax, ay, ez};
+        buf.e[lane] = {ay * ez, ax * ez, fma(ax, ey, -(ay * ex)), edge ? ax * bx + ay * by : (T)1e30};
+    }
+    wave_lds_sync();
+}
+
+// Sum over the chunks that `flt` keeps, added to S[c * ZB + r] (component c, sample r),
+// for the ZB samples of each lane of a column; px, py, pz in offset units.  FP32
+// partials are flushed to FP64 every 32 edges.
 template <class T, int ZB>
-__global__ __launch_bounds__(64 * kGridWaves) void k_grad_grid(MeshView mv, GridArgs ga, int axis,
-                                                               T* __restrict__ g) {
-    __shared__ GRing<T> ring[kGridWaves];
+__device__ __forceinline__ void grad_column(const MeshView& mv, const ChunkFilter& flt, T px, T py, const T* pz, T f,
+                                            double* S, int part, int parts, GBuf<T>& buf) {
+    T rza[ZB], la[ZB];
+    GRec<T> va = {(T)0, (T)0, (T)0, (T)0};   // the vertex before the current one: none yet
+    GEdge<T> ea = {(T)0, (T)0, (T)0, (T)1e30};
+#pragma unroll
+    for (int r = 0; r < ZB; ++r) {
+        rza[r] = (T)0;
+        la[r] = (T)1;
+    }
+    ChunkQueue q(mv, part, parts, buf.queue);
+    while (true) {
+        const int n = q.next(mv, flt);
+        if (n == 0) break;
+        grad_fill<T>(mv, q.ids(n), n, px, py, f, buf);
+        for (int k = 0; k < n * kChunk;) {
+            const int ke = min(n * kChunk, k + 32);
+            T acc[ZB][3];
+#pragma unroll
+            for (int r = 0; r < ZB; ++r) acc[r][0] = acc[r][1] = acc[r][2] = (T)0;
+#pragma unroll 4
+            for (; k < ke; ++k) {
+                const GRec<T> vb = buf.v[k];
+                const GEdge<T> eb = buf.e[k];
+                T rzb[ZB], lb[ZB], dot[ZB];
+                bool neg = false;
+#pragma unroll
+                for (int r = 0; r < ZB; ++r) {
+                    rzb[r] = vb.zu - pz[r];
+                    lb[r] = Arith<T>::sqrt(fma(rzb[r], rzb[r], vb.rho2));
+                    dot[r] = fma(rza[r], rzb[r], ea.dot);
+                    neg |= dot[r] < (T)0;
+                }
+                const bool general = __builtin_amdgcn_ballot_w64(neg) != 0ull;
+#pragma unroll
+                for (int r = 0; r < ZB; ++r) {
+                    grad_term<T>(
+                        fma(-rza[r], va.ey, ea.a), fma(rza[r], va.ex, -ea.b), ea.cz, dot[r], la[r], lb[r],
+                        [&](T& x, T& y, T& z) {
+                            const GAux<T> a = buf.x[k > 0 ? k - 1 : 0];   // (record 0 is entered by no edge)
+                            x = diff_of_products(a.ry, a.ez, rza[r], va.ey);
+                            y = diff_of_products(rza[r], va.ex, a.rx, a.ez);
+                            z = diff_of_products(a.rx, va.ey, a.ry, va.ex);
+                        },
+                        general, acc[r]);
+                    rza[r] = rzb[r];
+                    la[r] = lb[r];
+                }
+                va = vb;
+                ea = eb;
+            }
+#pragma unroll
+            for (int r = 0; r < ZB; ++r)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) S[c * ZB + r] += (double)acc[r][c];
+        }
+    }
+}
+
+// Gradient on a grid: one wave per (column, z-chunk) as for w, ZB samples per lane
+// (lane l holds samples l + 64 r of the chunk); SPLIT as for w.
+template <class T, int ZB, bool SPLIT>
+__global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kGridWaves)) void k_grad_grid(MeshView mv, GridArgs ga, FarView far,
+                                                                                      int axis, T* __restrict__ g) {
+    constexpr int W = SPLIT ? kSplitWaves : kGridWaves;
+    __shared__ GBuf<T> buf[W];
+    __shared__ double farv[SPLIT ? 1 : W][kFarV];
+    __shared__ double part[SPLIT ? W : 1][SPLIT ? 64 * 3 * ZB : 1];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63;
-    const long long gw = ga.wave0 + (long long)blockIdx.x * kGridWaves + wave;
+    const long long gw = ga.wave0 + (SPLIT ? (long long)blockIdx.x : (long long)blockIdx.x * W + wave);
     if (gw >= ga.nwaves) return;
     const long long col = gw / ga.nchunks;
-    const long long chunk = gw - col * ga.nchunks;
-    const long long ci = col / ga.ny, cj = col - ci * ga.ny;
+    const int chunk = __builtin_amdgcn_readfirstlane((int)(gw - col * ga.nchunks));
+    const int ci = __builtin_amdgcn_readfirstlane((int)(col / ga.ny));
+    const int cj = __builtin_amdgcn_readfirstlane((int)(col - (long long)ci * ga.ny));
     const float px = grid_coord(ga.o[0], ga.s[0], ci);
     const float py = grid_coord(ga.o[1], ga.s[1], cj);
-    const long long k0 = chunk * 64 * ZB + lane;   // sample r is k0 + 64 r
+    const int nz = (int)ga.nz, k0 = chunk * 64 * ZB + lane;   // sample r is k0 + 64 r
     float pz[ZB], pzm = 0.f;
 #pragma unroll
     for (int r = 0; r < ZB; ++r) {
-        pz[r] = grid_coord(ga.o[2], ga.s[2], min(k0 + 64 * r, ga.nz - 1));
+        pz[r] = grid_coord(ga.o[2], ga.s[2], min(k0 + 64 * r, nz - 1));
         pzm = fmaxf(pzm, fabsf(pz[r]));
     }
-    const FarScale<T> fs = far_scale<T>(px, py, pzm, mv.g.scale);
+    // one scale for the column: its lanes share the records
+    for (int o = 32; o > 0; o >>= 1) pzm = fmaxf(pzm, __shfl_xor(pzm, o));
+    const GPoint<T> p = grad_point<T>(mv.g, px, py, 0.f, pzm);
+    constexpr T u = (T)1 / (T)kGradUnit<T>;
+    const T s = far_scale<T>(px, py, pzm, mv.g.scale).scf * u;
     T pzs[ZB];
-#pragma unroll
-    for (int r = 0; r < ZB; ++r) pzs[r] = (T)pz[r] * fs.scf;
-    const T pxs = (T)px * fs.scf, pys = (T)py * fs.scf;
-    double G[ZB][3];
-    grad_column_loops<T, ZB>(mv, pxs, pys, pzs, fs.f, G, ring[wave]);
-    bool bad = false;
-#pragma unroll
-    for (int r = 0; r < ZB; ++r) bad |= !finite3(G[r]);
-    if (__builtin_amdgcn_ballot_w64(bad) != 0ull) {
-        double H[ZB][3];
-        grad_loops<T, ZB, true>(mv, pxs, pys, pzs, fs.f, H);
-#pragma unroll
-        for (int r = 0; r < ZB; ++r)
-            if (!finite3(G[r]))
-                for (int c = 0; c < 3; ++c) G[r][c] = H[r][c];
-    }
-    const double f = kInv2Pi * (double)fs.scf;
-    const long long base = ci * ga.st[0] + cj * ga.st[1];
+    double S[3 * ZB];
 #pragma unroll
     for (int r = 0; r < ZB; ++r) {
-        const long long k = k0 + 64 * r;
-        if (k < ga.nz)
-            for (int c = 0; c < 3; ++c) g[3 * (base + k * ga.st[2]) + (c + axis) % 3] = (T)(G[r][c] * f);
+        pzs[r] = (T)pz[r] * s;
+        S[r] = S[ZB + r] = S[2 * ZB + r] = 0.0;
+    }
+    ChunkFilter flt{};
+    flt.mode = ChunkFilter::kAll;
+    if (far.on) {
+        flt.mode = ChunkFilter::kNear;
+        flt.x = far.cx[ci / far.bx];
+        flt.y = far.cy[cj / far.by];
+        flt.thr = far.thr;
+    }
+    grad_column<T, ZB>(mv, flt, p.x, p.y, pzs, p.f, S, SPLIT ? wave : 0, SPLIT ? W : 1, buf[wave]);
+    if constexpr (SPLIT) {
+        split_sum<3 * ZB, W>(wave, lane, S, part);
+        if (wave > 0) return;
+    }
+    if (far.on)
+        for (int c = 0; c < 3; ++c)
+            far_add<ZB>(far, ci, cj, chunk * 64 * ZB, nz, c, S + c * ZB, farv[SPLIT ? 0 : wave]);
+    const long long base = (long long)ci * ga.st[0] + (long long)cj * ga.st[1];
+#pragma unroll
+    for (int r = 0; r < ZB; ++r) {
+        const int k = k0 + 64 * r;
+        if (k < nz)
+            for (int c = 0; c < 3; ++c)
+                g[3 * (base + (long long)k * ga.st[2]) + (c + axis) % 3] = (T)(S[c * ZB + r] * p.out);
     }
 }
 
-// The third pass (grad_run_axis) as kernels of its own, so that the main
-// kernels keep their register budgets: every output with a component that is
-// not finite (both folded forms 0/0; also a query on the boundary itself, which
-// stays 0/0) is summed again with the general axis.  Arbitrary points:
-template <class T>
-__global__ __launch_bounds__(256) void k_grad_fix_points(MeshView mv, const float* __restrict__ qx,
-                                                         const float* __restrict__ qy, const float* __restrict__ qz,
-                                                         long long qs, long long nq, int axis, T* __restrict__ g) {
-    const long long i = blockIdx.x * 256ll + threadIdx.x;
-    if (i >= nq) return;
-    T* gi = g + 3 * i;
-    if (isfinite(gi[0]) && isfinite(gi[1]) && isfinite(gi[2])) return;
-    const float px = qx[i * qs], py = qy[i * qs], pz = qz[i * qs];
-    const FarScale<T> fs = far_scale<T>(px, py, fabsf(pz), mv.g.scale);
-    const double pzd = (double)((T)pz * fs.scf);
-    double G[1][3];
-    grad_run_axis<1>(mv, 0, mv.loop_off[mv.nloops], (double)((T)px * fs.scf), (double)((T)py * fs.scf), &pzd,
-                     (double)fs.f, G);
-    const double f = kInv2Pi * (double)fs.scf;
-    for (int c = 0; c < 3; ++c) gi[(c + axis) % 3] = (T)(G[0][c] * f);
-}
-
-// ... and grid samples, t = n0 + thread in the frame's order (z fastest)
-template <class T>
-__global__ __launch_bounds__(256) void k_grad_fix_grid(MeshView mv, GridArgs ga, long long n0, long long n, int axis,
-                                                       T* __restrict__ g) {
-    const long long t = n0 + blockIdx.x * 256ll + threadIdx.x;
-    if (t >= n) return;
-    const long long k = t % ga.nz, col = t / ga.nz;
-    const long long ci = col / ga.ny, cj = col - ci * ga.ny;
-    T* gi = g + 3 * (ci * ga.st[0] + cj * ga.st[1] + k * ga.st[2]);
-    if (isfinite(gi[0]) && isfinite(gi[1]) && isfinite(gi[2])) return;
-    const float px = grid_coord(ga.o[0], ga.s[0], ci), py = grid_coord(ga.o[1], ga.s[1], cj);
-    const float pz = grid_coord(ga.o[2], ga.s[2], k);
-    const FarScale<T> fs = far_scale<T>(px, py, fabsf(pz), mv.g.scale);
-    const double pzd = (double)((T)pz * fs.scf);
-    double G[1][3];
-    grad_run_axis<1>(mv, 0, mv.loop_off[mv.nloops], (double)((T)px * fs.scf), (double)((T)py * fs.scf), &pzd,
-                     (double)fs.f, G);
-    const double f = kInv2Pi * (double)fs.scf;
-    for (int c = 0; c < 3; ++c) gi[(c + axis) % 3] = (T)(G[0][c] * f);
-}
-
-template <class T, int ZB>
-gwn_status launch_grad_grid(const gwn_mesh_s* m, GridArgs ga, T* g, hipStream_t st) {
-    ga.nchunks = (ga.nz + 64 * ZB - 1) / (64 * ZB);
-    ga.nwaves = ga.nx * ga.ny * ga.nchunks;
-    const long long kMaxWaves = max_launch_queries() / 64;   // 2^30 work-items per launch
-    for (long long w0 = 0; w0 < ga.nwaves; w0 += kMaxWaves) {
-        ga.wave0 = w0;
-        const long long blocks = (std::min(kMaxWaves, ga.nwaves - w0) + kGridWaves - 1) / kGridWaves;
-        k_grad_grid<T, ZB><<<(unsigned)blocks, 64 * kGridWaves, 0, st>>>(m->view(), ga, m->axis, g);
-        GWN_HIP_TRY(hipGetLastError());
+// the sums at one level's nodes (gwn_far.h; see k_far_columns)
+template <class T, int ZB, bool SPLIT>
+__global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kGridWaves)) void k_grad_far(MeshView mv, FarNodes f, int nchunks,
+                                                                                     long long wave0, long long nwaves) {
+    constexpr int W = SPLIT ? kSplitWaves : kGridWaves;
+    __shared__ GBuf<T> buf[W];
+    __shared__ double part[SPLIT ? W : 1][SPLIT ? 64 * 3 * ZB : 1];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63;
+    const long long gw = wave0 + (SPLIT ? (long long)blockIdx.x : (long long)blockIdx.x * W + wave);
+    if (gw >= nwaves) return;
+    const long long col = gw / nchunks;
+    const int chunk = __builtin_amdgcn_readfirstlane((int)(gw - col * nchunks));
+    const int ci = __builtin_amdgcn_readfirstlane((int)(col / f.nn[1]));
+    const int cj = __builtin_amdgcn_readfirstlane((int)(col - (long long)ci * f.nn[1]));
+    const int k0 = chunk * 64 * ZB + lane;
+    constexpr T u = (T)1 / (T)kGradUnit<T>;
+    T pzs[ZB];
+    double S[3 * ZB];
+#pragma unroll
+    for (int r = 0; r < ZB; ++r) {
+        pzs[r] = (T)f.pz[min(k0 + 64 * r, f.nn[2] - 1)] * u;
+        S[r] = S[ZB + r] = S[2 * ZB + r] = 0.0;
     }
-    const long long ns = ga.nx * ga.ny * ga.nz, chunk = max_launch_queries();
-    for (long long n0 = 0; n0 < ns; n0 += chunk) {
-        const long long n = std::min(chunk, ns - n0);
-        k_grad_fix_grid<T><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(m->view(), ga, n0, n0 + n, m->axis, g);
+    grad_column<T, ZB>(mv, far_filter(f, ci, cj), (T)f.px[ci] * u, (T)f.py[cj] * u, pzs, u, S, SPLIT ? wave : 0,
+                       SPLIT ? W : 1, buf[wave]);
+    if constexpr (SPLIT) {
+        split_sum<3 * ZB, W>(wave, lane, S, part);
+        if (wave > 0) return;
+    }
+    double* out = f.T + ((size_t)ci * f.nn[1] + cj) * f.nn[2];
+#pragma unroll
+    for (int r = 0; r < ZB; ++r)
+        if (k0 + 64 * r < f.nn[2])
+            for (int c = 0; c < 3; ++c) out[c * f.tstep + k0 + 64 * r] = S[c * ZB + r];
+}
+
+template <class T, int ZB, bool SPLIT>
+gwn_status launch_grad_far(const gwn_mesh_s* m, const FarNodes& f, hipStream_t st) {
+    const int nchunks = (f.nn[2] + 64 * ZB - 1) / (64 * ZB);
+    const long long nwaves = (long long)f.nn[0] * f.nn[1] * nchunks, most = max_launch_queries() / 64;
+    for (long long w0 = 0; w0 < nwaves; w0 += most) {
+        const long long n = std::min(most, nwaves - w0), blocks = SPLIT ? n : (n + kGridWaves - 1) / kGridWaves;
+        k_grad_far<T, ZB, SPLIT><<<(unsigned)blocks, 64 * (SPLIT ? kSplitWaves : kGridWaves), 0, st>>>(
+            m->view(), f, nchunks, w0, std::min(nwaves, w0 + most));
         GWN_HIP_TRY(hipGetLastError());
     }
     return GWN_OK;
+}
+
+template <class T, int ZB, bool SPLIT>
+gwn_status launch_grad_columns(const gwn_mesh_s* m, GridArgs ga, const FarView& far, T* g, hipStream_t st) {
+    ga.nchunks = (ga.nz + 64 * ZB - 1) / (64 * ZB);
+    ga.nwaves = ga.nx * ga.ny * ga.nchunks;
+    const long long kMaxWaves = max_launch_queries() / 64;
+    for (long long w0 = 0; w0 < ga.nwaves; w0 += kMaxWaves) {
+        ga.wave0 = w0;
+        const long long n = std::min(kMaxWaves, ga.nwaves - w0), blocks = SPLIT ? n : (n + kGridWaves - 1) / kGridWaves;
+        k_grad_grid<T, ZB, SPLIT><<<(unsigned)blocks, 64 * (SPLIT ? kSplitWaves : kGridWaves), 0, st>>>(m->view(), ga, far,
+                                                                                                      m->axis, g);
+        GWN_HIP_TRY(hipGetLastError());
+    }
+    return GWN_OK;
+}
+
+// The far part under the same conditions as for w (see launch_grid in grid.hip).
+template <class T>
+gwn_status launch_grad_grid(const gwn_mesh_s* m, const GridArgs& ga, T* g, hipStream_t st) {
+    constexpr int prec = sizeof(T) == 8 ? GWN_PREC_FP64 : GWN_PREC_FP32;
+    constexpr int ZB = 2;
+    FarPlan p;
+    void* ws = nullptr;
+    if (!stream_captures(st)) p = far_plan(m, ga, prec, 3);
+    if (p.levels > 0 && gwn::dmalloc_async(&ws, p.bytes, st) != hipSuccess) {
+        (void)hipGetLastError();
+        p.levels = 0;
+    }
+    gwn_status s = GWN_OK;
+    if (p.levels > 0) {
+        s = far_setup(p, m, ga, prec, ws, st);
+        for (int l = 0; l < p.levels && s == GWN_OK; ++l) {
+            const FarNodes f = far_nodes(p, l);
+            const long long blocks = (f.nn[2] + 63) / 64;
+            if ((long long)f.nn[0] * f.nn[1] * blocks < kFewWaves) s = launch_grad_far<T, 1, true>(m, f, st);
+            else if (blocks == 1) s = launch_grad_far<T, 1, false>(m, f, st);
+            else s = launch_grad_far<T, ZB, false>(m, f, st);
+        }
+        if (s == GWN_OK) s = far_transfer(p, st);
+    }
+    if (s == GWN_OK) {
+        const FarView far = far_view(p);
+        const long long blocks = (ga.nz + 63) / 64;
+        if (ga.nx * ga.ny * blocks < kFewWaves) s = launch_grad_columns<T, 1, true>(m, ga, far, g, st);
+        else if (blocks == 1) s = launch_grad_columns<T, 1, false>(m, ga, far, g, st);
+        else s = launch_grad_columns<T, ZB, false>(m, ga, far, g, st);
+    }
+    if (ws) (void)hipFreeAsync(ws, st);
+    return s;
 }
 
 }  // namespace
@@ -607,9 +465,8 @@ gwn_status query_grid_gradient(const gwn_mesh_s* m, const double* origin, const 
                                int prec, void* g, hipStream_t st) {
     GridArgs ga = frame_grid(m->axis, origin, spacing, dims);
     if (ga.nx == 0 || ga.ny == 0 || ga.nz == 0) return GWN_OK;
-    // four samples per lane (two in FP64) share the column's x/y work
-    if (prec == GWN_PREC_FP64) return launch_grad_grid<double, 2>(m, ga, (double*)g, st);
-    return launch_grad_grid<float, 4>(m, ga, (float*)g, st);
+    if (prec == GWN_PREC_FP64) return launch_grad_grid<double>(m, ga, (double*)g, st);
+    return launch_grad_grid<float>(m, ga, (float*)g, st);
 }
 
 gwn_status query_gradient(const gwn_mesh_s* m, const float* qx, const float* qy, const float* qz, int64_t qs,
@@ -633,11 +490,6 @@ gwn_status query_gradient(const gwn_mesh_s* m, const float* qx, const float* qy,
         } else {
             k_grad_batch<float><<<blocks, 256, 0, st>>>(mv, x, y, z, qs, n, m->axis, (float*)g + 3 * o);
         }
-        GWN_HIP_TRY(hipGetLastError());
-        if (prec == GWN_PREC_FP64)
-            k_grad_fix_points<double><<<blocks, 256, 0, st>>>(mv, x, y, z, qs, n, m->axis, (double*)g + 3 * o);
-        else
-            k_grad_fix_points<float><<<blocks, 256, 0, st>>>(mv, x, y, z, qs, n, m->axis, (float*)g + 3 * o);
         GWN_HIP_TRY(hipGetLastError());
     }
     return GWN_OK;

@@ -111,29 +111,11 @@ __global__ __launch_bounds__(256) void k_raster(MeshView mv, GridArgs ga, ColCro
     }
 }
 
-constexpr int kSplitWaves = 8;
-
 // Waves per SIMD that the column kernels' registers are held to.  FP32: one more than
 // the compiler's own choice at 2 samples per lane and above (512^3 grid: 25.7 ms, 27.5
 // without); FP64: three, the rare path's arctangent alone would take 200 registers.
 template <class T, int ZB>
 constexpr int col_waves = sizeof(T) == 8 ? 3 : ZB >= 4 ? 4 : ZB == 3 ? 5 : ZB == 2 ? 6 : 1;
-
-// the first wave's S plus the other waves', in order
-template <int ZB, int W>
-__device__ __forceinline__ void split_sum(int wave, int lane, double* S, double (*part)[64 * ZB]) {
-    if (wave > 0) {
-#pragma unroll
-        for (int r = 0; r < ZB; ++r) part[wave][64 * r + lane] = S[r];
-    }
-    __syncthreads();
-    if (wave == 0) {
-        for (int v = 1; v < W; ++v) {
-#pragma unroll
-            for (int r = 0; r < ZB; ++r) S[r] += part[v][64 * r + lane];
-        }
-    }
-}
 
 // One wave owns one (x, y) column and a chunk of 64*ZB consecutive z samples;
 // lane l holds samples l, l+64, ..., l+64(ZB-1) of the chunk.  The column's crossings
@@ -321,17 +303,6 @@ __global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kGridWaves)) __attribut
     const int ci = __builtin_amdgcn_readfirstlane((int)(col / f.nn[1]));
     const int cj = __builtin_amdgcn_readfirstlane((int)(col - (long long)ci * f.nn[1]));
     const int k0 = chunk * 64 * ZB + lane;
-    const int bx = ci / f.nodes[0], by = cj / f.nodes[1];
-    ChunkFilter flt{};
-    flt.mode = ChunkFilter::kRing;
-    flt.x = f.cx[bx];
-    flt.y = f.cy[by];
-    flt.thr = f.thr;
-    flt.pthr = f.pthr;
-    if (f.pthr >= 0) {
-        flt.px = f.pcx[bx / 2];
-        flt.py = f.pcy[by / 2];
-    }
     T pzs[ZB];
     double S[ZB];
 #pragma unroll
@@ -339,7 +310,7 @@ __global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kGridWaves)) __attribut
         pzs[r] = (T)f.pz[min(k0 + 64 * r, f.nn[2] - 1)];
         S[r] = 0.0;
     }
-    column_chunks<T, ZB>(mv, flt, f.px[ci], f.py[cj], pzs, S, true, true, SPLIT ? wave : 0, SPLIT ? W : 1, buf[wave]);
+    column_chunks<T, ZB>(mv, far_filter(f, ci, cj), (int)f.px[ci], (int)f.py[cj], pzs, S, true, true, SPLIT ? wave : 0, SPLIT ? W : 1, buf[wave]);
     if constexpr (SPLIT) {
         split_sum<ZB, W>(wave, lane, S, part);
         if (wave > 0) return;
@@ -350,9 +321,6 @@ __global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kGridWaves)) __attribut
     for (int r = 0; r < ZB; ++r)
         if (k1 + 64 * r < f.nn[2]) out[k1 + 64 * r] = S[r];
 }
-
-// Fewer waves than kFewWaves (four per SIMD) take the split form, one sample per lane.
-constexpr long long kFewWaves = 4096;
 
 template <class T, int ZB, bool SPLIT = false>
 gwn_status launch_far_zb(const gwn_mesh_s* m, const FarNodes& f, hipStream_t st) {
@@ -454,18 +422,13 @@ gwn_status launch_crossings(const gwn_mesh_s* m, const GridArgs& ga, const ColCr
 template <class T>
 gwn_status launch_grid(const gwn_mesh_s* m, GridArgs ga, T* w, int32_t* chi_out, hipStream_t st) {
     constexpr int prec = sizeof(T) == 8 ? GWN_PREC_FP64 : GWN_PREC_FP32;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
-        (void)hipGetLastError();
-        cap = hipStreamCaptureStatusActive;   // not known to be free of a capture
-    }
     FarPlan p;
     ColCrossings cc{};
     const long long ncols = ga.nx * ga.ny;
     void* ws = nullptr;
     size_t clist = 0;
     double slack[2];
-    if (cap == hipStreamCaptureStatusNone) {
+    if (!stream_captures(st)) {
         p = far_plan(m, ga, prec, 1);
         if (want_crossings(m, ga, slack)) clist = sizeof(int) * (size_t)(kCrossings + 1) * (size_t)ncols;
         const size_t far_bytes = p.levels > 0 ? p.bytes : 0;

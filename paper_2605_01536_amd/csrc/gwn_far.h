@@ -20,8 +20,9 @@
 // 120 x 97 x 121 grid of 30,000 triangles (n = 14: 7e-15 and 1.4e-13); FP32 RMS error
 // against FP64 3.35e-8 all chunks, 3.37e-8 with the far part.
 //
-// Nodes have the samples' kind of coordinates (quantised x and y, z in offset
-// units of the type), and the interpolation uses the nodes' and samples' actual
+// Nodes have the samples' kind of coordinates (w: quantised x and y, z in cells in
+// the type; the gradient, whose samples are not quantised: all in cells in the type),
+// and the interpolation uses the nodes' and samples' actual
 // positions, so rounding them costs no accuracy.  Sums stay in FP64 throughout.
 #pragma once
 
@@ -43,9 +44,7 @@ struct FarLevel {
     int b[3], nc[3], nn[3];
     int thr;                     // kappa half-widths, in cells
     int2 *cx, *cy;               // per block: quantised range
-    double2* cz;                 // per block: z range in cells
-    int *px, *py;                // node positions
-    double* pz;
+    double* pos[3];              // node positions in cells
     double* w[3];                // [nn][nodes]: interpolation from the next coarser level's nodes
     double* T;                   // [C][nn x][nn y][nn z]: sums at the nodes
 };
@@ -112,8 +111,7 @@ struct FarNodes {
     int nodes[3], nn[3];
     int thr, pthr;               // pthr < 0: the coarsest level
     const int2 *cx, *cy, *pcx, *pcy;
-    const int *px, *py;
-    const double* pz;
+    const double *px, *py, *pz;
     double* T;
     size_t tstep;                // doubles per value in T
 };
@@ -134,15 +132,40 @@ inline FarNodes far_nodes(const FarPlan& p, int l) {
     }
     f.cx = v.cx;
     f.cy = v.cy;
-    f.px = v.px;
-    f.py = v.py;
-    f.pz = v.pz;
+    f.px = v.pos[0];
+    f.py = v.pos[1];
+    f.pz = v.pos[2];
     f.T = v.T;
     f.tstep = (size_t)v.nn[0] * v.nn[1] * v.nn[2];
     return f;
 }
 
+// A stream that may be under capture takes no far part: its workspace would belong to
+// the graph.
+inline bool stream_captures(hipStream_t st) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 namespace {
+
+// the chunks of node column (ci, cj): far from its block, not from the block's parent
+__device__ __forceinline__ ChunkFilter far_filter(const FarNodes& f, int ci, int cj) {
+    const int bx = ci / f.nodes[0], by = cj / f.nodes[1];
+    ChunkFilter flt{};
+    flt.mode = ChunkFilter::kRing;
+    flt.x = f.cx[bx];
+    flt.y = f.cy[by];
+    flt.thr = f.thr;
+    flt.pthr = f.pthr;
+    if (f.pthr >= 0) {
+        flt.px = f.pcx[bx / 2];
+        flt.py = f.pcy[by / 2];
+    }
+    return flt;
+}
 
 constexpr int kFarV = 320;   // node values of 64 samples in LDS: at most 64 / 8 + 2 blocks
 

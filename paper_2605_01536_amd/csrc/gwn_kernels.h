@@ -343,65 +343,6 @@ __device__ __forceinline__ void edge_pair(const ColV<T>& a, const ColV<T>& b, co
     }
 }
 
-// s per block given R, the number of blocks with a sample below the vertex
-// (r_z > 0).  With z ascending in r (and in the lane) blocks 0..R-2 lie wholly
-// below the vertex (s = rho^2 / t, no select), block R-1 may straddle it (the
-// two-sided form) and blocks R.. lie wholly at or above it (s = t).  R > ZB:
-// no order known, the two-sided form everywhere.
-//
-// FARV: every sample below the vertex has r_z^2 <= 3 rho^2.  There
-// s = l - r_z = t - 2 max(r_z, 0) loses at most ~16 ulps to cancellation (its
-// rounding error is ~2 u l, and s = rho^2 / (l + r_z) >= l / 8 there), so the
-// blocks take it without the reciprocal.
-template <class T, int ZB, int R, bool FARV>
-__device__ __forceinline__ void s_blocks(const T* rz, T rho2, T* sv) {
-#pragma unroll
-    for (int r = 0; r < ZB; ++r) {   // sv holds t = l + |r_z| on entry
-        if (FARV && R <= ZB) {
-            if (r < R - 1) sv[r] = fma((T)-2, rz[r], sv[r]);
-            else if (r == R - 1) sv[r] = fma((T)-2, fmax(rz[r], (T)0), sv[r]);
-        } else if (R > ZB || r == R - 1) {
-            sv[r] = rz[r] > (T)0 ? rho2 * Arith<T>::rcp(sv[r]) : sv[r];
-        } else if (r < R - 1) {
-            sv[r] = rho2 * Arith<T>::rcp(sv[r]);
-        }
-    }
-}
-
-// R as above; farv: the FARV case (wave-uniform)
-template <class T, int ZB>
-__device__ __forceinline__ void s_prefix(int R, const T* rz, T rho2, T* sv, bool farv = false) {
-#define GWN_S_CASE(K)                                                                          \
-    case K:                                                                                    \
-        if (farv) s_blocks<T, ZB, (K <= ZB ? K : ZB + 1), true>(rz, rho2, sv);                 \
-        else s_blocks<T, ZB, (K <= ZB ? K : ZB + 1), false>(rz, rho2, sv);                     \
-        break;
-    switch (R) {
-        case 0: break;
-        GWN_S_CASE(1)
-        GWN_S_CASE(2)
-        GWN_S_CASE(3)
-        GWN_S_CASE(4)
-        GWN_S_CASE(5)
-        GWN_S_CASE(6)
-        GWN_S_CASE(7)
-        GWN_S_CASE(8)
-        default: s_blocks<T, ZB, ZB + 1, false>(rz, rho2, sv); break;
-    }
-#undef GWN_S_CASE
-}
-
-// Sample blocks.  Where the samples of a grid wave share a column, register r
-// is a block of 64 consecutive samples and bminr[r] (the same in every lane)
-// holds the block's smallest z.  A vertex at or below every sample of a block
-// (r_z <= 0 in all its lanes) has s = l + |r_z| there with no reciprocal;
-// fma(z, u, -bminr[r]) > 0 is exactly "some lane of block r has r_z > 0" (r_z
-// is the same fma and falls as the sample's z rises).  When every block
-// ascends in the lane and the blocks' smallest z do not fall with r (asc) the
-// samples ascend through the whole column, so the blocks needing the
-// reciprocal are a prefix, all but its last wholly below the vertex (their
-// largest z is at most the next block's smallest).
-
 // pzs: the samples' z in offset units (cells times EdgePairs' kUnit inside the box)
 template <class T, int ZB, bool FAR>
 __device__ __forceinline__ void load_vertex(const BVert& b, int qqx, int qqy, T pxs, T pys, const T* pzs, T f,
@@ -514,7 +455,6 @@ struct ColAux {   // read on the rare paths only
     int dx, dy;
 };
 
-constexpr int kColRing = 128;   // slots of the gradient's ring per wave
 constexpr int kColChunks = 8;   // chunks per fill
 constexpr int kColRecs = kColChunks * kChunk;
 static_assert(kColRecs == 64, "one lane per record");
@@ -554,6 +494,48 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
+
+// A wave's way through the chunks that a filter keeps, 64 looked at a time, up to 8
+// handed out at a time (every lane of the wave calls together).  parts > 1: only the
+// part-th of `parts` shares of the chunks, dealt out in eights.
+struct ChunkQueue {
+    int* queue;   // the wave's LDS, 64 + kColChunks ints
+    int base = 0, head = 0, have = 0, share, part, parts;
+
+    __device__ __forceinline__ ChunkQueue(const MeshView& mv, int part_, int parts_, int* queue_)
+        : queue(queue_), share((mv.nchunk + 8 * parts_ - 1) / (8 * parts_) * 8), part(part_), parts(parts_) {}
+
+    // the number of chunks to take next (0: done); ids(n) are theirs
+    __device__ __forceinline__ int next(const MeshView& mv, const ChunkFilter& flt) {
+        const int lane = (int)(threadIdx.x & 63);
+        if (have < kColChunks && base < share) {
+            if (head > 0) {   // the rest to the front: fewer than 8 chunks
+                const int t = lane < have ? queue[head + lane] : 0;
+                wave_lds_sync();
+                if (lane < have) queue[lane] = t;
+                head = 0;
+            }
+            while (have < kColChunks && base < share) {
+                const int j = base + lane, id = parts == 1 ? j : (j >> 3) * 8 * parts + part * 8 + (j & 7);
+                const bool keep = j < share && id < mv.nchunk && (flt.mode == ChunkFilter::kAll || chunk_kept(mv.cbox[id], flt));
+                const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
+                if (keep)
+                    queue[have + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                           __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = id;
+                have += __builtin_popcountll(m);
+                base += 64;
+            }
+            wave_lds_sync();
+        }
+        return min(have, kColChunks);
+    }
+    __device__ __forceinline__ const int* ids(int n) {
+        const int* q = queue + head;
+        head += n;
+        have -= n;
+        return q;
+    }
+};
 
 // Records of the chunks queue[0 .. n) (n <= 8), record k = 8 c + e for entry e of
 // chunk c.  zmin: the samples' smallest z in offset units.  Bit k of m2 (m4): the edge
@@ -811,35 +793,12 @@ __device__ __forceinline__ void column_chunks(const MeshView& mv, const ChunkFil
     T sp[ZB], Np = (T)0, dotp = (T)1;
 #pragma unroll
     for (int r = 0; r < ZB; ++r) sp[r] = (T)1;
-    const int lane = (int)(threadIdx.x & 63);
-    int base = 0, head = 0, have = 0;   // next of the share to look at; the queue's first and number of chunks
-    const int share = (mv.nchunk + 8 * parts - 1) / (8 * parts) * 8;
+    ChunkQueue q(mv, part, parts, buf.queue);
     while (true) {
-        if (have < kColChunks && base < share) {
-            if (head > 0) {   // the rest to the front: fewer than 8 chunks
-                const int t = lane < have ? buf.queue[head + lane] : 0;
-                wave_lds_sync();
-                if (lane < have) buf.queue[lane] = t;
-                head = 0;
-            }
-            while (have < kColChunks && base < share) {
-                const int j = base + lane, id = parts == 1 ? j : (j >> 3) * 8 * parts + part * 8 + (j & 7);
-                const bool keep = j < share && id < mv.nchunk && (flt.mode == ChunkFilter::kAll || chunk_kept(mv.cbox[id], flt));
-                const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
-                if (keep)
-                    buf.queue[have + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
-                                                               __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = id;
-                have += __builtin_popcountll(m);
-                base += 64;
-            }
-            wave_lds_sync();
-        }
-        if (have == 0) break;
-        const int n = min(have, kColChunks);
+        const int n = q.next(mv, flt);
+        if (n == 0) break;
         unsigned long long ms, mq, mf, mt;
-        col_fill<T, ZB>(mv, buf.queue + head, n, qqx, qqy, zmin, pairs, quads, buf, ms, mq, mf, mt);
-        head += n;
-        have -= n;
+        col_fill<T, ZB>(mv, q.ids(n), n, qqx, qqy, zmin, pairs, quads, buf, ms, mq, mf, mt);
         // bit k from here on: the edge entering record k (record 0 is entered by an edge of no angle)
         ms = (ms << 1) | (pairs ? 1ull : 0ull);
         mq = (mq << 1) | (quads ? 1ull : 0ull);
@@ -904,6 +863,28 @@ __device__ __forceinline__ float grid_coord(double o, double s, long long i) {
 #pragma clang fp contract(off)
     const double t = ((double)i + 0.5) * s;
     return (float)(o + t);
+}
+
+// Fewer waves than kFewWaves (four per SIMD) take the split form of the column
+// kernels: a workgroup of kSplitWaves waves per column, one sample per lane, each wave
+// a share of the chunks, the partial sums added in a fixed order.
+constexpr long long kFewWaves = 4096;
+constexpr int kSplitWaves = 8;
+
+// the first wave's NV values per lane plus the other waves', in order
+template <int NV, int W>
+__device__ __forceinline__ void split_sum(int wave, int lane, double* S, double (*part)[64 * NV]) {
+    if (wave > 0) {
+#pragma unroll
+        for (int r = 0; r < NV; ++r) part[wave][64 * r + lane] = S[r];
+    }
+    __syncthreads();
+    if (wave == 0) {
+        for (int v = 1; v < W; ++v) {
+#pragma unroll
+            for (int r = 0; r < NV; ++r) S[r] += part[v][64 * r + lane];
+        }
+    }
 }
 
 // ---------------------------------------------------------------- chi, batch

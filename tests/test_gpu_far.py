@@ -8,6 +8,8 @@ another order; the bound is a tenth of the FP32 bar, and 1e-11 in FP64."""
 import numpy as np
 import pytest
 
+import oracle as O
+
 from paper_2605_01536_amd import workloads as W
 from tests._util import TOL_FP32, TOL_FP64, compare, fan_soup
 
@@ -115,3 +117,30 @@ def test_capture_takes_the_sum_over_all_chunks(gwn, monkeypatch):
         graph.replay()
         torch.cuda.synchronize()
         assert (out - ref).abs().max().item() <= SAME["fp32"]
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("soup,dims,block,axis,flip", [
+    ("spheres", (40, 33, 65), 8, "z", (1, 1, 1)),
+    ("torus", (64, 1, 64), 8, "y", (1, 1, 1)),
+    ("ellipsoids", (33, 9, 50), 8, "x", (-1, 1, -1)),
+    ("fans", (20, 29, 257), 10, "z", (1, -1, 1)),
+])
+def test_gradient_far_part_equals_all_chunks(gwn, monkeypatch, prec, soup, dims, block, axis, flip):
+    # the gradient's own bar against the oracle: relative to the sum of its edge terms' norms
+    s = SOUPS[soup]()
+    m = _mesh(gwn, s.V, s.F, axis=axis)
+    g = _grid(s.V, dims, flip)
+    monkeypatch.setenv("GWN_GRID_FAR", "0")
+    g0 = gwn.query_grid_gradient(m, *g, prec=prec)
+    monkeypatch.setenv("GWN_GRID_FAR", str(block))
+    g1 = gwn.query_grid_gradient(m, *g, prec=prec)
+    assert torch.equal(gwn.query_grid_gradient(m, *g, prec=prec), g1)
+    P = W.grid_points(W.GridSpec(*g))
+    pick = np.random.default_rng(2).choice(P.shape[0], min(1000, P.shape[0]), replace=False)
+    ref, l1 = O.gradient(s.V, s.F, P[pick], axis=np.eye(3)[{"z": 2, "x": 0, "y": 1}[axis]], with_l1=True)
+    ok = np.isfinite(ref).all(1) & np.isfinite(l1)
+    bound = (2e-5 if prec == "fp32" else 1e-10) * np.maximum(1.0, l1[ok])[:, None]
+    for got in (g0, g1):
+        assert (np.abs(got.double().cpu().numpy()[pick][ok] - ref[ok]) <= bound).all()
+    assert (np.abs((g1 - g0).double().cpu().numpy()[pick][ok]) <= bound).all()
