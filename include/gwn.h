@@ -126,15 +126,16 @@ gwn_status gwn_mesh_destroy(gwn_mesh m);
 
 /*
  * Per-mesh query tuning.  Three choices of the query paths depend on the mesh
- * and the device, not on the arithmetic: the largest batch that gives each
- * point a workgroup with the boundary edges split among its lanes (per
- * precision; this changes the summation order of w, i.e. its last bits), the
- * smallest batch worth a Morton order of the points for the crossing walk (no
- * result changes), and the grid kernel's samples per lane (per precision;
- * w's last bits).  Crossing counts never change.  A field of 0 takes the
- * built-in rule (split: at most 8,192 points on meshes with at least 4,096
- * boundary edges; order: at least 2^18 points on meshes of at least 2^15
- * triangles; samples: the largest of 8 (FP32) or 4 (FP64), 4, 2, 1 that the
+ * and the device, not on the arithmetic: the largest batch that shares each
+ * point's boundary sum among lanes (per precision; FP64: this changes the
+ * summation order of w, i.e. its last bits), the smallest batch worth an order
+ * of the points for the crossing walk and FP32's boundary sum (no result
+ * changes), and the grid kernel's samples per lane (per precision; w's last
+ * bits).  Crossing counts never change.  A field of 0 takes the built-in rule
+ * (split: FP32 fewer than 49,152 points on meshes with at least 512 boundary
+ * edges, up to 16,384 points 64 edges, FP64 at most 8,192 points and at least 4,096 edges; order: at least
+ * 2^18 points on meshes of at least 2^15 triangles for the crossing walk, 16,384
+ * points and 10^8 pairs of a point and an edge for the boundary sum; samples: the largest of 8 (FP32) or 4 (FP64), 4, 2, 1 that the
  * column length fills), -1 never (split, order).  The environment variables
  * GWN_SPLIT_BOUNDARY, GWN_ORDER_QUERIES and GWN_GRID_SAMPLES_PER_LANE override
  * any tuning.
@@ -184,10 +185,11 @@ gwn_status gwn_mesh_autotune(gwn_mesh m, const gwn_autotune_opts* opts, void* st
  * not meaningful (w is undefined on M).  A point's w does not depend on the
  * other points of the call or their order, and repeated calls give the same
  * bits; gwn_query_multi gives the same bits too.  The one exception is the
- * summation order: small batches (at most 8,192 points on meshes with at least
- * 4,096 boundary edges, or the mesh's tuning, see gwn_mesh_set_tuning) give
+ * summation order in FP64: small batches (at most 8,192 points on meshes with at
+ * least 4,096 boundary edges, or the mesh's tuning, see gwn_mesh_set_tuning) give
  * each point a workgroup that splits its edges among lanes (GWN_SPLIT_BOUNDARY=
- * 0/1 overrides), which agrees with the other form to rounding.
+ * 0/1 overrides), which agrees with the other form to rounding.  FP32 sums are
+ * exact sums of rounded terms (for |w| below 2^14), whatever the form.
  */
 gwn_status gwn_query_batch(gwn_mesh m, const float* qx, const float* qy, const float* qz, int64_t qstride,
                            int64_t nq, int32_t prec, void* w_out, int32_t* chi_out, void* stream);
@@ -278,8 +280,10 @@ gwn_status gwn_query_direct(gwn_mesh m, const float* qx, const float* qy, const 
  * strided arrays qx, qy, qz (q_offsets: host array of nmesh+1 non-decreasing
  * values, q_offsets[0] = 0).  It splits the queries into work items (mesh,
  * query tile), orders them (largest estimated cost first by default), and
- * captures one HIP graph: reset of a work counter, crossing counts for every
- * query, and a persistent kernel whose waves claim items from the counter.
+ * captures one HIP graph: reset of the work counters, crossing counts for every
+ * query, and persistent kernels whose waves claim items from a counter.  Meshes
+ * with at least 16,384 queries take them in orders made at creation from the
+ * query values then (4 or 8 bytes per query).
  * With opts->autotune the candidate schedules (tile size, item order, resident
  * waves, and the best of those with each mesh's queries in Morton order) are
  * timed on the real inputs and the fastest is kept; with
@@ -304,7 +308,8 @@ typedef struct {
     int32_t waves_per_simd;   /* resident persistent waves per SIMD, 1..8; 0 = default or tuned */
     int32_t order;            /* 0 = largest estimated cost first, 1 = mesh order; +2: each mesh's queries
                                  taken in Morton order of their quantised x, y (a permutation made once at
-                                 creation from the query values then; results are the same bits either way) */
+                                 creation from the query values then; results are the same bits either way;
+                                 FP32 orders meshes of many queries by itself, and others gain nothing) */
     int32_t autotune;         /* nonzero: time candidate schedules at creation and keep the fastest */
     const char* tune_cache;   /* nullable JSON-lines file read before tuning and appended after */
 } gwn_multi_opts;

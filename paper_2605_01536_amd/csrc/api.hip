@@ -70,6 +70,9 @@ void release(gwn_mesh_s* m) {
     (void)hipFree(m->loop_off);
     (void)hipFree(m->chain);
     (void)hipFree(m->cbox);
+    (void)hipFree(m->gchain);
+    (void)hipFree(m->clusters);
+    (void)hipFree(m->moments);
     delete m;
 }
 

@@ -41,20 +41,21 @@ __device__ __forceinline__ T diff_of_products(T x, T y, T z, T w) {
     return fma(x, y, -p) + fma(-z, w, p);
 }
 
-// One edge's term added to g, given c, the dot product and the two lengths.  A lane
-// with dot < 0 (the query beside the edge) takes c from exact(), without
-// cancellation; the wave looks for one first, and each lane's result is its own.
+// One edge's term added to g, given c, the dot product, h = |e|^2 / 2 and the two
+// lengths.  A lane with dot < h (the edge as long as its distance, or longer) takes c
+// from exact(), without cancellation, and with dot < 0 the other form of the bracket;
+// the wave looks for one first, and each lane's result is its own.
 template <class T, class F>
-__device__ __forceinline__ void grad_term(T cx, T cy, T cz, T dot, T la, T lb, F&& exact, bool general, T* g) {
+__device__ __forceinline__ void grad_term(T cx, T cy, T cz, T dot, T h, T la, T lb, F&& exact, bool general, T* g) {
     const T ll = la * lb;
     T den = ll * (ll + dot), num = la + lb;
     if (general) {
-        const bool neg = dot < (T)0;
+        const bool near = dot < h, neg = dot < (T)0;
         T x, y, z;
         exact(x, y, z);
-        cx = neg ? x : cx;
-        cy = neg ? y : cy;
-        cz = neg ? z : cz;
+        cx = near ? x : cx;
+        cy = near ? y : cy;
+        cz = near ? z : cz;
         den = neg ? ll * fma(x, x, fma(y, y, z * z)) : den;
         num = neg ? num * (ll - dot) : num;
     }
@@ -72,7 +73,7 @@ struct GVert {
 };
 
 template <class T>
-__device__ __forceinline__ GVert<T> grad_vert(const BVert& b, T px, T py, T pz, T f) {
+__device__ __forceinline__ GVert<T> grad_vert(const GVertex& b, T px, T py, T pz, T f) {
     GVert<T> v;
     v.x = fma((T)b.x, f, -px);
     v.y = fma((T)b.y, f, -py);
@@ -89,24 +90,26 @@ __device__ __forceinline__ void grad_chunks_point(const MeshView& mv, int c0, in
     T acc[3] = {(T)0, (T)0, (T)0};
     int left = 4;
     for (int c = c0; c < mv.nchunk; c += step) {
-        const BVert* __restrict__ v = mv.chain + (size_t)c * kChunk;
-        BVert a = v[0];
+        const GVertex* __restrict__ v = mv.gchain + (size_t)c * kChunk;
+        GVertex a = v[0];
         GVert<T> ra = grad_vert<T>(a, px, py, pz, f);
 #pragma unroll
         for (int e = 1; e < kChunk; ++e) {
-            const BVert b = v[e];
+            const GVertex b = v[e];
             const GVert<T> rb = grad_vert<T>(b, px, py, pz, f);
-            if (a.pad1 & kChainEdge) {
+            if (a.flags & kChainEdge) {
                 const T ex = ((T)b.x - (T)a.x) * f, ey = ((T)b.y - (T)a.y) * f, ez = ((T)b.z - (T)a.z) * f;
                 const T dot = fma(ra.x, rb.x, fma(ra.y, rb.y, ra.z * rb.z));
+                const T h = (T)0.5 * fma(ex, ex, fma(ey, ey, ez * ez));
                 grad_term<T>(
-                    fma(ra.y, ez, -(ra.z * ey)), fma(ra.z, ex, -(ra.x * ez)), fma(ra.x, ey, -(ra.y * ex)), dot, ra.l, rb.l,
+                    fma(ra.y, ez, -(ra.z * ey)), fma(ra.z, ex, -(ra.x * ez)), fma(ra.x, ey, -(ra.y * ex)), dot, h, ra.l,
+                    rb.l,
                     [&](T& x, T& y, T& z) {
                         x = diff_of_products(ra.y, ez, ra.z, ey);
                         y = diff_of_products(ra.z, ex, ra.x, ez);
                         z = diff_of_products(ra.x, ey, ra.y, ex);
                     },
-                    __builtin_amdgcn_ballot_w64(dot < (T)0) != 0ull, acc);
+                    __builtin_amdgcn_ballot_w64(dot < h) != 0ull, acc);
             }
             a = b;
             ra = rb;
@@ -208,6 +211,7 @@ struct GBuf {
     GRec<T> v[kColRecs];
     GEdge<T> e[kColRecs];
     GAux<T> x[kColRecs];
+    T h[kColRecs];        // |e|^2 / 2 (no edge: 0)
     int queue[64 + kColChunks];
 };
 
@@ -217,9 +221,9 @@ __device__ __forceinline__ void grad_fill(const MeshView& mv, const int* queue, 
     asm volatile("" : "+v"(lane));   // addresses formed per fill (see col_fill)
     const int c = lane >> 3, en = lane & 7;
     if (c < n) {
-        const BVert* v = mv.chain + (size_t)queue[c] * kChunk;
-        const BVert a = v[en], b = v[min(en + 1, kChunk - 1)];
-        const bool edge = (a.pad1 & kChainEdge) != 0;
+        const GVertex* v = mv.gchain + (size_t)queue[c] * kChunk;
+        const GVertex a = v[en], b = v[min(en + 1, kChunk - 1)];
+        const bool edge = (a.flags & kChainEdge) != 0;
         const T ax = fma((T)a.x, f, -px), ay = fma((T)a.y, f, -py);
         const T bx = fma((T)b.x, f, -px), by = fma((T)b.y, f, -py);
         const T ex = edge ? ((T)b.x - (T)a.x) * f : (T)0, ey = edge ? ((T)b.y - (T)a.y) * f : (T)0;
@@ -227,6 +231,7 @@ __device__ __forceinline__ void grad_fill(const MeshView& mv, const int* queue, 
         // between two pieces no edge: c = 0, and a large dot product keeps the bracket positive
         buf.v[lane] = {(T)a.z * f, ax * ax + ay * ay, ex, ey};
         buf.x[lane] = {ax, ay, ez};
+        buf.h[lane] = (T)0.5 * fma(ex, ex, fma(ey, ey, ez * ez));
         buf.e[lane] = {ay * ez, ax * ez, fma(ax, ey, -(ay * ex)), edge ? ax * bx + ay * by : (T)1e30};
     }
     wave_lds_sync();
@@ -241,6 +246,7 @@ __device__ __forceinline__ void grad_column(const MeshView& mv, const ChunkFilte
     T rza[ZB], la[ZB];
     GRec<T> va = {(T)0, (T)0, (T)0, (T)0};   // the vertex before the current one: none yet
     GEdge<T> ea = {(T)0, (T)0, (T)0, (T)1e30};
+    T ha = (T)0;
 #pragma unroll
     for (int r = 0; r < ZB; ++r) {
         rza[r] = (T)0;
@@ -260,20 +266,21 @@ __device__ __forceinline__ void grad_column(const MeshView& mv, const ChunkFilte
             for (; k < ke; ++k) {
                 const GRec<T> vb = buf.v[k];
                 const GEdge<T> eb = buf.e[k];
+                const T hb = buf.h[k];
                 T rzb[ZB], lb[ZB], dot[ZB];
-                bool neg = false;
+                bool near = false;
 #pragma unroll
                 for (int r = 0; r < ZB; ++r) {
                     rzb[r] = vb.zu - pz[r];
                     lb[r] = Arith<T>::sqrt(fma(rzb[r], rzb[r], vb.rho2));
                     dot[r] = fma(rza[r], rzb[r], ea.dot);
-                    neg |= dot[r] < (T)0;
+                    near |= dot[r] < ha;
                 }
-                const bool general = __builtin_amdgcn_ballot_w64(neg) != 0ull;
+                const bool general = __builtin_amdgcn_ballot_w64(near) != 0ull;
 #pragma unroll
                 for (int r = 0; r < ZB; ++r) {
                     grad_term<T>(
-                        fma(-rza[r], va.ey, ea.a), fma(rza[r], va.ex, -ea.b), ea.cz, dot[r], la[r], lb[r],
+                        fma(-rza[r], va.ey, ea.a), fma(rza[r], va.ex, -ea.b), ea.cz, dot[r], ha, la[r], lb[r],
                         [&](T& x, T& y, T& z) {
                             const GAux<T> a = buf.x[k > 0 ? k - 1 : 0];   // (record 0 is entered by no edge)
                             x = diff_of_products(a.ry, a.ez, rza[r], va.ey);
@@ -286,6 +293,7 @@ __device__ __forceinline__ void grad_column(const MeshView& mv, const ChunkFilte
                 }
                 va = vb;
                 ea = eb;
+                ha = hb;
             }
 #pragma unroll
             for (int r = 0; r < ZB; ++r)

@@ -271,7 +271,7 @@ __attribute__((amdgpu_waves_per_eu(col_waves<T, ZB>))) void k_grid(MeshView mv, 
             pzs[r] = (T)pz[r] * fs.scf;
             S[r] = (double)chi[r] * k2Pi;
         }
-        boundary_loops<T, ZB, true>(mv, 0, 0, (T)px * fs.scf, (T)py * fs.scf, pzs, S, fs.f);
+        boundary_loops_far<T, ZB>(mv, (T)px * fs.scf, (T)py * fs.scf, pzs, S, fs.f);
     }
 
     // output positions from the wave-uniform column and the lane, recomputed

@@ -38,12 +38,52 @@ struct alignas(32) BVert {
 };
 
 // The boundary again as chunks of kChunk chained vertices (see k_emit_chain in
-// build.hip): entry e of a chunk leads to entry e + 1 where pad1 & kChainEdge.
+// build.hip): entry e of a chunk leads to entry e + 1 where flags & kChainEdge.
 // A long loop is cut every kChunk - 1 edges, loops (or their ends) of at most
 // three edges share a chunk in pairs; loops follow each other in Morton order, so
 // a chunk is small.  Entries past a piece's end repeat a vertex, without an edge.
 constexpr int kChunk = 8;
-constexpr int kChainEdge = 1, kChainValid = 2, kChainTri = 4;   // kChainTri: first vertex of a loop of three edges
+constexpr int kChainEdge = 1, kChainValid = 2;
+constexpr int kChainTri = 4;    // first vertex of a loop of three edges
+constexpr int kChainCont = 8;   // first of a chunk: the vertex that the chunk before ends with
+struct alignas(32) CVert {
+    float z;          // as BVert
+    int qx, qy;
+    float ex, ey;     // the edge's quantised x, y in units of 2^18 cells (0 without one)
+    float m;          // the smallest D (units squared) that lets it share an arctangent, see point_run
+    int flags;
+    float none;       // added to D: 2^27 where there is no edge (x/y dot products inside the box stay above -2^26), 0 else
+};
+
+// Raw positions of the chain's vertices (BVert's x, y, z) and the flags, for the gradient.
+struct alignas(16) GVertex {
+    float x, y, z;
+    int flags;
+};
+
+// A cluster: consecutive whole loops and the multipole expansion of their solid angle
+// (see cluster_far).  kFan clusters of one level (in order) make one of the next, up to a
+// level of at most kRoots.
+struct alignas(64) Cluster {
+    float x, y, z;            // centre, as BVert
+    float inva;               // 1 / radius of the sphere about it that holds the loops
+    float far2[3];            // squared distances (cells) from which degree kPoles, kPolesMid, kPolesLow will do
+    float ztop;               // the loops' largest z
+    int xlo, xhi, ylo, yhi;   // their quantised box
+    int first, count;         // children; on the lowest level chunks, and minus their number
+    float zlow;               // the loops' smallest z
+    float area;               // of triangle fans spanning the loops, cells squared
+};
+
+constexpr int kFanBits = 3, kFan = 1 << kFanBits, kRoots = 64, kLevels = 12;
+
+// Meshes of fewer clusters sum all edges: little is far from such a mesh's points, and the
+// lanes of a wave of unordered points differ in what is (171 edges in 7 clusters, 2 M
+// points: 0.44 ms with the expansions).
+constexpr int kFewClusters = 16;
+
+constexpr int kPoles = 10, kPolesMid = 6, kPolesLow = 4;       // degrees of the expansions
+constexpr int kMoments = (kPoles + 1) * (kPoles + 1) - 1;    // real coefficients, degree 1 up (l^2 - 1: degree l's first)
 
 // Fixed-point grid parameters: q = rint((x - lo) * scale), scale = 2^k.
 struct QGrid {
@@ -54,12 +94,18 @@ struct QGrid {
 };
 
 // Read-only view of a built mesh handed to query kernels.
-struct MeshView {
+struct alignas(16) MeshView {
     const Node* nodes;
     const TriQ* tris;
     const BVert* bverts;
     const int* loop_off;   // nloops + 1 offsets into bverts
-    const BVert* chain;    // kChunk vertices per chunk
+    const CVert* chain;    // kChunk vertices per chunk
+    const GVertex* gchain;
+    const Cluster* clusters;
+    const float* moments;  // kMoments per cluster
+    int nclusters;         // on the lowest level
+    int top;               // the highest level
+    const int* level;      // first cluster of each level, and the end of the last
     const int4* cbox;      // per chunk: quantised xlo, xhi, ylo, yhi
     int nchunk;
     int nloops;
@@ -121,6 +167,48 @@ __device__ __forceinline__ QPoint quantize_point(float px, float py, float pz, c
     tz = fmin(fmax(tz, -1.0), (double)(kQMax + 1));   // NaN -> -1 via fmax
     q.z = (int)tz;
     return q;
+}
+
+// Position of the cell (x, y, z), 10 bits each, along a Hilbert curve (Skilling's transform
+// of the axes, "Programming the Hilbert curve", 2004).  Consecutive cells touch, so a run
+// of points in this order is compact; in Morton order one in ten runs of 28 edges of a
+// torus of loops spans a jump and has twice the radius.
+__device__ __forceinline__ uint32_t hilbert_key(uint32_t x, uint32_t y, uint32_t z) {
+    uint32_t v[3] = {x & 1023u, y & 1023u, z & 1023u};
+    for (uint32_t q = 512u; q > 1u; q >>= 1) {
+        const uint32_t low = q - 1u;
+        for (int a = 0; a < 3; ++a) {
+            const uint32_t t = (v[a] & q) ? 0u : (v[0] ^ v[a]) & low;   // exchange the low bits, or
+            v[0] ^= (v[a] & q) ? low : t;                               // invert the first axis'
+            v[a] ^= t;
+        }
+    }
+    v[1] ^= v[0];
+    v[2] ^= v[1];
+    uint32_t t = 0u;
+    for (uint32_t q = 512u; q > 1u; q >>= 1)
+        if (v[2] & q) t ^= q - 1u;
+    uint32_t key = 0u;
+    for (int b = 9; b >= 0; --b)
+        for (int a = 0; a < 3; ++a) key = (key << 1) | (((v[a] ^ t) >> b) & 1u);
+    return key;
+}
+
+// The traversal orders' key of a point: Morton order of 16 bits of x and y each (the rays
+// are vertical), or (space) the Hilbert curve; points outside the box come last.
+__device__ __forceinline__ uint32_t spread16(uint32_t v) {
+    v &= 0xffffu;
+    v = (v | (v << 8)) & 0x00ff00ffu;
+    v = (v | (v << 4)) & 0x0f0f0f0fu;
+    v = (v | (v << 2)) & 0x33333333u;
+    v = (v | (v << 1)) & 0x55555555u;
+    return v;
+}
+
+__device__ __forceinline__ uint32_t point_key(const QPoint& q, bool space) {
+    const uint32_t z = (uint32_t)min(max(q.z, 0), (int)kQMax);
+    if (space) return q.inbox ? hilbert_key((uint32_t)q.x >> 20, (uint32_t)q.y >> 20, z >> 20) : 0x3fffffffu;
+    return q.inbox ? (spread16((uint32_t)q.x >> 14) | (spread16((uint32_t)q.y >> 14) << 1)) : 0xffffffffu;
 }
 
 __device__ __forceinline__ int sgnll(long long v) { return (v > 0) - (v < 0); }

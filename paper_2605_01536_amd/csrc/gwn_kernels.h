@@ -203,12 +203,12 @@ struct EdgePairs {
     static constexpr float kTan8 = 0.41421354f;                    // just below tan(pi/8)
 };
 
-template <class T, int ZB, bool FAR>
-__device__ __forceinline__ ColV<T> col_vtx(const BVert& b, int qqx, int qqy, T pxs, T pys, T f) {
+template <class T, int ZB, bool FAR, class V>
+__device__ __forceinline__ ColV<T> col_vtx(const V& b, int qqx, int qqy, T pxs, T pys, T f) {
     ColV<T> c;
     c.dx = b.qx - qqx;
     c.dy = b.qy - qqy;
-    if (FAR) {
+    if constexpr (FAR) {
         c.rx = fma((T)b.x, f, -pxs);
         c.ry = fma((T)b.y, f, -pys);
     } else {
@@ -217,6 +217,24 @@ __device__ __forceinline__ ColV<T> col_vtx(const BVert& b, int qqx, int qqy, T p
     }
     c.rho2 = c.rx * c.rx + c.ry * c.ry;
     return c;
+}
+
+// a chained edge's x or y in offset units: as kept in FP32, from the integers in FP64
+template <class T>
+__device__ __forceinline__ T edge_e(float e, int d) {
+    if constexpr (sizeof(T) == 4) return e;
+    else return (T)d;
+}
+
+// N = r_a,y r_b,x - r_a,x r_b,y of the edge a -> b through the edge's own x, y (exact
+// integers): r x e is the same for either endpoint's r, and with the nearer one its error
+// goes with that distance times the edge's length, not with the product of the two
+// distances.
+template <class T>
+__device__ __forceinline__ T edge_N(const ColV<T>& a, const ColV<T>& b, T ex, T ey) {
+    const bool na = a.rho2 <= b.rho2;
+    const T rx = na ? a.rx : b.rx, ry = na ? a.ry : b.ry;
+    return ry * ex - rx * ey;
 }
 
 // s = l - r_z without cancellation
@@ -300,129 +318,40 @@ __device__ __forceinline__ bool quad_z(float pz, const QGrid& g) {
     return fabs(((double)pz - g.lo[2]) * g.scale) <= 0x1p32;
 }
 
-// Edges a -> b -> c for ZB samples: as one pair where allowed, else one by one.
-// Each lane chooses for its own point, so a point's result does not depend on
-// which points share its wave (the single-edge fast and exact forms agree bit
-// for bit where |N| < D, so their wave-uniform choice never mattered).
-template <class T, int ZB, bool FAR>
-__device__ __forceinline__ void edge_pair(const ColV<T>& a, const ColV<T>& b, const ColV<T>& c, const T* sa,
-                                          const T* sb, const T* sc, T* acc,
-                                          bool pairs) {
-    using P = EdgePairs<T, ZB, FAR>;
-    if constexpr (!P::on) {
-        edge_step<T, ZB, FAR>(a, b, sa, sb, acc);
-        edge_step<T, ZB, FAR>(b, c, sb, sc, acc);
-    } else {
-        const T N1 = a.ry * b.rx - a.rx * b.ry, dot1 = a.rx * b.rx + a.ry * b.ry;
-        const T N2 = b.ry * c.rx - b.rx * c.ry, dot2 = b.rx * c.rx + b.ry * c.ry;
-        const T m1 = fmax(fabs(N1) * (T)P::kInvTan, (T)P::kMinD);
-        const T m2 = fmax(fabs(N2) * (T)P::kInvTan, (T)P::kMinD);
-        T D1[ZB], D2[ZB];
+// s of a vertex for ZB samples of a query outside the box (pzs in units of 2^e cells)
+template <class T, int ZB>
+__device__ __forceinline__ void load_vertex(const BVert& b, T pxs, T pys, const T* pzs, T f, ColV<T>& c, T* sv) {
+    c = col_vtx<T, ZB, true>(b, 0, 0, pxs, pys, f);
 #pragma unroll
-        for (int r = 0; r < ZB; ++r) {
-            D1[r] = fma(sa[r], sb[r], dot1);
-            D2[r] = fma(sb[r], sc[r], dot2);
-        }
-        bool slow = !pairs;
-#pragma unroll
-        for (int r = 0; r < ZB; ++r) slow |= !(m1 < D1[r]) | !(m2 < D2[r]);
-        if (!slow) {
-            const T N12 = N1 * N2;
-#pragma unroll
-            for (int r = 0; r < ZB; ++r) {
-                const T re = fma(D1[r], D2[r], -N12);
-                const T im = fma(D1[r], N2, N1 * D2[r]);
-                const T t = im * Arith<T>::rcp(re);
-                if constexpr (P::f32) acc[r] = atan_pair_acc(t, acc[r]);
-                else acc[r] += Arith<T>::atan_small(t);   // |t| < tan(pi/8)
-            }
-        } else {
-            edge_finish<T, ZB, FAR>(a, b, sa, sb, N1, D1, acc);
-            edge_finish<T, ZB, FAR>(b, c, sb, sc, N2, D2, acc);
-        }
-    }
-}
-
-// pzs: the samples' z in offset units (cells times EdgePairs' kUnit inside the box)
-template <class T, int ZB, bool FAR>
-__device__ __forceinline__ void load_vertex(const BVert& b, int qqx, int qqy, T pxs, T pys, const T* pzs, T f,
-                                            ColV<T>& c, T* sv) {
-    c = col_vtx<T, ZB, FAR>(b, qqx, qqy, pxs, pys, f);
-    constexpr T u = (T)EdgePairs<T, ZB, FAR>::kUnit;
-#pragma unroll
-    for (int r = 0; r < ZB; ++r) {
-        const T rz = FAR ? fma((T)b.z, f, -pzs[r]) : (u == (T)1 ? (T)b.z - pzs[r] : fma((T)b.z, u, -pzs[r]));
-        sv[r] = samp_s<T>(c.rho2, rz);
-    }
+    for (int r = 0; r < ZB; ++r) sv[r] = samp_s<T>(c.rho2, fma((T)b.z, f, -pzs[r]));
 }
 
 // Boundary sum S = sum of atan2 over the chained loops for ZB samples sharing one
-// (x, y).  FP32 partials are flushed into the FP64 sum every 32 edges.  pzs in
-// cells inside the box (FAR: in units of 2^e cells).  pairs: this lane's
-// samples may take edge pairs (see near_z).  (Grid columns use column_loops.)
-template <class T, int ZB, bool FAR>
-__device__ __forceinline__ void boundary_loops(const MeshView& mv, int qqx, int qqy, T pxs, T pys, const T* pzs,
-                                               double* S, T f = (T)1, bool pairs = true) {
+// (x, y) outside the fixed-point box, raw offsets in units of 2^e cells, edge by edge.
+// FP32 partials are flushed into the FP64 sum every 32 edges.
+template <class T, int ZB>
+__device__ __forceinline__ void boundary_loops_far(const MeshView& mv, T pxs, T pys, const T* pzs, double* S, T f) {
     const BVert* __restrict__ bv = mv.bverts;
-    T pz[ZB];
-#pragma unroll
-    for (int r = 0; r < ZB; ++r) pz[r] = FAR ? pzs[r] : pzs[r] * (T)EdgePairs<T, ZB, FAR>::kUnit;
     for (int l = 0; l < mv.nloops; ++l) {
         const int b0 = mv.loop_off[l], b1 = mv.loop_off[l + 1];
-        ColV<T> cf, cp, cq, cr;
-        T sf[ZB], sp[ZB], sq[ZB], sr[ZB];
-        load_vertex<T, ZB, FAR>(bv[b0], qqx, qqy, pxs, pys, pz, f, cf, sf);
-        cp = cf;
-#pragma unroll
-        for (int r = 0; r < ZB; ++r) {
-            sp[r] = sf[r];
-        }
-        int j = b0 + 1;
-        while (j < b1) {
-            const int je = min(b1, j + 32);
+        ColV<T> cp, cq;
+        T sp[ZB], sq[ZB];
+        load_vertex<T, ZB>(bv[b0], pxs, pys, pzs, f, cp, sp);
+        for (int j = b0 + 1; j <= b1;) {   // j = b1 closes the loop
+            const int je = min(b1 + 1, j + 32);
             T acc[ZB];
 #pragma unroll
             for (int r = 0; r < ZB; ++r) acc[r] = (T)0;
-            // four vertices (two edge pairs) per trip: p-q-r, then r-q-p with q and p
-            // reloaded, so the loop-carried vertex ends in the set it started in
-            for (; j + 3 < je; j += 4) {
-                load_vertex<T, ZB, FAR>(bv[j], qqx, qqy, pxs, pys, pz, f, cq, sq);
-                load_vertex<T, ZB, FAR>(bv[j + 1], qqx, qqy, pxs, pys, pz, f, cr, sr);
-                edge_pair<T, ZB, FAR>(cp, cq, cr, sp, sq, sr, acc, pairs);
-                load_vertex<T, ZB, FAR>(bv[j + 2], qqx, qqy, pxs, pys, pz, f, cq, sq);
-                load_vertex<T, ZB, FAR>(bv[j + 3], qqx, qqy, pxs, pys, pz, f, cp, sp);
-                edge_pair<T, ZB, FAR>(cr, cq, cp, sr, sq, sp, acc, pairs);
-            }
-            if (j + 1 < je) {
-                load_vertex<T, ZB, FAR>(bv[j], qqx, qqy, pxs, pys, pz, f, cq, sq);
-                load_vertex<T, ZB, FAR>(bv[j + 1], qqx, qqy, pxs, pys, pz, f, cr, sr);
-                edge_pair<T, ZB, FAR>(cp, cq, cr, sp, sq, sr, acc, pairs);
-                cp = cr;
-#pragma unroll
-                for (int r = 0; r < ZB; ++r) {
-                    sp[r] = sr[r];
-                }
-                j += 2;
-            }
-            if (j < je) {
-                load_vertex<T, ZB, FAR>(bv[j], qqx, qqy, pxs, pys, pz, f, cq, sq);
-                edge_step<T, ZB, FAR>(cp, cq, sp, sq, acc);
+            for (; j < je; ++j) {
+                load_vertex<T, ZB>(bv[j < b1 ? j : b0], pxs, pys, pzs, f, cq, sq);
+                edge_step<T, ZB, true>(cp, cq, sp, sq, acc);
                 cp = cq;
 #pragma unroll
-                for (int r = 0; r < ZB; ++r) {
-                    sp[r] = sq[r];
-                }
-                ++j;
+                for (int r = 0; r < ZB; ++r) sp[r] = sq[r];
             }
 #pragma unroll
             for (int r = 0; r < ZB; ++r) S[r] += (double)acc[r];
         }
-        T acc[ZB];
-#pragma unroll
-        for (int r = 0; r < ZB; ++r) acc[r] = (T)0;
-        edge_step<T, ZB, FAR>(cp, cf, sp, sf, acc);
-#pragma unroll
-        for (int r = 0; r < ZB; ++r) S[r] += (double)acc[r];
     }
 }
 
@@ -555,19 +484,16 @@ __device__ __forceinline__ void col_fill(const MeshView& mv, const int* queue, i
     const int c = lane >> 3, en = lane & 7;
     bool e = false, e4 = false, ef = false, et = false;
     if (c < n) {
-        const BVert* v = mv.chain + (size_t)queue[c] * kChunk;
-        const BVert a = v[en], b = v[min(en + 1, kChunk - 1)];
+        const CVert* v = mv.chain + (size_t)queue[c] * kChunk;
+        const CVert a = v[en], b = v[min(en + 1, kChunk - 1)];
         const ColV<T> ca = col_vtx<T, ZB, false>(a, qqx, qqy, (T)0, (T)0, (T)1);
         const ColV<T> cb = col_vtx<T, ZB, false>(b, qqx, qqy, (T)0, (T)0, (T)1);
-        const bool edge = (a.pad1 & kChainEdge) != 0;
-        et = (a.pad1 & kChainTri) != 0;
+        const bool edge = (a.flags & kChainEdge) != 0;
+        et = (a.flags & kChainTri) != 0;
         ColRec<T> rc;
         rc.zu = u == (T)1 ? (T)a.z : (T)a.z * u;   // exact (u is a power of two)
         rc.rho2 = ca.rho2;
-        // N = r_a,y r_b,x - r_a,x r_b,y through the edge's own x and y (exact integers), so
-        // that its error goes with the edge's length and not with the distance
-        const T ex = (T)(b.qx - a.qx) * u, ey = (T)(b.qy - a.qy) * u;
-        rc.N = edge ? ca.ry * ex - ca.rx * ey : (T)0;
+        rc.N = edge ? edge_N<T>(ca, cb, edge_e<T>(a.ex, b.qx - a.qx), edge_e<T>(a.ey, b.qy - a.qy)) : (T)0;
         rc.dot = edge ? ca.rx * cb.rx + ca.ry * cb.ry : (T)1;
         ColAux<T> ax;
         ax.m = fmax(fabs(rc.N) * (T)P::kInvTan, (T)P::kMinD);
@@ -829,6 +755,551 @@ __device__ __forceinline__ void column_chunks(const MeshView& mv, const ChunkFil
             for (int r = 0; r < ZB; ++r) S[r] += (double)acc[r];
         }
     }
+}
+
+// ---------------------------------------------------------------- points
+// Boundary sum of one point inside the fixed-point box over chunks (see kChunk).  As in
+// the grid columns up to four edges take one arctangent, but each lane chooses for its
+// own point, so that a point's result does not depend on which points share its wave.
+// No contraction in these functions: their operations, and with them the results, are
+// the same in every kernel that calls them.
+// Per edge about 35 VALU slots: per vertex 23 (the integer offsets and their conversion
+// 8, r_z, l, s with a square root and a reciprocal of four slots each), per edge N, the
+// x/y dot and D 5, a share of the product, the tests and the arctangent.
+// *p at a wave-uniform address of data that no kernel of the launch writes, by scalar loads
+// (the compiler takes vector loads for it in a kernel with atomics or LDS lists)
+template <class X>
+__device__ __forceinline__ X uniform_load(const X* p) {
+    using W = std::conditional_t<sizeof(X) % 16 == 0, unsigned __attribute__((ext_vector_type(4))), unsigned>;
+    static_assert(sizeof(X) % sizeof(W) == 0, "whole words");
+    const unsigned long long a = (unsigned long long)p;
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)a);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(a >> 32));
+    const auto q = (const __attribute__((address_space(4))) W*)(((unsigned long long)hi << 32) | lo);
+    struct Words {
+        W w[sizeof(X) / sizeof(W)];
+    } u;
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(X) / sizeof(W); ++i) u.w[i] = q[i];
+    return __builtin_bit_cast(X, u);
+}
+
+template <class T>
+struct PVert {
+    int dx, dy;
+    T rx, ry, rho2, s;
+};
+
+template <class T>
+__device__ __forceinline__ PVert<T> point_vertex(const CVert& b, int qqx, int qqy, T pz) {
+#pragma clang fp contract(off)
+    constexpr T u = (T)EdgePairs<T, 1, false>::kUnit;
+    PVert<T> v;
+    v.dx = b.qx - qqx;
+    v.dy = b.qy - qqy;
+    v.rx = (T)v.dx * u;
+    v.ry = (T)v.dy * u;
+    v.rho2 = fma(v.rx, v.rx, v.ry * v.ry);
+    const T rz = fma((T)b.z, u, -pz);
+    const T l = Arith<T>::sqrt(fma(rz, rz, v.rho2));
+    const T t = l + fabs(rz);
+    v.s = rz > (T)0 ? v.rho2 * Arith<T>::rcp(t) : t;   // l - r_z without cancellation
+    return v;
+}
+
+// N and D of the edge from entry ba to bb.  Where ba leads nowhere N is 0 and D > 0, no
+// angle.  FP32 forms N from one endpoint's offset and the edge's own x, y (exact integers,
+// kept in offset units): from the nearer one (NEARER) its error goes with that distance
+// times the edge's length, see edge_N.  FP64 has the digits for the product of both.
+template <class T, bool NEARER>
+__device__ __forceinline__ T point_N(const CVert& ba, const PVert<T>& a, const PVert<T>& b) {
+    if constexpr (sizeof(T) == 4) {
+        const bool nb = NEARER && !(a.rho2 <= b.rho2);
+        return fma(nb ? b.ry : a.ry, ba.ex, -((nb ? b.rx : a.rx) * ba.ey));
+    } else {
+        const T N = fma(a.ry, b.rx, -(a.rx * b.ry));
+        return (ba.flags & kChainEdge) ? N : (T)0;
+    }
+}
+
+template <class T>
+__device__ __forceinline__ T point_D(const CVert& ba, const PVert<T>& a, const PVert<T>& b) {
+    const T k = sizeof(T) == 4 ? (T)ba.none : (ba.flags & kChainEdge) ? (T)0 : (T)0x1p63;
+    return fma(a.s, b.s, fma(a.rx, b.rx, fma(a.ry, b.ry, k)));
+}
+
+// an edge of any angle
+template <class T>
+__device__ T point_wide(const CVert& ba, const CVert& bb, int qqx, int qqy, T pz) {
+#pragma clang fp contract(off)
+    const PVert<T> a = point_vertex<T>(ba, qqx, qqy, pz), b = point_vertex<T>(bb, qqx, qqy, pz);
+    return edge_slow<T>({a.dx, a.dy, a.rx, a.ry, a.rho2}, {b.dx, b.dy, b.rx, b.ry, b.rho2}, a.s, b.s,
+                        point_N<T, true>(ba, a, b), point_D<T>(ba, a, b), true);
+}
+
+// acc + the angles of n (2, 3 or 4) consecutive edges v[0] -> ... -> v[n].  By one
+// arctangent of the product of the D + i N where each D > m >= the edge's squared length (FP32: so N from the first endpoint is off by about
+// two ulps of D at most; also D > 0, and D^4 is far from FP32's ends, see quad_z) and the
+// sum's tangent is below tan(pi/8) (up to three angles below pi/2 are it themselves; of four,
+// the first two must be below pi/2 together).  Else each by its own where |N| < kFast D; the
+// others are left out and set their bits in odd.
+template <class T, int n>
+__device__ __forceinline__ T point_run(const CVert* b, const PVert<T>* v, bool quads, T acc, unsigned& odd) {
+#pragma clang fp contract(off)
+    using P = EdgePairs<T, 1, false>;
+    T N[n], D[n];
+    bool ok = quads;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+        N[i] = point_N<T, false>(b[i], v[i], v[i + 1]);
+        D[i] = point_D<T>(b[i], v[i], v[i + 1]);
+        ok &= D[i] > (sizeof(T) == 4 ? (T)b[i].m : (T)1);
+    }
+    T gr = fma(D[0], D[1], -(N[0] * N[1])), gi = fma(D[0], N[1], D[1] * N[0]);
+    if constexpr (n > 2) {
+        T r2 = D[2], i2 = N[2];
+        if constexpr (n == 4) {
+            ok &= gr > (T)0;
+            r2 = fma(D[2], D[3], -(N[2] * N[3]));
+            i2 = fma(D[2], N[3], D[3] * N[2]);
+        }
+        const T re = gr;
+        gr = fma(re, r2, -(gi * i2));
+        gi = fma(re, i2, gi * r2);
+    }
+    ok &= fabs(gi) < (T)P::kTan8 * gr;
+    odd = 0u;
+    if (ok) return pair_acc<T>({gr, gi}, acc);
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+        const T Ni = point_N<T, true>(b[i], v[i], v[i + 1]);
+        const bool fast = fabs(Ni) < Arith<T>::kFast * D[i];
+        const T t = Arith<T>::atan_small(Ni * Arith<T>::rcp(D[i]));
+        acc += fast ? t : (T)0;
+        odd |= fast ? 0u : 1u << i;
+    }
+    return acc;
+}
+
+// The edges of one chunk: its first three, then the other four (of which the first may
+// be none, or the last two).
+// UNIFORM: the same chunk for the wave; last: the chunk's last vertex; with cont, on entry
+// that of the chunk before it.
+struct Chunk {
+    CVert v[kChunk];
+};
+
+template <class T, bool UNIFORM>
+__device__ __forceinline__ T point_chunk(const CVert* __restrict__ chunk, int qqx, int qqy, T pz, bool quads,
+                                         PVert<T>& last, bool cont) {
+    const CVert* b = chunk;
+    Chunk c;
+    if constexpr (UNIFORM) {
+        c = uniform_load((const Chunk*)chunk);
+        b = c.v;
+    }
+    PVert<T> v[kChunk];
+    T acc = (T)0;
+#pragma unroll
+    for (int e = 1; e < 3; ++e) v[e] = point_vertex<T>(b[e], qqx, qqy, pz);
+    v[0] = cont && (b[0].flags & kChainCont) ? last : point_vertex<T>(b[0], qqx, qqy, pz);
+    v[3] = b[0].flags & kChainTri ? v[0] : point_vertex<T>(b[3], qqx, qqy, pz);
+    unsigned odd, odd1;
+    acc = point_run<T, 3>(b, v, quads, acc, odd);
+    v[4] = point_vertex<T>(b[4], qqx, qqy, pz);
+    v[5] = point_vertex<T>(b[5], qqx, qqy, pz);
+    if ((b[5].flags | b[6].flags) & kChainEdge) {
+        v[6] = point_vertex<T>(b[6], qqx, qqy, pz);
+        v[7] = b[4].flags & kChainTri ? v[4] : point_vertex<T>(b[7], qqx, qqy, pz);
+        last = v[7];
+        acc = point_run<T, 4>(b + 3, v + 3, quads, acc, odd1);
+    } else {
+        acc = point_run<T, 2>(b + 3, v + 3, quads, acc, odd1);
+    }
+    odd |= odd1 << 3;
+    while (odd) {
+        const int e = __ffs(odd) - 1;
+        odd &= odd - 1u;
+        acc += point_wide<T>(chunk[e], chunk[e + 1], qqx, qqy, pz);
+    }
+    return acc;
+}
+
+// FP32 sums are kept in units of 2^-e: rounded to whole units, the FP64 additions are
+// exact up to 2^(53 - e), so that the order of the chunks and clusters, which differs
+// between the kernels, does not show.  FP64 sums are plain.  e is 36, more for a point so
+// far away that its terms are small: above the box they go with the height's inverse
+// square, outside with the inverse distance.
+constexpr int kSumUnit = 36;
+
+template <class T>
+__device__ __forceinline__ void point_add(double& S, T v, int e) {
+    if constexpr (sizeof(T) == 4) S += rint(ldexp((double)v, e));
+    else S += v;
+}
+
+template <class T>
+__device__ __forceinline__ double point_total(double S, int e) {
+    return sizeof(T) == 4 ? ldexp(S, -e) : S;
+}
+
+__device__ __forceinline__ int point_unit(float px, float py, float pz, bool inbox, const QGrid& g) {
+    const double h = inbox ? ((double)pz - g.lo[2]) * g.scale
+                           : fmax(fmax(fabs((double)px), fabs((double)py)), fabs((double)pz)) * g.scale;
+    if (!(h > 0x1p32 && h < 1e300)) return kSumUnit;
+    const int k = ilogb(h) - 32;
+    return kSumUnit + min(inbox ? 2 * k : k, 400);
+}
+
+// the sum over chunks c0, c0 + step, ..., < c1.  pz: the point's z in offset units
+template <class T, bool UNIFORM>
+__device__ __forceinline__ void point_chunks(const MeshView& mv, int c0, int c1, int step, int qqx, int qqy, T pz,
+                                             bool quads, int unit, double& S) {
+    PVert<T> last = {};
+    for (int c = c0; c < c1; c += step)
+        point_add<T>(S, point_chunk<T, UNIFORM>(mv.chain + (size_t)c * kChunk, qqx, qqy, pz, quads,
+                                                last, UNIFORM && step == 1 && c > c0), unit);
+}
+
+// A point outside the box: boundary vertices [a, e), edge j leading from vertex j to the
+// next vertex of its loop, raw offsets in units of 2^e cells.
+template <class T>
+__device__ T outside_run(const MeshView& mv, int a, int e, T pxs, T pys, T pzs, T f) {
+    const BVert* __restrict__ bv = mv.bverts;
+    ColV<T> cp;
+    T sp;
+    load_vertex<T, 1>(bv[a], pxs, pys, &pzs, f, cp, &sp);
+    T acc = (T)0;
+    for (int j = a; j < e; ++j) {
+        const int lp = min(max(bv[j].loop, 0), mv.nloops - 1);   // in range for any stored value
+        const int nx = j + 1 < mv.loop_off[lp + 1] ? j + 1 : mv.loop_off[lp];
+        ColV<T> cn;
+        T sn;
+        load_vertex<T, 1>(bv[nx], pxs, pys, &pzs, f, cn, &sn);
+        edge_step<T, 1, true>(cp, cn, &sp, &sn, &acc);
+        if (j + 1 < e) {
+            if (nx == j + 1) {
+                cp = cn;
+                sp = sn;
+            } else {   // the next edge starts a new loop
+                load_vertex<T, 1>(bv[j + 1], pxs, pys, &pzs, f, cp, &sp);
+            }
+        }
+    }
+    return acc;
+}
+
+// its whole sum, runs of 32 edges part, part + parts, ...
+template <class T>
+__device__ void outside_sum(const MeshView& mv, float px, float py, float pz, int part, int parts, int unit,
+                            double& S) {
+    const int nb = mv.nloops > 0 ? mv.loop_off[mv.nloops] : 0;
+    const FarScale<T> fs = far_scale<T>(px, py, fabsf(pz), mv.g.scale);
+    for (int a = part * 32; a < nb; a += parts * 32)
+        point_add<T>(S, outside_run<T>(mv, a, min(nb, a + 32), (T)px * fs.scf, (T)py * fs.scf, (T)pz * fs.scf, fs.f), unit);
+}
+
+// ---------------------------------------------------------------- points, clusters
+// The boundary sum of a cluster's loops from its expansion to degree P (see
+// k_cluster_moments in build.hip for the formula; p: the point's raw position in cells).
+// About 430 VALU slots for degree 10, 200 for 6, 120 for 4: as much as 12, 6 or 4 edges.
+template <int P, bool UNIFORM>
+__device__ __forceinline__ float cluster_far(const Cluster& k, const float4* __restrict__ W, float px, float py, float pz) {
+#pragma clang fp contract(off)
+    const float x0 = (px - k.x) * k.inva, y0 = (py - k.y) * k.inva, z0 = (pz - k.z) * k.inva;
+    const float i2 = Arith<float>::rcp(fmaf(x0, x0, fmaf(y0, y0, z0 * z0)));
+    const float x = x0 * i2, y = y0 * i2, z = z0 * i2;   // u = p / |p|^2, |u|^2 = i2
+    auto w = [&](int i) {
+        const float4 t = UNIFORM ? uniform_load(W + (i >> 2)) : W[i >> 2];
+        return (i & 3) == 0 ? t.x : (i & 3) == 1 ? t.y : (i & 3) == 2 ? t.z : t.w;
+    };
+    float c = 1.f, s = 0.f, sum = 0.f;
+#pragma unroll
+    for (int m = 0; m <= P; ++m) {
+        float q0 = 0.f, q1 = 1.f, re = 0.f, im = 0.f;
+#pragma unroll
+        for (int l = m; l <= P; ++l) {
+            if (l >= 1) {
+                re = fmaf(w(l * l - 1 + (m > 0 ? 2 * m - 1 : 0)), q1, re);
+                if (m > 0) im = fmaf(w(l * l - 1 + 2 * m), q1, im);
+            }
+            const float beta = (float)(l * l - m * m) / (float)(4 * l * l - 1);
+            const float t = l == m ? z * q1 : fmaf(z, q1, -(beta * i2) * q0);
+            q0 = q1;
+            q1 = t;
+        }
+        sum = fmaf(c, re, sum);
+        if (m > 0) sum = fmaf(s, im, sum);
+        const float t = fmaf(c, x, -(s * y));
+        s = fmaf(s, x, c * y);
+        c = t;
+    }
+    return sum * Arith<float>::sqrt(i2);
+}
+
+// The degree class (index into far2) with which a cluster may stand for its loops at a
+// point, -1: none.  Beyond the distance, the vertical ray up from the point must miss the
+// loops' box (a surface spanned inside it has no crossing to be counted in chi).
+__device__ __forceinline__ int cluster_class(const Cluster& k, int qqx, int qqy, float px, float py, float pz) {
+#pragma clang fp contract(off)
+    const float x = px - k.x, y = py - k.y, z = pz - k.z, d2 = fmaf(x, x, fmaf(y, y, z * z));
+    const bool aside = (qqx < k.xlo) | (qqx > k.xhi) | (qqy < k.ylo) | (qqy > k.yhi);
+    if (!(aside | (pz > k.ztop))) return -1;
+    return d2 >= k.far2[2] ? 2 : d2 >= k.far2[1] ? 1 : d2 >= k.far2[0] ? 0 : -1;
+}
+
+struct PointPos {
+    int qx, qy;
+    float x, y, z;   // cells
+    bool quads;
+    int unit;        // see point_unit
+};
+
+// One point per lane: the clusters in depth-first order, every step the same for the
+// wave; a lane that took a cluster as far sits out its children (skip: the first cluster
+// of the lowest level that the lane has not yet got).  Of the top level only clusters part,
+// part + parts, ...
+__device__ __forceinline__ double point_clusters(const MeshView& mv, const PointPos& p, int part, int parts) {
+    double S = 0.0;
+    if (mv.nclusters < kFewClusters) {
+        point_chunks<float, true>(mv, part, mv.nchunk, parts, p.qx, p.qy, p.z * 0x1p-18f, p.quads, p.unit, S);
+        return S;
+    }
+    int L = mv.top, i = part, skip = 0;
+    while (true) {
+        const int base = uniform_load(mv.level + L), id = base + i;
+        if (id >= uniform_load(mv.level + L + 1)) break;
+        const Cluster k = uniform_load(mv.clusters + id);
+        const bool act = (i << (kFanBits * L)) >= skip;
+        const int cls = act && p.quads ? cluster_class(k, p.qx, p.qy, p.x, p.y, p.z) : -1;
+        const float4* W = (const float4*)(mv.moments + (size_t)id * kMoments);
+        if (cls >= 0) {
+            float v;
+            if (cls == 2) v = cluster_far<kPolesLow, true>(k, W, p.x, p.y, p.z);
+            else if (cls == 1) v = cluster_far<kPolesMid, true>(k, W, p.x, p.y, p.z);
+            else v = cluster_far<kPoles, true>(k, W, p.x, p.y, p.z);
+            point_add<float>(S, v, p.unit);
+            skip = (i + 1) << (kFanBits * L);
+        }
+        if (__ballot(act && cls < 0)) {
+            if (L > 0) {
+                --L;
+                i <<= kFanBits;
+                continue;
+            }
+            if (act && cls < 0) point_chunks<float, true>(mv, k.first, k.first - k.count, 1, p.qx, p.qy, p.z * 0x1p-18f, p.quads, p.unit, S);
+        }
+        ++i;
+        while (L < mv.top && (i & (kFan - 1)) == 0) {
+            i >>= kFanBits;
+            ++L;
+        }
+        if (L == mv.top) i += parts - 1;
+    }
+    return S;
+}
+
+// G points per wave: the lanes share out (cluster, point) pairs to be tested, far pairs
+// and (chunk, point) pairs of near clusters, each kind from a list in LDS, 64 at a time.
+// For few points, or points so far apart that those of a wave of one point per lane would
+// have few clusters in common.  A lane's moments are its own loads here, 30 of 16 bytes,
+// and what bounds it is their way through the cache's address unit (64 lines a load where
+// every lane has another cluster): neighbouring points in a group share those lines.
+template <int G>
+struct PointLists {
+    PointPos p[G];
+    double S[G];
+    int far[3][128], far_pt[3][128];   // by degree class
+    int leaf[128], leaf_mask[128];
+    int sum[64];
+};
+
+// of the cluster stack (ids, then masks of points).  A step pops up to 64 / G entries and
+// pushes up to kFan children of each, one level down; an entry's siblings are popped with
+// or before it, so a level has at most kFan * 64 / G entries, less 64 / G while it has
+// descendants on the stack.
+template <int G>
+inline size_t point_stack_ints(int top) {
+    return (G == 1 ? 1 : 2) * (kRoots + (size_t)(kFan - 1) * (64 / G) * top + 64);
+}
+
+__device__ __forceinline__ int lane_rank(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
+
+// position of the k-th set bit (k from 0, fewer than G set bits before the end)
+template <int G>
+__device__ __forceinline__ int nth_bit(unsigned m, int k) {
+#pragma unroll
+    for (int i = 0; i < G - 1; ++i)
+        if (i < k) m &= m - 1;
+    return __ffs(m) - 1;
+}
+
+// sums of the points ls.p[g] with a bit in mask, in their units: of point lane % G
+template <int G>
+__device__ __forceinline__ double point_group(const MeshView& mv, unsigned mask, int* stack, int stack_ints,
+                                              PointLists<G>& ls) {
+    constexpr int kEntries = 64 / G;
+    constexpr unsigned kAll = (1u << G) - 1u;
+    const int lane = threadIdx.x & 63, pt = lane % G, en = lane / G;
+    int* const smask = stack + stack_ints / 2;
+    const PointPos mine = ls.p[pt];
+    double S = 0.0;   // G == 1
+    auto add = [&](int g, int unit, float v) {
+        if constexpr (G == 1) point_add<float>(S, v, unit);
+        else __hip_atomic_fetch_add(&ls.S[g], rint(ldexp((double)v, unit)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    if (lane < G) ls.S[lane] = 0.0;
+    const int root = uniform_load(mv.level + mv.top);
+    int n = uniform_load(mv.level + mv.top + 1) - root, nleaf = 0, nfar[3] = {0, 0, 0};
+    if (lane < n) {
+        stack[lane] = root + lane;
+        if (G > 1) smask[lane] = (int)mask;
+    }
+    wave_lds_sync();
+    while (true) {
+        bool some = false;
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+            if (nfar[f] < 64 && (n > 0 || nfar[f] == 0)) continue;
+            const int m = min(nfar[f], 64);
+            nfar[f] -= m;
+            if (lane < m) {
+                const int id = ls.far[f][nfar[f] + lane], g = G == 1 ? 0 : ls.far_pt[f][nfar[f] + lane];
+                const PointPos p = G == 1 ? mine : ls.p[g];
+                const Cluster& k = mv.clusters[id];
+                const float4* W = (const float4*)(mv.moments + (size_t)id * kMoments);
+                add(g, p.unit, f == 0   ? cluster_far<kPoles, false>(k, W, p.x, p.y, p.z)
+                       : f == 1 ? cluster_far<kPolesMid, false>(k, W, p.x, p.y, p.z)
+                                : cluster_far<kPolesLow, false>(k, W, p.x, p.y, p.z));
+            }
+            some = true;
+        }
+        if (some) {
+            wave_lds_sync();
+            continue;
+        }
+        if (nleaf >= 64 || (n == 0 && nleaf > 0)) {
+            const int m = min(nleaf, 64);
+            nleaf -= m;
+            int c0 = 0, cn = 0;
+            unsigned lm = 1u;
+            if (lane < m) {
+                const Cluster& k = mv.clusters[ls.leaf[nleaf + lane]];
+                lm = G == 1 ? 1u : (unsigned)ls.leaf_mask[nleaf + lane];
+                c0 = k.first;
+                cn = -k.count * (G == 1 ? 1 : __popc(lm));
+            }
+            int t = cn;   // inclusive sums
+            for (int d = 1; d < 64; d <<= 1) {
+                const int o = __shfl_up(t, d);
+                if (lane >= d) t += o;
+            }
+            ls.sum[lane] = t;
+            const int total = __shfl(t, 63), before = t - cn;
+            wave_lds_sync();
+            for (int j0 = 0; j0 < total; j0 += 64) {
+                const int j = min(j0 + lane, total - 1);
+                int a = 0;   // the first range whose sum exceeds j
+                for (int h = 32; h > 0; h >>= 1)
+                    if (ls.sum[a + h - 1] <= j) a += h;
+                int r = j - __shfl(before, a), g = 0;
+                if constexpr (G > 1) {
+                    const unsigned am = (unsigned)__shfl((int)lm, a);
+                    const int np = __popc(am), q = r / np;
+                    g = nth_bit<G>(am, r - q * np);
+                    r = q;
+                }
+                const int c = __shfl(c0, a) + r;
+                const PointPos p = G == 1 ? mine : ls.p[g];
+                PVert<float> end;
+                if (j0 + lane < total)
+                    add(g, p.unit, point_chunk<float, false>(mv.chain + (size_t)c * kChunk, p.qx, p.qy, p.z * 0x1p-18f, p.quads, end, false));
+            }
+            wave_lds_sync();
+            continue;
+        }
+        if (n == 0) break;
+        const int m = min(n, kEntries);
+        n -= m;
+        int cls = -2, id = 0, first = 0, count = 0;   // -2: no pair
+        if (en < m && (G == 1 || ((unsigned)smask[n + en] >> pt & 1u))) {
+            id = stack[n + en];
+            const Cluster& k = mv.clusters[id];
+            cls = mine.quads ? cluster_class(k, mine.qx, mine.qy, mine.x, mine.y, mine.z) : -1;
+            first = k.first;
+            count = k.count;
+        }
+        wave_lds_sync();
+        const bool near = cls == -1;
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+            const unsigned long long b = __ballot(cls == f);
+            if (cls == f) {
+                ls.far[f][nfar[f] + lane_rank(b)] = id;
+                if (G > 1) ls.far_pt[f][nfar[f] + lane_rank(b)] = pt;
+            }
+            nfar[f] += __popcll(b);
+        }
+        // one lane per entry that is near for some point: its first such point's
+        unsigned long long b = __ballot(near);
+        const unsigned nm = G == 1 ? (near ? 1u : 0u) : (unsigned)(b >> (en * G)) & kAll;
+        const bool lead = near && (G == 1 || (nm & ((1u << pt) - 1u)) == 0u);
+        b = __ballot(lead && count <= 0);
+        if (lead && count <= 0) {
+            ls.leaf[nleaf + lane_rank(b)] = id;
+            if (G > 1) ls.leaf_mask[nleaf + lane_rank(b)] = (int)nm;
+        }
+        nleaf += __popcll(b);
+        if (!lead) count = 0;
+        if (__ballot(count > 0)) {
+#pragma unroll
+            for (int c = 0; c < kFan; ++c) {
+                b = __ballot(c < count);
+                if (c < count) {
+                    stack[n + lane_rank(b)] = first + c;
+                    if (G > 1) smask[n + lane_rank(b)] = (int)nm;
+                }
+                n += __popcll(b);
+            }
+        }
+        wave_lds_sync();
+    }
+    if constexpr (G == 1) {
+        for (int o = 32; o > 0; o >>= 1) S += __shfl_xor(S, o);
+        return S;
+    } else {
+        return ls.S[pt];
+    }
+}
+
+// points j0 ... j0 + m - 1 of the order perm (nullable), m <= G: w from chi and the sums
+template <int G>
+__device__ __forceinline__ void point_group_out(const MeshView& mv, const float* __restrict__ qx,
+                                                const float* __restrict__ qy, const float* __restrict__ qz,
+                                                long long qs, long long j0, int m, const int* __restrict__ perm,
+                                                int* stack, int stack_ints, PointLists<G>& ls,
+                                                const int* __restrict__ chi, float* __restrict__ w) {
+    const int lane = threadIdx.x & 63;
+    const long long j = j0 + min(lane, m - 1), i = perm ? (long long)perm[j] : j;
+    const float px = qx[i * qs], py = qy[i * qs], pz = qz[i * qs];
+    const QPoint q = quantize_point(px, py, pz, mv.g);
+    const float sc = mv.g.scalef;
+    const int unit = point_unit(px, py, pz, q.inbox, mv.g);
+    if (lane < G) ls.p[lane] = {q.x, q.y, px * sc, py * sc, pz * sc, quad_z(pz, mv.g), unit};
+    const unsigned in = (unsigned)__ballot(lane < m && q.inbox), out = (unsigned)__ballot(lane < m && !q.inbox);
+    wave_lds_sync();
+    double S = in && mv.nclusters > 0 ? point_group<G>(mv, in, stack, stack_ints, ls) : 0.0;
+    for (int g = 0; g < m; ++g) {   // rare: outside the box
+        if (!(out >> g & 1u)) continue;
+        double So = 0.0;
+        outside_sum<float>(mv, __shfl(px, g), __shfl(py, g), __shfl(pz, g), lane, 64, __shfl(unit, g), So);
+        for (int o = 32; o > 0; o >>= 1) So += __shfl_xor(So, o);
+        if (lane == g) S = So;
+    }
+    if (lane < m) w[i] = (float)((double)chi[i] + point_total<float>(S, unit) * kInv2Pi);
+    wave_lds_sync();
 }
 
 // ---------------------------------------------------------------- grids

@@ -25,8 +25,14 @@ struct gwn_mesh_s {
     float4* trif = nullptr;        // float corners in Morton order (direct sum)
     gwn::BVert* bverts = nullptr;
     int* loop_off = nullptr;
-    gwn::BVert* chain = nullptr;   // the boundary in chunks (gwn_internal.h)
+    gwn::CVert* chain = nullptr;   // the boundary in chunks (gwn_internal.h)
+    gwn::GVertex* gchain = nullptr;
     int4* cbox = nullptr;
+    gwn::Cluster* clusters = nullptr;
+    float* moments = nullptr;
+    int64_t nclusters = 0;   // on the lowest level
+    int cluster_top = 0;
+    int cluster_level[gwn::kLevels + 1] = {};
     int64_t nchunk = 0;
     double chunk_w = 0.0;          // mean of the chunks' x and y extents, in cells
     // query tuning (gwn_mesh_set_tuning / gwn_mesh_autotune); 0 = the built-in rule
@@ -43,6 +49,12 @@ struct gwn_mesh_s {
         v.loop_off = loop_off;
         v.chain = chain;
         v.cbox = cbox;
+        v.gchain = gchain;
+        v.clusters = clusters;
+        v.moments = moments;
+        v.nclusters = (int)nclusters;
+        v.top = cluster_top;
+        v.level = reinterpret_cast<const int*>(clusters + cluster_level[gwn::kLevels]);   // behind the clusters
         v.nchunk = (int)nchunk;
         v.nloops = (int)nloops;
         v.nf = (int)nf;
@@ -87,23 +99,34 @@ gwn_status query_grid(const gwn_mesh_s* m, const double* origin, const double* s
 // GWN_MAX_LAUNCH_QUERIES (a positive multiple of 256) lowers it, for tests.
 int64_t max_launch_queries();
 
-// Few points against many boundary edges take a workgroup per point with the
-// edges split among its lanes: batches of at most 8,192 points on meshes with at
-// least 16 boundary edges per lane of a 256-lane workgroup.
+// Few points share a point's boundary sum among lanes.  FP64 and the gradient (prec -1: the
+// built-in rule only): a workgroup per point in batches of at most 8,192 points on meshes
+// with at least 16 boundary edges per lane of a 256-lane workgroup.  FP32: a wave per point
+// up to kSinglePoints, groups of four points per wave up to kDensePoints, on meshes of at
+// least kGroupEdges edges (64 up to 16,384 points); else a point per lane, up to kSharedPoints with four waves to
+// share 64 points' clusters.
+// ms for a wave per point / groups / shared lanes / a point per lane on a torus of loops of
+// 63 k edges: 1 k points 0.06 / 0.08 / - / 11.1 (unordered), 4 k 0.15 / 0.15 / - / 11.9,
+// 33 k 0.86 / 0.76 / 1.1 / 2.6, 66 k 1.20 / 1.49 / 1.30 / 2.1, 262 k - / 3.3 / 2.1 / 2.7,
+// 1 M - / - / 4.4 / 4.5, 2 M - / - / 7.6 / 7.2; on 171 edges (the sums alone) 66 k
+// points groups 0.073, shared lanes 0.028; 16 k with the crossings 0.055 each.
 // GWN_SPLIT_BOUNDARY=0/1 overrides.
-// prec: the precision whose tuning applies (-1: the built-in rule only).
 bool want_split(const gwn_mesh_s* m, int64_t n, int prec);
+
+constexpr int64_t kDensePoints = 48 << 10, kSinglePoints = 6144, kSharedPoints = 1 << 20, kGroupEdges = 512;
 
 // Morton order of the points' quantised x, y for the crossing traversal (perm is
 // stream-ordered device memory the caller frees with hipFreeAsync).
 // GWN_ORDER_QUERIES=0/1 overrides the size heuristic.
 bool want_xy_order(const gwn_mesh_s* m, int64_t n);
+// space: along a curve through x, y and z instead, for the boundary sum over clusters.
+bool want_space_order(const gwn_mesh_s* m, int64_t n, int prec);
 gwn_status xy_order(const gwn_mesh_s* m, const float* qx, const float* qy, const float* qz, int64_t qstride, int64_t n,
-                    int** perm, hipStream_t stream);
+                    bool space, int** perm, hipStream_t stream);
 // the same into caller memory: perm (n ints) and temp (xy_order_temp_bytes(n))
 size_t xy_order_temp_bytes(int64_t n);
 gwn_status xy_order_into(const gwn_mesh_s* m, const float* qx, const float* qy, const float* qz, int64_t qstride,
-                         int64_t n, int* perm, void* temp, hipStream_t stream);
+                         int64_t n, bool space, int* perm, void* temp, hipStream_t stream);
 
 gwn_status query_grid_gradient(const gwn_mesh_s* m, const double* origin, const double* spacing, const int64_t* dims,
                                int prec, void* g_out, hipStream_t stream);

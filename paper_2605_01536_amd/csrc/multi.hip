@@ -1,14 +1,14 @@
 // multi.hip -- many meshes with uneven sizes and query counts in one captured
-// HIP graph: [reset work counter] -> [crossing counts for every query of every
-// mesh] -> [persistent boundary-term kernel].  The persistent kernel keeps
-// waves resident and hands out (mesh, query tile) work items through an atomic
+// HIP graph: [reset work counters] -> [crossing counts for every query of every
+// mesh] -> [persistent boundary-term kernels].  The persistent kernels keep
+// waves resident and hand out (mesh, query tile) work items through an atomic
 // counter, largest estimated cost first, so meshes whose cost spans orders of
 // magnitude share the GPU without a long tail.  The schedule (tile size, item
 // order, resident waves) is chosen by timing candidates (autotune) and can be
-// cached in a JSON-lines file keyed by device and problem size.  Optionally the
-// queries of each mesh are taken in Morton order of their quantised x, y (an
-// index permutation made once at creation), so that the 64 queries of a wave
-// lie close together and take the same branches of the boundary loop.
+// cached in a JSON-lines file keyed by device and problem size.  Meshes with
+// many queries take them 64 neighbours to a wave, in orders (index
+// permutations) made once at creation from the query values then; the others a
+// few queries per wave as they come.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -20,6 +20,7 @@
 #include "gwn_alloc.h"
 #include "gwn_kernels.h"
 #include "gwn_mesh.h"
+#include "gwn_sort.h"
 
 namespace gwn {
 namespace {
@@ -31,7 +32,7 @@ struct alignas(16) Item {
 };
 
 __global__ void k_reset_counter(int* c) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *c = 0;
+    if (threadIdx.x < 2 && blockIdx.x == 0) c[threadIdx.x] = 0;
 }
 
 // Crossing counts along +z for every query, one wave per work item: the item's
@@ -63,54 +64,102 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_chi_items(const MeshView* _
     }
 }
 
-// global query index i0 + perm_local[i - i0] for i in [i0, i0 + n)
-__global__ void k_perm_offset(const int* __restrict__ local, long long i0, int n, int* __restrict__ perm) {
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k < n) perm[i0 + k] = (int)(i0 + (local ? local[k] : k));
-}
-
-// Persistent boundary-term kernel: every wave claims items until none are left
-// (the counter only grows, so every wave reaches the exit).  perm (nullable):
-// position i of the work list is query perm[i], a permutation within each mesh.
-// T is the geometry precision; per query it takes the same steps, in the same
-// order, as the one-lane-per-point batch kernel, so the results are the same bits.
-// FP32 is held to 64 VGPRs, so the 8 resident waves per SIMD the schedules ask
-// for all fit (68 unconstrained, i.e. 7).
-template <class T>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 8 : 1)))
-void k_bdry_persistent(const MeshView* __restrict__ table, const Item* __restrict__ items, int nitems,
-                       int* __restrict__ counter, const float* __restrict__ qx, const float* __restrict__ qy,
-                       const float* __restrict__ qz, long long qs, const int* __restrict__ perm,
-                       const int* __restrict__ chi, T* __restrict__ w) {
-    const int lane = threadIdx.x & 63;
-    while (true) {
-        int it = 0;
-        if (lane == 0) it = atomicAdd(counter, 1);
-        it = __builtin_amdgcn_readfirstlane(__shfl(it, 0));
-        if (it >= nitems) break;
-        const Item I = items[it];
-        const MeshView mv = table[I.mesh];
-        const float *x = qx, *y = qy, *z = qz;
-        axis_ptrs(mv.axis, x, y, z);   // the mesh's frame
-        for (int sub = 0; sub < I.nq; sub += 64) {
-            const int k = sub + lane;
-            const long long i0 = I.q0 + min(k, I.nq - 1);
-            const long long i = perm ? (long long)perm[i0] : i0;
-            const float px = x[i * qs], py = y[i * qs], pz = z[i * qs];
-            const QPoint q = quantize_point(px, py, pz, mv.g);
-            double S = 0.0;
-            if (q.inbox) {
-                const T pzs = (T)pz * (T)mv.g.scale;
-                boundary_loops<T, 1, false>(mv, q.x, q.y, (T)0, (T)0, &pzs, &S, (T)1, near_z(pz, mv.g));
-            } else {
-                const FarScale<T> fs = far_scale<T>(px, py, fabsf(pz), mv.g.scale);
-                const T pzs = (T)pz * fs.scf;
-                boundary_loops<T, 1, true>(mv, 0, 0, (T)px * fs.scf, (T)py * fs.scf, &pzs, &S, fs.f);
-            }
-            if (k < I.nq) w[i] = (T)((double)chi[i] + S * kInv2Pi);
-        }
+// sort keys of all queries: the mesh, then (items [0, nkeyed)) the query's place in the order
+__global__ void k_plan_keys(const MeshView* __restrict__ table, const Item* __restrict__ items, int nkeyed,
+                            const float* __restrict__ qx, const float* __restrict__ qy, const float* __restrict__ qz,
+                            long long qs, bool space, uint64_t* __restrict__ key, int* __restrict__ idx) {
+    const Item I = items[blockIdx.x];
+    const QGrid g = table[I.mesh].g;
+    const float *x = qx, *y = qy, *z = qz;
+    axis_ptrs(table[I.mesh].axis, x, y, z);
+    for (int k = threadIdx.x; k < I.nq; k += blockDim.x) {
+        const long long i = I.q0 + k;
+        uint32_t c = 0;
+        if ((int)blockIdx.x < nkeyed) c = point_key(quantize_point(x[i * qs], y[i * qs], z[i * qs], g), space);
+        key[i] = ((uint64_t)I.mesh << 32) | c;
+        idx[i] = (int)i;
     }
 }
+
+// Persistent boundary-term kernel: every wave claims 64 queries of an item at a time, one
+// per lane, until none are left (the counter only grows, so every wave reaches the exit).
+// perm (nullable): position i of the work list is query perm[i], a permutation within each
+// mesh.  T is the geometry precision; per query the sums have the batch kernels' terms, so
+// the results are the same bits.
+// The mesh's data are read by scalar loads (see uniform_load): 7.2 ms instead of 10.3 for
+// 3.2 M queries on 48 soups; claims of 64 queries instead of 128 shorten the last wave's
+// way (a wave's way through the largest soup takes 2.5 ms).
+template <class T>
+__global__ __launch_bounds__(256) void k_bdry_persistent(const MeshView* __restrict__ table,
+                                                        const Item* __restrict__ items, int nitems, int claims,
+                                                        int* __restrict__ counter, const float* __restrict__ qx,
+                                                        const float* __restrict__ qy, const float* __restrict__ qz,
+                                                        long long qs, const int* __restrict__ perm,
+                                                        const int* __restrict__ chi, T* __restrict__ w) {
+    const int lane = threadIdx.x & 63;
+    while (true) {
+        int t = 0;
+        if (lane == 0) t = atomicAdd(counter, 1);
+        t = __builtin_amdgcn_readfirstlane(__shfl(t, 0));
+        const int it = t / claims, sub = (t - it * claims) * 64;
+        if (it >= nitems) break;
+        const Item I = uniform_load(items + it);
+        if (sub >= I.nq) continue;
+        const MeshView mv = uniform_load(table + I.mesh);
+        const float *x = qx, *y = qy, *z = qz;
+        axis_ptrs(mv.axis, x, y, z);   // the mesh's frame
+        const int k = sub + lane;
+        const long long i0 = I.q0 + min(k, I.nq - 1);
+        const long long i = perm ? (long long)perm[i0] : i0;
+        const float px = x[i * qs], py = y[i * qs], pz = z[i * qs];
+        const QPoint q = quantize_point(px, py, pz, mv.g);
+        const int unit = sizeof(T) == 4 ? point_unit(px, py, pz, q.inbox, mv.g) : 0;
+        double S = 0.0;
+        if (!q.inbox) {
+            outside_sum<T>(mv, px, py, pz, 0, 1, unit, S);
+        } else if constexpr (sizeof(T) == 4) {
+            const float sc = mv.g.scalef;
+            S = point_clusters(mv, {q.x, q.y, px * sc, py * sc, pz * sc, quad_z(pz, mv.g), unit}, 0, 1);
+        } else {
+            point_chunks<T, true>(mv, 0, mv.nchunk, 1, q.x, q.y, (T)pz * (T)mv.g.scale, quad_z(pz, mv.g), unit, S);
+        }
+        if (k < I.nq) w[i] = (T)((double)chi[i] + point_total<T>(S, unit) * kInv2Pi);
+    }
+}
+
+// FP32 boundary term, groups of kPlanGroup queries per wave (see point_group): a wave claims
+// kPlanClaim queries of an item at a time.
+constexpr int kPlanGroup = 4, kPlanClaim = 16;
+
+__global__ __launch_bounds__(256) void k_group_persistent(const MeshView* __restrict__ table,
+                                                         const Item* __restrict__ items, int nitems, int claims,
+                                                         int* __restrict__ counter, const float* __restrict__ qx,
+                                                         const float* __restrict__ qy, const float* __restrict__ qz,
+                                                         long long qs, const int* __restrict__ perm, int stack_ints,
+                                                         const int* __restrict__ chi, float* __restrict__ w) {
+    __shared__ PointLists<kPlanGroup> lists[4];
+    extern __shared__ int stacks[];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    while (true) {
+        int t = 0;
+        if (lane == 0) t = atomicAdd(counter, 1);
+        t = __builtin_amdgcn_readfirstlane(__shfl(t, 0));
+        const int it = t / claims, k0 = (t - it * claims) * kPlanClaim;
+        if (it >= nitems) break;
+        const Item I = uniform_load(items + it);
+        if (k0 >= I.nq) continue;
+        const MeshView mv = uniform_load(table + I.mesh);
+        const float *x = qx, *y = qy, *z = qz;
+        axis_ptrs(mv.axis, x, y, z);   // the mesh's frame
+        for (int k = k0; k < min(I.nq, k0 + kPlanClaim); k += kPlanGroup)
+            point_group_out<kPlanGroup>(mv, x, y, z, qs, I.q0 + k, min(kPlanGroup, I.nq - k), perm,
+                                        stacks + (size_t)wave * stack_ints, stack_ints, lists[wave], chi, w);
+    }
+}
+
+// 48 soups of 0.5 to 11 k edges, queries per soup on average, ms in order against in groups:
+// 67 k 5.9 / 19.6, 34 k 4.4 / 10.0, 17 k 4.2 / 5.1, 8 k 4.0 / 2.7, 4 k 3.6 / 1.5.
+constexpr long long kDenseQueries = 16384;
 
 struct Schedule {
     int item_queries = 128;   // multiple of 64
@@ -142,8 +191,12 @@ struct gwn_multi_s {
     gwn::MeshView* table = nullptr;
     gwn::Item* items = nullptr;
     int nitems = 0;
-    int* perm = nullptr;   // Morton order of each mesh's queries (made when a schedule asks for it)
-    int* counter = nullptr;
+    int ndense = 0;        // of them, in front: those of meshes with many queries (see is_dense)
+    // each mesh's queries in an order: Morton order of x and y (for the crossing walk, and what a
+    // schedule asks for), and a space-filling curve's (FP32 boundary term)
+    int *perm = nullptr, *sperm = nullptr;
+    int sorted = 0;           // perm holds: 0 nothing, 1 the dense meshes' queries, 2 all
+    int* counter = nullptr;   // two
     int grid = 0;
     hipStream_t cap = nullptr;
     hipGraph_t graph = nullptr;
@@ -167,9 +220,17 @@ void release(gwn_multi_s* p) {
     (void)hipFree(p->table);
     (void)hipFree(p->items);
     (void)hipFree(p->perm);
+    (void)hipFree(p->sperm);
     (void)hipFree(p->counter);
     if (p->own_chi) (void)hipFree(p->chi);
     delete p;
+}
+
+// Meshes with at least kDenseQueries queries take them in order, 64 neighbours to a wave: for
+// the crossing walk, and in FP32 for the boundary term's clusters.  The others' queries lie
+// too far apart for that: a wave per query and groups of queries.
+bool is_dense(const gwn_multi_s* p, int mesh) {
+    return p->nq <= 0x7fffffffll && p->qoff_h[mesh + 1] - p->qoff_h[mesh] >= kDenseQueries;
 }
 
 // Work list for a schedule: tiles of item_queries queries, ordered by estimated
@@ -197,6 +258,7 @@ gwn_status build_items(gwn_multi_s* p, const Schedule& s, hipStream_t st) {
         for (size_t i = 0; i < idx.size(); ++i) s2[i] = h[idx[i]];
         h.swap(s2);
     }
+    p->ndense = (int)(std::stable_partition(h.begin(), h.end(), [&](const Item& i) { return is_dense(p, i.mesh); }) - h.begin());
     (void)hipFree(p->items);
     p->items = nullptr;
     p->nitems = (int)h.size();
@@ -207,28 +269,29 @@ gwn_status build_items(gwn_multi_s* p, const Schedule& s, hipStream_t st) {
     return GWN_OK;
 }
 
-// Each mesh's queries in Morton order of their quantised x, y in the mesh's
-// frame (the batch path's traversal order), as one permutation of all queries.
-gwn_status build_perm(gwn_multi_s* p, hipStream_t st) {
-    if (p->perm) return GWN_OK;
-    GWN_HIP_TRY(gwn::dmalloc((void**)&p->perm, sizeof(int) * (size_t)std::max<long long>(1, p->nq)));
-    for (int m = 0; m < p->nmesh; ++m) {
-        const long long q0 = p->qoff_h[m], n = p->qoff_h[m + 1] - q0;
-        if (n <= 0) continue;
-        const float *x = p->qx, *y = p->qy, *z = p->qz;
-        axis_ptrs(p->meshes[m]->axis, x, y, z);
-        int* local = nullptr;
-        if (n > 1) {
-            const gwn_status r = xy_order(p->meshes[m], x + q0 * p->qs, y + q0 * p->qs, z + q0 * p->qs, p->qs, n,
-                                          &local, st);
-            if (r != GWN_OK) return r;
-        }
-        k_perm_offset<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(local, q0, (int)n, p->perm);
-        const hipError_t e = hipGetLastError();
-        if (local) (void)hipFreeAsync(local, st);
-        GWN_HIP_TRY(e);
-    }
-    GWN_HIP_TRY(hipStreamSynchronize(st));
+// Each mesh's queries in Morton order of their quantised x, y in the mesh's frame, or along
+// the space-filling curve (the batch path's traversal orders), as one permutation of all
+// queries; all: not only of the dense meshes.  One sort for all meshes: with a sort each, 48
+// meshes of 67 k queries took 10 ms per order.
+gwn_status build_perm(gwn_multi_s* p, bool space, bool all, int** perm, hipStream_t st) {
+    const int64_t n = p->nq;
+    if (n <= 0) return GWN_OK;
+    if (!*perm) GWN_HIP_TRY(gwn::dmalloc((void**)perm, sizeof(int) * (size_t)n));
+    int bits = 32;
+    while ((1ll << (bits - 32)) < p->nmesh) ++bits;
+    const size_t kb = ((size_t)n * 8 + 255) & ~(size_t)255, ib = ((size_t)n * 4 + 255) & ~(size_t)255;
+    unsigned char* tmp = nullptr;
+    GWN_HIP_TRY(gwn::dmalloc((void**)&tmp, 2 * kb + ib + sort_temp_bytes(n, 8, true)));
+    uint64_t *k0 = (uint64_t*)tmp, *k1 = (uint64_t*)(tmp + kb);
+    int* i0 = (int*)(tmp + 2 * kb);
+    k_plan_keys<<<(unsigned)p->nitems, 128, 0, st>>>(p->table, p->items, all ? p->nitems : p->ndense, p->qx, p->qy, p->qz,
+                                                    p->qs, space, k0, i0);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = radix_sort_u64(k0, k1, i0, *perm, n, 0, bits, tmp + 2 * kb + ib, st);
+    const hipError_t e2 = hipStreamSynchronize(st);
+    (void)hipFree(tmp);
+    GWN_HIP_TRY(e);
+    GWN_HIP_TRY(e2);
     return GWN_OK;
 }
 
@@ -237,21 +300,37 @@ gwn_status capture(gwn_multi_s* p, const Schedule& s) {
     int ncu = 0;
     GWN_HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, p->device));
     const long long waves = (long long)ncu * 4 * s.waves_per_simd;
-    const long long need = ((long long)p->nitems + 3) / 4;   // no more blocks than 4-wave groups of items
+    const int claims = (s.item_queries + kPlanClaim - 1) / kPlanClaim, lanes = (s.item_queries + 63) / 64;
+    const long long need = (p->ndense < p->nitems && p->prec != GWN_PREC_FP64 ? (long long)p->nitems * claims : (long long)p->nitems * lanes) / 4 + 1;   // no more waves than claims
     p->grid = (int)std::max<long long>(1, std::min<long long>(waves / 4, std::max<long long>(need, 1)));
     GWN_HIP_TRY(hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal));
     k_reset_counter<<<1, 64, 0, p->cap>>>(p->counter);
     if (p->nq > 0) {
-        const int* perm = (s.order & kOrderSorted) ? p->perm : nullptr;
-        k_chi_items<<<(unsigned)((p->nitems + kGridWaves - 1) / kGridWaves), 64 * kGridWaves, 0, p->cap>>>(
-            p->table, p->items, p->nitems, p->qx, p->qy, p->qz, p->qs, perm, p->chi);
-        if (p->prec == GWN_PREC_FP64)
-            k_bdry_persistent<double><<<p->grid, 256, 0, p->cap>>>(p->table, p->items, p->nitems, p->counter, p->qx,
-                                                                   p->qy, p->qz, p->qs, perm, p->chi,
-                                                                   (double*)p->w);
-        else
-            k_bdry_persistent<float><<<p->grid, 256, 0, p->cap>>>(p->table, p->items, p->nitems, p->counter, p->qx,
-                                                                  p->qy, p->qz, p->qs, perm, p->chi, (float*)p->w);
+        const int nd = p->ndense, ns = p->nitems - nd;
+        if (nd > 0)
+            k_chi_items<<<(unsigned)((nd + kGridWaves - 1) / kGridWaves), 64 * kGridWaves, 0, p->cap>>>(
+                p->table, p->items, nd, p->qx, p->qy, p->qz, p->qs, p->perm, p->chi);
+        if (ns > 0)
+            k_chi_items<<<(unsigned)((ns + kGridWaves - 1) / kGridWaves), 64 * kGridWaves, 0, p->cap>>>(
+                p->table, p->items + nd, ns, p->qx, p->qy, p->qz, p->qs, (s.order & kOrderSorted) ? p->perm : nullptr,
+                p->chi);
+        if (p->prec == GWN_PREC_FP64) {
+            k_bdry_persistent<double><<<p->grid, 256, 0, p->cap>>>(
+                p->table, p->items, p->nitems, lanes, p->counter, p->qx, p->qy, p->qz, p->qs,
+                (s.order & kOrderSorted) ? p->perm : nullptr, p->chi, (double*)p->w);
+        } else {
+            if (nd > 0)
+                k_bdry_persistent<float><<<p->grid, 256, 0, p->cap>>>(p->table, p->items, nd, lanes, p->counter, p->qx, p->qy,
+                                                                      p->qz, p->qs, p->sperm, p->chi, (float*)p->w);
+            if (ns > 0) {
+                int top = 0;
+                for (const gwn_mesh_s* m : p->meshes) top = std::max(top, m->cluster_top);
+                const size_t ints = point_stack_ints<kPlanGroup>(top);
+                k_group_persistent<<<p->grid, 256, 4 * ints * sizeof(int), p->cap>>>(
+                    p->table, p->items + nd, ns, claims, p->counter + 1, p->qx, p->qy, p->qz, p->qs, nullptr, (int)ints,
+                    p->chi, (float*)p->w);
+            }
+        }
     }
     hipError_t e = hipStreamEndCapture(p->cap, &p->graph);
     GWN_HIP_TRY(e);
@@ -261,10 +340,15 @@ gwn_status capture(gwn_multi_s* p, const Schedule& s) {
 
 gwn_status apply(gwn_multi_s* p, Schedule s, hipStream_t st) {
     if (p->nq > 0x7fffffffll) s.order &= ~kOrderSorted;   // the permutation holds 32-bit indices
-    gwn_status r = (s.order & kOrderSorted) ? build_perm(p, st) : GWN_OK;
+    gwn_status r = build_items(p, s, st);
     if (r != GWN_OK) return r;
-    r = build_items(p, s, st);
-    if (r != GWN_OK) return r;
+    const bool all = (s.order & kOrderSorted) != 0;
+    if ((all && p->sorted < 2) || (p->ndense > 0 && p->sorted < 1)) {
+        r = build_perm(p, false, all, &p->perm, st);
+        if (r == GWN_OK && p->prec != GWN_PREC_FP64 && p->ndense > 0 && !p->sperm) r = build_perm(p, true, false, &p->sperm, st);
+        if (r != GWN_OK) return r;
+        p->sorted = all ? 2 : 1;
+    }
     r = capture(p, s);
     if (r != GWN_OK) return r;
     p->sched = s;
@@ -364,7 +448,7 @@ gwn_status multi_create(const gwn_mesh* meshes, int nmesh, const float* qx, cons
     std::vector<MeshView> tab(nmesh);
     for (int m = 0; m < nmesh; ++m) tab[m] = p->meshes[m]->view();
     GWN_HIP_TRY(gwn::dmalloc((void**)&p->table, sizeof(MeshView) * (size_t)nmesh));
-    GWN_HIP_TRY(gwn::dmalloc((void**)&p->counter, sizeof(int)));
+    GWN_HIP_TRY(gwn::dmalloc((void**)&p->counter, 2 * sizeof(int)));
     GWN_HIP_TRY(hipMemcpyAsync(p->table, tab.data(), sizeof(MeshView) * nmesh, hipMemcpyHostToDevice, st));
     GWN_HIP_TRY(hipStreamSynchronize(st));
     GWN_HIP_TRY(hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking));

@@ -25,7 +25,6 @@ __global__ __launch_bounds__(kChiBlock) void k_chi_batch(MeshView mv, const floa
     chi[i] = q.inbox ? chi_up(mv, q, stk + threadIdx.x) : 0;
 }
 
-
 // Crossing counts of Morton-ordered points, one wave-uniform traversal per wave
 // (chi_wave_walk): neighbouring lines share almost their whole path, so the
 // wave walks about one path instead of 64 divergent ones.  UP: the +z ray only
@@ -69,104 +68,91 @@ __global__ __launch_bounds__(kChiBlock) void k_chi_line(MeshView mv, const float
 
 // ---------------------------------------------------------------- boundary, batch
 
-template <class T>
+// PARTS > 1 (FP32): that many waves share 64 points, each with a part of the clusters, the
+// sums added in LDS.
+template <class T, int PARTS>
 __global__ __launch_bounds__(256) void k_bdry_batch(MeshView mv, const float* __restrict__ qx, const float* __restrict__ qy,
                                                     const float* __restrict__ qz, long long qs, long long nq,
                                                     const int* __restrict__ perm, const int* __restrict__ chi,
                                                     T* __restrict__ w) {
-    const long long j = blockIdx.x * 256ll + threadIdx.x;
-    if (nq <= 0 || blockIdx.x * 256ll >= nq) return;
+    static_assert(PARTS == 1 || (PARTS == 4 && sizeof(T) == 4), "a workgroup of four waves");
+    const int wave = PARTS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const long long j = (long long)blockIdx.x * (256 / PARTS) + (PARTS == 1 ? threadIdx.x : threadIdx.x & 63);
     const long long jj = j < nq ? j : nq - 1;
     // with a traversal order, lane j takes point perm[j]: the lanes of a wave are
-    // neighbours in x/y, so an edge's pair test passes or fails for all of them
+    // neighbours, with the same clusters near and far
     const long long i = j < nq ? (perm ? (long long)perm[j] : j) : nq;
     const long long ii = perm ? (long long)perm[jj] : jj;
     const float px = qx[ii * qs], py = qy[ii * qs], pz = qz[ii * qs];
     const QPoint q = quantize_point(px, py, pz, mv.g);
-    // lanes outside the fixed-point grid (rare) take the raw-offset loop
+    const int unit = sizeof(T) == 4 ? point_unit(px, py, pz, q.inbox, mv.g) : 0;
     double S = 0.0;
-    if (q.inbox) {
-        const T pzs = (T)pz * (T)mv.g.scale;
-        boundary_loops<T, 1, false>(mv, q.x, q.y, (T)0, (T)0, &pzs, &S, (T)1, near_z(pz, mv.g));
+    if (!q.inbox) {   // rare: raw offsets, edge by edge
+        outside_sum<T>(mv, px, py, pz, wave, PARTS, unit, S);
+    } else if constexpr (sizeof(T) == 4) {
+        const float sc = mv.g.scalef;
+        S = point_clusters(mv, {q.x, q.y, px * sc, py * sc, pz * sc, quad_z(pz, mv.g), unit}, wave, PARTS);
     } else {
-        const FarScale<T> fs = far_scale<T>(px, py, fabsf(pz), mv.g.scale);
-        const T pzs = (T)pz * fs.scf;
-        boundary_loops<T, 1, true>(mv, 0, 0, (T)px * fs.scf, (T)py * fs.scf, &pzs, &S, fs.f);
+        point_chunks<T, true>(mv, 0, mv.nchunk, 1, q.x, q.y, (T)pz * (T)mv.g.scale, quad_z(pz, mv.g), unit, S);
     }
-    if (i < nq) w[i] = (T)((double)chi[i] + S * kInv2Pi);
+    if constexpr (PARTS > 1) {
+        __shared__ double part[PARTS][64];
+        const int lane = threadIdx.x & 63;
+        part[wave][lane] = S;
+        __syncthreads();
+        if (wave > 0) return;
+        for (int v = 1; v < PARTS; ++v) S += part[v][lane];
+    }
+    if (i < nq) w[i] = (T)((double)chi[i] + point_total<T>(S, unit) * kInv2Pi);
 }
 
-// ---------------------------------------------------------------- boundary, split
-// Few points against many boundary edges: one workgroup per point, each lane
-// a contiguous run of boundary vertices (edge j leads from vertex j to the next
-// vertex of its loop), the partial sums reduced across the wave by shuffles and
-// across the workgroup in LDS, in a fixed order.  Fills the GPU where one lane
-// per point would leave most of it idle.
+// ---------------------------------------------------------------- boundary, few points
+// FP32: G points per wave (see point_group).
+constexpr int kPointWaves = 4;
 
+template <int G>
+__global__ __launch_bounds__(64 * kPointWaves) void k_bdry_group(MeshView mv, const float* __restrict__ qx,
+                                                                const float* __restrict__ qy,
+                                                                const float* __restrict__ qz, long long qs,
+                                                                long long nq, const int* __restrict__ perm,
+                                                                int stack_ints, const int* __restrict__ chi,
+                                                                float* __restrict__ w) {
+    __shared__ PointLists<G> lists[kPointWaves];
+    extern __shared__ int stacks[];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const long long j0 = ((long long)blockIdx.x * kPointWaves + wave) * G;
+    if (j0 >= nq) return;   // the whole wave
+    point_group_out<G>(mv, qx, qy, qz, qs, j0, (int)min((long long)G, nq - j0), perm, stacks + (size_t)wave * stack_ints,
+                       stack_ints, lists[wave], chi, w);
+}
+
+// FP64, few points against many boundary edges: one workgroup per point, the chunks dealt
+// out to its lanes, the partial sums reduced across the wave by shuffles and across the
+// workgroup in LDS, in a fixed order.
 constexpr int kSplitThreads = 256;
 
-template <class T, bool FAR>
-__device__ void split_run(const MeshView& mv, int a, int e, int qqx, int qqy, T pxs, T pys, T pzs, T f,
-                          double* S) {
-    if (a >= e) return;
-    const BVert* __restrict__ bv = mv.bverts;
-    ColV<T> cp;
-    T sp;
-    load_vertex<T, 1, FAR>(bv[a], qqx, qqy, pxs, pys, &pzs, f, cp, &sp);
-    T acc = (T)0;
-    int cnt = 0;
-    for (int j = a; j < e; ++j) {
-        const int lp = min(max(bv[j].loop, 0), mv.nloops - 1);   // in range for any stored value
-        const int nx = j + 1 < mv.loop_off[lp + 1] ? j + 1 : mv.loop_off[lp];
-        ColV<T> cn;
-        T sn;
-        load_vertex<T, 1, FAR>(bv[nx], qqx, qqy, pxs, pys, &pzs, f, cn, &sn);
-        edge_step<T, 1, FAR>(cp, cn, &sp, &sn, &acc);
-        if (++cnt == 32) {   // FP32 partials flushed into the FP64 sum every 32 edges
-            *S += (double)acc;
-            acc = (T)0;
-            cnt = 0;
-        }
-        if (j + 1 < e) {
-            if (nx == j + 1) {
-                cp = cn;
-                sp = sn;
-            } else {   // the next edge starts a new loop
-                load_vertex<T, 1, FAR>(bv[j + 1], qqx, qqy, pxs, pys, &pzs, f, cp, &sp);
-            }
-        }
-    }
-    *S += (double)acc;
-}
-
-template <class T>
 __global__ __launch_bounds__(kSplitThreads) void k_bdry_split(MeshView mv, const float* __restrict__ qx,
                                                              const float* __restrict__ qy,
                                                              const float* __restrict__ qz, long long qs, long long nq,
-                                                             const int* __restrict__ chi, T* __restrict__ w) {
+                                                             const int* __restrict__ chi, double* __restrict__ w) {
     __shared__ double red[kSplitThreads / 64];
     const long long i = blockIdx.x;   // one point per workgroup
     if (i >= nq) return;
     const float px = qx[i * qs], py = qy[i * qs], pz = qz[i * qs];
     const QPoint q = quantize_point(px, py, pz, mv.g);
-    const int nb = mv.loop_off[mv.nloops];
-    const int per = (nb + kSplitThreads - 1) / kSplitThreads;
-    const int a = (int)threadIdx.x * per, e = min(nb, a + per);
     double S = 0.0;
-    if (q.inbox) {
-        split_run<T, false>(mv, a, e, q.x, q.y, (T)0, (T)0,
-                            (T)pz * (T)mv.g.scale * (T)EdgePairs<T, 1, false>::kUnit, (T)1, &S);
-    } else {
-        const FarScale<T> fs = far_scale<T>(px, py, fabsf(pz), mv.g.scale);
-        split_run<T, true>(mv, a, e, 0, 0, (T)px * fs.scf, (T)py * fs.scf, (T)pz * fs.scf, fs.f, &S);
-    }
+    if (q.inbox)
+        point_chunks<double, false>(mv, (int)threadIdx.x, mv.nchunk, kSplitThreads, q.x, q.y, (double)pz * mv.g.scale,
+                             quad_z(pz, mv.g), 0, S);
+    else
+        outside_sum<double>(mv, px, py, pz, (int)threadIdx.x, kSplitThreads, 0, S);
     for (int o = 32; o > 0; o >>= 1) S += __shfl_xor(S, o);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = S;
     __syncthreads();
     if (threadIdx.x == 0) {
         double t = 0.0;
         for (int k = 0; k < kSplitThreads / 64; ++k) t += red[k];
-        w[i] = (T)((double)chi[i] + t * kInv2Pi);
+        w[i] = (double)chi[i] + t * kInv2Pi;
     }
 }
 
@@ -184,39 +170,72 @@ gwn_status launch_batch(const gwn_mesh_s* m, const float* qx, const float* qy, c
     }
     const bool own_chi = !chi_out && !ws;
     const MeshView mv = m->view();
+    constexpr int kPrec = sizeof(T) == 8 ? GWN_PREC_FP64 : GWN_PREC_FP32;
     hipError_t e = hipSuccess;
     // one launch covers at most max_launch_queries() points (the 32-bit grid size)
     const int64_t chunk = max_launch_queries();
     for (int64_t o = 0; o < nq && e == hipSuccess; o += chunk) {
         const int64_t n = std::min<int64_t>(chunk, nq - o);
         const float *x = qx + o * qs, *y = qy + o * qs, *z = qz + o * qs;
+        // a traversal order for either pass (with ws in the same memory, one after the other)
         int* perm = nullptr;
-        if (want_xy_order(m, n)) {
-            const gwn_status so = ws ? xy_order_into(m, x, y, z, qs, n, ws->perm, ws->order_temp, st)
-                                     : xy_order(m, x, y, z, qs, n, &perm, st);
-            if (so != GWN_OK) {
-                if (own_chi) (void)hipFreeAsync(chi, st);
-                return so;   // the order has set the message
+        auto order = [&](bool space) {
+            if (!ws) return xy_order(m, x, y, z, qs, n, space, &perm, st);
+            perm = ws->perm;
+            return xy_order_into(m, x, y, z, qs, n, space, ws->perm, ws->order_temp, st);
+        };
+        auto drop = [&] {
+            if (perm && !ws) (void)hipFreeAsync(perm, st);
+            perm = nullptr;
+        };
+        gwn_status so = want_xy_order(m, n) ? order(false) : GWN_OK;
+        if (so == GWN_OK) {
+            if (perm) {
+                k_chi_wave<true><<<(unsigned)((n + 64 * kGridWaves - 1) / (64 * kGridWaves)), 64 * kGridWaves, 0, st>>>(
+                    mv, x, y, z, qs, n, perm, chi + o, nullptr);
+            } else {
+                k_chi_batch<<<(unsigned)((n + kChiBlock - 1) / kChiBlock), kChiBlock, 0, st>>>(mv, x, y, z, qs, n,
+                                                                                               chi + o);
             }
-            if (ws) perm = ws->perm;
-        }
-        if (perm) {
-            k_chi_wave<true><<<(unsigned)((n + 64 * kGridWaves - 1) / (64 * kGridWaves)), 64 * kGridWaves, 0, st>>>(
-                mv, x, y, z, qs, n, perm, chi + o, nullptr);
-        } else {
-            k_chi_batch<<<(unsigned)((n + kChiBlock - 1) / kChiBlock), kChiBlock, 0, st>>>(mv, x, y, z, qs, n,
-                                                                                           chi + o);
-        }
-        e = hipGetLastError();
-        if (e == hipSuccess) {
-            if (want_split(m, n, sizeof(T) == 8 ? GWN_PREC_FP64 : GWN_PREC_FP32))
-                k_bdry_split<T><<<(unsigned)n, kSplitThreads, 0, st>>>(mv, x, y, z, qs, n, chi + o, w + o);
-            else
-                k_bdry_batch<T><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(mv, x, y, z, qs, n, perm, chi + o,
-                                                                             w + o);
             e = hipGetLastError();
         }
-        if (perm && !ws) (void)hipFreeAsync(perm, st);
+        const bool few = want_split(m, n, kPrec);
+        if (so == GWN_OK && e == hipSuccess && !few && want_space_order(m, n, kPrec)) {
+            drop();
+            so = order(true);
+        }
+        if (so != GWN_OK) {
+            if (own_chi) (void)hipFreeAsync(chi, st);
+            return so;   // the order has set the message
+        }
+        if (e == hipSuccess) {
+            if (!few) {
+                bool parts = false;
+                if constexpr (sizeof(T) == 4) {
+                    parts = n <= kSharedPoints && m->nclusters > 1;
+                    if (parts)
+                        k_bdry_batch<float, 4><<<(unsigned)((n + 63) / 64), 256, 0, st>>>(mv, x, y, z, qs, n, perm, chi + o,
+                                                                                          w + o);
+                }
+                if (!parts)
+                    k_bdry_batch<T, 1><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(mv, x, y, z, qs, n, perm, chi + o, w + o);
+            } else if constexpr (sizeof(T) == 4) {
+                auto go = [&](auto G) {
+                    constexpr int kG = decltype(G)::value;
+                    const size_t ints = point_stack_ints<kG>(m->cluster_top);
+                    const long long groups = (n + kG - 1) / kG;
+                    k_bdry_group<kG><<<(unsigned)((groups + kPointWaves - 1) / kPointWaves), 64 * kPointWaves,
+                                       kPointWaves * ints * sizeof(int), st>>>(mv, x, y, z, qs, n, perm, (int)ints,
+                                                                               chi + o, w + o);
+                };
+                if (n <= kSinglePoints) go(std::integral_constant<int, 1>{});
+                else go(std::integral_constant<int, 4>{});
+            } else {
+                k_bdry_split<<<(unsigned)n, kSplitThreads, 0, st>>>(mv, x, y, z, qs, n, chi + o, w + o);
+            }
+            e = hipGetLastError();
+        }
+        drop();
     }
     if (own_chi) (void)hipFreeAsync(chi, st);
     GWN_HIP_TRY(e);
@@ -235,7 +254,7 @@ gwn_status query_crossings(const gwn_mesh_s* m, const float* qx, const float* qy
         const float *x = qx + o * qs, *y = qy + o * qs, *z = qz + o * qs;
         int* perm = nullptr;
         if (want_xy_order(m, n)) {
-            const gwn_status so = xy_order(m, x, y, z, qs, n, &perm, st);
+            const gwn_status so = xy_order(m, x, y, z, qs, n, false, &perm, st);
             if (so != GWN_OK) return so;
         }
         if (perm) {
@@ -255,6 +274,7 @@ gwn_status query_crossings(const gwn_mesh_s* m, const float* qx, const float* qy
 bool want_split(const gwn_mesh_s* m, int64_t n, int prec) {
     if (const char* e = std::getenv("GWN_SPLIT_BOUNDARY")) return std::atoi(e) != 0 && m->nb > 0;
     if (prec >= 0 && prec < 2 && m->split_max[prec] != 0) return m->split_max[prec] > 0 && n <= m->split_max[prec] && m->nb > 0;
+    if (prec == GWN_PREC_FP32) return n < kDensePoints && m->nb >= (n <= 16384 ? 64 : kGroupEdges);
     return n <= 8192 && m->nb >= 16 * 256;
 }
 

@@ -1,0 +1,113 @@
+"""FP32 boundary sums of points over clusters of loops: every form (a wave per point,
+groups of four points per wave, a point per lane, plans of few and of many queries) gives
+the same bits, and the sums stand against the oracle and against FP64 (all edges).
+Soups at the edges of the clustering: one loop, a lowest cluster's 28 edges and one loop
+more, 64 clusters (one level) and more, a second and a third level, a loop too long for
+moments of its own workgroup's share, loops of 3, 4, 7, 8 and more edges.  Points inside
+loops' boxes, above and below them, outside the fixed-point box, at heights beyond the
+range of shared arctangents and at infinity."""
+import numpy as np
+import pytest
+
+from paper_2605_01536_amd import workloads as W
+from tests._util import TOL_FP32, compare, fan_soup
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _triangles(n, size, seed):
+    rng = np.random.default_rng(seed)
+    V = (rng.uniform(-1, 1, (n, 1, 3)) + size * rng.standard_normal((n, 3, 3))).reshape(-1, 3)
+    return V.astype(np.float32), np.arange(3 * n, dtype=np.int32).reshape(-1, 3)
+
+
+def _points(V, n, seed):
+    rng = np.random.default_rng(seed)
+    lo, hi = V.min(0), V.max(0)
+    P = rng.uniform(lo - 0.02, hi + 0.02, (n, 3))
+    P[::5] = V[rng.integers(0, len(V), len(P[::5]))] + 0.02 * rng.standard_normal((len(P[::5]), 3))
+    ext = float((hi - lo).max())
+    P[1::17, 2] = hi[2] + ext * rng.uniform(0.01, 3.0, len(P[1::17]))      # above everything
+    P[2::17, 2] = lo[2] - ext * rng.uniform(0.01, 3.0, len(P[2::17]))
+    P[3::29] = rng.uniform(-40, 40, (len(P[3::29]), 3)) * ext              # mostly outside the box
+    P[4::31, 2] = 200.0 * ext * rng.choice([-1, 1], len(P[4::31]))         # no shared arctangents
+    return P.astype(np.float32)
+
+
+SOUPS = {
+    "tri": lambda: _triangles(1, 0.3, 0),
+    "leaf": lambda: _triangles(9, 0.2, 1),           # 27 edges: one cluster
+    "leaf+1": lambda: _triangles(10, 0.2, 2),        # 30: two
+    "roots": lambda: _triangles(597, 0.05, 3),       # 64 clusters
+    "level2": lambda: _triangles(640, 0.05, 4),
+    "level3": lambda: _triangles(5200, 0.02, 5),
+    "small": lambda: _triangles(3000, 1e-3, 6),      # clusters far apart
+    "fans": lambda: fan_soup([3, 7, 8, 14, 15, 4, 3, 6, 29, 64, 5, 9] * 6, 4),
+    "long": lambda: fan_soup([3] * 200 + [3000], 5),  # one loop of 3,000 edges (over 400 chunks)
+    "spheres": lambda: (lambda s: (s.V, s.F))(W.opened_spheres(seed=9, n_surf=6, tris_per_surf=900)),
+}
+
+
+@pytest.mark.parametrize("axis", ["z", "x"])
+@pytest.mark.parametrize("soup", list(SOUPS))
+def test_all_forms_give_the_same_bits(gwn, monkeypatch, soup, axis):
+    V, F = SOUPS[soup]()
+    m = gwn.Mesh(_dev(V), _dev(F), axis=axis)
+    P = _points(V, 9001, 7)
+    Q = _dev(P)
+    monkeypatch.setenv("GWN_SPLIT_BOUNDARY", "0")
+    w0, c0 = gwn.query_batch(m, Q, want_chi=True)                    # a point per lane
+    monkeypatch.setenv("GWN_ORDER_QUERIES", "1")
+    w1, c1 = gwn.query_batch(m, Q, want_chi=True)                    # in order
+    monkeypatch.delenv("GWN_ORDER_QUERIES")
+    assert torch.equal(w0, w1) and torch.equal(c0, c1)
+    monkeypatch.setenv("GWN_SPLIT_BOUNDARY", "1")
+    for n in (1, 3, 4, 5, 255, 6144, 6145, 9001):                    # a wave per point, then groups
+        w, c = gwn.query_batch(m, Q[:n], want_chi=True)
+        assert torch.equal(w, w0[:n]) and torch.equal(c, c0[:n]), n
+    monkeypatch.delenv("GWN_SPLIT_BOUNDARY")
+    plan = gwn.MultiPlan([m, m, m], torch.cat([Q, Q[:5], Q, Q]), [0, 9001, 9006, 27008])   # groups; 18,002: lanes
+    plan.run()
+    torch.cuda.synchronize()
+    assert torch.equal(plan.w, torch.cat([w0, w0[:5], w0, w0]))
+    pick = np.random.default_rng(8).choice(len(P), 300, replace=False)
+    if axis == "z":
+        compare(w0.cpu().numpy()[pick], c0.cpu().numpy()[pick], V, F, P[pick], TOL_FP32, soup)
+    d = (w0.double() - gwn.query_batch(m, Q, prec="fp64")).abs()
+    assert d.max().item() <= TOL_FP32 and d.square().mean().sqrt().item() <= TOL_FP32 / 10
+
+
+def test_points_at_infinity_and_far_away(gwn, monkeypatch):
+    """every form the same; w goes to zero, and a thousand box heights above it keeps FP32's
+    relative accuracy (terms of one sign order: 64 rounded terms' worth, 64 x 2^-24)"""
+    V, F = SOUPS["roots"]()
+    m = gwn.Mesh(_dev(V), _dev(F))
+    P = np.zeros((7, 3), np.float32)
+    P[0, 2], P[1, 2], P[2, 0], P[3, 2], P[4, 2], P[5, 2], P[6, 2] = np.inf, -np.inf, np.nan, np.nan, 3e38, -3e38, 2e3
+    got = []
+    for split in "01":
+        monkeypatch.setenv("GWN_SPLIT_BOUNDARY", split)
+        got.append(gwn.query_batch(m, _dev(P)).cpu().numpy())
+    np.testing.assert_array_equal(got[0], got[1])
+    w = got[0]
+    assert np.abs(w[[0, 1, 4, 5]]).max() < 1e-6
+    w64 = gwn.query_batch(m, _dev(P[6:]), prec="fp64").item()
+    assert abs(w[6] - w64) <= 64 * 2.0 ** -24 * abs(w64)
+
+
+def test_points_above_and_below_vertices(gwn, monkeypatch):
+    """lattice points straight above, below and beside boundary vertices and edges"""
+    rng = np.random.default_rng(31)
+    V = (np.round(rng.uniform(-1, 1, (90, 3)) * 8) / 8).astype(np.float32)
+    F = np.arange(90, dtype=np.int32).reshape(-1, 3)
+    P = (np.round(rng.uniform(-1.2, 1.2, (3000, 3)) * 8) / 8).astype(np.float32)
+    m = gwn.Mesh(_dev(V), _dev(F))
+    for split in "01":
+        monkeypatch.setenv("GWN_SPLIT_BOUNDARY", split)
+        w, c = gwn.query_batch(m, _dev(P), want_chi=True)
+        compare(w.cpu().numpy(), c.cpu().numpy(), V, F, P, TOL_FP32, f"lattice-{split}")
