@@ -1403,6 +1403,60 @@ __device__ int chi_up(const MeshView& mv, const QPoint& q, int* stk) {
     return c;
 }
 
+// chi_up of one point by a whole wave: a stack of nodes in LDS, up to 64 popped at a
+// time, hit leaves tested 64 at a time.  A lane's walk is a chain of dependent loads, one
+// per node on the way (some hundred); this is about one per level of the tree.  Near the
+// stack's end nodes are popped singly, in depth-first order: at most one more entry per
+// level, for which 64 are kept back (kLdsStack bounds the depth).
+constexpr int kFrontier = 384;
+struct ChiLists {
+    int node[kFrontier];
+    int leaf[192];
+};
+
+__device__ __forceinline__ int chi_up_wave(const MeshView& mv, const QPoint& q, ChiLists& ls) {
+    if (mv.root == kNoRoot) return 0;
+    if (mv.root < 0) return leaf_up(mv, ~mv.root, q);
+    const int lane = threadIdx.x & 63;
+    int c = 0, n = 1, nleaf = 0;
+    if (lane == 0) ls.node[0] = mv.root;
+    wave_lds_sync();
+    while (n > 0 || nleaf > 0) {
+        if (nleaf >= 64 || n == 0) {
+            const int m = min(nleaf, 64);
+            nleaf -= m;
+            if (lane < m) c += leaf_up(mv, ls.leaf[nleaf + lane], q);
+            wave_lds_sync();
+            continue;
+        }
+        const int m = min(n, max(1, min(64, kFrontier - kLdsStack - n)));
+        n -= m;
+        bool hl = false, hr = false;
+        int L = 0, R = 0;
+        if (lane < m) {
+            const Node nd = mv.nodes[ls.node[n + lane]];
+            hl = box_has_xy(nd.lxy.x, nd.lxy.y, nd.lxy.z, nd.lxy.w, q.x, q.y) & (q.z <= nd.z.y);
+            hr = box_has_xy(nd.rxy.x, nd.rxy.y, nd.rxy.z, nd.rxy.w, q.x, q.y) & (q.z <= nd.z.w);
+            L = nd.link.x;
+            R = nd.link.y;
+        }
+        wave_lds_sync();
+        auto put = [&](bool hit, int link) {
+            unsigned long long b = __ballot(hit && link < 0);
+            if (hit && link < 0) ls.leaf[nleaf + lane_rank(b)] = ~link;
+            nleaf += __popcll(b);
+            b = __ballot(hit && link >= 0);
+            if (hit && link >= 0) ls.node[n + lane_rank(b)] = link;
+            n += __popcll(b);
+        };
+        put(hl, L);
+        put(hr, R);
+        wave_lds_sync();
+    }
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+    return c;
+}
+
 // Signed crossings of the whole vertical line through q, split at q: up = the
 // sum of s over crossings above q (chi along +z), down = minus the sum over
 // crossings below it (chi along -z).  Same traversal as chi_up without the

@@ -115,6 +115,14 @@ bool want_split(const gwn_mesh_s* m, int64_t n, int prec);
 
 constexpr int64_t kDensePoints = 48 << 10, kSinglePoints = 6144, kSharedPoints = 1 << 20, kGroupEdges = 512;
 
+// Crossing counts of few points take a wave per point: a lane's walk is a chain of loads,
+// 65 us for 1,000 points on 1,280 triangles and 238 us on 85 k (9 and 30 with a wave each),
+// until there are points enough to hide it: 33 k points on 85 k triangles 0.68 ms with the
+// boundary sum against 0.86, on 1,280 0.06 against 0.11, on 12 0.045 against 0.035; 131 k
+// points on 1,280 0.18 against 0.12.  From 2^15 triangles on up to the batches that are
+// taken in order: 66 k points on 1 M triangles 0.4 against 2.4.
+bool want_chi_point(const gwn_mesh_s* m, int64_t n);
+
 // Morton order of the points' quantised x, y for the crossing traversal (perm is
 // stream-ordered device memory the caller frees with hipFreeAsync).
 // GWN_ORDER_QUERIES=0/1 overrides the size heuristic.

@@ -64,6 +64,32 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_chi_items(const MeshView* _
     }
 }
 
+// the same for queries in no order, a wave per query (chi_up_wave): kChiParts workgroups
+// share an item's queries
+constexpr int kChiParts = 4;
+
+__global__ __launch_bounds__(64 * kGridWaves) void k_chi_items_point(const MeshView* __restrict__ table,
+                                                                    const Item* __restrict__ items, int nitems,
+                                                                    const float* __restrict__ qx,
+                                                                    const float* __restrict__ qy,
+                                                                    const float* __restrict__ qz, long long qs,
+                                                                    int* __restrict__ chi) {
+    __shared__ ChiLists lists[kGridWaves];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int it = (int)(blockIdx.x / kChiParts), part = (int)(blockIdx.x % kChiParts) * kGridWaves + wave;
+    if (it >= nitems) return;
+    const Item I = items[it];
+    const MeshView mv = table[I.mesh];
+    const float *x = qx, *y = qy, *z = qz;
+    axis_ptrs(mv.axis, x, y, z);   // the mesh's frame
+    for (int k = part; k < I.nq; k += kChiParts * kGridWaves) {
+        const long long i = I.q0 + k;
+        const QPoint q = quantize_point(x[i * qs], y[i * qs], z[i * qs], mv.g);
+        const int c = q.inbox ? chi_up_wave(mv, q, lists[wave]) : 0;
+        if ((threadIdx.x & 63) == 0) chi[i] = c;
+    }
+}
+
 // sort keys of all queries: the mesh, then (items [0, nkeyed)) the query's place in the order
 __global__ void k_plan_keys(const MeshView* __restrict__ table, const Item* __restrict__ items, int nkeyed,
                             const float* __restrict__ qx, const float* __restrict__ qy, const float* __restrict__ qz,
@@ -311,9 +337,8 @@ gwn_status capture(gwn_multi_s* p, const Schedule& s) {
             k_chi_items<<<(unsigned)((nd + kGridWaves - 1) / kGridWaves), 64 * kGridWaves, 0, p->cap>>>(
                 p->table, p->items, nd, p->qx, p->qy, p->qz, p->qs, p->perm, p->chi);
         if (ns > 0)
-            k_chi_items<<<(unsigned)((ns + kGridWaves - 1) / kGridWaves), 64 * kGridWaves, 0, p->cap>>>(
-                p->table, p->items + nd, ns, p->qx, p->qy, p->qz, p->qs, (s.order & kOrderSorted) ? p->perm : nullptr,
-                p->chi);
+            k_chi_items_point<<<(unsigned)ns * kChiParts, 64 * kGridWaves, 0, p->cap>>>(
+                p->table, p->items + nd, ns, p->qx, p->qy, p->qz, p->qs, p->chi);
         if (p->prec == GWN_PREC_FP64) {
             k_bdry_persistent<double><<<p->grid, 256, 0, p->cap>>>(
                 p->table, p->items, p->nitems, lanes, p->counter, p->qx, p->qy, p->qz, p->qs,

@@ -25,6 +25,20 @@ __global__ __launch_bounds__(kChiBlock) void k_chi_batch(MeshView mv, const floa
     chi[i] = q.inbox ? chi_up(mv, q, stk + threadIdx.x) : 0;
 }
 
+// the same for few points, a wave per point
+__global__ __launch_bounds__(64 * kGridWaves) void k_chi_point(MeshView mv, const float* __restrict__ qx,
+                                                              const float* __restrict__ qy,
+                                                              const float* __restrict__ qz, long long qs, long long nq,
+                                                              int* __restrict__ chi) {
+    __shared__ ChiLists lists[kGridWaves];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const long long i = (long long)blockIdx.x * kGridWaves + wave;
+    if (i >= nq) return;   // the whole wave
+    const QPoint q = quantize_point(qx[i * qs], qy[i * qs], qz[i * qs], mv.g);
+    const int c = q.inbox ? chi_up_wave(mv, q, lists[wave]) : 0;
+    if ((threadIdx.x & 63) == 0) chi[i] = c;
+}
+
 // Crossing counts of Morton-ordered points, one wave-uniform traversal per wave
 // (chi_wave_walk): neighbouring lines share almost their whole path, so the
 // wave walks about one path instead of 64 divergent ones.  UP: the +z ray only
@@ -193,6 +207,8 @@ gwn_status launch_batch(const gwn_mesh_s* m, const float* qx, const float* qy, c
             if (perm) {
                 k_chi_wave<true><<<(unsigned)((n + 64 * kGridWaves - 1) / (64 * kGridWaves)), 64 * kGridWaves, 0, st>>>(
                     mv, x, y, z, qs, n, perm, chi + o, nullptr);
+            } else if (want_chi_point(m, n)) {
+                k_chi_point<<<(unsigned)((n + kGridWaves - 1) / kGridWaves), 64 * kGridWaves, 0, st>>>(mv, x, y, z, qs, n, chi + o);
             } else {
                 k_chi_batch<<<(unsigned)((n + kChiBlock - 1) / kChiBlock), kChiBlock, 0, st>>>(mv, x, y, z, qs, n,
                                                                                                chi + o);
@@ -269,6 +285,10 @@ gwn_status query_crossings(const gwn_mesh_s* m, const float* qx, const float* qy
         GWN_HIP_TRY(e);
     }
     return GWN_OK;
+}
+
+bool want_chi_point(const gwn_mesh_s* m, int64_t n) {
+    return n <= (m->nf >= (1 << 15) ? (1 << 18) : m->nf >= 1024 ? 32768 : 8192);
 }
 
 bool want_split(const gwn_mesh_s* m, int64_t n, int prec) {

@@ -82,6 +82,31 @@ def test_all_forms_give_the_same_bits(gwn, monkeypatch, soup, axis):
     assert d.max().item() <= TOL_FP32 and d.square().mean().sqrt().item() <= TOL_FP32 / 10
 
 
+@pytest.mark.parametrize("n", [1, 64, 8192, 8193, 32768, 32769])
+@pytest.mark.parametrize("soup", ["tri", "level3", "spheres"])
+def test_crossings_of_few_points(gwn, monkeypatch, soup, n):
+    """a wave per point, a lane per point and the ordered walk count the same"""
+    V, F = SOUPS[soup]()
+    m = gwn.Mesh(_dev(V), _dev(F))
+    Q = _dev(np.resize(_points(V, 4000, 3), (n, 3)))
+    _, c = gwn.query_batch(m, Q, want_chi=True)
+    up, _ = gwn.query_crossings(m, Q)
+    assert torch.equal(c, up)
+
+
+def test_deep_tree_and_many_hits(gwn):
+    """a stack of 4,000 like triangles (every node hit, the depth of equal keys), a wave per point"""
+    n = 4000
+    V = np.tile(np.array([[0, 0, 0], [1, 0, 0], [0, 1, 0]], np.float32), (n, 1, 1))
+    V[:, :, 2] = np.linspace(0, 1, n, dtype=np.float32)[:, None]
+    F = np.arange(3 * n, dtype=np.int32).reshape(-1, 3)
+    m = gwn.Mesh(_dev(V.reshape(-1, 3)), _dev(F))
+    z = np.linspace(-0.1, 1.1, 200, dtype=np.float32)
+    Q = np.stack([np.full(200, 0.25, np.float32), np.full(200, 0.3, np.float32), z], -1)
+    _, c = gwn.query_batch(m, _dev(Q), want_chi=True)
+    assert c.cpu().numpy().tolist() == [int((V[:, 0, 2] > t).sum()) for t in z]
+
+
 def test_points_at_infinity_and_far_away(gwn, monkeypatch):
     """every form the same; w goes to zero, and a thousand box heights above it keeps FP32's
     relative accuracy (terms of one sign order: 64 rounded terms' worth, 64 x 2^-24)"""
