@@ -136,3 +136,20 @@ def test_points_above_and_below_vertices(gwn, monkeypatch):
         monkeypatch.setenv("GWN_SPLIT_BOUNDARY", split)
         w, c = gwn.query_batch(m, _dev(P), want_chi=True)
         compare(w.cpu().numpy(), c.cpu().numpy(), V, F, P, TOL_FP32, f"lattice-{split}")
+
+
+@pytest.mark.parametrize("n", [1, 8193, 300_001])
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_closed_meshes_are_their_crossings(gwn, monkeypatch, n, prec):
+    """no boundary: w is chi, with and without the counts returned, ordered or not, outside the box too"""
+    V = np.array([[0, 0, 0], [1, 0, 0], [0, 1, 0], [0, 0, 1]], np.float32)
+    F = np.array([[0, 2, 1], [0, 1, 3], [1, 2, 3], [0, 3, 2]], np.int32)
+    m = gwn.Mesh(_dev(V), _dev(F))
+    assert m.info()["nboundary"] == 0
+    Q = _dev(np.random.default_rng(1).uniform(-3, 3, (n, 3)).astype(np.float32) * np.float32(0.3))
+    up, _ = gwn.query_crossings(m, Q)
+    for order in "01":
+        monkeypatch.setenv("GWN_ORDER_QUERIES", order)
+        w, c = gwn.query_batch(m, Q, prec=prec, want_chi=True)
+        assert torch.equal(c, up) and torch.equal(w, up.to(w.dtype))
+        assert torch.equal(gwn.query_batch(m, Q, prec=prec), w)
