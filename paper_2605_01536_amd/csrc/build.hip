@@ -297,7 +297,10 @@ __global__ void k_depth(int n, const Node* __restrict__ nodes, const int* __rest
 
 // ---- boundary chain
 
-__global__ void k_edge_keys(const int32_t* __restrict__ tri, int64_t nf, uint64_t* __restrict__ keys,
+// Both vertices of an edge in 2 bits bits (the smaller above), so that the sort has passes
+// for those only.  Degenerate edges have all bits set: their low bits (twice the same vertex)
+// are no edge's either.
+__global__ void k_edge_keys(const int32_t* __restrict__ tri, int64_t nf, int bits, uint64_t* __restrict__ keys,
                             int* __restrict__ sgn) {
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= 3 * nf) return;
@@ -309,7 +312,7 @@ __global__ void k_edge_keys(const int32_t* __restrict__ tri, int64_t nf, uint64_
         keys[i] = ~0ull;
         sgn[i] = 0;
     } else {
-        keys[i] = ((uint64_t)min(u, v) << 32) | (uint64_t)max(u, v);
+        keys[i] = ((uint64_t)min(u, v) << bits) | (uint64_t)max(u, v);
         sgn[i] = u < v ? 1 : -1;
     }
 }
@@ -329,10 +332,10 @@ __global__ void k_edge_runs(const uint64_t* __restrict__ keys, const int* __rest
 }
 
 __global__ void k_edge_emit(const uint64_t* __restrict__ keys, const int* __restrict__ net, const int* __restrict__ cnt,
-                            const int* __restrict__ off, int64_t n, int* __restrict__ efrom, int* __restrict__ eto) {
+                            const int* __restrict__ off, int64_t n, int bits, int* __restrict__ efrom, int* __restrict__ eto) {
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= n || cnt[i] == 0) return;
-    int lo = (int)(keys[i] >> 32), hi = (int)(keys[i] & 0xffffffffull);
+    int lo = (int)(keys[i] >> bits), hi = (int)(keys[i] & ((1ull << bits) - 1ull));
     int m = net[i];
     for (int r = 0; r < cnt[i]; ++r) {
         efrom[off[i] + r] = m > 0 ? lo : hi;
@@ -383,6 +386,114 @@ __global__ void k_rank_round(const int* __restrict__ nxt, const int* __restrict_
         nxt2[i] = nxt[j];
         dist2[i] = dist[i] + dist[j];
     }
+}
+
+// Representatives, ranks and both scans for few edges in one workgroup, in LDS: the rounds
+// are two launches a power of two otherwise, 26 for 7 k edges.
+constexpr int kFewEdges = 8192, kRankThreads = 1024, kRankPer = kFewEdges / kRankThreads;
+
+__global__ __launch_bounds__(kRankThreads) void k_rank_loops(const int* __restrict__ succ, int nb, int rounds,
+                                                            int* __restrict__ rep_out, int* __restrict__ dist_out,
+                                                            int* __restrict__ voff, int* __restrict__ lid,
+                                                            int* __restrict__ nloops) {
+    __shared__ int A[kFewEdges], B[kFewEdges];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    int rep[kRankPer], jmp[kRankPer], dist[kRankPer];
+    // element k of thread t: t * kRankPer + k, so that scans go in order
+#pragma unroll
+    for (int k = 0; k < kRankPer; ++k) {
+        const int i = t * kRankPer + k;
+        rep[k] = i;
+        jmp[k] = i < nb ? succ[i] : i;
+        A[i] = rep[k];
+        B[i] = jmp[k];
+    }
+    __syncthreads();
+    for (int r = 0; r < rounds; ++r) {   // the smallest edge of the cycle
+#pragma unroll
+        for (int k = 0; k < kRankPer; ++k) {
+            const int j = jmp[k];
+            rep[k] = min(rep[k], A[j]);
+            jmp[k] = B[j];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kRankPer; ++k) {
+            A[t * kRankPer + k] = rep[k];
+            B[t * kRankPer + k] = jmp[k];
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < kRankPer; ++k) {   // the distance to the cycle's end, opened there
+        const int i = t * kRankPer + k, s = i < nb ? succ[i] : i;
+        const bool end = s == rep[k];
+        jmp[k] = end ? -1 : s;
+        dist[k] = end ? 0 : 1;
+        A[i] = jmp[k];
+        B[i] = dist[k];
+    }
+    __syncthreads();
+    for (int r = 0; r < rounds; ++r) {
+#pragma unroll
+        for (int k = 0; k < kRankPer; ++k) {
+            const int j = jmp[k];
+            if (j >= 0) {
+                dist[k] += B[j];
+                jmp[k] = A[j];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kRankPer; ++k) {
+            A[t * kRankPer + k] = jmp[k];
+            B[t * kRankPer + k] = dist[k];
+        }
+        __syncthreads();
+    }
+    // exclusive sums over the representatives: loop lengths, loops
+    int len = 0, heads = 0;
+#pragma unroll
+    for (int k = 0; k < kRankPer; ++k) {
+        const int i = t * kRankPer + k;
+        if (i < nb && rep[k] == i) {
+            len += dist[k] + 1;
+            ++heads;
+        }
+    }
+    int pl = len, ph = heads;
+    for (int d = 1; d < 64; d <<= 1) {
+        const int a = __shfl_up(pl, d), b = __shfl_up(ph, d);
+        if (lane >= d) {
+            pl += a;
+            ph += b;
+        }
+    }
+    if (lane == 63) {
+        A[wave] = pl;
+        B[wave] = ph;
+    }
+    __syncthreads();
+    pl -= len;
+    ph -= heads;
+    for (int w = 0; w < wave; ++w) {
+        pl += A[w];
+        ph += B[w];
+    }
+#pragma unroll
+    for (int k = 0; k < kRankPer; ++k) {
+        const int i = t * kRankPer + k;
+        if (i >= nb) continue;
+        rep_out[i] = rep[k];
+        dist_out[i] = dist[k];
+        voff[i] = pl;
+        lid[i] = ph;
+        if (rep[k] == i) {
+            pl += dist[k] + 1;
+            ++ph;
+        }
+    }
+    if (t == kRankThreads - 1) *nloops = ph;
 }
 
 __global__ void k_loop_counts(const int* __restrict__ rep, const int* __restrict__ dist, int64_t n, int* __restrict__ len,
@@ -1165,47 +1276,55 @@ __global__ __launch_bounds__(kThreads) void k_proj_area(const float* __restrict_
 
 // ---------------------------------------------------------------- welding
 // Vertices with equal float coordinates (+0 and -0 equal) become one index, the
-// smallest: sort by (x, y, z) bit patterns (stable LSD passes), find runs, map.
+// smallest: sort by a hash of the position (stable), find runs, map.
 
 __device__ __forceinline__ uint32_t weld_bits(float f) {
     const uint32_t b = __float_as_uint(f);
     return (b & 0x7fffffffu) == 0u ? 0u : b;
 }
 
-__global__ void k_weld_zkeys(const float* __restrict__ vz, int64_t vs, int64_t nv, uint32_t* __restrict__ kz,
-                             int* __restrict__ idx) {
+// Equal positions have equal hashes; a sort by the hash (four passes; the three coordinates
+// themselves take twelve) brings them together.
+__global__ void k_weld_keys(const float* __restrict__ vx, const float* __restrict__ vy, const float* __restrict__ vz,
+                            int64_t vs, int64_t nv, uint32_t* __restrict__ key, int* __restrict__ idx) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= nv) return;
-    kz[i] = weld_bits(vz[i * vs]);
+    uint64_t h = ((uint64_t)weld_bits(vx[i * vs]) << 32) | weld_bits(vy[i * vs]);
+    h = (h ^ (h >> 33)) * 0xff51afd7ed558ccdull;
+    h ^= (uint64_t)weld_bits(vz[i * vs]) * 0x9e3779b97f4a7c15ull;
+    h = (h ^ (h >> 33)) * 0xc4ceb9fe1a85ec53ull;
+    key[i] = (uint32_t)(h >> 32);
     idx[i] = (int)i;
 }
 
-__global__ void k_weld_xykeys(const float* __restrict__ vx, const float* __restrict__ vy, int64_t vs, int64_t nv,
-                              const int* __restrict__ idx, uint64_t* __restrict__ kxy) {
+// start of each sorted hash's run (0 where it continues one)
+__global__ void k_weld_heads(int64_t nv, const uint32_t* __restrict__ key, int* __restrict__ head) {
     const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (j >= nv) return;
-    const int64_t v = idx[j];
-    kxy[j] = ((uint64_t)weld_bits(vx[v * vs]) << 32) | weld_bits(vy[v * vs]);
+    head[j] = j == 0 || key[j] != key[j - 1] ? (int)j : 0;
 }
 
-// run start of each sorted position (0 where the position continues a run)
-__global__ void k_weld_heads(const float* __restrict__ vz, int64_t vs, int64_t nv, const uint64_t* __restrict__ kxy,
-                             const int* __restrict__ idx, int* __restrict__ head) {
-    const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (j >= nv) return;
-    bool h = j == 0;
-    if (!h) h = kxy[j] != kxy[j - 1] || weld_bits(vz[(int64_t)idx[j] * vs]) != weld_bits(vz[(int64_t)idx[j - 1] * vs]);
-    head[j] = h ? (int)j : 0;
-}
-
-__global__ __launch_bounds__(kThreads) void k_weld_map(const int* __restrict__ idx, const int* __restrict__ start,
+// A vertex goes to the first of its run with its position: the smallest index (the sort is
+// stable).  That is the run's first but for two positions of one hash.
+__global__ __launch_bounds__(kThreads) void k_weld_map(const float* __restrict__ vx, const float* __restrict__ vy,
+                                                      const float* __restrict__ vz, int64_t vs,
+                                                      const int* __restrict__ idx, const int* __restrict__ start,
                                                       int64_t nv, int* __restrict__ remap, int* __restrict__ nunique) {
     int heads = 0;
     for (int64_t j0 = blockIdx.x * (int64_t)kThreads; j0 < nv; j0 += (int64_t)gridDim.x * kThreads) {
         const int64_t j = j0 + threadIdx.x;
-        const int s = j < nv ? start[j] : -1;
-        if (j < nv) remap[idx[j]] = idx[s];   // the stable sort keeps the smallest index first in a run
-        heads += __syncthreads_count(j < nv && s == (int)j);
+        bool own = false;
+        if (j < nv) {
+            const int v = idx[j];
+            const uint32_t x = weld_bits(vx[v * vs]), y = weld_bits(vy[v * vs]), z = weld_bits(vz[v * vs]);
+            int64_t k = start[j];
+            int u = idx[k];
+            while (k < j && (weld_bits(vx[u * vs]) != x || weld_bits(vy[u * vs]) != y || weld_bits(vz[u * vs]) != z))
+                u = idx[++k];
+            remap[v] = u;
+            own = u == v;
+        }
+        heads += __syncthreads_count(own);
     }
     if (threadIdx.x == 0) atomicAdd(nunique, heads);   // one per workgroup: they all meet at one address
 }
@@ -1325,40 +1444,30 @@ gwn_status build_mesh(const float* vx, const float* vy, const float* vz, int64_t
     // ---- optional welding of equal positions (the boundary is extracted by index)
     m->nunique = nv;
     if (weld && nv > 1 && nf > 0) {
-        uint32_t *kz = nullptr, *kz2 = nullptr;
-        uint64_t *kxy = nullptr, *kxy2 = nullptr;
-        int *idx = nullptr, *idx2 = nullptr, *idx3 = nullptr, *head = nullptr, *start = nullptr, *remap = nullptr,
-            *nuq = nullptr;
+        uint32_t *key = nullptr, *key2 = nullptr;
+        int *idx = nullptr, *idx2 = nullptr, *head = nullptr, *start = nullptr, *remap = nullptr, *nuq = nullptr;
         int32_t* triw = nullptr;
-        GWN_HIP_TRY(S.alloc(&kz, nv));
-        GWN_HIP_TRY(S.alloc(&kz2, nv));
-        GWN_HIP_TRY(S.alloc(&kxy, nv));
-        GWN_HIP_TRY(S.alloc(&kxy2, nv));
+        GWN_HIP_TRY(S.alloc(&key, nv));
+        GWN_HIP_TRY(S.alloc(&key2, nv));
         GWN_HIP_TRY(S.alloc(&idx, nv));
         GWN_HIP_TRY(S.alloc(&idx2, nv));
-        GWN_HIP_TRY(S.alloc(&idx3, nv));
         GWN_HIP_TRY(S.alloc(&head, nv));
         GWN_HIP_TRY(S.alloc(&start, nv));
         GWN_HIP_TRY(S.alloc(&remap, nv));
         GWN_HIP_TRY(S.alloc(&nuq, 1));
         GWN_HIP_TRY(S.alloc(&triw, 3 * nf));
         GWN_HIP_TRY(hipMemsetAsync(nuq, 0, sizeof(int), st));
-        k_weld_zkeys<<<nblocks(nv), kThreads, 0, st>>>(vz, vs, nv, kz, idx);
+        k_weld_keys<<<nblocks(nv), kThreads, 0, st>>>(vx, vy, vz, vs, nv, key, idx);
         GWN_HIP_TRY(hipGetLastError());
         GWN_HIP_TRY(with_temp(S, sort_temp_bytes(nv, 4, true), [&](void* tmp) {
-            return radix_sort_u32(kz, kz2, idx, idx2, nv, 0, 32, tmp, st);
+            return radix_sort_u32(key, key2, idx, idx2, nv, 0, 32, tmp, st);
         }));
-        k_weld_xykeys<<<nblocks(nv), kThreads, 0, st>>>(vx, vy, vs, nv, idx2, kxy);
-        GWN_HIP_TRY(hipGetLastError());
-        GWN_HIP_TRY(with_temp(S, sort_temp_bytes(nv, 8, true), [&](void* tmp) {
-            return radix_sort_u64(kxy, kxy2, idx2, idx3, nv, 0, 64, tmp, st);
-        }));
-        k_weld_heads<<<nblocks(nv), kThreads, 0, st>>>(vz, vs, nv, kxy2, idx3, head);
+        k_weld_heads<<<nblocks(nv), kThreads, 0, st>>>(nv, key2, head);
         GWN_HIP_TRY(hipGetLastError());
         GWN_HIP_TRY(with_temp(S, scan_temp_bytes(nv), [&](void* tmp) {
             return scan_inclusive_max(head, start, nv, tmp, st);
         }));
-        k_weld_map<<<std::min(nblocks(nv), 1024), kThreads, 0, st>>>(idx3, start, nv, remap, nuq);
+        k_weld_map<<<std::min(nblocks(nv), 1024), kThreads, 0, st>>>(vx, vy, vz, vs, idx2, start, nv, remap, nuq);
         GWN_HIP_TRY(hipGetLastError());
         k_weld_tris<<<nblocks(3 * nf), kThreads, 0, st>>>(tri, 3 * nf, remap, triw);
         GWN_HIP_TRY(hipGetLastError());
@@ -1466,10 +1575,11 @@ gwn_status build_mesh(const float* vx, const float* vy, const float* vz, int64_t
         GWN_HIP_TRY(S.alloc(&net, ne));
         GWN_HIP_TRY(S.alloc(&cnt, ne));
         GWN_HIP_TRY(S.alloc(&off, ne));
-        k_edge_keys<<<nblocks(ne), kThreads, 0, st>>>(tri, nf, ek, es);
+        const int vb = bits_for(nv);
+        k_edge_keys<<<nblocks(ne), kThreads, 0, st>>>(tri, nf, vb, ek, es);
         GWN_HIP_TRY(hipGetLastError());
         GWN_HIP_TRY(with_temp(S, sort_temp_bytes(ne, 8, true), [&](void* tmp) {
-            return radix_sort_u64(ek, ek2, es, es2, ne, 0, 64, tmp, st);
+            return radix_sort_u64(ek, ek2, es, es2, ne, 0, 2 * vb, tmp, st);
         }));
         k_edge_runs<<<nblocks(ne), kThreads, 0, st>>>(ek2, es2, ne, net, cnt);
         GWN_HIP_TRY(hipGetLastError());
@@ -1490,10 +1600,9 @@ gwn_status build_mesh(const float* vx, const float* vy, const float* vz, int64_t
             for (int** p : {&efrom, &eto, &ids, &kk, &in_by_to, &out_by_from, &succ, &repA, &repB, &jA, &jB, &dA, &dB,
                             &len, &head, &voff, &lid})
                 GWN_HIP_TRY(S.alloc(p, nb));
-            k_edge_emit<<<nblocks(ne), kThreads, 0, st>>>(ek2, net, cnt, off, ne, efrom, eto);
+            k_edge_emit<<<nblocks(ne), kThreads, 0, st>>>(ek2, net, cnt, off, ne, vb, efrom, eto);
             GWN_HIP_TRY(hipGetLastError());
             k_iota<<<nblocks(nb), kThreads, 0, st>>>(ids, nb);
-            const int vb = bits_for(nv);
             GWN_HIP_TRY(with_temp(S, sort_temp_bytes(nb, 4, true), [&](void* tmp) {
                 return radix_sort_u32((const uint32_t*)eto, (uint32_t*)kk, ids, in_by_to, nb, 0, vb, tmp, st);
             }));
@@ -1502,36 +1611,45 @@ gwn_status build_mesh(const float* vx, const float* vy, const float* vz, int64_t
             }));
             k_link<<<nblocks(nb), kThreads, 0, st>>>(in_by_to, out_by_from, nb, succ);
             GWN_HIP_TRY(hipGetLastError());
-            // cycle representative = smallest edge id on the cycle (pointer jumping)
-            GWN_HIP_TRY(hipMemcpyAsync(jA, succ, sizeof(int) * nb, hipMemcpyDeviceToDevice, st));
-            k_iota<<<nblocks(nb), kThreads, 0, st>>>(repA, nb);
-            const int rounds = bits_for(nb) + 1;
-            for (int r = 0; r < rounds; ++r) {
-                k_rep_round<<<nblocks(nb), kThreads, 0, st>>>(repA, jA, nb, repB, jB);
-                std::swap(repA, repB);
-                std::swap(jA, jB);
+            if (nb <= kFewEdges) {
+                k_rank_loops<<<1, kRankThreads, 0, st>>>(succ, (int)nb, bits_for(nb) + 1, repA, dA, voff, lid, head);
+                GWN_HIP_TRY(hipGetLastError());
+                int loops = 0;
+                GWN_HIP_TRY(hipMemcpyAsync(&loops, head, sizeof(int), hipMemcpyDeviceToHost, st));
+                GWN_HIP_TRY(hipStreamSynchronize(st));
+                m->nloops = loops;
+            } else {
+                // cycle representative = smallest edge id on the cycle (pointer jumping)
+                GWN_HIP_TRY(hipMemcpyAsync(jA, succ, sizeof(int) * nb, hipMemcpyDeviceToDevice, st));
+                k_iota<<<nblocks(nb), kThreads, 0, st>>>(repA, nb);
+                const int rounds = bits_for(nb) + 1;
+                for (int r = 0; r < rounds; ++r) {
+                    k_rep_round<<<nblocks(nb), kThreads, 0, st>>>(repA, jA, nb, repB, jB);
+                    std::swap(repA, repB);
+                    std::swap(jA, jB);
+                }
+                GWN_HIP_TRY(hipGetLastError());
+                // distance to the end of the cycle opened at its representative (list ranking)
+                k_rank_init<<<nblocks(nb), kThreads, 0, st>>>(succ, repA, nb, jA, dA);
+                for (int r = 0; r < rounds; ++r) {
+                    k_rank_round<<<nblocks(nb), kThreads, 0, st>>>(jA, dA, nb, jB, dB);
+                    std::swap(jA, jB);
+                    std::swap(dA, dB);
+                }
+                GWN_HIP_TRY(hipGetLastError());
+                k_loop_counts<<<nblocks(nb), kThreads, 0, st>>>(repA, dA, nb, len, head);
+                GWN_HIP_TRY(with_temp(S, scan_temp_bytes(nb), [&](void* tmp) {
+                    return scan_exclusive_sum(len, voff, nb, tmp, st);
+                }));
+                GWN_HIP_TRY(with_temp(S, scan_temp_bytes(nb), [&](void* tmp) {
+                    return scan_exclusive_sum(head, lid, nb, tmp, st);
+                }));
+                int last[2] = {0, 0};
+                GWN_HIP_TRY(hipMemcpyAsync(&last[0], lid + nb - 1, sizeof(int), hipMemcpyDeviceToHost, st));
+                GWN_HIP_TRY(hipMemcpyAsync(&last[1], head + nb - 1, sizeof(int), hipMemcpyDeviceToHost, st));
+                GWN_HIP_TRY(hipStreamSynchronize(st));
+                m->nloops = (int64_t)last[0] + last[1];
             }
-            GWN_HIP_TRY(hipGetLastError());
-            // distance to the end of the cycle opened at its representative (list ranking)
-            k_rank_init<<<nblocks(nb), kThreads, 0, st>>>(succ, repA, nb, jA, dA);
-            for (int r = 0; r < rounds; ++r) {
-                k_rank_round<<<nblocks(nb), kThreads, 0, st>>>(jA, dA, nb, jB, dB);
-                std::swap(jA, jB);
-                std::swap(dA, dB);
-            }
-            GWN_HIP_TRY(hipGetLastError());
-            k_loop_counts<<<nblocks(nb), kThreads, 0, st>>>(repA, dA, nb, len, head);
-            GWN_HIP_TRY(with_temp(S, scan_temp_bytes(nb), [&](void* tmp) {
-                return scan_exclusive_sum(len, voff, nb, tmp, st);
-            }));
-            GWN_HIP_TRY(with_temp(S, scan_temp_bytes(nb), [&](void* tmp) {
-                return scan_exclusive_sum(head, lid, nb, tmp, st);
-            }));
-            int last_lid = 0, last_head = 0;
-            GWN_HIP_TRY(hipMemcpyAsync(&last_lid, lid + nb - 1, sizeof(int), hipMemcpyDeviceToHost, st));
-            GWN_HIP_TRY(hipMemcpyAsync(&last_head, head + nb - 1, sizeof(int), hipMemcpyDeviceToHost, st));
-            GWN_HIP_TRY(hipStreamSynchronize(st));
-            m->nloops = (int64_t)last_lid + last_head;
             GWN_HIP_TRY(gwn::dmalloc((void**)&m->bverts, sizeof(BVert) * (size_t)nb));
             GWN_HIP_TRY(gwn::dmalloc((void**)&m->loop_off, sizeof(int) * (size_t)(m->nloops + 1)));
             k_emit_loops<<<nblocks(nb), kThreads, 0, st>>>(efrom, repA, dA, voff, lid, nb, vx, vy, vz, vs, qv, g.scalef,
