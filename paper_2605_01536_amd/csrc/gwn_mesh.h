@@ -105,10 +105,10 @@ int64_t max_launch_queries();
 // up to kSinglePoints, groups of four points per wave up to kDensePoints, on meshes of at
 // least kGroupEdges edges (64 up to 16,384 points); else a point per lane, up to kSharedPoints with four waves to
 // share 64 points' clusters.
-// ms for a wave per point / groups / shared lanes / a point per lane on a torus of loops of
-// 63 k edges: 1 k points 0.06 / 0.08 / - / 11.1 (unordered), 4 k 0.15 / 0.15 / - / 11.9,
-// 33 k 0.86 / 0.76 / 1.1 / 2.6, 66 k 1.20 / 1.49 / 1.30 / 2.1, 262 k - / 3.3 / 2.1 / 2.7,
-// 1 M - / - / 4.4 / 4.5, 2 M - / - / 7.6 / 7.2; on 171 edges (the sums alone) 66 k
+// ms with the crossings for a wave per point / groups / shared lanes / a point per lane on a
+// torus of loops of 63 k edges: 1 k points 0.07 / 0.08 / 3.3 / 11.1 (unordered), 4 k 0.17 /
+// 0.17 / 2.9 / 11.9, 33 k 1.2 / 0.89 / 1.2 / 2.7, 66 k - / 1.56 / 1.28 / 2.1, 262 k - / 3.7 /
+// 2.2 / 2.7, 1 M - / - / 4.9 / 5.0, 2 M - / - / 8.5 / 8.1; on 171 edges (the sums alone) 66 k
 // points groups 0.073, shared lanes 0.028; 16 k with the crossings 0.055 each.
 // GWN_SPLIT_BOUNDARY=0/1 overrides.
 bool want_split(const gwn_mesh_s* m, int64_t n, int prec);
