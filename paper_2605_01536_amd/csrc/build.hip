@@ -773,7 +773,7 @@ __global__ void k_emit_chain(const BVert* __restrict__ bv, const int* __restrict
         const int r = m % (kChunk - 1);
         const int end = r == 0 ? kChunk : (r > 3 ? kChunk : kChunk / 2);
         const BVert c = bv[b0];
-        for (int e = s + 1; e < end; ++e) put(base + e, c, kChainValid);
+        for (int e = s + 1; e < end; ++e) put(base + e, c, kChainValid | (e == s + 1 && k == s && m >= 3 ? kChainClose : 0));
     }
 }
 

@@ -46,6 +46,7 @@ constexpr int kChunk = 8;
 constexpr int kChainEdge = 1, kChainValid = 2;
 constexpr int kChainTri = 4;    // first vertex of a loop of three edges
 constexpr int kChainCont = 8;   // first of a chunk: the vertex that the chunk before ends with
+constexpr int kChainClose = 16; // closes a loop that its chunk holds whole: the loop's first vertex again
 struct alignas(32) CVert {
     float z;          // as BVert
     int qx, qy;

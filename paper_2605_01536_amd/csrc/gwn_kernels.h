@@ -881,8 +881,8 @@ __device__ __forceinline__ T point_run(const CVert* b, const PVert<T>* v, bool q
     return acc;
 }
 
-// The edges of one chunk: its first three, then the other four (of which the first may
-// be none, or the last two).
+// The edges of one chunk: four if that is all, else the first three, then the other four,
+// or (two halves) three, or the last two of them.  A loop's closing vertex is its first.
 // UNIFORM: the same chunk for the wave; last: the chunk's last vertex; with cont, on entry
 // that of the chunk before it.
 struct Chunk {
@@ -898,25 +898,43 @@ __device__ __forceinline__ T point_chunk(const CVert* __restrict__ chunk, int qq
         c = uniform_load((const Chunk*)chunk);
         b = c.v;
     }
+    auto vertex = [&](int e) { return point_vertex<T>(b[e], qqx, qqy, pz); };
     PVert<T> v[kChunk];
     T acc = (T)0;
-#pragma unroll
-    for (int e = 1; e < 3; ++e) v[e] = point_vertex<T>(b[e], qqx, qqy, pz);
-    v[0] = cont && (b[0].flags & kChainCont) ? last : point_vertex<T>(b[0], qqx, qqy, pz);
-    v[3] = b[0].flags & kChainTri ? v[0] : point_vertex<T>(b[3], qqx, qqy, pz);
     unsigned odd, odd1;
-    acc = point_run<T, 3>(b, v, quads, acc, odd);
-    v[4] = point_vertex<T>(b[4], qqx, qqy, pz);
-    v[5] = point_vertex<T>(b[5], qqx, qqy, pz);
-    if ((b[5].flags | b[6].flags) & kChainEdge) {
-        v[6] = point_vertex<T>(b[6], qqx, qqy, pz);
-        v[7] = b[4].flags & kChainTri ? v[4] : point_vertex<T>(b[7], qqx, qqy, pz);
-        last = v[7];
-        acc = point_run<T, 4>(b + 3, v + 3, quads, acc, odd1);
+    v[0] = cont && (b[0].flags & kChainCont) ? last : vertex(0);
+    v[1] = vertex(1);
+    v[2] = vertex(2);
+    v[3] = b[3].flags & kChainClose ? v[0] : vertex(3);
+    if (!(b[4].flags & kChainEdge)) {
+        if (b[3].flags & kChainEdge) {
+            v[4] = b[4].flags & kChainClose ? v[0] : vertex(4);
+            acc = point_run<T, 4>(b, v, quads, acc, odd);
+        } else {
+            acc = point_run<T, 3>(b, v, quads, acc, odd);
+        }
     } else {
-        acc = point_run<T, 2>(b + 3, v + 3, quads, acc, odd1);
+        acc = point_run<T, 3>(b, v, quads, acc, odd);
+        v[4] = vertex(4);
+        v[5] = b[5].flags & kChainClose ? v[0] : vertex(5);
+        if ((b[5].flags | b[6].flags) & kChainEdge) {
+            v[6] = b[6].flags & kChainClose ? v[0] : vertex(6);
+            if (!(b[6].flags & kChainEdge)) v[7] = v[6];   // no edge: any vertex
+            else if (!(b[7].flags & kChainClose)) v[7] = vertex(7);
+            else if (b[4].flags & kChainTri) v[7] = v[4];
+            else v[7] = v[0];
+            last = v[7];
+            if (b[3].flags & kChainEdge) {
+                acc = point_run<T, 4>(b + 3, v + 3, quads, acc, odd1);
+            } else {   // two halves
+                acc = point_run<T, 3>(b + 4, v + 4, quads, acc, odd1);
+                odd1 <<= 1;
+            }
+        } else {
+            acc = point_run<T, 2>(b + 3, v + 3, quads, acc, odd1);
+        }
+        odd |= odd1 << 3;
     }
-    odd |= odd1 << 3;
     while (odd) {
         const int e = __ffs(odd) - 1;
         odd &= odd - 1u;

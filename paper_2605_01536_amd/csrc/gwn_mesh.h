@@ -103,8 +103,8 @@ int64_t max_launch_queries();
 // built-in rule only): a workgroup per point in batches of at most 8,192 points on meshes
 // with at least 16 boundary edges per lane of a 256-lane workgroup.  FP32: a wave per point
 // up to kSinglePoints, groups of four points per wave up to kDensePoints, on meshes of at
-// least kGroupEdges edges (64 up to 16,384 points); else a point per lane, up to kSharedPoints with four waves to
-// share 64 points' clusters.
+// least kGroupEdges edges (64 up to 16,384 points); else a point per lane, up to
+// kSharedPoints with four waves to share 64 points' clusters.
 // ms with the crossings for a wave per point / groups / shared lanes / a point per lane on a
 // torus of loops of 63 k edges: 1 k points 0.07 / 0.08 / 3.3 / 11.1 (unordered), 4 k 0.17 /
 // 0.17 / 2.9 / 11.9, 33 k 1.2 / 0.89 / 1.2 / 2.7, 66 k - / 1.56 / 1.28 / 2.1, 262 k - / 3.7 /
