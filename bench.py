@@ -8,8 +8,10 @@ predicates and FP64 accumulation.  One step = one full grid evaluation (ray
 reuse + boundary term + combine).  The mesh build is precomputation and is not
 timed (Sec. 5.1 excludes it); its time is reported separately.
 
-Prints ONE JSON line (see the keys below).  `roofline` prices the dominant
-kernel (the fused grid kernel) against the VALU issue ceiling; `cpu_baseline`
+Prints ONE JSON line (see the keys below).  `roofline` prices the vector
+instructions that the call's kernels issue against the VALU issue ceiling;
+`all_pairs` says what the sum over all (query, edge) pairs would take at that
+ceiling; `cpu_baseline`
 times the CPU oracle on a bounded random sample of the same grid and also
 reports the max |w_gpu - w_oracle| on that sample.
 """
@@ -91,16 +93,20 @@ PEAK_F16 = 2.5e15
 # each; half a packed conversion per value, 1) and the 128-term output dot
 # product on mixed-precision FMAs (128)
 NET_VALU_SLOTS = 512 * 5 + 32 * 12 + 128     # = 3,072 per point
-# HBM bytes moved per k_grid<float, 8> launch on the default workload (512^3 grid,
-# 1.05M-triangle soup), from two rocprofv3 --pmc passes over this command:
-# FETCH_SIZE 231,964.50 KiB and WRITE_SIZE 524,288.0 KiB per dispatch, scaled by
-# what the same counters read for a plain 1 GiB device copy (bench.py
-# --copy-probe: FETCH_SIZE shows 524,308.25 KiB -> x2.000, WRITE_SIZE
-# 1,048,576 KiB -> x1.000).  Writes are exactly the w output (134,217,728 x 4 B);
-# fetches are the BVH, triangles and boundary vertices read by the 8 XCD L2s.
-# Measured on the kernel as it stands; re-take the counters after any change to
-# k_grid or the workload.
-K_GRID_TRAFFIC_BYTES = (231964.5 * 2.0 + 524288.0 * 1.0) * 1024
+# The default grid call (512^3, 1.05M-triangle soup, FP32) in counters, all its kernels
+# (k_grid, k_far_*, k_raster) together, from rocprofv3 --pmc passes over this command:
+# wave instructions on the VALU (64 lane slots each), and HBM bytes: FETCH_SIZE and
+# WRITE_SIZE in KiB, scaled by what the same counters read for a plain 1 GiB device copy
+# (bench.py --copy-probe: FETCH_SIZE shows 524,308.25 KiB -> x2.000, WRITE_SIZE
+# 1,048,576 KiB -> x1.000).  524,288 KiB of the writes are the output, the others the node
+# sums of the far part (FP64) and registers spilled in k_far_columns.
+# Re-take the counters after any change to these kernels or the workload.
+GRID_VALU_WAVE_INSTS = 1.3193e10
+GRID_TRAFFIC_BYTES = (1179649.4 * 2.0 + 5358163.8 * 1.0) * 1024
+# the same for 2M points of the torus soup (--workload batch; k_bdry_batch and k_chi_wave)
+# and for their gradient (--workload gradient; k_grad_batch)
+BATCH_VALU_WAVE_INSTS = 5.7099e9
+GRAD_VALU_WAVE_INSTS = 8.2886e10
 FP64_OP_SLOTS, FP64_TRANS_SLOTS = 1.5, 5.4
 I_MIN_GRID_FP64 = (16 + 2 + 21 / 2) * FP64_OP_SLOTS + 2.5 * FP64_TRANS_SLOTS + 2   # = 58.25
 # Parametric path (FP64), per unit of work the kernel reports, counted from its
@@ -264,24 +270,11 @@ def main():
     qps = n / (ms_per_step / 1e3)
     avg_kernel_s = float(np.mean(kern_ms)) / 1e3
     pairs = float(n) * B
-    slots, skip_frac, below_frac = grid_slots(soup, grid, args.prec)
-    achieved = pairs * slots / avg_kernel_s
-    roof = {
-        "bound": "alu",
-        "achieved": achieved / 1e12,
-        "peak": PEAK_SLOTS / 1e12,
-        "unit": "T FP32-VALU-slots/s",
-        "frac": achieved / PEAK_SLOTS,
-        # HBM bytes per launch (rocprofv3 counters); only measured for the default workload
-        "traffic": K_GRID_TRAFFIC_BYTES if (args.n == 512 and args.prec == "fp32") else None,
-        "traffic_unit": "bytes per launch",
-        "kernel": "k_grid",
-        "slots_per_pair": slots,
-        "block_above_fraction": skip_frac,
-        "block_below_fraction": below_frac,
-        "pairs_per_launch": pairs,
-        "avg_kernel_ms": avg_kernel_s * 1e3,
-    }
+    slots, _, _ = grid_slots(soup, grid, args.prec)
+    counted = args.n == 512 and args.prec == "fp32"   # the counters are this workload's
+    roof = _issue_roof(GRID_VALU_WAVE_INSTS if counted else None, avg_kernel_s * 1e3, "k_grid + k_far_* + k_raster",
+                       GRID_TRAFFIC_BYTES if counted else None)
+    roof["all_pairs"] = _all_pairs(pairs, slots, avg_kernel_s * 1e3)
     print(f"[bench] {n} queries, B={B}, {ms_per_step:.1f} ms/step, {qps:.3e} q/s, "
           f"{pairs / avg_kernel_s:.3e} pairs/s", file=sys.stderr, flush=True)
 
@@ -370,10 +363,18 @@ def _timed(fn, steps, warmup, stream):
     return a.elapsed_time(b) / steps, (time.perf_counter() - t0) * 1e3 / steps
 
 
-def _alu_roof(pairs, slots, ms, kernel):
-    a = pairs * slots / (ms / 1e3)
-    return {"bound": "alu", "achieved": a / 1e12, "peak": PEAK_SLOTS / 1e12, "unit": "T FP32-VALU-slots/s",
-            "frac": a / PEAK_SLOTS, "traffic": None, "kernel": kernel, "slots_per_pair": slots}
+def _issue_roof(wave_insts, ms, kernel, traffic=None):
+    """Issued VALU lane slots per second against the ceiling (None where the workload has no counters)."""
+    a = None if wave_insts is None else wave_insts * 64.0 / (ms / 1e3)
+    return {"bound": "alu", "achieved": None if a is None else a / 1e12, "peak": PEAK_SLOTS / 1e12,
+            "unit": "T FP32-VALU-slots/s", "frac": None if a is None else a / PEAK_SLOTS, "traffic": traffic,
+            "traffic_unit": "bytes per call", "kernel": kernel, "valu_wave_instructions": wave_insts, "ms": ms}
+
+
+def _all_pairs(pairs, slots, ms):
+    """What every (query, boundary edge) pair at its minimal slots would take at the issue ceiling."""
+    t = pairs * slots / PEAK_SLOTS * 1e3
+    return {"pairs": pairs, "slots_per_pair": slots, "ms_at_ceiling": t, "ratio": t / ms}
 
 
 def _emit(metric, value, unit, args, ms, config, extra=None, dtype="f32"):
@@ -400,8 +401,8 @@ def bench_batch(args):
     pairs = Q.shape[0] * info["nboundary"]
     print(f"[bench] batch {Q.shape[0]} pts B={info['nboundary']}: {wall_ms:.1f} ms, {pairs / wall_ms * 1e3:.3e} pairs/s",
           file=sys.stderr, flush=True)
-    # a small batch (4,096 points): one workgroup per point with the edges split
-    # among its lanes (the default at this size) against one lane per point
+    # a small batch (4,096 points): a point's sum shared among lanes (the default at
+    # this size) against one lane per point
     small = {}
     Qs = Qd[:4096].contiguous()
     ws = torch.empty(4096, device="cuda", dtype=w.dtype)
@@ -416,7 +417,8 @@ def bench_batch(args):
           {"workload": f"torus soup ({info['nf']} tris, {info['nboundary']} boundary edges), 1M uniform + 1M "
                        f"near-surface points", "precision": args.prec, "pairs_per_s": pairs / (ev_ms / 1e3),
            "small_batch_4096": small},
-          extra={"roofline": _alu_roof(pairs, I_MIN_BATCH, ev_ms, "k_chi_* + k_bdry_batch")}
+          extra={"roofline": {**_issue_roof(BATCH_VALU_WAVE_INSTS, ev_ms, "k_chi_wave + k_bdry_batch"),
+                              "all_pairs": _all_pairs(pairs, I_MIN_BATCH, ev_ms)}}
           if args.prec == "fp32" else None, dtype="f32" if args.prec == "fp32" else "f64")
 
 
@@ -464,7 +466,8 @@ def bench_gradient(args):
           {"workload": f"torus soup ({info['nf']} tris, {info['nboundary']} boundary edges), 1M uniform + 1M "
                        f"near-surface points", "precision": args.prec, "pairs_per_s": pairs / (ev_g / 1e3),
            "w_ms_same_points": wall_w, "small_batch_4096": small, "grid_512_ms": ev_gg, "grid_512_pairs_per_s": pairs4 / (ev_gg / 1e3)},
-          extra={"roofline": _alu_roof(pairs, I_MIN_GRAD, ev_g, "k_grad_batch")} if args.prec == "fp32" else None,
+          extra={"roofline": {**_issue_roof(GRAD_VALU_WAVE_INSTS, ev_g, "k_grad_batch"),
+                              "all_pairs": _all_pairs(pairs, I_MIN_GRAD, ev_g)}} if args.prec == "fp32" else None,
           dtype="f32" if args.prec == "fp32" else "f64")
 
 
@@ -667,7 +670,8 @@ def bench_batched(args):
                     "pairs_per_s": pairs / (ev_ms / 1e3), "schedule": inf, "autotune_s": tune_s,
                     "per_mesh_launches_ms": wall2, "graph_speedup_vs_per_mesh": wall2 / wall_ms,
                     "bitwise_equal_to_per_mesh": same},
-          extra={"roofline": _alu_roof(pairs, I_MIN_BATCH, ev_ms, "graph: k_chi_items + k_bdry_persistent")})
+          extra={"roofline": {**_issue_roof(None, ev_ms, "graph: k_chi_items + k_bdry_persistent + k_group_persistent"),
+                              "all_pairs": _all_pairs(pairs, I_MIN_BATCH, ev_ms)}})
 
 
 def bench_surrogate(args):
@@ -807,9 +811,7 @@ def bench_precision(args):
         res[prec] = {"ms": ms, "queries_per_s": grid.n / (ms / 1e3), "max_abs_err": float(e.max()),
                      "p99_abs_err": float(np.quantile(e, 0.99)), "rms_err": float(np.sqrt(np.mean(e * e))),
                      "chi_bit_exact": chi_ok,
-                     "roofline": {"bound": "alu", "slots_per_pair": slots, "unit": "T FP32-VALU-slots/s",
-                                  "achieved": pairs * slots / (ev / 1e3) / 1e12, "peak": PEAK_SLOTS / 1e12,
-                                  "frac": pairs * slots / (ev / 1e3) / PEAK_SLOTS}}
+                     "roofline": {"all_pairs": _all_pairs(pairs, slots, ev)}}
         print(f"[bench] {prec}: {ms:.1f} ms, max|err| {e.max():.3e}, chi exact {chi_ok}", file=sys.stderr, flush=True)
         del w, chi
         torch.cuda.empty_cache()
