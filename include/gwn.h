@@ -135,8 +135,10 @@ gwn_status gwn_mesh_destroy(gwn_mesh m);
  * (split: FP32 fewer than 49,152 points on meshes with at least 512 boundary
  * edges, up to 16,384 points 64 edges, FP64 at most 8,192 points and at least 4,096 edges; order: at least
  * 2^18 points on meshes of at least 2^15 triangles for the crossing walk, 16,384
- * points and 10^8 pairs of a point and an edge for the boundary sum; samples: the largest of 8 (FP32) or 4 (FP64), 4, 2, 1 that the
- * column length fills), -1 never (split, order).  The environment variables
+ * points and 10^8 pairs of a point and an edge for the boundary sum; samples: 4 (FP64: 2) on columns of
+ * 8 blocks of 64 samples or more, 2 where the blocks fill it, else 1; larger values take the
+ * largest of those; FP32 grids of few samples against a ragged boundary that are summed in boxes
+ * of samples have no columns), -1 never (split, order).  The environment variables
  * GWN_SPLIT_BOUNDARY, GWN_ORDER_QUERIES and GWN_GRID_SAMPLES_PER_LANE override
  * any tuning.
  *

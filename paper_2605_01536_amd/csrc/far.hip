@@ -175,15 +175,24 @@ size_t far_layout(FarPlan& p, char* base) {
 
 FarPlan far_plan(const gwn_mesh_s* m, const GridArgs& ga, int prec, int C) {
     FarPlan none;
+    const long long N[3] = {ga.nx, ga.ny, ga.nz};
+    // Expected time in seconds.  Chained vertices per second, measured: all chunks 3.0e12
+    // (FP64 8.3e11), near chunks alone 2.4e12 (8e11; their edges look wider), node columns
+    // 2.1e12 (9e11); interpolation per sample and node value; launches.
+    // The gradient's rates likewise, for its three sums together.
+    const bool f32 = prec != GWN_PREC_FP64;
+    const double rate = f32 ? 3.0e12 : 0.83e12, near_rate = f32 ? 2.4e12 : 0.8e12, node_rate = f32 ? 2.1e12 : 0.9e12;
+    const double B = (double)m->nchunk * kChunk * (C == 3 ? 1.3 : 1.0), all = (double)N[0] * N[1] * N[2];
+    auto padded = [](double z) { return std::ceil(z / 64.0) * 64.0; };
+    const double columns = (double)N[0] * N[1] * padded((double)N[2]), direct = columns * B / rate;
+    none.cost = direct;
     // GWN_GRID_FAR: 0 never; 8 to 96 blocks of that many samples wherever the form allows
     int forced = 0;
     if (const char* e = std::getenv("GWN_GRID_FAR")) {
         forced = std::atoi(e);
         if (forced <= 0) return none;
     }
-    const bool f32 = prec != GWN_PREC_FP64;
     const int n = f32 ? 10 : 16;
-    const long long N[3] = {ga.nx, ga.ny, ga.nz};
     if (m->nchunk < 1) return none;
     // every sample inside the fixed-point box in x and y, and no farther than its
     // size in z; rising or falling coordinates
@@ -218,14 +227,6 @@ FarPlan far_plan(const gwn_mesh_s* m, const GridArgs& ga, int prec, int C) {
     for (int a = 0; a < 3; ++a)
         if (N[a] > n) smin = smin > 0.0 ? std::min(smin, step[a]) : step[a];
     if (!(smin > 0.0)) return none;
-    // Expected time in seconds.  Chained vertices per second, measured: all chunks 3.0e12
-    // (FP64 8.3e11), near chunks alone 2.4e12 (8e11; their edges look wider), node columns
-    // 2.1e12 (9e11); interpolation per sample and node value; launches.
-    // The gradient's rates likewise, for its three sums together.
-    const double rate = f32 ? 3.0e12 : 0.83e12, near_rate = f32 ? 2.4e12 : 0.8e12, node_rate = f32 ? 2.1e12 : 0.9e12;
-    const double B = (double)m->nchunk * kChunk * (C == 3 ? 1.3 : 1.0), all = (double)N[0] * N[1] * N[2];
-    auto padded = [](double z) { return std::ceil(z / 64.0) * 64.0; };
-    const double columns = (double)N[0] * N[1] * padded((double)N[2]), direct = columns * B / rate;
     double cost = forced > 0 ? 1e30 : 0.9 * direct;
     for (int bs : {8, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 56, 64, 80, 96}) {
         if (forced > 0) bs = forced;
@@ -291,6 +292,7 @@ FarPlan far_plan(const gwn_mesh_s* m, const GridArgs& ga, int prec, int C) {
         if (t < cost) {
             cost = t;
             best = q;
+            best.cost = t;
         }
     }
     if (best.levels == 0) return none;

@@ -30,14 +30,6 @@ namespace {
 // loads, here every load is independent: of the 512^3 grid of the 1.05M-triangle
 // soup 9.2 ms were that walk with 8 exact tests per lane and crossing.  A column of
 // more than kCrossings crossings is left to its wave.
-constexpr int kCrossings = 32;
-
-struct ColCrossings {
-    int* count;        // per column; null: no lists
-    int* list;         // [kCrossings][ncols]: samples below the crossing * 2 + (sign < 0)
-    long long ncols;
-};
-
 // column indices whose quantised coordinate may lie in [lo, hi] (rising coordinates;
 // slack: rounding of a coordinate, in columns)
 __device__ __forceinline__ void col_range(const GridArgs& ga, const QGrid& g, int axis, double slack, int n, int lo,
@@ -418,7 +410,9 @@ gwn_status launch_crossings(const gwn_mesh_s* m, const GridArgs& ga, const ColCr
 
 // With a far part where far_plan() expects one to pay: its node sums and their
 // interpolation first, in a stream-ordered workspace.  A stream that is being
-// captured and a workspace that cannot be had take the sum over all chunks instead.
+// captured and a workspace that cannot be had take the sum over all chunks instead.  FP32
+// grids of few samples take boxes (boxes.hip), captured or not; without crossing lists
+// these walk the BVH per sample.
 template <class T>
 gwn_status launch_grid(const gwn_mesh_s* m, GridArgs ga, T* w, int32_t* chi_out, hipStream_t st) {
     constexpr int prec = sizeof(T) == 8 ? GWN_PREC_FP64 : GWN_PREC_FP32;
@@ -428,8 +422,13 @@ gwn_status launch_grid(const gwn_mesh_s* m, GridArgs ga, T* w, int32_t* chi_out,
     void* ws = nullptr;
     size_t clist = 0;
     double slack[2];
-    if (!stream_captures(st)) {
-        p = far_plan(m, ga, prec, 1);
+    long long boxes = 0;
+    bool box = false;
+    p = far_plan(m, ga, prec, 1);
+    if constexpr (sizeof(T) == 4) box = want_boxes(m, ga, p, &boxes);
+    const bool captures = stream_captures(st);
+    if (box || captures) p.levels = 0;
+    if (!captures) {
         if (want_crossings(m, ga, slack)) clist = sizeof(int) * (size_t)(kCrossings + 1) * (size_t)ncols;
         const size_t far_bytes = p.levels > 0 ? p.bytes : 0;
         if (far_bytes + clist > 0) {
@@ -450,7 +449,9 @@ gwn_status launch_grid(const gwn_mesh_s* m, GridArgs ga, T* w, int32_t* chi_out,
         for (int l = 0; l < p.levels && s == GWN_OK; ++l) s = launch_far<T>(m, far_nodes(p, l), st);
         if (s == GWN_OK) s = far_transfer(p, st);
     }
-    if (s == GWN_OK) s = launch_columns<T>(m, ga, far_view(p), cc, w, chi_out, st);
+    if constexpr (sizeof(T) == 4)
+        if (s == GWN_OK && box) s = launch_boxes(m, ga, boxes, cc, w, chi_out, st);
+    if (s == GWN_OK && !box) s = launch_columns<T>(m, ga, far_view(p), cc, w, chi_out, st);
     if (ws) (void)hipFreeAsync(ws, st);
     return s;
 }

@@ -59,7 +59,17 @@ struct FarPlan {
     double* s[3];                // [ns][nodes]: interpolation from level 0's nodes to the samples
     double* U;                   // [C][nn x][ns y][nn z]: level 0's sums interpolated in y
     size_t bytes = 0;
+    double cost = 0.0;           // expected time of the boundary sum, s, with or without a far part
     double t[kFarMaxNodes];      // Chebyshev nodes of [-1, 1], ascending
+};
+
+// The crossings of a grid's columns (k_raster in grid.hip).
+constexpr int kCrossings = 32;
+
+struct ColCrossings {
+    int* count;        // per column; null: no lists
+    int* list;         // [kCrossings][ncols]: samples below the crossing * 2 + (sign < 0)
+    long long ncols;
 };
 
 // Lays out a far part for the grid, or none (levels = 0) where the direct sum is
@@ -72,6 +82,11 @@ gwn_status far_setup(FarPlan& p, const gwn_mesh_s* m, const GridArgs& ga, int pr
 
 // After the node sums: down the levels, then level 0's interpolation in y.
 gwn_status far_transfer(const FarPlan& p, hipStream_t st);
+
+// Boxes of samples (boxes.hip) instead of the columns of plan p: whether, and how many.
+bool want_boxes(const gwn_mesh_s* m, const GridArgs& ga, const FarPlan& p, long long* boxes);
+gwn_status launch_boxes(const gwn_mesh_s* m, const GridArgs& ga, long long boxes, const ColCrossings& cc, float* w,
+                        int32_t* chi_out, hipStream_t st);
 
 // What the column kernels take: level 0 and the samples' weights.
 struct FarView {

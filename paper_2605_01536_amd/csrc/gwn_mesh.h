@@ -39,6 +39,7 @@ struct gwn_mesh_s {
     int split_max[2] = {0, 0};     // per precision: batches of at most this many points split their edges
     int order_min = 0;             // batches of at least this many points are Morton-ordered
     int grid_zb[2] = {0, 0};       // per precision: grid samples per lane
+    bool columns_only = false;     // grids in columns while the tuner times them
     int tuned = 0;                 // bit p: precision p was tuned
 
     gwn::MeshView view() const {

@@ -2,15 +2,15 @@
 // autotuner gwn_mesh_autotune.
 //
 // Three choices of the single-mesh paths depend on the mesh and the device
-// rather than on the arithmetic (none changes a crossing count; the first
-// changes w's summation order, the other two none of its bits):
-//   * the largest batch that gives each point a workgroup with the boundary
-//     edges split among its lanes (few points against many edges), per
-//     precision;
-//   * the smallest batch worth a Morton order of the points for the crossing
-//     walk (dense points share BVH paths, sparse ones pay for the sort);
-//   * the grid kernel's samples per lane (more share more x/y work, fewer leave
-//     registers for more resident waves), per precision.
+// rather than on the arithmetic (none changes a crossing count):
+//   * the largest batch that shares each point's boundary sum among lanes (few
+//     points against many edges), per precision (FP64: changes w's summation
+//     order; FP32 sums are exact in fixed units, whose bits do not change);
+//   * the smallest batch worth an order of the points for the crossing walk and
+//     FP32's boundary sum (dense points share BVH paths and clusters, sparse ones
+//     pay for the sort; no bits change);
+//   * the grid's samples per lane in columns (more share more x/y work, fewer
+//     leave registers for more resident waves), per precision; w's last bits.
 // The tuner sets the mesh's tuning to each candidate in turn and times the
 // ordinary query calls on points it draws uniformly in the mesh's bounding box
 // (and on a 64 x 64 x nz grid over it), keeping the fastest; the choice can be
@@ -216,8 +216,10 @@ gwn_status autotune(gwn_mesh_s* m, int prec, int nz, int reps, hipStream_t st, T
             if (cand == 8 && prec == GWN_PREC_FP64) continue;
             float t = 0.f;
             m->grid_zb[prec] = cand;
+            m->columns_only = true;
             const gwn_status s = time_ms([&]() { return query_grid(m, org, sp, dims, prec, W, nullptr, st); }, reps,
                                          st, &t);
+            m->columns_only = false;
             if (s != GWN_OK) return s;
             if (t < bt) {
                 bt = t;
