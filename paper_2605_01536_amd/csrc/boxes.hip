@@ -16,7 +16,7 @@
 namespace gwn {
 namespace {
 
-// A workgroup of PARTS waves takes a box of 4 x 4 x 4 samples, one per lane, and walks the
+// A workgroup of PARTS waves takes a box of 64 samples, one per lane, and walks the
 // clusters that serve scattered points (point_clusters): the samples of a box have the same
 // clusters near and far, and the waves share the top level out.  A sample's w has the bits
 // of a query at its position.
@@ -24,26 +24,27 @@ namespace {
 // Bound by VALU issue of expansions and near edges, as the points are; few boxes by the
 // chain of clusters that a wave walks, hence more waves per box for fewer boxes (us at 16,
 // 8, 4 waves: 125 boxes 399, 462, 610; 1,040 boxes 974, 666, 604; 4,096 boxes 3033, 1828,
-// 1191, all on a torus of loops of 25 k edges).
-constexpr int kBox = 4;
-
-struct BoxCount {
-    int y, z;   // boxes along y and z
+// 1191, all on a torus of loops of 25 k edges).  The box is the nearest to a cube that the
+// spacing and the grid allow (20 x 150 x 30 samples over a cube, us: 4 x 4 x 4 703, 2 x 16 x 2
+// 548).
+struct Boxes {
+    int l[3];   // log2 of a box's samples along each axis, 6 in all
+    int n[3];   // boxes along each axis
 };
 
 template <int PARTS>
-__global__ __launch_bounds__(64 * PARTS) void k_grid_boxes(MeshView mv, GridArgs ga, BoxCount nb, ColCrossings cc,
+__global__ __launch_bounds__(64 * PARTS) void k_grid_boxes(MeshView mv, GridArgs ga, Boxes nb, ColCrossings cc,
                                                            int* __restrict__ chi_out, float* __restrict__ w) {
     __shared__ int stack[kLdsStack * kChiBlock];
     __shared__ double part[PARTS][64];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     int lane = threadIdx.x & 63;
     // the lane's sample; beyond the grid's end the last one
-    const int bz = (int)blockIdx.x % nb.z, bxy = (int)blockIdx.x / nb.z, bx = bxy / nb.y, by = bxy - bx * nb.y;
+    const int bz = (int)blockIdx.x % nb.n[2], bxy = (int)blockIdx.x / nb.n[2], bx = bxy / nb.n[1], by = bxy - bx * nb.n[1];
     auto sample = [&](int& i, int& j, int& k) {
-        i = bx * kBox + (lane >> 4);
-        j = by * kBox + (lane >> 2 & 3);
-        k = bz * kBox + (lane & 3);
+        i = (bx << nb.l[0]) + (lane >> (nb.l[1] + nb.l[2]));
+        j = (by << nb.l[1]) + ((lane >> nb.l[2]) & ((1 << nb.l[1]) - 1));
+        k = (bz << nb.l[2]) + (lane & ((1 << nb.l[2]) - 1));
         const bool in = i < ga.nx && j < ga.ny && k < ga.nz;
         i = min(i, (int)ga.nx - 1);
         j = min(j, (int)ga.ny - 1);
@@ -91,6 +92,26 @@ __global__ __launch_bounds__(64 * PARTS) void k_grid_boxes(MeshView mv, GridArgs
     w[o] = (float)((double)chi + point_total<float>(S, unit) * kInv2Pi);
 }
 
+// The box nearest to a cube: its shortest side doubled six times, no side beyond the grid's.
+Boxes box_shape(const GridArgs& ga) {
+    const long long N[3] = {ga.nx, ga.ny, ga.nz};
+    Boxes b{};
+    for (int k = 0; k < 6; ++k) {
+        int best = -1;
+        double len = 0.0;
+        for (int a = 0; a < 3; ++a) {
+            const double side = std::fabs(ga.s[a]) * (double)(1 << b.l[a]);
+            if ((1ll << b.l[a]) < N[a] && (best < 0 || side < len)) {
+                best = a;
+                len = side;
+            }
+        }
+        ++b.l[best < 0 ? 0 : best];
+    }
+    for (int a = 0; a < 3; ++a) b.n[a] = (int)((N[a] + (1 << b.l[a]) - 1) >> b.l[a]);
+    return b;
+}
+
 }  // namespace
 
 // By the expected time, on meshes of short loops (at most 8 edges on average: clusters of
@@ -98,19 +119,24 @@ __global__ __launch_bounds__(64 * PARTS) void k_grid_boxes(MeshView mv, GridArgs
 // boxes, 0.7 in columns).  Boxes: per sample the far clusters, whose number goes with
 // the root of the edges' number B until the levels of the tree take over, and the edges
 // near the box, which go with B times the square of its side over the mesh's until most are
-// near; and a wave's walk.  Measured, us, columns / boxes: B = 1,001 (ellipsoids) 37 x 50 x 29
+// near; and a wave's walk.  Columns: far_plan's estimate with what it leaves out, the part
+// of a column's wave that does not go with the boundary, and a column's length where there
+// are few; 15% less with a far part, whose estimate is the looser one.  Measured, us, columns / boxes: B = 1,001 (ellipsoids) 37 x 50 x 29
 // 124 / 98, 64^3 254 / 217, 100^3 634 / 614, 130^3 949 / 1342; B = 2,538 (torus) 20^3 88 / 97,
 // 64^3 524 / 371, 100^3 929 / 1126; B = 25,229 20^3 517 / 399, 64^3 3720 / 1191, 100^3 5735 /
-// 3264, 160^3 9143 / 11738; B = 53,776 (ellipsoids) 64^3 7668 / 1473, 160^3 27478 / 12323.
+// 3264, 160^3 9143 / 11738; B = 53,776 (ellipsoids) 64^3 7668 / 1473,
+// 160^3 27478 / 12323, slices 512 x 512 x 1 29489 / 1191, 1 x 256 x 256 1236 / 636.
 // GWN_GRID_BOXES: 0 never, 1 wherever the mesh has clusters; a choice of column form
 // by GWN_GRID_FAR or GWN_GRID_SAMPLES_PER_LANE is a choice of columns, as is the tuner's
 // timing of the samples per lane (columns_only).
 bool want_boxes(const gwn_mesh_s* m, const GridArgs& ga, const FarPlan& p, long long* boxes) {
+    const Boxes b = box_shape(ga);
     const long long N[3] = {ga.nx, ga.ny, ga.nz};
     double n = 1.0, side = 0.0, ext = 0.0;
     for (int a = 0; a < 3; ++a) {
-        n *= (double)((N[a] + kBox - 1) / kBox);
-        side += kBox * kBox * ga.s[a] * ga.s[a];
+        const double h = N[a] > 1 ? (double)(1 << b.l[a]) * ga.s[a] : 0.0;
+        n *= (double)b.n[a];
+        side += h * h;
         ext += (m->bbox[3 + a] - m->bbox[a]) * (m->bbox[3 + a] - m->bbox[a]);
     }
     if (m->nclusters < kFewClusters || !(n * 64.0 <= (double)max_launch_queries())) return false;
@@ -119,14 +145,16 @@ bool want_boxes(const gwn_mesh_s* m, const GridArgs& ga, const FarPlan& p, long 
     if (std::getenv("GWN_GRID_FAR") || std::getenv("GWN_GRID_SAMPLES_PER_LANE") || m->columns_only) return false;
     if (m->nb > 8 * m->nloops) return false;
     const double B = (double)m->nb, x = B * side / ext;
-    const double share = std::min(2.2, 0.018 * std::sqrt(B)) + 0.02 * x / (1.0 + x / 400.0);   // ns
+    const double share = std::min(2.4, 0.018 * std::sqrt(B)) + 0.02 * x / (1.0 + x / 400.0);   // ns
     const double t = 64e-9 * n * share + 1e-6 * std::sqrt(B);
-    return t < (p.levels > 0 ? 1.0 : 1.4) * p.cost + 2.5e-5;
+    const double waves = (double)ga.nx * (double)ga.ny * std::ceil((double)ga.nz / 64.0);
+    const double columns = p.levels > 0 ? 0.85 * p.cost : std::max(1.4 * p.cost, 1.4e-8 * B);
+    return t < columns + 2e-9 * waves + 2.5e-5;
 }
 
 gwn_status launch_boxes(const gwn_mesh_s* m, const GridArgs& ga, long long boxes, const ColCrossings& cc, float* w,
                         int32_t* chi_out, hipStream_t st) {
-    const BoxCount nb{(int)((ga.ny + kBox - 1) / kBox), (int)((ga.nz + kBox - 1) / kBox)};
+    const Boxes nb = box_shape(ga);
     if (boxes <= 256) k_grid_boxes<16><<<(unsigned)boxes, 1024, 0, st>>>(m->view(), ga, nb, cc, chi_out, w);
     else if (boxes <= 1024) k_grid_boxes<8><<<(unsigned)boxes, 512, 0, st>>>(m->view(), ga, nb, cc, chi_out, w);
     else k_grid_boxes<4><<<(unsigned)boxes, 256, 0, st>>>(m->view(), ga, nb, cc, chi_out, w);

@@ -33,7 +33,7 @@ def _check(mesh, origin, spacing, dims):
 
 # boxes: 1, 1, 2 x 2 x 2, 125 and 256 (16 waves each), 260 and 1,024 (8), 1,040 and 1,560 (4)
 @pytest.mark.parametrize("dims", [(1, 1, 1), (4, 4, 4), (5, 7, 8), (20, 20, 20), (32, 32, 13), (20, 49, 13),
-                                  (64, 29, 31), (37, 50, 29), (3, 240, 101)])
+                                  (64, 29, 31), (37, 50, 29), (3, 240, 101), (70, 1, 31), (1, 1, 100), (130, 90, 1)])
 @pytest.mark.parametrize("axis", ["x", "y", "z"])
 def test_bits_of_the_points(monkeypatch, dims, axis):
     monkeypatch.setenv("GWN_GRID_BOXES", "1")
