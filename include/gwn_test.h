@@ -9,6 +9,14 @@
  * gwn_last_error() and releases whatever it had allocated.  Process-wide, for
  * all devices and threads.  Returns the number of allocations made since the
  * previous call (host-side count), so a test can find out how many a call makes.
+ *
+ * gwn_test_far_plan(...): the far part that a grid call would lay out (host code
+ * only, no device needed) for a mesh of the bounding box bbox (minimum x, y, z,
+ * maximum x, y, z), nchunk boundary chunks and a mean chunk extent of chunk_w
+ * fixed-point cells, along the z ray; values: 1 for w, 3 for the gradient.  Writes
+ * the number of levels (0: no far part), then per level, finest first, the far
+ * distance in cells and for x and y the number of blocks and each block's first
+ * and last sample.  Returns the count of numbers, -1 if cap is too small.
  */
 #ifndef GWN_TEST_H
 #define GWN_TEST_H
@@ -20,6 +28,10 @@ extern "C" {
 #endif
 
 int64_t gwn_test_fail_alloc_after(int64_t n);
+
+int64_t gwn_test_far_plan(const double* bbox, int64_t nchunk, double chunk_w, const double* origin,
+                          const double* spacing, const int64_t* dims, int32_t prec, int32_t values, int64_t* out,
+                          int64_t cap);
 
 #ifdef __cplusplus
 }

@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdlib>
 
+#include "../../include/gwn_test.h"
 #include "gwn_far.h"
 
 namespace gwn {
@@ -25,12 +26,10 @@ __global__ void k_far_nodes(FarPlan p, GridArgs ga, QGrid g, bool f32) {
     const FarLevel& l = p.lv[blockIdx.z];
     const int c = blockIdx.x * 64 + threadIdx.x, n = p.nodes[axis];
     if (c >= l.nc[axis]) return;
-    // a last block of fewer samples reaches one step past the grid, at every level, so
-    // that a single sample has a range too and a block lies inside its parent
-    const long long i0 = (long long)c * l.b[axis], i1 = min(i0 + l.b[axis] - 1, (long long)p.ns[axis]);
-    const double a = far_sample(ga, g, f32, p.C, axis, i0), b = far_sample(ga, g, f32, p.C, axis, i1);
+    const FarRange i = far_range(p, l, axis, c);
+    const double a = far_sample(ga, g, f32, p.C, axis, i.first), b = far_sample(ga, g, f32, p.C, axis, i.last);
     if (axis < 2) {
-        const double qa = far_sample(ga, g, f32, 1, axis, i0), qb = far_sample(ga, g, f32, 1, axis, i1);
+        const double qa = far_sample(ga, g, f32, 1, axis, i.first), qb = far_sample(ga, g, f32, 1, axis, i.last);
         (axis == 0 ? l.cx : l.cy)[c] = make_int2((int)fmin(qa, qb), (int)fmax(qa, qb));
     }
     for (int j = 0; j < n; ++j) {
@@ -235,21 +234,18 @@ FarPlan far_plan(const gwn_mesh_s* m, const GridArgs& ga, int prec, int C) {
         q.levels = 0;
         double near_up = 1.0, t = 2e-5;
         double nodes_t = 0.0;
-        bool ok = true;
         // levels from fine to coarse until a level's blocks span the grid
-        for (int l = 0; l < kFarLevels && ok; ++l) {
+        for (int l = 0; l < kFarLevels; ++l) {
             FarLevel& v = q.lv[l];
             double half = 0.0;
             bool one = true;
             for (int a = 0; a < 3; ++a) {
                 long long b = l == 0 ? std::max<long long>(8, (long long)std::llround(h / step[a])) : 2ll * q.lv[l - 1].b[a];
                 if (N[a] <= n) b = N[a];
-                b = std::min<long long>(b, std::max<long long>(N[a], 1));
-                if (l > 0 && b < N[a] && b != 2ll * q.lv[l - 1].b[a]) ok = false;
                 v.b[a] = (int)b;
                 v.nc[a] = (int)((N[a] + b - 1) / b);
                 v.nn[a] = v.nc[a] * q.nodes[a];
-                if (N[a] > n) half = std::max(half, 0.5 * (double)(b - 1) * step[a]);
+                if (N[a] > n) half = std::max(half, 0.5 * (double)far_range(q, v, a, 0).last * step[a]);
                 one &= v.nc[a] == 1;
             }
             const double thr = std::ceil((f32 ? kFarKappa32 : kFarKappa64) * half) + 4.0;
@@ -258,12 +254,12 @@ FarPlan far_plan(const gwn_mesh_s* m, const GridArgs& ga, int prec, int C) {
             q.levels = l + 1;
             if (one) break;
         }
-        if (!ok || q.levels == 0) continue;
+        if (q.levels == 0) continue;
         // expected share of the boundary near a block, averaged over the blocks
         auto share = [&](const FarLevel& v) {
             double f = 1.0;
             for (int a = 0; a < 2; ++a) {
-                const double w = (double)v.b[a] * step[a], reach = (double)v.thr + 0.5 * m->chunk_w, len = (double)N[a] * step[a];
+                const double len = (double)N[a] * step[a], w = std::min((double)v.b[a] * step[a], len), reach = (double)v.thr + 0.5 * m->chunk_w;
                 // blocks over the grid's length; the boundary over ext in its middle
                 double s = 0.0;
                 for (int c = 0; c < v.nc[a]; ++c) {
@@ -334,3 +330,32 @@ gwn_status far_transfer(const FarPlan& p, hipStream_t st) {
 }
 
 }  // namespace gwn
+
+extern "C" int64_t gwn_test_far_plan(const double* bbox, int64_t nchunk, double chunk_w, const double* origin,
+                                     const double* spacing, const int64_t* dims, int32_t prec, int32_t values,
+                                     int64_t* out, int64_t cap) {
+    gwn_mesh_s m;
+    std::copy(bbox, bbox + 6, m.bbox);
+    m.g = gwn::make_qgrid(bbox);
+    m.nchunk = nchunk;
+    m.chunk_w = chunk_w;
+    const gwn::FarPlan p = gwn::far_plan(&m, gwn::frame_grid(0, origin, spacing, dims), prec, values);
+    int64_t n = 0;
+    auto put = [&](int64_t v) {
+        if (n < cap) out[n] = v;
+        ++n;
+    };
+    put(p.levels);
+    for (int l = 0; l < p.levels; ++l) {
+        put(p.lv[l].thr);
+        for (int a = 0; a < 2; ++a) {
+            put(p.lv[l].nc[a]);
+            for (int c = 0; c < p.lv[l].nc[a]; ++c) {
+                const gwn::FarRange r = gwn::far_range(p, p.lv[l], a, c);
+                put(r.first);
+                put(r.last);
+            }
+        }
+    }
+    return n <= cap ? n : -1;
+}

@@ -38,8 +38,8 @@ constexpr int kFarMaxNodes = 16;                  // nodes per block and axis: 1
 constexpr double kFarKappa32 = 2.5, kFarKappa64 = 3.0;
 constexpr size_t kFarMaxBytes = size_t(16) << 30;   // larger workspaces: larger blocks instead
 
-// One level: blocks of b samples per axis (the last may hold fewer), nc blocks and
-// nn = nc * nodes node positions per axis.
+// One level: blocks of b samples per axis (the last may hold fewer; b itself may exceed
+// the axis), nc blocks and nn = nc * nodes node positions per axis.
 struct FarLevel {
     int b[3], nc[3], nn[3];
     int thr;                     // kappa half-widths, in cells
@@ -62,6 +62,23 @@ struct FarPlan {
     double cost = 0.0;           // expected time of the boundary sum, s, with or without a far part
     double t[kFarMaxNodes];      // Chebyshev nodes of [-1, 1], ascending
 };
+
+// The samples first ... last that block c of a level reaches over along an axis.  A block
+// with room for more samples than are left reaches one step past the grid, so that a
+// single sample has a range too.  Blocks of the next level hold two of this one's, so the
+// ranges nest: first is the parent's or later, and last, the smaller of two ends of which
+// the parent has the same or a later one, lies within the parent's.  A chunk far from a
+// block's parent is then far from the block (the distances do not fall with the level),
+// which is what makes the levels' shares of the chunks disjoint.
+struct FarRange {
+    long long first, last;
+};
+
+__host__ __device__ inline FarRange far_range(const FarPlan& p, const FarLevel& l, int axis, long long c) {
+    FarRange r{c * l.b[axis], (c + 1) * l.b[axis] - 1};
+    if (r.last > p.ns[axis]) r.last = p.ns[axis];
+    return r;
+}
 
 // The crossings of a grid's columns (k_raster in grid.hip).
 constexpr int kCrossings = 32;
