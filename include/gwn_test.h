@@ -17,6 +17,10 @@
  * the number of levels (0: no far part), then per level, finest first, the far
  * distance in cells and for x and y the number of blocks and each block's first
  * and last sample.  Returns the count of numbers, -1 if cap is too small.
+ *
+ * gwn_test_plan_launches(nitems, kernel, work_items): how many launches a plan of
+ * nitems work items makes of its key (0), ordered crossing (1) or unordered
+ * crossing (2) kernel, and in *work_items the largest one's (host code only).
  */
 #ifndef GWN_TEST_H
 #define GWN_TEST_H
@@ -32,6 +36,8 @@ int64_t gwn_test_fail_alloc_after(int64_t n);
 int64_t gwn_test_far_plan(const double* bbox, int64_t nchunk, double chunk_w, const double* origin,
                           const double* spacing, const int64_t* dims, int32_t prec, int32_t values, int64_t* out,
                           int64_t cap);
+
+int64_t gwn_test_plan_launches(int64_t nitems, int32_t kernel, int64_t* work_items);
 
 #ifdef __cplusplus
 }

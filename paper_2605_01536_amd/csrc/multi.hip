@@ -17,6 +17,7 @@
 #include <string>
 #include <vector>
 
+#include "../../include/gwn_test.h"
 #include "gwn_alloc.h"
 #include "gwn_kernels.h"
 #include "gwn_mesh.h"
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_chi_items_point(const MeshV
 __global__ void k_plan_keys(const MeshView* __restrict__ table, const Item* __restrict__ items, int nkeyed,
                             const float* __restrict__ qx, const float* __restrict__ qy, const float* __restrict__ qz,
                             long long qs, bool space, uint64_t* __restrict__ key, int* __restrict__ idx) {
-    const Item I = items[blockIdx.x];
+    const Item I = items[blockIdx.x];   // items, nkeyed: from the launch's first item on
     const QGrid g = table[I.mesh].g;
     const float *x = qx, *y = qy, *z = qz;
     axis_ptrs(table[I.mesh].axis, x, y, z);
@@ -259,6 +260,17 @@ bool is_dense(const gwn_multi_s* p, int mesh) {
     return p->nq <= 0x7fffffffll && p->qoff_h[mesh + 1] - p->qoff_h[mesh] >= kDenseQueries;
 }
 
+// f(first, count) for runs of n items, `threads` work-items each, whose launches stay within
+// max_launch_queries(): an item of the crossing kernels takes up to 1,024 work-items, so 2^31
+// queries in items of 128 exceed a launch's 2^32.
+constexpr int kKeyThreads = 128, kWalkThreads = 64, kPointThreads = kChiParts * 64 * kGridWaves;
+
+template <class F>
+void item_slices(int64_t n, int threads, F&& f) {
+    const int64_t most = std::max<int64_t>(1, max_launch_queries() / threads);
+    for (int64_t i = 0; i < n; i += most) f(i, std::min(most, n - i));
+}
+
 // Work list for a schedule: tiles of item_queries queries, ordered by estimated
 // cost (queries x (boundary edges + a traversal allowance)) or by mesh.
 gwn_status build_items(gwn_multi_s* p, const Schedule& s, hipStream_t st) {
@@ -310,9 +322,12 @@ gwn_status build_perm(gwn_multi_s* p, bool space, bool all, int** perm, hipStrea
     GWN_HIP_TRY(gwn::dmalloc((void**)&tmp, 2 * kb + ib + sort_temp_bytes(n, 8, true)));
     uint64_t *k0 = (uint64_t*)tmp, *k1 = (uint64_t*)(tmp + kb);
     int* i0 = (int*)(tmp + 2 * kb);
-    k_plan_keys<<<(unsigned)p->nitems, 128, 0, st>>>(p->table, p->items, all ? p->nitems : p->ndense, p->qx, p->qy, p->qz,
-                                                    p->qs, space, k0, i0);
-    hipError_t e = hipGetLastError();
+    hipError_t e = hipSuccess;
+    item_slices(p->nitems, kKeyThreads, [&](int64_t i, int64_t ni) {
+        k_plan_keys<<<(unsigned)ni, kKeyThreads, 0, st>>>(p->table, p->items + i, (int)((all ? p->nitems : p->ndense) - i), p->qx,
+                                                         p->qy, p->qz, p->qs, space, k0, i0);
+        if (e == hipSuccess) e = hipGetLastError();
+    });
     if (e == hipSuccess) e = radix_sort_u64(k0, k1, i0, *perm, n, 0, bits, tmp + 2 * kb + ib, st);
     const hipError_t e2 = hipStreamSynchronize(st);
     (void)hipFree(tmp);
@@ -330,23 +345,36 @@ gwn_status capture(gwn_multi_s* p, const Schedule& s) {
     const long long need = (p->ndense < p->nitems && p->prec != GWN_PREC_FP64 ? (long long)p->nitems * claims : (long long)p->nitems * lanes) / 4 + 1;   // no more waves than claims
     p->grid = (int)std::max<long long>(1, std::min<long long>(waves / 4, std::max<long long>(need, 1)));
     GWN_HIP_TRY(hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal));
+    hipError_t le = hipSuccess;   // of the first launch that was refused
+    auto launched = [&] {
+        const hipError_t e = hipGetLastError();
+        if (le == hipSuccess) le = e;
+    };
     k_reset_counter<<<1, 64, 0, p->cap>>>(p->counter);
+    launched();
     if (p->nq > 0) {
         const int nd = p->ndense, ns = p->nitems - nd;
-        if (nd > 0)
-            k_chi_items<<<(unsigned)((nd + kGridWaves - 1) / kGridWaves), 64 * kGridWaves, 0, p->cap>>>(
-                p->table, p->items, nd, p->qx, p->qy, p->qz, p->qs, p->perm, p->chi);
-        if (ns > 0)
-            k_chi_items_point<<<(unsigned)ns * kChiParts, 64 * kGridWaves, 0, p->cap>>>(
-                p->table, p->items + nd, ns, p->qx, p->qy, p->qz, p->qs, p->chi);
+        item_slices(nd, kWalkThreads, [&](int64_t i, int64_t n) {
+            k_chi_items<<<(unsigned)((n + kGridWaves - 1) / kGridWaves), 64 * kGridWaves, 0, p->cap>>>(
+                p->table, p->items + i, (int)n, p->qx, p->qy, p->qz, p->qs, p->perm, p->chi);
+            launched();
+        });
+        item_slices(ns, kPointThreads, [&](int64_t i, int64_t n) {
+            k_chi_items_point<<<(unsigned)n * kChiParts, 64 * kGridWaves, 0, p->cap>>>(
+                p->table, p->items + nd + i, (int)n, p->qx, p->qy, p->qz, p->qs, p->chi);
+            launched();
+        });
         if (p->prec == GWN_PREC_FP64) {
             k_bdry_persistent<double><<<p->grid, 256, 0, p->cap>>>(
                 p->table, p->items, p->nitems, lanes, p->counter, p->qx, p->qy, p->qz, p->qs,
                 (s.order & kOrderSorted) ? p->perm : nullptr, p->chi, (double*)p->w);
+            launched();
         } else {
-            if (nd > 0)
+            if (nd > 0) {
                 k_bdry_persistent<float><<<p->grid, 256, 0, p->cap>>>(p->table, p->items, nd, lanes, p->counter, p->qx, p->qy,
                                                                       p->qz, p->qs, p->sperm, p->chi, (float*)p->w);
+                launched();
+            }
             if (ns > 0) {
                 int top = 0;
                 for (const gwn_mesh_s* m : p->meshes) top = std::max(top, m->cluster_top);
@@ -354,10 +382,12 @@ gwn_status capture(gwn_multi_s* p, const Schedule& s) {
                 k_group_persistent<<<p->grid, 256, 4 * ints * sizeof(int), p->cap>>>(
                     p->table, p->items + nd, ns, claims, p->counter + 1, p->qx, p->qy, p->qz, p->qs, nullptr, (int)ints,
                     p->chi, (float*)p->w);
+                launched();
             }
         }
     }
-    hipError_t e = hipStreamEndCapture(p->cap, &p->graph);
+    const hipError_t e = hipStreamEndCapture(p->cap, &p->graph);
+    GWN_HIP_TRY(le);
     GWN_HIP_TRY(e);
     GWN_HIP_TRY(hipGraphInstantiate(&p->exec, p->graph, nullptr, nullptr, 0));
     return GWN_OK;
@@ -557,3 +587,15 @@ void multi_info(const gwn_multi_s* p, gwn_multi_info* o) {
 }
 
 }  // namespace gwn
+
+extern "C" int64_t gwn_test_plan_launches(int64_t nitems, int32_t kernel, int64_t* work_items) {
+    const int threads = kernel == 0 ? gwn::kKeyThreads : kernel == 1 ? gwn::kWalkThreads : gwn::kPointThreads;
+    int64_t launches = 0, next = 0;
+    *work_items = 0;
+    gwn::item_slices(nitems, threads, [&](int64_t i, int64_t n) {
+        launches += i == next;   // the slices follow each other
+        next = i + n;
+        *work_items = std::max(*work_items, n * threads);
+    });
+    return next == nitems ? launches : -1;
+}
