@@ -31,7 +31,7 @@ def _slab(axis, flip):
             x0 = (n - 0.5 + d) * coarse if side > 0 else (0.5 - d) * coarse
             t = np.linspace(0.0, 200.0, 29)
             p = np.zeros((2, 29, 3))
-            p[:, :, a] = x0 + np.array([0.0, 0.1 * coarse])[:, None] * side
+            p[:, :, a] = x0 + np.array([0.0, 3.0 * coarse])[:, None] * side
             p[:, :, 1 - a] = t
             p[:, :, 2] = 350.0 + 40.0 * np.sin(0.05 * t + d)
             b = len(V) * 58
