@@ -21,6 +21,11 @@
  * gwn_test_plan_launches(nitems, kernel, work_items): how many launches a plan of
  * nitems work items makes of its key (0), ordered crossing (1) or unordered
  * crossing (2) kernel, and in *work_items the largest one's (host code only).
+ *
+ * gwn_test_boxes(...): the number of boxes of samples in which an FP32 grid call
+ * would be summed (0: in columns) for such a mesh of nb boundary edges in nloops
+ * loops and nclusters lowest clusters, and the work-items of its largest launch
+ * (host code only).
  */
 #ifndef GWN_TEST_H
 #define GWN_TEST_H
@@ -37,6 +42,9 @@ int64_t gwn_test_far_plan(const double* bbox, int64_t nchunk, double chunk_w, co
                           const double* spacing, const int64_t* dims, int32_t prec, int32_t values, int64_t* out,
                           int64_t cap);
 
+int64_t gwn_test_boxes(const double* bbox, int64_t nchunk, double chunk_w, int64_t nb, int64_t nloops,
+                       int64_t nclusters, const double* origin, const double* spacing, const int64_t* dims,
+                       int64_t* work_items);
 int64_t gwn_test_plan_launches(int64_t nitems, int32_t kernel, int64_t* work_items);
 
 #ifdef __cplusplus

@@ -9,6 +9,7 @@
 
 #include <algorithm>
 
+#include "../../include/gwn_test.h"
 #include "gwn_far.h"
 #include "gwn_kernels.h"
 #include "gwn_mesh.h"
@@ -33,14 +34,16 @@ struct Boxes {
 };
 
 template <int PARTS>
-__global__ __launch_bounds__(64 * PARTS) void k_grid_boxes(MeshView mv, GridArgs ga, Boxes nb, ColCrossings cc,
-                                                           int* __restrict__ chi_out, float* __restrict__ w) {
+__global__ __launch_bounds__(64 * PARTS) void k_grid_boxes(MeshView mv, GridArgs ga, Boxes nb, int box0,
+                                                           ColCrossings cc, int* __restrict__ chi_out,
+                                                           float* __restrict__ w) {
     __shared__ int stack[kLdsStack * kChiBlock];
     __shared__ double part[PARTS][64];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     int lane = threadIdx.x & 63;
     // the lane's sample; beyond the grid's end the last one
-    const int bz = (int)blockIdx.x % nb.n[2], bxy = (int)blockIdx.x / nb.n[2], bx = bxy / nb.n[1], by = bxy - bx * nb.n[1];
+    const int box = box0 + (int)blockIdx.x;
+    const int bz = box % nb.n[2], bxy = box / nb.n[2], bx = bxy / nb.n[1], by = bxy - bx * nb.n[1];
     auto sample = [&](int& i, int& j, int& k) {
         i = (bx << nb.l[0]) + (lane >> (nb.l[1] + nb.l[2]));
         j = (by << nb.l[1]) + ((lane >> nb.l[2]) & ((1 << nb.l[1]) - 1));
@@ -112,6 +115,8 @@ Boxes box_shape(const GridArgs& ga) {
     return b;
 }
 
+int box_waves(long long boxes) { return boxes <= 256 ? 16 : boxes <= 1024 ? 8 : 4; }
+
 }  // namespace
 
 // By the expected time, on meshes of short loops (at most 8 edges on average: clusters of
@@ -139,7 +144,7 @@ bool want_boxes(const gwn_mesh_s* m, const GridArgs& ga, const FarPlan& p, long 
         side += h * h;
         ext += (m->bbox[3 + a] - m->bbox[a]) * (m->bbox[3 + a] - m->bbox[a]);
     }
-    if (m->nclusters < kFewClusters || !(n * 64.0 <= (double)max_launch_queries())) return false;
+    if (m->nclusters < kFewClusters || !(n < 0x1p31)) return false;
     *boxes = (long long)n;
     if (const char* e = std::getenv("GWN_GRID_BOXES")) return std::atoi(e) != 0;
     if (std::getenv("GWN_GRID_FAR") || std::getenv("GWN_GRID_SAMPLES_PER_LANE") || m->columns_only) return false;
@@ -155,11 +160,37 @@ bool want_boxes(const gwn_mesh_s* m, const GridArgs& ga, const FarPlan& p, long 
 gwn_status launch_boxes(const gwn_mesh_s* m, const GridArgs& ga, long long boxes, const ColCrossings& cc, float* w,
                         int32_t* chi_out, hipStream_t st) {
     const Boxes nb = box_shape(ga);
-    if (boxes <= 256) k_grid_boxes<16><<<(unsigned)boxes, 1024, 0, st>>>(m->view(), ga, nb, cc, chi_out, w);
-    else if (boxes <= 1024) k_grid_boxes<8><<<(unsigned)boxes, 512, 0, st>>>(m->view(), ga, nb, cc, chi_out, w);
-    else k_grid_boxes<4><<<(unsigned)boxes, 256, 0, st>>>(m->view(), ga, nb, cc, chi_out, w);
-    GWN_HIP_TRY(hipGetLastError());
+    const int parts = box_waves(boxes);
+    hipError_t e = hipSuccess;
+    launch_slices(boxes, 64 * parts, [&](int64_t b, int64_t n) {   // 1,021^3 samples: 2^32 work-items and more
+        auto go = [&](auto kernel) { kernel<<<(unsigned)n, 64 * parts, 0, st>>>(m->view(), ga, nb, (int)b, cc, chi_out, w); };
+        if (parts == 16) go(k_grid_boxes<16>);
+        else if (parts == 8) go(k_grid_boxes<8>);
+        else go(k_grid_boxes<4>);
+        if (e == hipSuccess) e = hipGetLastError();
+    });
+    GWN_HIP_TRY(e);
     return GWN_OK;
 }
 
 }  // namespace gwn
+
+extern "C" int64_t gwn_test_boxes(const double* bbox, int64_t nchunk, double chunk_w, int64_t nb, int64_t nloops,
+                                  int64_t nclusters, const double* origin, const double* spacing, const int64_t* dims,
+                                  int64_t* work_items) {
+    gwn_mesh_s m;
+    std::copy(bbox, bbox + 6, m.bbox);
+    m.g = gwn::make_qgrid(bbox);
+    m.nchunk = nchunk;
+    m.chunk_w = chunk_w;
+    m.nb = nb;
+    m.nloops = nloops;
+    m.nclusters = nclusters;
+    const gwn::GridArgs ga = gwn::frame_grid(0, origin, spacing, dims);
+    long long boxes = 0;
+    *work_items = 0;
+    if (!gwn::want_boxes(&m, ga, gwn::far_plan(&m, ga, GWN_PREC_FP32, 1), &boxes)) return 0;
+    const int threads = 64 * gwn::box_waves(boxes);
+    gwn::launch_slices(boxes, threads, [&](int64_t, int64_t n) { *work_items = std::max(*work_items, n * threads); });
+    return boxes;
+}

@@ -6,6 +6,8 @@
 #include <string>
 
 #include "../../include/gwn.h"
+#include <algorithm>
+
 #include "gwn_internal.h"
 
 struct gwn_mesh_s {
@@ -99,6 +101,14 @@ gwn_status query_grid(const gwn_mesh_s* m, const double* origin, const double* s
 // within the 32-bit work-item count); larger batches take several launches.
 // GWN_MAX_LAUNCH_QUERIES (a positive multiple of 256) lowers it, for tests.
 int64_t max_launch_queries();
+
+// f(first, count) for runs of n workgroups (or items) of `threads` work-items each whose
+// launches stay within max_launch_queries().
+template <class F>
+void launch_slices(int64_t n, int threads, F&& f) {
+    const int64_t most = std::max<int64_t>(1, max_launch_queries() / threads);
+    for (int64_t i = 0; i < n; i += most) f(i, std::min(most, n - i));
+}
 
 // Few points share a point's boundary sum among lanes.  FP64 and the gradient (prec -1: the
 // built-in rule only): a workgroup per point in batches of at most 8,192 points on meshes

@@ -260,16 +260,8 @@ bool is_dense(const gwn_multi_s* p, int mesh) {
     return p->nq <= 0x7fffffffll && p->qoff_h[mesh + 1] - p->qoff_h[mesh] >= kDenseQueries;
 }
 
-// f(first, count) for runs of n items, `threads` work-items each, whose launches stay within
-// max_launch_queries(): an item of the crossing kernels takes up to 1,024 work-items, so 2^31
-// queries in items of 128 exceed a launch's 2^32.
+// work-items per item; 2^31 queries in items of 128 at 1,024 each exceed a launch's 2^32
 constexpr int kKeyThreads = 128, kWalkThreads = 64, kPointThreads = kChiParts * 64 * kGridWaves;
-
-template <class F>
-void item_slices(int64_t n, int threads, F&& f) {
-    const int64_t most = std::max<int64_t>(1, max_launch_queries() / threads);
-    for (int64_t i = 0; i < n; i += most) f(i, std::min(most, n - i));
-}
 
 // Work list for a schedule: tiles of item_queries queries, ordered by estimated
 // cost (queries x (boundary edges + a traversal allowance)) or by mesh.
@@ -323,7 +315,7 @@ gwn_status build_perm(gwn_multi_s* p, bool space, bool all, int** perm, hipStrea
     uint64_t *k0 = (uint64_t*)tmp, *k1 = (uint64_t*)(tmp + kb);
     int* i0 = (int*)(tmp + 2 * kb);
     hipError_t e = hipSuccess;
-    item_slices(p->nitems, kKeyThreads, [&](int64_t i, int64_t ni) {
+    launch_slices(p->nitems, kKeyThreads, [&](int64_t i, int64_t ni) {
         k_plan_keys<<<(unsigned)ni, kKeyThreads, 0, st>>>(p->table, p->items + i, (int)((all ? p->nitems : p->ndense) - i), p->qx,
                                                          p->qy, p->qz, p->qs, space, k0, i0);
         if (e == hipSuccess) e = hipGetLastError();
@@ -354,12 +346,12 @@ gwn_status capture(gwn_multi_s* p, const Schedule& s) {
     launched();
     if (p->nq > 0) {
         const int nd = p->ndense, ns = p->nitems - nd;
-        item_slices(nd, kWalkThreads, [&](int64_t i, int64_t n) {
+        launch_slices(nd, kWalkThreads, [&](int64_t i, int64_t n) {
             k_chi_items<<<(unsigned)((n + kGridWaves - 1) / kGridWaves), 64 * kGridWaves, 0, p->cap>>>(
                 p->table, p->items + i, (int)n, p->qx, p->qy, p->qz, p->qs, p->perm, p->chi);
             launched();
         });
-        item_slices(ns, kPointThreads, [&](int64_t i, int64_t n) {
+        launch_slices(ns, kPointThreads, [&](int64_t i, int64_t n) {
             k_chi_items_point<<<(unsigned)n * kChiParts, 64 * kGridWaves, 0, p->cap>>>(
                 p->table, p->items + nd + i, (int)n, p->qx, p->qy, p->qz, p->qs, p->chi);
             launched();
@@ -592,7 +584,7 @@ extern "C" int64_t gwn_test_plan_launches(int64_t nitems, int32_t kernel, int64_
     const int threads = kernel == 0 ? gwn::kKeyThreads : kernel == 1 ? gwn::kWalkThreads : gwn::kPointThreads;
     int64_t launches = 0, next = 0;
     *work_items = 0;
-    gwn::item_slices(nitems, threads, [&](int64_t i, int64_t n) {
+    gwn::launch_slices(nitems, threads, [&](int64_t i, int64_t n) {
         launches += i == next;   // the slices follow each other
         next = i + n;
         *work_items = std::max(*work_items, n * threads);

@@ -20,3 +20,22 @@ def test_plan_kernels(monkeypatch, kernel, limit):
         launches = f(ctypes.c_int64(n), ctypes.c_int32(kernel), ctypes.byref(w))
         assert launches >= 1 and w.value < 1 << 32
         assert limit is None or w.value <= 1024   # one item
+
+
+@pytest.mark.parametrize("n", [64, 645, 646, 1020, 1021, 1024])
+def test_boxes_of_samples(monkeypatch, n):
+    # an unwelded soup of 333,000 triangles: as many loops of three edges
+    d = lambda *x: (ctypes.c_double * len(x))(*x)
+    f = gwn.load().gwn_test_boxes
+    f.restype = ctypes.c_int64
+    w = ctypes.c_int64()
+
+    def boxes():
+        return f(d(0, 0, 0, 1, 1, 1), ctypes.c_int64(167_000), ctypes.c_double(1e6), ctypes.c_int64(999_000),
+                 ctypes.c_int64(333_000), ctypes.c_int64(33_300), d(0, 0, 0), d(1 / n, 1 / n, 1 / n),
+                 (ctypes.c_int64 * 3)(n, n, n), ctypes.byref(w))
+    b = boxes()
+    assert b * 64 >= n ** 3 and w.value < 1 << 32   # in boxes, and every launch is one that can be made
+    if n == 64:
+        monkeypatch.setenv("GWN_MAX_LAUNCH_QUERIES", "1024")
+        assert boxes() == b and w.value <= 1024
