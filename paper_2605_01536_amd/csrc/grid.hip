@@ -30,6 +30,7 @@ namespace {
 // loads, here every load is independent: of the 512^3 grid of the 1.05M-triangle
 // soup 9.2 ms were that walk with 8 exact tests per lane and crossing.  A column of
 // more than kCrossings crossings is left to its wave.
+
 // column indices whose quantised coordinate may lie in [lo, hi] (rising coordinates;
 // slack: rounding of a coordinate, in columns)
 __device__ __forceinline__ void col_range(const GridArgs& ga, const QGrid& g, int axis, double slack, int n, int lo,
@@ -361,10 +362,13 @@ gwn_status launch_grid_zb(const gwn_mesh_s* m, GridArgs ga, const FarView& far, 
 // registers for more resident waves and fill short columns.  Measured (far part on,
 // ms at 1, 2, 4): 512^3 33.8, 25.8, 24.1; 256^3 10.0, 9.1, 9.8; 120 x 97 x 121 3.1, 3.0,
 // 5.2; 160 x 160 x 64 15.8, 21.0, 33.3; FP64 120 x 97 x 121 13.7, 13.7 (4: registers spill).
-// So 4 (FP64: 2) from 8 blocks of 64 samples on, 2 where the blocks fill it, else 1.
+// So 4 (FP64: 2) from 8 blocks of 64 samples on, 2 where the blocks fill it, else 1; with
+// hardly any boundary a wave is all prologue: 160^3 samples of one triangle 57 us at 1.
 // GWN_GRID_SAMPLES_PER_LANE (1, 2, 4 or 8) overrides everything; then the mesh's tuning
 // for the precision (gwn_mesh_set_tuning, gwn_mesh_autotune); larger values take the
 // largest of 4 (FP64: 2).
+constexpr int kFewChunks = 4;
+
 template <class T>
 gwn_status launch_columns(const gwn_mesh_s* m, GridArgs ga, const FarView& far, const ColCrossings& cc, T* w, int32_t* chi_out,
                           hipStream_t st) {
@@ -373,8 +377,9 @@ gwn_status launch_columns(const gwn_mesh_s* m, GridArgs ga, const FarView& far, 
     if (zb == 0) zb = m->grid_zb[sizeof(T) == 8 ? GWN_PREC_FP64 : GWN_PREC_FP32];
     const long long blocks = (ga.nz + 63) / 64;
     if (zb == 0) {
-        if (ga.nx * ga.ny * blocks < kFewWaves) return launch_grid_zb<T, 1, true>(m, ga, far, cc, w, chi_out, st);
+        if (split_columns(ga.nx * ga.ny * blocks, m->nchunk, sizeof(T) == 8)) return launch_grid_zb<T, 1, true>(m, ga, far, cc, w, chi_out, st);
         zb = blocks >= 8 ? 4 : blocks == 2 || blocks >= 4 ? 2 : 1;
+        if (m->nchunk < kFewChunks && blocks == 3) zb = 4;   // the fewest waves
     }
     if constexpr (sizeof(T) == 4)
         if (zb >= 4) return launch_grid_zb<T, 4>(m, ga, far, cc, w, chi_out, st);
@@ -384,9 +389,19 @@ gwn_status launch_columns(const gwn_mesh_s* m, GridArgs ga, const FarView& far, 
 
 // Crossing lists (132 bytes per column, at most 4 GiB) where the columns' x, y rise by
 // steps well above a float's rounding, so that a triangle's columns follow from its
-// box, and z rises, so that a crossing is one number.
+// box, and z rises, so that a crossing is one number; and where they pay.  Lists cost 22 us
+// whatever the grid: an allocation, a clear and a launch.  Without them each column's wave
+// walks the BVH, about 0.1 us log2(triangles)^2 for up to 3,000 waves at once, half as much
+// again on a soup (us, lists / walk: 320 closed triangles 32^3 samples 37 / 14, 100^3 42 / 39,
+// 160^3 83 / 207; 5,120 32^3 36 / 24, 64^3 36 / 35, 100^3 36 / 57; 20,480 48^3 35 / 33, 64^3
+// 35 / 45; four open spheres of 1,329 48^3 38 / 35, 64^3 41 / 46); soups of many chunks of
+// boundary are as many shells, whose walk is longer (770 triangles in 36 chunks 32^3 40 / 59).
 bool want_crossings(const gwn_mesh_s* m, const GridArgs& ga, double* slack) {
     if (m->nf < 1 || ga.nx * ga.ny > (1ll << 25) || !(ga.s[2] > 0.0)) return false;
+    if (m->nchunk < 16) {
+        const double waves = (double)ga.nx * (double)ga.ny * std::ceil((double)ga.nz / 64.0), depth = std::log2((double)m->nf);
+        if ((m->nb > 0 ? 0.16 : 0.1) * depth * depth * std::max(1.0, waves / 3000.0) < 22.0) return false;
+    }
     const long long n[2] = {ga.nx, ga.ny};
     for (int a = 0; a < 2; ++a) {
         const double big = std::max(std::fabs(ga.o[a]), std::fabs(ga.o[a] + (double)n[a] * ga.s[a]));

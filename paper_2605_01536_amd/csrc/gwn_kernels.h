@@ -21,6 +21,7 @@
 // chi and of the boundary sum coincide.
 #pragma once
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -1354,11 +1355,21 @@ __device__ __forceinline__ float grid_coord(double o, double s, long long i) {
     return (float)(o + t);
 }
 
-// Fewer waves than kFewWaves (four per SIMD) take the split form of the column
-// kernels: a workgroup of kSplitWaves waves per column, one sample per lane, each wave
-// a share of the chunks, the partial sums added in a fixed order.
+// Grids of few columns take the split form of the column kernels: a workgroup of
+// kSplitWaves waves per column, one sample per lane, each wave a share of the chunks, the
+// partial sums added in a fixed order.
 constexpr long long kFewWaves = 4096;
 constexpr int kSplitWaves = 8;
+
+// Whether `waves` waves of one sample per lane are few: up to four per SIMD (FP64, whose
+// registers leave room for fewer: two), and fewer where a wave's share of the chunks does not
+// pay for what every wave of the column repeats.  us split / not, with crossing lists: 10
+// chunks 2,115 waves 50 / 38 (FP64 121 / 46); 36 chunks 1,024 waves 40 / 59 (86 / 79), 2,115
+// 58 / 64 (160 / 112); 70 chunks 3,000 waves 71 / 78 (209 / 154); 150 chunks 1,024 waves 71 /
+// 165 (175 / 234), 3,000 156 / 215 (466 / 413).
+inline bool split_columns(long long waves, int64_t nchunk, bool f64) {
+    return waves < std::min<long long>(f64 ? kFewWaves / 2 : kFewWaves, (f64 ? 24 : 64) * nchunk);
+}
 
 // the first wave's NV values per lane plus the other waves', in order
 template <int NV, int W>
