@@ -252,7 +252,10 @@ __device__ __forceinline__ T samp_s(T rho2, T rz) {
 // (dx = dy = 0, so rho = 0 exactly) lies on the ray above it exactly when its
 // s = rho^2 / (l + r_z) is 0 (below it s = 2 |r_z| > 0); s = 0 with r_z = 0 is a
 // vertex at the sample itself, on the surface, where w is undefined.
-template <class T>
+// CALL: FP64's arctangent by a call, see point_wide_call.
+__device__ __attribute__((noinline)) double atan2_call(double y, double x) { return Arith<double>::atan2(y, x); }
+
+template <class T, bool CALL = false>
 __device__ __forceinline__ T edge_slow(const ColV<T>& a, const ColV<T>& b, T sa, T sb, T N, T D, bool exact) {
     if (exact && D <= (T)0) {
         const bool aon = (a.dx == 0) & (a.dy == 0) & (sa == (T)0);
@@ -274,7 +277,8 @@ __device__ __forceinline__ T edge_slow(const ColV<T>& a, const ColV<T>& b, T sa,
             else if (o < 0) N = fabs(N);
         }
     }
-    return Arith<T>::atan2(N, D);
+    if constexpr (CALL && sizeof(T) == 8) return atan2_call(N, D);
+    else return Arith<T>::atan2(N, D);
 }
 
 // One boundary edge for ZB samples given N and D.  Fast path (wave-uniform):
@@ -292,7 +296,7 @@ __device__ __forceinline__ void edge_finish(const ColV<T>& a, const ColV<T>& b, 
         for (int r = 0; r < ZB; ++r) acc[r] += Arith<T>::atan_small(N * Arith<T>::rcp(D[r]));
     } else {
 #pragma unroll
-        for (int r = 0; r < ZB; ++r) acc[r] += edge_slow<T>(a, b, sa[r], sb[r], N, D[r], !FAR);
+        for (int r = 0; r < ZB; ++r) acc[r] += edge_slow<T, FAR>(a, b, sa[r], sb[r], N, D[r], !FAR);
     }
 }
 
@@ -808,8 +812,8 @@ __device__ __forceinline__ PVert<T> point_vertex(const CVert& b, int qqx, int qq
     return v;
 }
 
-// N and D of the edge from entry ba to bb.  Where ba leads nowhere N is 0 and D > 0, no
-// angle.  FP32 forms N from one endpoint's offset and the edge's own x, y (exact integers,
+// N and D of the edge from entry ba to bb.  Where ba leads nowhere N is 0 (FP64: nothing beside
+// D) and D > 0, no angle.  FP32 forms N from one endpoint's offset and the edge's own x, y (exact integers,
 // kept in offset units): from the nearer one (NEARER) its error goes with that distance
 // times the edge's length, see edge_N.  FP64 has the digits for the product of both.
 template <class T, bool NEARER>
@@ -818,24 +822,37 @@ __device__ __forceinline__ T point_N(const CVert& ba, const PVert<T>& a, const P
         const bool nb = NEARER && !(a.rho2 <= b.rho2);
         return fma(nb ? b.ry : a.ry, ba.ex, -((nb ? b.rx : a.rx) * ba.ey));
     } else {
-        const T N = fma(a.ry, b.rx, -(a.rx * b.ry));
-        return (ba.flags & kChainEdge) ? N : (T)0;
+        return fma(a.ry, b.rx, -(a.rx * b.ry));   // without an edge b is a: below 2^8, against D's 2^200
     }
 }
 
 template <class T>
 __device__ __forceinline__ T point_D(const CVert& ba, const PVert<T>& a, const PVert<T>& b) {
-    const T k = sizeof(T) == 4 ? (T)ba.none : (ba.flags & kChainEdge) ? (T)0 : (T)0x1p63;
+    const T k = sizeof(T) == 4 ? (T)ba.none : (ba.flags & kChainEdge) ? (T)0 : (T)0x1p200;
     return fma(a.s, b.s, fma(a.rx, b.rx, fma(a.ry, b.ry, k)));
 }
 
-// an edge of any angle
+// the edge from entry b[0] to b[1], of any angle
 template <class T>
-__device__ T point_wide(const CVert& ba, const CVert& bb, int qqx, int qqy, T pz) {
+__device__ __forceinline__ T point_wide_edge(const CVert* b, int qqx, int qqy, T pz) {
 #pragma clang fp contract(off)
-    const PVert<T> a = point_vertex<T>(ba, qqx, qqy, pz), b = point_vertex<T>(bb, qqx, qqy, pz);
-    return edge_slow<T>({a.dx, a.dy, a.rx, a.ry, a.rho2}, {b.dx, b.dy, b.rx, b.ry, b.rho2}, a.s, b.s,
-                        point_N<T, true>(ba, a, b), point_D<T>(ba, a, b), true);
+    const PVert<T> a = point_vertex<T>(b[0], qqx, qqy, pz), c = point_vertex<T>(b[1], qqx, qqy, pz);
+    return edge_slow<T>({a.dx, a.dy, a.rx, a.ry, a.rho2}, {c.dx, c.dy, c.rx, c.ry, c.rho2}, a.s, c.s,
+                        point_N<T, true>(b[0], a, c), point_D<T>(b[0], a, c), true);
+}
+
+// In FP64 by a call: with the library's arctangent inline a point per lane takes 162 registers,
+// three waves per SIMD, without it 115, four (1.1 M points on a loop of 2,002 edges 4.43 ->
+// 4.33 ms, 530 k on 1,026 short-looped edges 2.25 -> 2.21; in plans 173 and 127, 800 k queries on
+// 100 such soups 3.42 -> 3.07 ms).
+__device__ __attribute__((noinline)) double point_wide_call(const CVert* b, int qqx, int qqy, double pz) {
+    return point_wide_edge<double>(b, qqx, qqy, pz);
+}
+
+template <class T>
+__device__ __forceinline__ T point_wide(const CVert* b, int qqx, int qqy, T pz) {
+    if constexpr (sizeof(T) == 8) return point_wide_call(b, qqx, qqy, pz);
+    else return point_wide_edge<T>(b, qqx, qqy, pz);
 }
 
 // acc + the angles of n (2, 3 or 4) consecutive edges v[0] -> ... -> v[n].  By one
@@ -939,7 +956,7 @@ __device__ __forceinline__ T point_chunk(const CVert* __restrict__ chunk, int qq
     while (odd) {
         const int e = __ffs(odd) - 1;
         odd &= odd - 1u;
-        acc += point_wide<T>(chunk[e], chunk[e + 1], qqx, qqy, pz);
+        acc += point_wide<T>(chunk + e, qqx, qqy, pz);
     }
     return acc;
 }

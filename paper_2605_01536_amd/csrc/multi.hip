@@ -117,7 +117,7 @@ __global__ void k_plan_keys(const MeshView* __restrict__ table, const Item* __re
 // 3.2 M queries on 48 soups; claims of 64 queries instead of 128 shorten the last wave's
 // way (a wave's way through the largest soup takes 2.5 ms).
 template <class T>
-__global__ __launch_bounds__(256) void k_bdry_persistent(const MeshView* __restrict__ table,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 4 : 1))) void k_bdry_persistent(const MeshView* __restrict__ table,
                                                         const Item* __restrict__ items, int nitems, int claims,
                                                         int* __restrict__ counter, const float* __restrict__ qx,
                                                         const float* __restrict__ qy, const float* __restrict__ qz,
