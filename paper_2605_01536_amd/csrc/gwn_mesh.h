@@ -126,6 +126,14 @@ bool want_split(const gwn_mesh_s* m, int64_t n, int prec);
 
 constexpr int64_t kDensePoints = 48 << 10, kSinglePoints = 6144, kSharedPoints = 1 << 20, kGroupEdges = 512;
 
+// A point per lane, with four waves to share 64 points' sums.  FP64, ms shared / not (and at
+// first, edge by edge): 63 k edges 16 k points 4.3 / 15.3 (14.5), 66 k 11.7 / 18.9 (20.7), 131 k
+// 17.3 / 19.5; 2,002 edges in a loop 66 k 0.45 / 0.63 (0.61), 131 k 0.65 / 0.64; 61 edges 66 k
+// 0.159 / 0.173 (0.167), 140 k 0.178 / 0.189 (0.184).
+bool want_parts(const gwn_mesh_s* m, int64_t n, int prec);
+
+constexpr int64_t kSharedPoints64 = 96 << 10;
+
 // Crossing counts of few points take a wave per point: a lane's walk is a chain of loads,
 // 65 us for 1,000 points on 1,280 triangles and 238 us on 85 k (9 and 30 with a wave each),
 // until there are points enough to hide it: 33 k points on 85 k triangles 0.68 ms with the

@@ -97,14 +97,15 @@ __global__ __launch_bounds__(kChiBlock) void k_chi_line(MeshView mv, const float
 
 // ---------------------------------------------------------------- boundary, batch
 
-// PARTS > 1 (FP32): that many waves share 64 points, each with a part of the clusters, the
-// sums added in LDS.
+// PARTS > 1: that many waves share 64 points, in FP32 each with a part of the clusters, the
+// sums added in LDS; in FP64 in turn with a chunk each, whose sums the first wave adds in the
+// chunks' order, so that the bits are those of a lane alone.
 template <class T, int PARTS>
 __global__ __launch_bounds__(256) void k_bdry_batch(MeshView mv, const float* __restrict__ qx, const float* __restrict__ qy,
                                                     const float* __restrict__ qz, long long qs, long long nq,
                                                     const int* __restrict__ perm, const int* __restrict__ chi,
                                                     T* __restrict__ w) {
-    static_assert(PARTS == 1 || (PARTS == 4 && sizeof(T) == 4), "a workgroup of four waves");
+    static_assert(PARTS == 1 || PARTS == 4, "a workgroup of four waves");
     const int wave = PARTS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const long long j = (long long)blockIdx.x * (256 / PARTS) + (PARTS == 1 ? threadIdx.x : threadIdx.x & 63);
     const long long jj = j < nq ? j : nq - 1;
@@ -116,7 +117,22 @@ __global__ __launch_bounds__(256) void k_bdry_batch(MeshView mv, const float* __
     const QPoint q = quantize_point(px, py, pz, mv.g);
     const int unit = sizeof(T) == 4 ? point_unit(px, py, pz, q.inbox, mv.g) : 0;
     double S = 0.0;
-    if (!q.inbox) {   // rare: raw offsets, edge by edge
+    if constexpr (sizeof(T) == 8 && PARTS > 1) {
+        __shared__ double part[2][PARTS][64];
+        const int lane = threadIdx.x & 63;
+        const T pzs = (T)pz * (T)mv.g.scale;
+        const bool quads = quad_z(pz, mv.g);
+        PVert<T> last;
+        for (int c0 = 0, b = 0; c0 < mv.nchunk; c0 += PARTS, b ^= 1) {
+            if (q.inbox && c0 + wave < mv.nchunk)
+                part[b][wave][lane] = point_chunk<T, true>(mv.chain + (size_t)(c0 + wave) * kChunk, q.x, q.y, pzs, quads, last, false);
+            __syncthreads();   // one a step: the other half is written meanwhile
+            if (wave == 0 && q.inbox)
+                for (int v = 0; v < min(PARTS, mv.nchunk - c0); ++v) S += part[b][v][lane];
+        }
+        if (wave > 0) return;
+        if (!q.inbox) outside_sum<T>(mv, px, py, pz, 0, 1, unit, S);
+    } else if (!q.inbox) {   // rare: raw offsets, edge by edge
         outside_sum<T>(mv, px, py, pz, wave, PARTS, unit, S);
     } else if constexpr (sizeof(T) == 4) {
         const float sc = mv.g.scalef;
@@ -124,7 +140,7 @@ __global__ __launch_bounds__(256) void k_bdry_batch(MeshView mv, const float* __
     } else {
         point_chunks<T, true>(mv, 0, mv.nchunk, 1, q.x, q.y, (T)pz * (T)mv.g.scale, quad_z(pz, mv.g), unit, S);
     }
-    if constexpr (PARTS > 1) {
+    if constexpr (PARTS > 1 && sizeof(T) == 4) {
         __shared__ double part[PARTS][64];
         const int lane = threadIdx.x & 63;
         part[wave][lane] = S;
@@ -247,13 +263,9 @@ gwn_status launch_batch(const gwn_mesh_s* m, const float* qx, const float* qy, c
         }
         if (e == hipSuccess && !closed) {
             if (!few) {
-                bool parts = false;
-                if constexpr (sizeof(T) == 4) {
-                    parts = n <= kSharedPoints && m->nclusters > 1;
-                    if (parts)
-                        k_bdry_batch<float, 4><<<(unsigned)((n + 63) / 64), 256, 0, st>>>(mv, x, y, z, qs, n, perm, chi + o,
-                                                                                          w + o);
-                }
+                const bool parts = want_parts(m, n, kPrec);
+                if (parts)
+                    k_bdry_batch<T, 4><<<(unsigned)((n + 63) / 64), 256, 0, st>>>(mv, x, y, z, qs, n, perm, chi + o, w + o);
                 if (!parts)
                     k_bdry_batch<T, 1><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(mv, x, y, z, qs, n, perm, chi + o, w + o);
             } else if constexpr (sizeof(T) == 4) {
@@ -317,6 +329,11 @@ bool want_split(const gwn_mesh_s* m, int64_t n, int prec) {
     if (prec >= 0 && prec < 2 && m->split_max[prec] != 0) return m->split_max[prec] > 0 && n <= m->split_max[prec] && m->nb > 0;
     if (prec == GWN_PREC_FP32) return n < kDensePoints && m->nb >= (n <= 16384 ? 64 : kGroupEdges);
     return n <= 8192 && m->nb >= 16 * 256;
+}
+
+bool want_parts(const gwn_mesh_s* m, int64_t n, int prec) {
+    if (prec == GWN_PREC_FP64) return n <= (m->nchunk < 64 ? 4 * kSharedPoints64 : kSharedPoints64) && m->nchunk >= 8;
+    return n <= kSharedPoints && m->nclusters > 1;
 }
 
 int64_t max_launch_queries() {
