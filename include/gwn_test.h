@@ -19,8 +19,9 @@
  * and last sample.  Returns the count of numbers, -1 if cap is too small.
  *
  * gwn_test_plan_launches(nitems, kernel, work_items): how many launches a plan of
- * nitems work items makes of its key (0), ordered crossing (1) or unordered
- * crossing (2) kernel, and in *work_items the largest one's (host code only).
+ * nitems work items makes of its kernels for the keys of its orders (0), the
+ * crossings of ordered queries (1), of others by a wave each (2) or by a lane each in
+ * items of 512 (3), and in *work_items the largest one's (host code only).
  *
  * gwn_test_boxes(...): the number of boxes of samples in which an FP32 grid call
  * would be summed (0: in columns) for such a mesh of nb boundary edges in nloops

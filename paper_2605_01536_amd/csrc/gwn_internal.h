@@ -83,6 +83,10 @@ constexpr int kFanBits = 3, kFan = 1 << kFanBits, kRoots = 64, kLevels = 12;
 // points: 0.44 ms with the expansions).
 constexpr int kFewClusters = 16;
 
+// Of these, meshes of fewer chunks have edges that look wide from most of their points; their
+// FP32 sums are formed by a lane per point always.
+constexpr int kWideChunks = 64;
+
 constexpr int kPoles = 10, kPolesMid = 6, kPolesLow = 4;       // degrees of the expansions
 constexpr int kMoments = (kPoles + 1) * (kPoles + 1) - 1;    // real coefficients, degree 1 up (l^2 - 1: degree l's first)
 

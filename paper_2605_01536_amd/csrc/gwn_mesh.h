@@ -44,6 +44,8 @@ struct gwn_mesh_s {
     bool columns_only = false;     // grids in columns while the tuner times them
     int tuned = 0;                 // bit p: precision p was tuned
 
+    bool wide_edges() const { return nclusters < gwn::kFewClusters && nchunk < gwn::kWideChunks; }
+
     gwn::MeshView view() const {
         gwn::MeshView v;
         v.nodes = nodes;

@@ -7,8 +7,8 @@
 // order, resident waves) is chosen by timing candidates (autotune) and can be
 // cached in a JSON-lines file keyed by device and problem size.  Meshes with
 // many queries take them 64 neighbours to a wave, in orders (index
-// permutations) made once at creation from the query values then; the others a
-// few queries per wave as they come.
+// permutations) made once at creation from the query values then; the others as
+// they come, a few queries per wave or a query per lane (see plan_forms).
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -91,6 +91,26 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_chi_items_point(const MeshV
     }
 }
 
+// the same for queries in no order, a lane per query (chi_up): a workgroup of one wave per 64
+// queries, `claims` of them per item
+__global__ __launch_bounds__(kChiBlock) void k_chi_items_lane(const MeshView* __restrict__ table,
+                                                             const Item* __restrict__ items, int claims,
+                                                             const float* __restrict__ qx,
+                                                             const float* __restrict__ qy,
+                                                             const float* __restrict__ qz, long long qs,
+                                                             int* __restrict__ chi) {
+    __shared__ int stk[kLdsStack * kChiBlock];
+    const Item I = items[blockIdx.x / claims];
+    const int k = (int)(blockIdx.x % claims) * kChiBlock + threadIdx.x;
+    if (k >= I.nq) return;
+    const MeshView mv = table[I.mesh];
+    const float *x = qx, *y = qy, *z = qz;
+    axis_ptrs(mv.axis, x, y, z);   // the mesh's frame
+    const long long i = I.q0 + k;
+    const QPoint q = quantize_point(x[i * qs], y[i * qs], z[i * qs], mv.g);
+    chi[i] = q.inbox ? chi_up(mv, q, stk + threadIdx.x) : 0;
+}
+
 // sort keys of all queries: the mesh, then (items [0, nkeyed)) the query's place in the order
 __global__ void k_plan_keys(const MeshView* __restrict__ table, const Item* __restrict__ items, int nkeyed,
                             const float* __restrict__ qx, const float* __restrict__ qy, const float* __restrict__ qz,
@@ -108,49 +128,54 @@ __global__ void k_plan_keys(const MeshView* __restrict__ table, const Item* __re
     }
 }
 
-// Persistent boundary-term kernel: every wave claims 64 queries of an item at a time, one
-// per lane, until none are left (the counter only grows, so every wave reaches the exit).
-// perm (nullable): position i of the work list is query perm[i], a permutation within each
-// mesh.  T is the geometry precision; per query the sums have the batch kernels' terms, so
+// Persistent boundary-term kernel: every wave claims a share of an item at a time, `claims` to
+// an item, and takes its queries 64 at once, one per lane, until none are left (the counter
+// only grows, so every wave reaches the exit).
+// perm (nullable): in items [0, nperm) position i of the work list is query perm[i], a
+// permutation within each mesh.  T is the geometry precision; per query the sums have the batch kernels' terms, so
 // the results are the same bits.
 // The mesh's data are read by scalar loads (see uniform_load): 7.2 ms instead of 10.3 for
 // 3.2 M queries on 48 soups; claims of 64 queries instead of 128 shorten the last wave's
-// way (a wave's way through the largest soup takes 2.5 ms).
-template <class T>
+// way (a wave's way through the largest soup takes 2.5 ms).  Where queries take little, the
+// claims themselves do, some 12 ns each at their one address: there a claim is an item (ITEM; 1 M
+// queries on soups of a triangle 301 us at 64 queries a claim, 208 at 128).
+template <class T, bool ITEM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 4 : 1))) void k_bdry_persistent(const MeshView* __restrict__ table,
                                                         const Item* __restrict__ items, int nitems, int claims,
                                                         int* __restrict__ counter, const float* __restrict__ qx,
                                                         const float* __restrict__ qy, const float* __restrict__ qz,
-                                                        long long qs, const int* __restrict__ perm,
+                                                        long long qs, const int* __restrict__ perm, int nperm,
                                                         const int* __restrict__ chi, T* __restrict__ w) {
     const int lane = threadIdx.x & 63;
     while (true) {
         int t = 0;
         if (lane == 0) t = atomicAdd(counter, 1);
         t = __builtin_amdgcn_readfirstlane(__shfl(t, 0));
-        const int it = t / claims, sub = (t - it * claims) * 64;
+        const int it = ITEM ? t : t / claims, first = ITEM ? 0 : (t - it * claims) * 64;
         if (it >= nitems) break;
         const Item I = uniform_load(items + it);
-        if (sub >= I.nq) continue;
+        if (first >= I.nq) continue;
         const MeshView mv = uniform_load(table + I.mesh);
         const float *x = qx, *y = qy, *z = qz;
         axis_ptrs(mv.axis, x, y, z);   // the mesh's frame
-        const int k = sub + lane;
-        const long long i0 = I.q0 + min(k, I.nq - 1);
-        const long long i = perm ? (long long)perm[i0] : i0;
-        const float px = x[i * qs], py = y[i * qs], pz = z[i * qs];
-        const QPoint q = quantize_point(px, py, pz, mv.g);
-        const int unit = sizeof(T) == 4 ? point_unit(px, py, pz, q.inbox, mv.g) : 0;
-        double S = 0.0;
-        if (!q.inbox) {
-            outside_sum<T>(mv, px, py, pz, 0, 1, unit, S);
-        } else if constexpr (sizeof(T) == 4) {
-            const float sc = mv.g.scalef;
-            S = point_clusters(mv, {q.x, q.y, px * sc, py * sc, pz * sc, quad_z(pz, mv.g), unit}, 0, 1);
-        } else {
-            point_chunks<T, true>(mv, 0, mv.nchunk, 1, q.x, q.y, (T)pz * (T)mv.g.scale, quad_z(pz, mv.g), unit, S);
+        for (int sub = first; sub < (ITEM ? I.nq : first + 1); sub += 64) {
+            const int k = sub + lane;
+            const long long i0 = I.q0 + min(k, I.nq - 1);
+            const long long i = perm && it < nperm ? (long long)perm[i0] : i0;
+            const float px = x[i * qs], py = y[i * qs], pz = z[i * qs];
+            const QPoint q = quantize_point(px, py, pz, mv.g);
+            const int unit = sizeof(T) == 4 ? point_unit(px, py, pz, q.inbox, mv.g) : 0;
+            double S = 0.0;
+            if (!q.inbox) {
+                outside_sum<T>(mv, px, py, pz, 0, 1, unit, S);
+            } else if constexpr (sizeof(T) == 4) {
+                const float sc = mv.g.scalef;
+                S = point_clusters(mv, {q.x, q.y, px * sc, py * sc, pz * sc, quad_z(pz, mv.g), unit}, 0, 1);
+            } else {
+                point_chunks<T, true>(mv, 0, mv.nchunk, 1, q.x, q.y, (T)pz * (T)mv.g.scale, quad_z(pz, mv.g), unit, S);
+            }
+            if (k < I.nq) w[i] = (T)((double)chi[i] + point_total<T>(S, unit) * kInv2Pi);
         }
-        if (k < I.nq) w[i] = (T)((double)chi[i] + point_total<T>(S, unit) * kInv2Pi);
     }
 }
 
@@ -184,9 +209,18 @@ __global__ __launch_bounds__(256) void k_group_persistent(const MeshView* __rest
     }
 }
 
-// 48 soups of 0.5 to 11 k edges, queries per soup on average, ms in order against in groups:
-// 67 k 5.9 / 19.6, 34 k 4.4 / 10.0, 17 k 4.2 / 5.1, 8 k 4.0 / 2.7, 4 k 3.6 / 1.5.
+// Meshes of at least this many queries take them in orders.  48 soups of 0.5 to 11 k edges,
+// queries per soup on average, ms in order against in groups: 67 k 5.9 / 19.6, 34 k 4.4 / 10.0,
+// 17 k 4.2 / 5.1, 8 k 4.0 / 2.7, 4 k 3.6 / 1.5.
 constexpr long long kDenseQueries = 16384;
+
+// How a mesh's queries are taken, in the order of the items' ranges: crossings by a walk that a
+// wave's queries take together, in order or not, by a lane or by a wave per query; FP32 sums by a
+// lane per query, ordered or not, or in groups.
+enum { kChiOrdered, kChiTogether, kChiLane, kChiPoint, kSumOrdered = 0, kSumLane, kSumGroup };
+struct Form {
+    int chi, sum;
+};
 
 struct Schedule {
     int item_queries = 128;   // multiple of 64
@@ -216,13 +250,16 @@ struct gwn_multi_s {
     int* chi = nullptr;
     bool own_chi = false;
     gwn::MeshView* table = nullptr;
-    gwn::Item* items = nullptr;
+    std::vector<gwn::Form> forms;   // per mesh
+    // the work items twice: by the form of their crossings, and of their sums; and where each
+    // form's items end
+    gwn::Item *citems = nullptr, *items = nullptr;
     int nitems = 0;
-    int ndense = 0;        // of them, in front: those of meshes with many queries (see is_dense)
+    int cend[4] = {}, send[3] = {};
     // each mesh's queries in an order: Morton order of x and y (for the crossing walk, and what a
     // schedule asks for), and a space-filling curve's (FP32 boundary term)
     int *perm = nullptr, *sperm = nullptr;
-    int sorted = 0;           // perm holds: 0 nothing, 1 the dense meshes' queries, 2 all
+    int sorted = 0;           // perm holds: 0 nothing, 1 the ordered meshes' queries, 2 all
     int* counter = nullptr;   // two
     int grid = 0;
     hipStream_t cap = nullptr;
@@ -245,6 +282,7 @@ void release(gwn_multi_s* p) {
     drop_graph(p);
     if (p->cap) (void)hipStreamDestroy(p->cap);
     (void)hipFree(p->table);
+    (void)hipFree(p->citems);
     (void)hipFree(p->items);
     (void)hipFree(p->perm);
     (void)hipFree(p->sperm);
@@ -253,15 +291,46 @@ void release(gwn_multi_s* p) {
     delete p;
 }
 
-// Meshes with at least kDenseQueries queries take them in order, 64 neighbours to a wave: for
-// the crossing walk, and in FP32 for the boundary term's clusters.  The others' queries lie
-// too far apart for that: a wave per query and groups of queries.
-bool is_dense(const gwn_multi_s* p, int mesh) {
-    return p->nq <= 0x7fffffffll && p->qoff_h[mesh + 1] - p->qoff_h[mesh] >= kDenseQueries;
+// The forms by expected time.
+//
+// Meshes with at least kDenseQueries queries take them in order, 64 neighbours to a wave, for
+// the crossing walk and the boundary term; with fewer than 64 triangles or 32 boundary edges
+// there is less to share than reading through the order costs (64 x 20,000 queries on a
+// triangle 231 us, in order 377; on 320 closed triangles 479 in order, 990 without, 1,107 if the
+// queries are not those that the order was made from).
+//
+// The others' queries lie too far apart for an order.  Crossings by a wave per query until
+// there are queries enough to hide a lane's walk (want_chi_point, over all such meshes: they
+// run side by side).  FP32 sums in groups of queries, 0.13 ns sqrt(edges) a query; by a lane per
+// query 1.2 ps an edge and query, where the plan has work for the 0.07 us per edge that a
+// lane takes (us, groups / lanes: 100 x 8,000 queries on 1,026 edges 3,880 / 2,000 in all, 64 x
+// 8,000 on a loop of 2,002 edges 2,630 / 1,400, 256 x 4,000 on 216 edges 2,370 / 1,250).
+std::vector<Form> plan_forms(const std::vector<gwn_mesh_s*>& meshes, const std::vector<long long>& off) {
+    const int n = (int)meshes.size();
+    const bool order = off[n] <= 0x7fffffffll;   // the permutations hold 32-bit indices
+    auto queries = [&](int m) { return off[m + 1] - off[m]; };
+    auto lane = [&](int m) { return 1.2e-12 * (double)meshes[m]->nb; };
+    auto group = [&](int m) { return 0.13e-9 * std::sqrt((double)meshes[m]->nb); };
+    std::vector<Form> f(n);
+    long long loose = 0;    // queries that a lane or a wave walks for
+    double total = 3e-5;    // seconds of the plan's sums
+    for (int m = 0; m < n; ++m) {
+        const bool dense = order && queries(m) >= kDenseQueries;
+        f[m].chi = meshes[m]->nf < 64 ? kChiTogether : dense ? kChiOrdered : kChiLane;
+        f[m].sum = dense && meshes[m]->nb >= 32 ? kSumOrdered : kSumLane;
+        if (f[m].chi == kChiLane) loose += queries(m);
+        total += (double)queries(m) * std::min(lane(m), group(m));
+    }
+    for (int m = 0; m < n; ++m) {
+        if (f[m].chi == kChiLane && want_chi_point(meshes[m], loose)) f[m].chi = kChiPoint;
+        if (f[m].sum == kSumLane && !meshes[m]->wide_edges() && !(lane(m) < group(m) && 0.07e-6 * (double)meshes[m]->nb < total))
+            f[m].sum = kSumGroup;
+    }
+    return f;
 }
 
 // work-items per item; 2^31 queries in items of 128 at 1,024 each exceed a launch's 2^32
-constexpr int kKeyThreads = 128, kWalkThreads = 64, kPointThreads = kChiParts * 64 * kGridWaves;
+constexpr int kKeyThreads = 128, kWalkThreads = 64, kPointThreads = kChiParts * 64 * kGridWaves;   // (a lane per query: its queries)
 
 // Work list for a schedule: tiles of item_queries queries, ordered by estimated
 // cost (queries x (boundary edges + a traversal allowance)) or by mesh.
@@ -288,22 +357,36 @@ gwn_status build_items(gwn_multi_s* p, const Schedule& s, hipStream_t st) {
         for (size_t i = 0; i < idx.size(); ++i) s2[i] = h[idx[i]];
         h.swap(s2);
     }
-    p->ndense = (int)(std::stable_partition(h.begin(), h.end(), [&](const Item& i) { return is_dense(p, i.mesh); }) - h.begin());
     (void)hipFree(p->items);
-    p->items = nullptr;
+    (void)hipFree(p->citems);
+    p->items = p->citems = nullptr;
     p->nitems = (int)h.size();
-    GWN_HIP_TRY(gwn::dmalloc((void**)&p->items, sizeof(Item) * std::max<size_t>(1, h.size())));
-    if (!h.empty())
+    std::vector<Item> c(h);
+    auto by_form = [&](std::vector<Item>& v, int Form::*which, int n, int* end) {
+        auto it = v.begin();
+        for (int k = 0; k < n; ++k) {
+            it = std::stable_partition(it, v.end(), [&](const Item& i) { return p->forms[i.mesh].*which == k; });
+            end[k] = (int)(it - v.begin());
+        }
+    };
+    by_form(h, &Form::sum, 3, p->send);
+    by_form(c, &Form::chi, 4, p->cend);
+    const size_t bytes = sizeof(Item) * std::max<size_t>(1, h.size());
+    GWN_HIP_TRY(gwn::dmalloc((void**)&p->items, bytes));
+    GWN_HIP_TRY(gwn::dmalloc((void**)&p->citems, bytes));
+    if (!h.empty()) {
         GWN_HIP_TRY(hipMemcpyAsync(p->items, h.data(), sizeof(Item) * h.size(), hipMemcpyHostToDevice, st));
+        GWN_HIP_TRY(hipMemcpyAsync(p->citems, c.data(), sizeof(Item) * c.size(), hipMemcpyHostToDevice, st));
+    }
     GWN_HIP_TRY(hipStreamSynchronize(st));
     return GWN_OK;
 }
 
 // Each mesh's queries in Morton order of their quantised x, y in the mesh's frame, or along
 // the space-filling curve (the batch path's traversal orders), as one permutation of all
-// queries; all: not only of the dense meshes.  One sort for all meshes: with a sort each, 48
-// meshes of 67 k queries took 10 ms per order.
-gwn_status build_perm(gwn_multi_s* p, bool space, bool all, int** perm, hipStream_t st) {
+// queries; keyed: the first items that take an order, the others' queries stay as they are.
+// One sort for all meshes: with a sort each, 48 meshes of 67 k queries took 10 ms per order.
+gwn_status build_perm(gwn_multi_s* p, bool space, const Item* items, int keyed, int** perm, hipStream_t st) {
     const int64_t n = p->nq;
     if (n <= 0) return GWN_OK;
     if (!*perm) GWN_HIP_TRY(gwn::dmalloc((void**)perm, sizeof(int) * (size_t)n));
@@ -316,8 +399,8 @@ gwn_status build_perm(gwn_multi_s* p, bool space, bool all, int** perm, hipStrea
     int* i0 = (int*)(tmp + 2 * kb);
     hipError_t e = hipSuccess;
     launch_slices(p->nitems, kKeyThreads, [&](int64_t i, int64_t ni) {
-        k_plan_keys<<<(unsigned)ni, kKeyThreads, 0, st>>>(p->table, p->items + i, (int)((all ? p->nitems : p->ndense) - i), p->qx,
-                                                         p->qy, p->qz, p->qs, space, k0, i0);
+        k_plan_keys<<<(unsigned)ni, kKeyThreads, 0, st>>>(p->table, items + i, (int)(keyed - i), p->qx, p->qy, p->qz, p->qs,
+                                                         space, k0, i0);
         if (e == hipSuccess) e = hipGetLastError();
     });
     if (e == hipSuccess) e = radix_sort_u64(k0, k1, i0, *perm, n, 0, bits, tmp + 2 * kb + ib, st);
@@ -334,8 +417,19 @@ gwn_status capture(gwn_multi_s* p, const Schedule& s) {
     GWN_HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, p->device));
     const long long waves = (long long)ncu * 4 * s.waves_per_simd;
     const int claims = (s.item_queries + kPlanClaim - 1) / kPlanClaim, lanes = (s.item_queries + 63) / 64;
-    const long long need = (p->ndense < p->nitems && p->prec != GWN_PREC_FP64 ? (long long)p->nitems * claims : (long long)p->nitems * lanes) / 4 + 1;   // no more waves than claims
-    p->grid = (int)std::max<long long>(1, std::min<long long>(waves / 4, std::max<long long>(need, 1)));
+    const bool f32 = p->prec != GWN_PREC_FP64;
+    const int nlane = f32 ? p->send[kSumLane] : p->nitems, ngroup = p->nitems - nlane;
+    double edges = 0.0, queries = 0.0;   // of the lanes' items
+    for (int m = 0; m < p->nmesh; ++m)
+        if (!f32 || p->forms[m].sum != kSumGroup) {
+            queries += (double)(p->qoff_h[m + 1] - p->qoff_h[m]);
+            edges += (double)(p->qoff_h[m + 1] - p->qoff_h[m]) * (double)p->meshes[m]->nb;
+        }
+    // claims per item
+    const int sums = edges < 256.0 * queries && (long long)nlane * lanes > waves ? 1 : lanes;
+    // no more waves than claims
+    const long long need = std::max((long long)nlane * sums, (long long)ngroup * claims) / 4 + 1;
+    p->grid = (int)std::max<long long>(1, std::min<long long>(waves / 4, need));
     GWN_HIP_TRY(hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal));
     hipError_t le = hipSuccess;   // of the first launch that was refused
     auto launched = [&] {
@@ -345,34 +439,45 @@ gwn_status capture(gwn_multi_s* p, const Schedule& s) {
     k_reset_counter<<<1, 64, 0, p->cap>>>(p->counter);
     launched();
     if (p->nq > 0) {
-        const int nd = p->ndense, ns = p->nitems - nd;
-        launch_slices(nd, kWalkThreads, [&](int64_t i, int64_t n) {
-            k_chi_items<<<(unsigned)((n + kGridWaves - 1) / kGridWaves), 64 * kGridWaves, 0, p->cap>>>(
-                p->table, p->items + i, (int)n, p->qx, p->qy, p->qz, p->qs, p->perm, p->chi);
-            launched();
-        });
-        launch_slices(ns, kPointThreads, [&](int64_t i, int64_t n) {
-            k_chi_items_point<<<(unsigned)n * kChiParts, 64 * kGridWaves, 0, p->cap>>>(
-                p->table, p->items + nd + i, (int)n, p->qx, p->qy, p->qz, p->qs, p->chi);
-            launched();
-        });
-        if (p->prec == GWN_PREC_FP64) {
-            k_bdry_persistent<double><<<p->grid, 256, 0, p->cap>>>(
-                p->table, p->items, p->nitems, lanes, p->counter, p->qx, p->qy, p->qz, p->qs,
-                (s.order & kOrderSorted) ? p->perm : nullptr, p->chi, (double*)p->w);
-            launched();
-        } else {
-            if (nd > 0) {
-                k_bdry_persistent<float><<<p->grid, 256, 0, p->cap>>>(p->table, p->items, nd, lanes, p->counter, p->qx, p->qy,
-                                                                      p->qz, p->qs, p->sperm, p->chi, (float*)p->w);
+        const int* c = p->cend;
+        auto walk = [&](int first, int end, const int* perm) {
+            launch_slices(end - first, kWalkThreads, [&](int64_t i, int64_t n) {
+                k_chi_items<<<(unsigned)((n + kGridWaves - 1) / kGridWaves), 64 * kGridWaves, 0, p->cap>>>(
+                    p->table, p->citems + first + i, (int)n, p->qx, p->qy, p->qz, p->qs, perm, p->chi);
                 launched();
-            }
-            if (ns > 0) {
+            });
+        };
+        walk(0, c[kChiOrdered], p->perm);
+        walk(c[kChiOrdered], c[kChiTogether], nullptr);
+        launch_slices(c[kChiLane] - c[kChiTogether], lanes * kChiBlock, [&](int64_t i, int64_t n) {
+            k_chi_items_lane<<<(unsigned)(n * lanes), kChiBlock, 0, p->cap>>>(p->table, p->citems + c[kChiTogether] + i, lanes,
+                                                                              p->qx, p->qy, p->qz, p->qs, p->chi);
+            launched();
+        });
+        launch_slices(p->nitems - c[kChiLane], kPointThreads, [&](int64_t i, int64_t n) {
+            k_chi_items_point<<<(unsigned)n * kChiParts, 64 * kGridWaves, 0, p->cap>>>(
+                p->table, p->citems + c[kChiLane] + i, (int)n, p->qx, p->qy, p->qz, p->qs, p->chi);
+            launched();
+        });
+        auto lanes_sum = [&](auto kernel, auto* w, int n, const int* perm, int nperm) {
+            kernel<<<p->grid, 256, 0, p->cap>>>(p->table, p->items, n, sums, p->counter, p->qx, p->qy, p->qz, p->qs, perm, nperm,
+                                                p->chi, w);
+            launched();
+        };
+        if (!f32) {
+            const int* perm = (s.order & kOrderSorted) ? p->perm : nullptr;
+            if (sums == 1) lanes_sum(k_bdry_persistent<double, true>, (double*)p->w, p->nitems, perm, p->nitems);
+            else lanes_sum(k_bdry_persistent<double, false>, (double*)p->w, p->nitems, perm, p->nitems);
+        } else {
+            const int nperm = p->send[kSumOrdered];
+            if (nlane > 0 && sums == 1) lanes_sum(k_bdry_persistent<float, true>, (float*)p->w, nlane, p->sperm, nperm);
+            else if (nlane > 0) lanes_sum(k_bdry_persistent<float, false>, (float*)p->w, nlane, p->sperm, nperm);
+            if (ngroup > 0) {
                 int top = 0;
                 for (const gwn_mesh_s* m : p->meshes) top = std::max(top, m->cluster_top);
                 const size_t ints = point_stack_ints<kPlanGroup>(top);
                 k_group_persistent<<<p->grid, 256, 4 * ints * sizeof(int), p->cap>>>(
-                    p->table, p->items + nd, ns, claims, p->counter + 1, p->qx, p->qy, p->qz, p->qs, nullptr, (int)ints,
+                    p->table, p->items + nlane, ngroup, claims, p->counter + 1, p->qx, p->qy, p->qz, p->qs, nullptr, (int)ints,
                     p->chi, (float*)p->w);
                 launched();
             }
@@ -390,9 +495,11 @@ gwn_status apply(gwn_multi_s* p, Schedule s, hipStream_t st) {
     gwn_status r = build_items(p, s, st);
     if (r != GWN_OK) return r;
     const bool all = (s.order & kOrderSorted) != 0;
-    if ((all && p->sorted < 2) || (p->ndense > 0 && p->sorted < 1)) {
-        r = build_perm(p, false, all, &p->perm, st);
-        if (r == GWN_OK && p->prec != GWN_PREC_FP64 && p->ndense > 0 && !p->sperm) r = build_perm(p, true, false, &p->sperm, st);
+    const bool walk = p->cend[kChiOrdered] > 0, sums = p->prec != GWN_PREC_FP64 && p->send[kSumOrdered] > 0;
+    if (all ? p->sorted < 2 : (walk || sums) && p->sorted < 1) {
+        r = GWN_OK;
+        if (all || walk) r = build_perm(p, false, p->citems, all ? p->nitems : p->cend[kChiOrdered], &p->perm, st);
+        if (r == GWN_OK && sums && !p->sperm) r = build_perm(p, true, p->items, p->send[kSumOrdered], &p->sperm, st);
         if (r != GWN_OK) return r;
         p->sorted = all ? 2 : 1;
     }
@@ -492,6 +599,7 @@ gwn_status multi_create(const gwn_mesh* meshes, int nmesh, const float* qx, cons
         GWN_HIP_TRY(gwn::dmalloc((void**)&p->chi, sizeof(int) * (size_t)std::max<long long>(1, p->nq)));
         p->own_chi = true;
     }
+    p->forms = plan_forms(p->meshes, p->qoff_h);
     std::vector<MeshView> tab(nmesh);
     for (int m = 0; m < nmesh; ++m) tab[m] = p->meshes[m]->view();
     GWN_HIP_TRY(gwn::dmalloc((void**)&p->table, sizeof(MeshView) * (size_t)nmesh));
@@ -581,7 +689,7 @@ void multi_info(const gwn_multi_s* p, gwn_multi_info* o) {
 }  // namespace gwn
 
 extern "C" int64_t gwn_test_plan_launches(int64_t nitems, int32_t kernel, int64_t* work_items) {
-    const int threads = kernel == 0 ? gwn::kKeyThreads : kernel == 1 ? gwn::kWalkThreads : gwn::kPointThreads;
+    const int threads = kernel == 0 ? gwn::kKeyThreads : kernel == 1 ? gwn::kWalkThreads : kernel == 2 ? gwn::kPointThreads : 512;
     int64_t launches = 0, next = 0;
     *work_items = 0;
     gwn::launch_slices(nitems, threads, [&](int64_t i, int64_t n) {

@@ -7,7 +7,7 @@ import pytest
 from paper_2605_01536_amd import gwn
 
 
-@pytest.mark.parametrize("kernel", [0, 1, 2])
+@pytest.mark.parametrize("kernel", [0, 1, 2, 3])
 @pytest.mark.parametrize("limit", [None, "256"])
 def test_plan_kernels(monkeypatch, kernel, limit):
     if limit:
