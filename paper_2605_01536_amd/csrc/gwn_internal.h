@@ -83,8 +83,8 @@ constexpr int kFanBits = 3, kFan = 1 << kFanBits, kRoots = 64, kLevels = 12;
 // points: 0.44 ms with the expansions).
 constexpr int kFewClusters = 16;
 
-// Of these, meshes of fewer chunks have edges that look wide from most of their points; their
-// FP32 sums are formed by a lane per point always.
+// Of these, meshes of fewer chunks have edges that look wide from most of their points: the FP32
+// sums of their chunks have a form of their own (WIDE, see point_run), by a lane per point always.
 constexpr int kWideChunks = 64;
 
 constexpr int kPoles = 10, kPolesMid = 6, kPolesLow = 4;       // degrees of the expansions

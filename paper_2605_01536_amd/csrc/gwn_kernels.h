@@ -861,7 +861,12 @@ __device__ __forceinline__ T point_wide(const CVert* b, int qqx, int qqy, T pz) 
 // sum's tangent is below tan(pi/8) (up to three angles below pi/2 are it themselves; of four,
 // the first two must be below pi/2 together).  Else each by its own where |N| < kFast D; the
 // others are left out and set their bits in odd.
-template <class T, int n>
+// WIDE (FP32, meshes of few chunks): half of the runs have a lane in their wave for which that
+// does not do, and both forms are executed.  N from the nearer endpoint serves any D, and the
+// product's full-range arctangent any sum: with each pair below pi/2 the four are below pi.
+// 1.1 M points on 216 edges: 435 VALU instructions per chunk -> 369, 375 us -> 310 with the
+// rest of the call; on longer boundaries the nearer endpoint costs 4% and gains nothing.
+template <class T, int n, bool WIDE>
 __device__ __forceinline__ T point_run(const CVert* b, const PVert<T>* v, bool quads, T acc, unsigned& odd) {
 #pragma clang fp contract(off)
     using P = EdgePairs<T, 1, false>;
@@ -869,32 +874,43 @@ __device__ __forceinline__ T point_run(const CVert* b, const PVert<T>* v, bool q
     bool ok = quads;
 #pragma unroll
     for (int i = 0; i < n; ++i) {
-        N[i] = point_N<T, false>(b[i], v[i], v[i + 1]);
+        N[i] = point_N<T, WIDE>(b[i], v[i], v[i + 1]);
         D[i] = point_D<T>(b[i], v[i], v[i + 1]);
-        ok &= D[i] > (sizeof(T) == 4 ? (T)b[i].m : (T)1);
+        ok &= D[i] > (WIDE ? (T)P::kQuadDot : sizeof(T) == 4 ? (T)b[i].m : (T)1);
     }
     T gr = fma(D[0], D[1], -(N[0] * N[1])), gi = fma(D[0], N[1], D[1] * N[0]);
     if constexpr (n > 2) {
         T r2 = D[2], i2 = N[2];
         if constexpr (n == 4) {
-            ok &= gr > (T)0;
             r2 = fma(D[2], D[3], -(N[2] * N[3]));
             i2 = fma(D[2], N[3], D[3] * N[2]);
+            if constexpr (WIDE) ok &= r2 > (T)0;
         }
+        if constexpr (n == 4 || WIDE) ok &= gr > (T)0;
         const T re = gr;
         gr = fma(re, r2, -(gi * i2));
         gi = fma(re, i2, gi * r2);
     }
-    ok &= fabs(gi) < (T)P::kTan8 * gr;
+    if constexpr (!WIDE) ok &= fabs(gi) < (T)P::kTan8 * gr;
     odd = 0u;
-    if (ok) return pair_acc<T>({gr, gi}, acc);
+    if (ok) {
+        if constexpr (WIDE) return acc + atan2_full(gi, gr);
+        else return pair_acc<T>({gr, gi}, acc);
+    }
 #pragma unroll
     for (int i = 0; i < n; ++i) {
-        const T Ni = point_N<T, true>(b[i], v[i], v[i + 1]);
-        const bool fast = fabs(Ni) < Arith<T>::kFast * D[i];
-        const T t = Arith<T>::atan_small(Ni * Arith<T>::rcp(D[i]));
-        acc += fast ? t : (T)0;
-        odd |= fast ? 0u : 1u << i;
+        T t;
+        bool own;
+        if constexpr (WIDE) {
+            own = D[i] > (T)0;
+            t = atan2_full(N[i], D[i]);
+        } else {
+            const T Ni = point_N<T, true>(b[i], v[i], v[i + 1]);
+            own = fabs(Ni) < Arith<T>::kFast * D[i];
+            t = Arith<T>::atan_small(Ni * Arith<T>::rcp(D[i]));
+        }
+        acc += own ? t : (T)0;
+        odd |= own ? 0u : 1u << i;
     }
     return acc;
 }
@@ -907,7 +923,7 @@ struct Chunk {
     CVert v[kChunk];
 };
 
-template <class T, bool UNIFORM>
+template <class T, bool UNIFORM, bool WIDE = false>
 __device__ __forceinline__ T point_chunk(const CVert* __restrict__ chunk, int qqx, int qqy, T pz, bool quads,
                                          PVert<T>& last, bool cont) {
     const CVert* b = chunk;
@@ -927,12 +943,12 @@ __device__ __forceinline__ T point_chunk(const CVert* __restrict__ chunk, int qq
     if (!(b[4].flags & kChainEdge)) {
         if (b[3].flags & kChainEdge) {
             v[4] = b[4].flags & kChainClose ? v[0] : vertex(4);
-            acc = point_run<T, 4>(b, v, quads, acc, odd);
+            acc = point_run<T, 4, WIDE>(b, v, quads, acc, odd);
         } else {
-            acc = point_run<T, 3>(b, v, quads, acc, odd);
+            acc = point_run<T, 3, WIDE>(b, v, quads, acc, odd);
         }
     } else {
-        acc = point_run<T, 3>(b, v, quads, acc, odd);
+        acc = point_run<T, 3, WIDE>(b, v, quads, acc, odd);
         v[4] = vertex(4);
         v[5] = b[5].flags & kChainClose ? v[0] : vertex(5);
         if ((b[5].flags | b[6].flags) & kChainEdge) {
@@ -943,13 +959,13 @@ __device__ __forceinline__ T point_chunk(const CVert* __restrict__ chunk, int qq
             else v[7] = v[0];
             last = v[7];
             if (b[3].flags & kChainEdge) {
-                acc = point_run<T, 4>(b + 3, v + 3, quads, acc, odd1);
+                acc = point_run<T, 4, WIDE>(b + 3, v + 3, quads, acc, odd1);
             } else {   // two halves
-                acc = point_run<T, 3>(b + 4, v + 4, quads, acc, odd1);
+                acc = point_run<T, 3, WIDE>(b + 4, v + 4, quads, acc, odd1);
                 odd1 <<= 1;
             }
         } else {
-            acc = point_run<T, 2>(b + 3, v + 3, quads, acc, odd1);
+            acc = point_run<T, 2, WIDE>(b + 3, v + 3, quads, acc, odd1);
         }
         odd |= odd1 << 3;
     }
@@ -988,12 +1004,12 @@ __device__ __forceinline__ int point_unit(float px, float py, float pz, bool inb
 }
 
 // the sum over chunks c0, c0 + step, ..., < c1.  pz: the point's z in offset units
-template <class T, bool UNIFORM>
+template <class T, bool UNIFORM, bool WIDE = false>
 __device__ __forceinline__ void point_chunks(const MeshView& mv, int c0, int c1, int step, int qqx, int qqy, T pz,
                                              bool quads, int unit, double& S) {
     PVert<T> last = {};
     for (int c = c0; c < c1; c += step)
-        point_add<T>(S, point_chunk<T, UNIFORM>(mv.chain + (size_t)c * kChunk, qqx, qqy, pz, quads,
+        point_add<T>(S, point_chunk<T, UNIFORM, WIDE>(mv.chain + (size_t)c * kChunk, qqx, qqy, pz, quads,
                                                 last, UNIFORM && step == 1 && c > c0), unit);
 }
 
@@ -1098,7 +1114,10 @@ struct PointPos {
 __device__ __forceinline__ double point_clusters(const MeshView& mv, const PointPos& p, int part, int parts) {
     double S = 0.0;
     if (mv.nclusters < kFewClusters) {
-        point_chunks<float, true>(mv, part, mv.nchunk, parts, p.qx, p.qy, p.z * 0x1p-18f, p.quads, p.unit, S);
+        if (mv.nchunk < kWideChunks)
+            point_chunks<float, true, true>(mv, part, mv.nchunk, parts, p.qx, p.qy, p.z * 0x1p-18f, p.quads, p.unit, S);
+        else
+            point_chunks<float, true>(mv, part, mv.nchunk, parts, p.qx, p.qy, p.z * 0x1p-18f, p.quads, p.unit, S);
         return S;
     }
     int L = mv.top, i = part, skip = 0;
@@ -1135,6 +1154,7 @@ __device__ __forceinline__ double point_clusters(const MeshView& mv, const Point
     return S;
 }
 
+// (Meshes of at least kWideChunks chunks or kFewClusters clusters: see point_run's WIDE.)
 // G points per wave: the lanes share out (cluster, point) pairs to be tested, far pairs
 // and (chunk, point) pairs of near clusters, each kind from a list in LDS, 64 at a time.
 // For few points, or points so far apart that those of a wave of one point per lane would

@@ -44,6 +44,7 @@ struct gwn_mesh_s {
     bool columns_only = false;     // grids in columns while the tuner times them
     int tuned = 0;                 // bit p: precision p was tuned
 
+    // FP32 point sums in point_run's WIDE form
     bool wide_edges() const { return nclusters < gwn::kFewClusters && nchunk < gwn::kWideChunks; }
 
     gwn::MeshView view() const {
@@ -131,7 +132,9 @@ constexpr int64_t kDensePoints = 48 << 10, kSinglePoints = 6144, kSharedPoints =
 // A point per lane, with four waves to share 64 points' sums.  FP64, ms shared / not (and at
 // first, edge by edge): 63 k edges 16 k points 4.3 / 15.3 (14.5), 66 k 11.7 / 18.9 (20.7), 131 k
 // 17.3 / 19.5; 2,002 edges in a loop 66 k 0.45 / 0.63 (0.61), 131 k 0.65 / 0.64; 61 edges 66 k
-// 0.159 / 0.173 (0.167), 140 k 0.178 / 0.189 (0.184).
+// 0.159 / 0.173 (0.167), 140 k 0.178 / 0.189 (0.184).  FP32, where few chunks to share are not
+// worth the waves' own work: a loop of 2,002 edges 131 k 0.28 / 0.36 (0.32), 216 edges 131 k
+// 0.158 / 0.175, 530 k 0.51 / 0.51, 61 edges 530 k 0.408 / 0.406.
 bool want_parts(const gwn_mesh_s* m, int64_t n, int prec);
 
 constexpr int64_t kSharedPoints64 = 96 << 10;

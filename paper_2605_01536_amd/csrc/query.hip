@@ -252,7 +252,7 @@ gwn_status launch_batch(const gwn_mesh_s* m, const float* qx, const float* qy, c
             }
             e = hipGetLastError();
         }
-        const bool few = want_split(m, n, kPrec);
+        const bool few = want_split(m, n, kPrec) && !(sizeof(T) == 4 && m->wide_edges());
         if (so == GWN_OK && e == hipSuccess && !closed && !few && want_space_order(m, n, kPrec)) {
             drop();
             so = order(true);
@@ -333,7 +333,7 @@ bool want_split(const gwn_mesh_s* m, int64_t n, int prec) {
 
 bool want_parts(const gwn_mesh_s* m, int64_t n, int prec) {
     if (prec == GWN_PREC_FP64) return n <= (m->nchunk < 64 ? 4 * kSharedPoints64 : kSharedPoints64) && m->nchunk >= 8;
-    return n <= kSharedPoints && m->nclusters > 1;
+    return n <= (m->nclusters < kFewClusters ? 1 << 18 : kSharedPoints) && m->nchunk >= 8;
 }
 
 int64_t max_launch_queries() {
