@@ -133,9 +133,11 @@ gwn_status gwn_mesh_destroy(gwn_mesh m);
  * changes), and the grid kernel's samples per lane (per precision; w's last
  * bits).  Crossing counts never change.  A field of 0 takes the built-in rule
  * (split: FP32 fewer than 49,152 points on meshes with at least 512 boundary
- * edges, up to 16,384 points 64 edges, FP64 at most 8,192 points and at least 4,096 edges; order: at least
+ * edges, up to 16,384 points 64 edges, never where those are in fewer than 16 clusters and 64
+ * chunks; FP64 at most 8,192 points and at least 4,096 edges; order: at least
  * 2^18 points on meshes of at least 2^15 triangles for the crossing walk, 16,384
- * points and 10^8 pairs of a point and an edge for the boundary sum; samples: 4 (FP64: 2) on columns of
+ * points and 10^8 pairs of a point and an edge (below 2,048 edges 2.2 10^8) for the boundary
+ * sum; samples: 4 (FP64: 2) on columns of
  * 8 blocks of 64 samples or more, 2 where the blocks fill it, else 1; larger values take the
  * largest of those; FP32 grids of few samples against a ragged boundary that are summed in boxes
  * of samples have no columns), -1 never (split, order).  The environment variables

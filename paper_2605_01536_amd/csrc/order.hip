@@ -39,12 +39,14 @@ bool want_xy_order(const gwn_mesh_s* m, int64_t n) {
 // The boundary sum with clusters, a point per lane: a wave's lanes should see the same
 // clusters as near, or it sums nearly every cluster's chunks (85 k triangles with 63 k
 // edges, 8 k points in no order 11.9 ms, 33 k in order 2.7).  The sort is about 25 launches
-// (0.1 ms); on few clusters there is nothing to skip.
+// (0.1 ms); on few clusters there is nothing to skip, and on few edges little (us in order /
+// not: 131 k points on 1,026 edges 529 / 468, on 1,272 404 / 384, 262 k 766 / 797 and 583 / 681;
+// 33 k on 3,073 edges 514 / 527, on 7,827 700 / 872).
 bool want_space_order(const gwn_mesh_s* m, int64_t n, int prec) {
     if (prec == GWN_PREC_FP64 || m->nclusters < 16 || n < 2) return false;
     if (const char* e = std::getenv("GWN_ORDER_QUERIES")) return std::atoi(e) != 0;
     if (m->order_min != 0) return m->order_min > 0 && n >= m->order_min;
-    return n >= 16384 && (double)n * (double)m->nb >= 1e8;
+    return n >= 16384 && (double)n * (double)m->nb >= (m->nb < 2048 ? 2.2e8 : 1e8);
 }
 
 size_t xy_order_temp_bytes(int64_t n) {
