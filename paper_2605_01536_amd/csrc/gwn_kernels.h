@@ -1192,10 +1192,12 @@ __device__ __forceinline__ int nth_bit(unsigned m, int k) {
     return __ffs(m) - 1;
 }
 
-// sums of the points ls.p[g] with a bit in mask, in their units: of point lane % G
+// sums of the points ls.p[g] with a bit in mask, in their units: of point lane % G.
+// parts > 1 (G = 1): that many waves walk the clusters alike and share out what they find,
+// far clusters and near chunks; the part-th share.
 template <int G>
 __device__ __forceinline__ double point_group(const MeshView& mv, unsigned mask, int* stack, int stack_ints,
-                                              PointLists<G>& ls) {
+                                              PointLists<G>& ls, int part = 0, int parts = 1) {
     constexpr int kEntries = 64 / G;
     constexpr unsigned kAll = (1u << G) - 1u;
     const int lane = threadIdx.x & 63, pt = lane % G, en = lane / G;
@@ -1208,7 +1210,7 @@ __device__ __forceinline__ double point_group(const MeshView& mv, unsigned mask,
     };
     if (lane < G) ls.S[lane] = 0.0;
     const int root = uniform_load(mv.level + mv.top);
-    int n = uniform_load(mv.level + mv.top + 1) - root, nleaf = 0, nfar[3] = {0, 0, 0};
+    int n = uniform_load(mv.level + mv.top + 1) - root, nleaf = 0, nfar[3] = {0, 0, 0}, turn = 0;
     if (lane < n) {
         stack[lane] = root + lane;
         if (G > 1) smask[lane] = (int)mask;
@@ -1221,7 +1223,8 @@ __device__ __forceinline__ double point_group(const MeshView& mv, unsigned mask,
             if (nfar[f] < 64 && (n > 0 || nfar[f] == 0)) continue;
             const int m = min(nfar[f], 64);
             nfar[f] -= m;
-            if (lane < m) {
+            const bool ours = turn++ % parts == part;
+            if (lane < m && ours) {
                 const int id = ls.far[f][nfar[f] + lane], g = G == 1 ? 0 : ls.far_pt[f][nfar[f] + lane];
                 const PointPos p = G == 1 ? mine : ls.p[g];
                 const Cluster& k = mv.clusters[id];
@@ -1255,7 +1258,7 @@ __device__ __forceinline__ double point_group(const MeshView& mv, unsigned mask,
             ls.sum[lane] = t;
             const int total = __shfl(t, 63), before = t - cn;
             wave_lds_sync();
-            for (int j0 = 0; j0 < total; j0 += 64) {
+            for (int j0 = 64 * part; j0 < total; j0 += 64 * parts) {
                 const int j = min(j0 + lane, total - 1);
                 int a = 0;   // the first range whose sum exceeds j
                 for (int h = 32; h > 0; h >>= 1)

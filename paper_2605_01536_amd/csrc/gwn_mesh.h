@@ -127,7 +127,7 @@ void launch_slices(int64_t n, int threads, F&& f) {
 // GWN_SPLIT_BOUNDARY=0/1 overrides.
 bool want_split(const gwn_mesh_s* m, int64_t n, int prec);
 
-constexpr int64_t kDensePoints = 48 << 10, kSinglePoints = 6144, kSharedPoints = 1 << 20, kGroupEdges = 512;
+constexpr int64_t kFewPoints = 256, kDensePoints = 48 << 10, kSinglePoints = 6144, kSharedPoints = 1 << 20, kGroupEdges = 512;
 
 // A point per lane, with four waves to share 64 points' sums.  FP64, ms shared / not (and at
 // first, edge by edge): 63 k edges 16 k points 4.3 / 15.3 (14.5), 66 k 11.7 / 18.9 (20.7), 131 k
