@@ -1175,9 +1175,15 @@ struct PointLists {
 // or before it, so a level has at most kFan * 64 / G entries, less 64 / G while it has
 // descendants on the stack.
 template <int G>
-inline size_t point_stack_ints(int top) {
+constexpr size_t point_stack_ints(int top) {
     return (G == 1 ? 1 : 2) * (kRoots + (size_t)(kFan - 1) * (64 / G) * top + 64);
 }
+
+// The highest level for which four waves' lists and stacks fit the 64 KB of LDS that a launch
+// may ask for: with a point per wave 470 million edges are too many, groups of four always fit.
+constexpr int kSingleTop = 6;
+static_assert(4 * sizeof(PointLists<1>) + 16 * point_stack_ints<1>(kSingleTop) <= 65000, "a point per wave");
+static_assert(4 * sizeof(PointLists<4>) + 16 * point_stack_ints<4>(kLevels - 1) <= 65000, "groups");
 
 __device__ __forceinline__ int lane_rank(unsigned long long m) {
     return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));

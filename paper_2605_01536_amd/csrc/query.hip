@@ -310,11 +310,12 @@ gwn_status launch_batch(const gwn_mesh_s* m, const float* qx, const float* qy, c
                                        kPointWaves * ints * sizeof(int), st>>>(mv, x, y, z, qs, n, perm, (int)ints,
                                                                                chi + o, w + o);
                 };
-                if (n <= kFewPoints) {
+                const bool single = m->cluster_top <= kSingleTop;
+                if (n <= kFewPoints && single) {
                     const size_t ints = point_stack_ints<1>(m->cluster_top);
                     k_bdry_point<<<(unsigned)n, 64 * kPointWaves, kPointWaves * ints * sizeof(int), st>>>(
                         mv, x, y, z, qs, (int)ints, chi + o, w + o);
-                } else if (n <= kSinglePoints) go(std::integral_constant<int, 1>{});
+                } else if (n <= kSinglePoints && single) go(std::integral_constant<int, 1>{});
                 else go(std::integral_constant<int, 4>{});
             } else {
                 k_bdry_split<<<(unsigned)n, kSplitThreads, 0, st>>>(mv, x, y, z, qs, n, chi + o, w + o);
