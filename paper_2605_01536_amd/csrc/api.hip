@@ -68,11 +68,7 @@ void release(gwn_mesh_s* m) {
     (void)hipFree(m->trif);
     (void)hipFree(m->bverts);
     (void)hipFree(m->loop_off);
-    (void)hipFree(m->chain);
-    (void)hipFree(m->cbox);
-    (void)hipFree(m->gchain);
-    (void)hipFree(m->clusters);
-    (void)hipFree(m->moments);
+    (void)hipFree(m->chain);   // the boundary's other arrays follow it
     delete m;
 }
 

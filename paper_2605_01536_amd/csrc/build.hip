@@ -43,18 +43,24 @@ struct Scratch {
         if (!blocks.empty()) (void)hipStreamSynchronize(st);
         for (void* p : blocks) (void)hipFree(p);
     }
+    hipError_t block(size_t want) {
+        void* q = nullptr;
+        const hipError_t e = gwn::dmalloc(&q, want);
+        if (e != hipSuccess) return e;
+        blocks.push_back(q);
+        cur = (char*)q;
+        left = want;
+        return hipSuccess;
+    }
+    // one block for slices of `bytes` in all, if they do not fit the current one
+    hipError_t reserve(size_t bytes) { return bytes > left ? block(bytes) : hipSuccess; }
     template <class T>
     hipError_t alloc(T** p, int64_t n) {
         *p = nullptr;
         const size_t bytes = (sizeof(T) * (size_t)std::max<int64_t>(n, 1) + 255) & ~(size_t)255;
         if (bytes > left) {
-            const size_t want = std::max(bytes, blocks.empty() ? first : first / 8);
-            void* q = nullptr;
-            const hipError_t e = gwn::dmalloc(&q, want);
+            const hipError_t e = block(std::max(bytes, blocks.empty() ? first : first / 8));
             if (e != hipSuccess) return e;
-            blocks.push_back(q);
-            cur = (char*)q;
-            left = want;
         }
         *p = (T*)cur;
         cur += bytes;
@@ -356,13 +362,15 @@ __global__ void k_link(const int* __restrict__ in_by_to, const int* __restrict__
     if (k < n) succ[in_by_to[k]] = out_by_from[k];
 }
 
+// Pointer doubling, twice per launch: of 85 k edges 17 rounds of two launches each are 0.2 ms
+// of launches, whatever the loops' lengths.
 __global__ void k_rep_round(const int* __restrict__ rep, const int* __restrict__ jmp, int64_t n, int* __restrict__ rep2,
                             int* __restrict__ jmp2) {
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= n) return;
-    int j = jmp[i];
-    rep2[i] = min(rep[i], rep[j]);
-    jmp2[i] = jmp[j];
+    const int j = jmp[i], k = jmp[j], l = jmp[k];
+    rep2[i] = min(min(rep[i], rep[j]), min(rep[k], rep[l]));
+    jmp2[i] = jmp[l];
 }
 
 __global__ void k_rank_init(const int* __restrict__ succ, const int* __restrict__ rep, int64_t n, int* __restrict__ nxt,
@@ -378,14 +386,13 @@ __global__ void k_rank_round(const int* __restrict__ nxt, const int* __restrict_
                              int* __restrict__ dist2) {
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= n) return;
-    int j = nxt[i];
-    if (j < 0) {
-        nxt2[i] = -1;
-        dist2[i] = dist[i];
-    } else {
-        nxt2[i] = nxt[j];
-        dist2[i] = dist[i] + dist[j];
+    int j = nxt[i], d = dist[i];
+    for (int k = 0; k < 3 && j >= 0; ++k) {
+        d += dist[j];
+        j = nxt[j];
     }
+    nxt2[i] = j;
+    dist2[i] = d;
 }
 
 // Representatives, ranks and both scans for few edges in one workgroup, in LDS: the rounds
@@ -895,21 +902,38 @@ __host__ __device__ constexpr int pole_slot(int l, int m, int part) {
     return l * l - 1 + (m == 0 ? 0 : 2 * m - 1 + part);
 }
 
-// squared distances from which the truncation bound holds for each degree; never: none
+// The distances that are tried, in radii: from 2 up by 2% to a million.
+constexpr int kReaches = 664;
+struct ReachTable {
+    double d[kReaches];
+    constexpr ReachTable() : d() {
+        d[0] = 2.0;
+        for (int i = 1; i < kReaches; ++i) d[i] = d[i - 1] * 1.02;
+    }
+};
+constexpr ReachTable kReach;
+static_assert(kReach.d[kReaches - 2] < 1e6 && kReach.d[kReaches - 1] >= 1e6, "the last distance is the first of a million");
+
+// squared distances from which the truncation bound holds for each degree; never: none.  The
+// bound falls with the distance: bisected (tried in turn, 150 to 300 of 60 FP64 operations
+// each, this took 20 us of a cluster's 45).
 __device__ void cluster_reach(double radius, double area, bool never, float* far2) {
     const double rel = area / (radius * radius);
     const int degree[3] = {kPoles, kPolesMid, kPolesLow};
     const double bound[3] = {kPoleBound[0], kPoleBound[1], kPoleBound[2]};
-    double d = 2.0;   // in radii, from 2 up
+    int lo = 0;   // the least that is left to try
     for (int i = 0; i < 3; ++i) {
         const int P = degree[i];
-        while (d < 1e6) {
-            const double t = 1.0 / d;
+        int hi = kReaches - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            const double t = 1.0 / kReach.d[mid];
             double b = 0.5 * rel * (P + 1) / ((1.0 - t) * (1.0 - t));
             for (int k = 0; k < P + 2; ++k) b *= t;
-            if (b <= bound[i]) break;
-            d *= 1.02;
+            if (b <= bound[i]) hi = mid;
+            else lo = mid + 1;
         }
+        const double d = kReach.d[lo];
         far2[i] = never ? INFINITY : (float)fmin(d * radius * d * radius, 1e38);
     }
 }
@@ -931,13 +955,34 @@ __global__ __launch_bounds__(64) void k_cluster_frames(const BVert* __restrict__
     const int c = blockIdx.x, lane = threadIdx.x;
     if (c == 0 && lane <= kLevels) reinterpret_cast<int*>(out + levels.first[kLevels])[lane] = levels.first[lane];
     const int r0 = p.first[c], r1 = c + 1 < p.n ? p.first[c + 1] : (int)p.nl;
+    // an overlong loop's moments would keep one workgroup busy too long: never far, and no frame
+    // either (a million edges: two passes of 16,000 steps of one wave)
+    if (count[c] > kHugeCluster || p.n < kFewClusters) {
+        if (lane > 0) return;
+        const BVert v = bv[loop_off[order[r0]]];
+        Cluster k{};
+        k.x = v.x;
+        k.y = v.y;
+        k.z = k.ztop = k.zlow = v.z;
+        k.inva = 1.0f;
+        k.far2[0] = k.far2[1] = k.far2[2] = INFINITY;
+        k.xlo = k.xhi = v.qx;
+        k.ylo = k.yhi = v.qy;
+        k.first = p.base[c];
+        k.count = -count[c];
+        out[c] = k;
+        return;
+    }
+    // a wave per loop, or of short loops one per lane
+    const bool shorts = p.off[2 * p.nl + r1] - p.off[2 * p.nl + r0] <= 8 * (r1 - r0);
+    const int rl = shorts ? lane : 0, rstep = shorts ? 64 : 1, jl = shorts ? 0 : lane, jstep = shorts ? 1 : 64;
     float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
     int qlo[2] = {0x7fffffff, 0x7fffffff}, qhi[2] = {-1, -1};
     double area = 0.0;
-    for (int r = r0; r < r1; ++r) {
+    for (int r = r0 + rl; r < r1; r += rstep) {
         const int b0 = loop_off[order[r]], b1 = loop_off[order[r] + 1];
         const BVert o = bv[b0];
-        for (int j = b0 + lane; j < b1; j += 64) {
+        for (int j = b0 + jl; j < b1; j += jstep) {
             const BVert v = bv[j], w = bv[j + 1 < b1 ? j + 1 : b0];
             const float q[3] = {v.x, v.y, v.z};
             for (int a = 0; a < 3; ++a) {
@@ -967,9 +1012,9 @@ __global__ __launch_bounds__(64) void k_cluster_frames(const BVert* __restrict__
     area = wave_sum(area);
     const float cx = 0.5f * lo[0] + 0.5f * hi[0], cy = 0.5f * lo[1] + 0.5f * hi[1], cz = 0.5f * lo[2] + 0.5f * hi[2];
     double rad2 = 0.0;
-    for (int r = r0; r < r1; ++r) {
+    for (int r = r0 + rl; r < r1; r += rstep) {
         const int b0 = loop_off[order[r]], b1 = loop_off[order[r] + 1];
-        for (int j = b0 + lane; j < b1; j += 64) {
+        for (int j = b0 + jl; j < b1; j += jstep) {
             const double x = (double)bv[j].x - cx, y = (double)bv[j].y - cy, z = (double)bv[j].z - cz;
             rad2 = fmax(rad2, x * x + y * y + z * z);
         }
@@ -991,8 +1036,7 @@ __global__ __launch_bounds__(64) void k_cluster_frames(const BVert* __restrict__
     k.first = p.base[c];
     k.count = -count[c];
     k.area = (float)area;
-    // an overlong loop's moments would keep one workgroup busy too long: never far
-    cluster_reach(radius, area, count[c] > kHugeCluster || p.n < kFewClusters, k.far2);
+    cluster_reach(radius, area, false, k.far2);
     out[c] = k;
 }
 
@@ -1601,6 +1645,11 @@ gwn_status build_mesh(const float* vx, const float* vy, const float* vz, int64_t
                 *out_by_from = nullptr, *succ = nullptr;
             int *repA = nullptr, *repB = nullptr, *jA = nullptr, *jB = nullptr, *dA = nullptr, *dB = nullptr;
             int *len = nullptr, *head = nullptr, *voff = nullptr, *lid = nullptr;
+            // the boundary's temporaries: 17 numbers per edge and (at most nb / 2 loops) 18 per loop,
+            // the sorts' and scans'; of an unwelded soup as much as the triangles' (85 k of them: nine
+            // blocks of an eighth, a third of 3.2 ms)
+            GWN_HIP_TRY(S.reserve((size_t)nb * 4 * (17 + 9) + 2 * sort_temp_bytes(nb, 4, true) + sort_temp_bytes(nb / 2 + 1, 4, true) +
+                                  4 * scan_temp_bytes(2 * nb) + 64 * 256));
             for (int** p : {&efrom, &eto, &ids, &kk, &in_by_to, &out_by_from, &succ, &repA, &repB, &jA, &jB, &dA, &dB,
                             &len, &head, &voff, &lid})
                 GWN_HIP_TRY(S.alloc(p, nb));
@@ -1626,7 +1675,7 @@ gwn_status build_mesh(const float* vx, const float* vy, const float* vz, int64_t
                 // cycle representative = smallest edge id on the cycle (pointer jumping)
                 GWN_HIP_TRY(hipMemcpyAsync(jA, succ, sizeof(int) * nb, hipMemcpyDeviceToDevice, st));
                 k_iota<<<nblocks(nb), kThreads, 0, st>>>(repA, nb);
-                const int rounds = bits_for(nb) + 1;
+                const int rounds = (bits_for(nb) + 2) / 2;   // of two doublings
                 for (int r = 0; r < rounds; ++r) {
                     k_rep_round<<<nblocks(nb), kThreads, 0, st>>>(repA, jA, nb, repB, jB);
                     std::swap(repA, repB);
@@ -1722,9 +1771,6 @@ gwn_status build_mesh(const float* vx, const float* vy, const float* vz, int64_t
             m->nchunk = hchunks;
             m->nclusters = hclusters;
             const size_t nent = kChunk * (size_t)m->nchunk;
-            GWN_HIP_TRY(gwn::dmalloc((void**)&m->chain, sizeof(CVert) * nent));
-            GWN_HIP_TRY(gwn::dmalloc((void**)&m->gchain, sizeof(GVertex) * nent));
-            GWN_HIP_TRY(gwn::dmalloc((void**)&m->cbox, sizeof(int4) * (size_t)m->nchunk));
             // levels: kFan clusters of one make one of the next, until at most kRoots are left
             int nlev = 0, total = 0;
             for (int c = hclusters;; c = (c + kFan - 1) / kFan) {
@@ -1736,9 +1782,19 @@ gwn_status build_mesh(const float* vx, const float* vy, const float* vz, int64_t
             for (int l = nlev; l <= kLevels; ++l) m->cluster_level[l] = total;
             Levels levels;
             std::copy(m->cluster_level, m->cluster_level + kLevels + 1, levels.first);
-            GWN_HIP_TRY(gwn::dmalloc((void**)&m->clusters, sizeof(Cluster) * ((size_t)total + 1)));
             static_assert(sizeof(m->cluster_level) <= sizeof(Cluster), "the level table follows the clusters");
-            GWN_HIP_TRY(gwn::dmalloc((void**)&m->moments, sizeof(float) * kMoments * (size_t)total));
+            // one block for all of it: a hipMalloc and a hipFree each cost as much as a kernel
+            const size_t bytes[5] = {sizeof(CVert) * nent, sizeof(GVertex) * nent, sizeof(int4) * (size_t)m->nchunk,
+                                     sizeof(Cluster) * ((size_t)total + 1), sizeof(float) * kMoments * (size_t)total};
+            void** dst[5] = {(void**)&m->chain, (void**)&m->gchain, (void**)&m->cbox, (void**)&m->clusters, (void**)&m->moments};
+            size_t all = 0;
+            for (size_t b : bytes) all += (b + 255) & ~(size_t)255;
+            char* at = nullptr;
+            GWN_HIP_TRY(gwn::dmalloc((void**)&at, all));
+            for (int k = 0; k < 5; ++k) {
+                *dst[k] = at;
+                at += (bytes[k] + 255) & ~(size_t)255;
+            }
             GWN_HIP_TRY(hipMemsetAsync(m->chain, 0, sizeof(CVert) * nent, st));
             GWN_HIP_TRY(hipMemsetAsync(chunk_width, 0, sizeof(unsigned long long), st));
             const ChainPlan cp{rank, cid, cfirst, poff, cbase, nl, hclusters};

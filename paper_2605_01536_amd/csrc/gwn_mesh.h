@@ -27,7 +27,7 @@ struct gwn_mesh_s {
     float4* trif = nullptr;        // float corners in Morton order (direct sum)
     gwn::BVert* bverts = nullptr;
     int* loop_off = nullptr;
-    gwn::CVert* chain = nullptr;   // the boundary in chunks (gwn_internal.h)
+    gwn::CVert* chain = nullptr;   // the boundary in chunks (gwn_internal.h); the next four in its block
     gwn::GVertex* gchain = nullptr;
     int4* cbox = nullptr;
     gwn::Cluster* clusters = nullptr;

@@ -1,0 +1,62 @@
+"""Boundaries whose build takes another way: tens of thousands of loops of three edges (an unwelded
+soup), loops longer than a cluster's moments are formed for beside short ones and alone, few clusters.
+The counts, and w against the direct sum."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2605_01536_amd import workloads as W
+from tests._util import TOL_FP32, off_surface_mask
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _strip(n, turns=9.0):
+    x = np.linspace(0, 1, n + 1)
+    c = np.stack([np.cos(turns * x) * (1 + x), np.sin(turns * x) * (1 + x), x], 1)
+    i = np.arange(n)
+    F = np.concatenate([np.stack([i, i + 1, n + 1 + i], 1), np.stack([i + 1, n + 2 + i, n + 1 + i], 1)])
+    return W.Soup(V=np.concatenate([c, c * [0.9, 0.9, 1] + [0, 0, 0.05]]).astype(np.float32), F=F.astype(np.int32))
+
+
+def _union(*soups):
+    V, F, o = [], [], 0
+    for s in soups:
+        V.append(s.V)
+        F.append(s.F + o)
+        o += len(s.V)
+    return W.Soup(V=np.concatenate(V), F=np.concatenate(F).astype(np.int32))
+
+
+SOUPS = {   # edges, loops
+    "unwelded": (lambda: W.explode(W.torus_soup(seed=2, n_u=60, n_v=50), seed=1), None),
+    "unwelded, some thousand": (lambda: W.explode(W.ellipsoid_union(np.random.default_rng(1), 3000, 0.1), seed=1), None),
+    "a loop of 60,002": (lambda: _strip(30000), (60002, 1)),
+    "and short ones": (lambda: _union(_strip(30000), W.explode(W.torus_soup(seed=2, n_u=40, n_v=30), seed=3)), None),
+    "a loop of 28,000 and short ones": (lambda: _union(_strip(13999), W.explode(W.torus_soup(seed=2, n_u=40, n_v=30), seed=3)), None),
+    "few loops": (lambda: W.opened_spheres(seed=9, n_surf=6, tris_per_surf=4000), None),
+}
+
+
+@pytest.mark.parametrize("soup", list(SOUPS))
+def test_counts_and_sums(gwn, soup):
+    make, want = SOUPS[soup]
+    s = make()
+    m = gwn.Mesh(torch.from_numpy(s.V).cuda(), torch.from_numpy(s.F).cuda())
+    i = m.info()
+    e = O.boundary(s.F)
+    nb = len(e[0]) if isinstance(e, tuple) else len(e)
+    assert i["nboundary"] == nb
+    if want:
+        assert (i["nboundary"], i["nloops"]) == want
+    if soup.startswith("unwelded"):
+        assert i["nloops"] == s.nf
+    rng = np.random.default_rng(4)
+    lo, hi = s.bbox()
+    P = W.uniform_box(rng, 40000, lo - 0.1, hi + 0.1)
+    w = {n: gwn.query_batch(m, torch.from_numpy(P[:n]).cuda()).cpu().numpy() for n in (100, 3000, 40000)}
+    assert np.array_equal(w[100], w[40000][:100]) and np.array_equal(w[3000], w[40000][:3000])
+    pick = rng.choice(len(P), 250, replace=False)
+    ok = off_surface_mask(s.V, s.F, P[pick])
+    assert np.abs(w[40000][pick] - O.direct(s.V, s.F, P[pick]))[ok].max() <= TOL_FP32
