@@ -981,7 +981,8 @@ __device__ __forceinline__ T point_chunk(const CVert* __restrict__ chunk, int qq
 // exact up to 2^(53 - e), so that the order of the chunks and clusters, which differs
 // between the kernels, does not show.  FP64 sums are plain.  e is 36, more for a point so
 // far away that its terms are small: above the box they go with the height's inverse
-// square, outside with the inverse distance.
+// square, outside with the inverse distance, from the box in x and y or above it.  Below
+// the box they do not fall: each tends to the angle that its edge has in x and y.
 constexpr int kSumUnit = 36;
 
 template <class T>
@@ -996,8 +997,9 @@ __device__ __forceinline__ double point_total(double S, int e) {
 }
 
 __device__ __forceinline__ int point_unit(float px, float py, float pz, bool inbox, const QGrid& g) {
-    const double h = inbox ? ((double)pz - g.lo[2]) * g.scale
-                           : fmax(fmax(fabs((double)px), fabs((double)py)), fabs((double)pz)) * g.scale;
+    double h = ((double)pz - g.lo[2]) * g.scale;
+    if (!inbox)
+        h = fmax(h, fmax(fabs(((double)px - g.lo[0]) * g.scale - 0x1p29), fabs(((double)py - g.lo[1]) * g.scale - 0x1p29)));
     if (!(h > 0x1p32 && h < 1e300)) return kSumUnit;
     const int k = ilogb(h) - 32;
     return kSumUnit + min(inbox ? 2 * k : k, 400);
