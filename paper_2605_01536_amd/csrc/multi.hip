@@ -500,8 +500,17 @@ gwn_status apply(gwn_multi_s* p, Schedule s, hipStream_t st) {
         r = GWN_OK;
         if (all || walk) r = build_perm(p, false, p->citems, all ? p->nitems : p->cend[kChiOrdered], &p->perm, st);
         if (r == GWN_OK && sums && !p->sperm) r = build_perm(p, true, p->items, p->send[kSumOrdered], &p->sperm, st);
-        if (r != GWN_OK) return r;
-        p->sorted = all ? 2 : 1;
+        if (r == GWN_E_OOM && !all) {   // no memory for orders that nobody asked for: none
+            clear_error();
+            (void)hipGetLastError();
+            (void)hipFree(p->perm);
+            (void)hipFree(p->sperm);
+            p->perm = p->sperm = nullptr;
+        } else if (r != GWN_OK) {
+            return r;
+        } else {
+            p->sorted = all ? 2 : 1;
+        }
     }
     r = capture(p, s);
     if (r != GWN_OK) return r;

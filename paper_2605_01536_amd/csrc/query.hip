@@ -289,6 +289,12 @@ gwn_status launch_batch(const gwn_mesh_s* m, const float* qx, const float* qy, c
         if (so == GWN_OK && e == hipSuccess && !closed && !few && want_space_order(m, n, kPrec)) {
             drop();
             so = order(true);
+            if (so == GWN_E_OOM && !ws && !want_xy_order(m, n)) {   // unordered instead: the same bits, later
+                clear_error();
+                (void)hipGetLastError();
+                perm = nullptr;
+                so = GWN_OK;
+            }
         }
         if (so != GWN_OK) {
             if (own_chi) (void)hipFreeAsync(chi, st);
