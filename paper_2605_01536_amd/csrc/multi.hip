@@ -535,6 +535,7 @@ gwn_status time_replay(gwn_multi_s* p, hipStream_t st, double* ms) {
     return GWN_OK;
 }
 
+// plan2: schedules timed before the kernels over clusters are not used
 std::string cache_key(const gwn_multi_s* p) {
     hipDeviceProp_t prop;
     std::string arch = "gpu";
@@ -542,7 +543,7 @@ std::string cache_key(const gwn_multi_s* p) {
     const size_t colon = arch.find(':');
     if (colon != std::string::npos) arch = arch.substr(0, colon);
     char buf[256];
-    std::snprintf(buf, sizeof(buf), "%s|%s|meshes=%d|q=2^%d|pairs=2^%d", arch.c_str(),
+    std::snprintf(buf, sizeof(buf), "%s|%s|plan2|meshes=%d|q=2^%d|pairs=2^%d", arch.c_str(),
                   p->prec == GWN_PREC_FP64 ? "fp64" : "fp32", p->nmesh,
                   (int)std::lround(std::log2(std::max(1.0, (double)p->nq))),
                   (int)std::lround(std::log2(std::max(1.0, p->est_pairs))));

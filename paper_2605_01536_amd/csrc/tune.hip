@@ -60,9 +60,11 @@ std::string arch_of(int device) {
 
 int log2_bucket(double x) { return (int)std::lround(std::log2(std::max(1.0, x))); }
 
+// mesh2: a choice timed on kernels that summed every pair (mesh) is none for these; "no order"
+// from there costs 1.1 M points on 16 k edges 19 ms instead of 4.2
 std::string cache_key(const gwn_mesh_s* m, int prec, int nz) {
     char buf[256];
-    std::snprintf(buf, sizeof(buf), "%s|mesh|F=2^%d|B=2^%d|prec=%d|nz=%d", arch_of(m->device).c_str(),
+    std::snprintf(buf, sizeof(buf), "%s|mesh2|F=2^%d|B=2^%d|prec=%d|nz=%d", arch_of(m->device).c_str(),
                   log2_bucket((double)m->nf), log2_bucket((double)m->nb), prec, nz);
     return buf;
 }
