@@ -82,15 +82,16 @@ __device__ __forceinline__ GVert<T> grad_vert(const GVertex& b, T px, T py, T pz
     return v;
 }
 
-// Sum over chunks c0, c0 + step, ... for one point; FP32 partials are flushed to FP64
-// every 4 chunks.
+// Sum over chunks c0, c0 + step, ..., < nchunk for one point; FP32 partials are flushed to
+// FP64 every 4 chunks.
 template <class T>
-__device__ __forceinline__ void grad_chunks_point(const MeshView& mv, int c0, int step, T px, T py, T pz, T f, double* G) {
+__device__ __forceinline__ void grad_chunks_point(const GVertex* __restrict__ gchain, int nchunk, int c0, int step, T px, T py,
+                                                  T pz, T f, double* G) {
     G[0] = G[1] = G[2] = 0.0;
     T acc[3] = {(T)0, (T)0, (T)0};
     int left = 4;
-    for (int c = c0; c < mv.nchunk; c += step) {
-        const GVertex* __restrict__ v = mv.gchain + (size_t)c * kChunk;
+    for (int c = c0; c < nchunk; c += step) {
+        const GVertex* __restrict__ v = gchain + (size_t)c * kChunk;
         GVertex a = v[0];
         GVert<T> ra = grad_vert<T>(a, px, py, pz, f);
 #pragma unroll
@@ -146,18 +147,74 @@ __device__ __forceinline__ GPoint<T> grad_point(const QGrid& g, float px, float 
     return p;
 }
 
+// A point whose FP32 sum is not finite, again in FP64: next to a vertex the products of a
+// term leave FP32's range (from about 1e-18 of the mesh's size; where floats are that fine,
+// near the origin).  Rare, and out of line so that its registers do not count.
+struct Grad3 {
+    double g[3];
+};
+
+__device__ __attribute__((noinline)) Grad3 grad_again(const GVertex* gchain, int nentry, float scale, float px, float py, float pz) {
+    Grad3 r = {};
+#pragma unroll 1
+    for (const GVertex* v = gchain; v + 1 < gchain + nentry; ++v) {   // (a chunk's last entry has no edge)
+        if (!(v->flags & kChainEdge)) continue;
+        const double ax = v->x - (double)px * scale, ay = v->y - (double)py * scale, az = v->z - (double)pz * scale;
+        const double ex = (double)v[1].x - v->x, ey = (double)v[1].y - v->y, ez = (double)v[1].z - v->z;
+        const double bx = v[1].x - (double)px * scale, by = v[1].y - (double)py * scale, bz = v[1].z - (double)pz * scale;
+        const double dot = fma(ax, bx, fma(ay, by, az * bz));
+        const double lb = Arith<double>::sqrt(fma(bx, bx, fma(by, by, bz * bz)));
+        __builtin_amdgcn_sched_barrier(0);   // (few registers rather than speed)
+        const double la = Arith<double>::sqrt(fma(ax, ax, fma(ay, ay, az * az))), ll = la * lb;
+        const double cx = diff_of_products(ay, ez, az, ey), cy = diff_of_products(az, ex, ax, ez), cz = diff_of_products(ax, ey, ay, ex);
+        __builtin_amdgcn_sched_barrier(0);
+        const bool neg = dot < 0.0;
+        double f = (la + lb) * Arith<double>::rcp(ll) * (neg ? ll - dot : 1.0);
+        f *= Arith<double>::rcp(neg ? fma(cx, cx, fma(cy, cy, cz * cz)) : ll + dot);
+        r.g[0] = fma(cx, f, r.g[0]);
+        r.g[1] = fma(cy, f, r.g[1]);
+        r.g[2] = fma(cz, f, r.g[2]);
+    }
+    for (int c = 0; c < 3; ++c) r.g[c] *= 0.5 * kInv2Pi * scale;
+    return r;
+}
+
 template <class T>
+__device__ __forceinline__ void grad_out(const MeshView& mv, float px, float py, float pz, double g0, double g1, double g2, int axis,
+                                         T* __restrict__ g) {
+    Grad3 r = {{g0, g1, g2}};
+    if (sizeof(T) == 4 && !(fabs(g0) + fabs(g1) + fabs(g2) < 1e300)) r = grad_again(mv.gchain, mv.nchunk * kChunk, mv.g.scalef, px, py, pz);
+    for (int c = 0; c < 3; ++c) g[(c + axis) % 3] = (T)r.g[c];   // frame component c is world component (c + axis) % 3
+}
+
+// AGAIN: with grad_again's call, which costs the loop 5%; without, k_grad_again follows, which
+// costs a launch.
+template <class T, bool AGAIN>
 __global__ __launch_bounds__(256) void k_grad_batch(MeshView mv, const float* __restrict__ qx,
                                                     const float* __restrict__ qy, const float* __restrict__ qz,
                                                     long long qs, long long nq, int axis, T* __restrict__ g) {
     const long long i = blockIdx.x * 256ll + threadIdx.x;
     if (blockIdx.x * 256ll >= nq) return;
     const long long ii = i < nq ? i : nq - 1;
-    const GPoint<T> p = grad_point<T>(mv.g, qx[ii * qs], qy[ii * qs], qz[ii * qs], fabsf(qz[ii * qs]));
+    const float px = qx[ii * qs], py = qy[ii * qs], pz = qz[ii * qs];
+    const GPoint<T> p = grad_point<T>(mv.g, px, py, pz, fabsf(pz));
     double G[3];
-    grad_chunks_point<T>(mv, 0, 1, p.x, p.y, p.z, p.f, G);
-    if (i < nq)   // frame component c is world component (c + axis) % 3
+    grad_chunks_point<T>(mv.gchain, mv.nchunk, 0, 1, p.x, p.y, p.z, p.f, G);
+    if (i >= nq) return;
+    if constexpr (AGAIN) {
+        grad_out<T>(mv, px, py, pz, G[0] * p.out, G[1] * p.out, G[2] * p.out, axis, g + 3 * i);
+    } else {
         for (int c = 0; c < 3; ++c) g[3 * i + (c + axis) % 3] = (T)(G[c] * p.out);
+    }
+}
+
+__global__ __launch_bounds__(256) void k_grad_again(MeshView mv, const float* __restrict__ qx, const float* __restrict__ qy,
+                                                    const float* __restrict__ qz, long long qs, long long nq, int axis,
+                                                    float* __restrict__ g) {
+    const long long i = blockIdx.x * 256ll + threadIdx.x;
+    if (i >= nq) return;
+    const double s = (double)fabsf(g[3 * i]) + (double)fabsf(g[3 * i + 1]) + (double)fabsf(g[3 * i + 2]);
+    if (!(s < 1e300)) grad_out<float>(mv, qx[i * qs], qy[i * qs], qz[i * qs], s, s, s, axis, g + 3 * i);
 }
 
 // Few points against many boundary edges: one workgroup per point, the chunks dealt
@@ -172,19 +229,20 @@ __global__ __launch_bounds__(kSplitThreads) void k_grad_split(MeshView mv, const
     __shared__ double red[kSplitThreads / 64][3];
     const long long i = blockIdx.x;   // one point per workgroup
     if (i >= nq) return;
-    const GPoint<T> p = grad_point<T>(mv.g, qx[i * qs], qy[i * qs], qz[i * qs], fabsf(qz[i * qs]));
+    const float px = qx[i * qs], py = qy[i * qs], pz = qz[i * qs];
+    const GPoint<T> p = grad_point<T>(mv.g, px, py, pz, fabsf(pz));
     double G[3];
-    grad_chunks_point<T>(mv, (int)threadIdx.x, kSplitThreads, p.x, p.y, p.z, p.f, G);
+    grad_chunks_point<T>(mv.gchain, mv.nchunk, (int)threadIdx.x, kSplitThreads, p.x, p.y, p.z, p.f, G);
     for (int c = 0; c < 3; ++c)
         for (int o = 32; o > 0; o >>= 1) G[c] += __shfl_xor(G[c], o);
     if ((threadIdx.x & 63) == 0)
         for (int c = 0; c < 3; ++c) red[threadIdx.x >> 6][c] = G[c];
     __syncthreads();
-    if (threadIdx.x < 3) {
-        const int c = threadIdx.x;
-        double t = 0.0;
-        for (int k = 0; k < kSplitThreads / 64; ++k) t += red[k][c];
-        g[3 * i + (c + axis) % 3] = (T)(t * p.out);
+    if (threadIdx.x == 0) {
+        double t[3] = {0.0, 0.0, 0.0};
+        for (int k = 0; k < kSplitThreads / 64; ++k)
+            for (int c = 0; c < 3; ++c) t[c] += red[k][c];
+        grad_out<T>(mv, px, py, pz, t[0] * p.out, t[1] * p.out, t[2] * p.out, axis, g + 3 * i);
     }
 }
 
@@ -362,8 +420,8 @@ __global__ __launch_bounds__(64 * (SPLIT ? kSplitWaves : kGridWaves)) void k_gra
     for (int r = 0; r < ZB; ++r) {
         const int k = k0 + 64 * r;
         if (k < nz)
-            for (int c = 0; c < 3; ++c)
-                g[3 * (base + (long long)k * ga.st[2]) + (c + axis) % 3] = (T)(S[c * ZB + r] * p.out);
+            grad_out<T>(mv, px, py, pz[r], S[r] * p.out, S[ZB + r] * p.out, S[2 * ZB + r] * p.out, axis,
+                        g + 3 * (base + (long long)k * ga.st[2]));
     }
 }
 
@@ -494,9 +552,13 @@ gwn_status query_gradient(const gwn_mesh_s* m, const float* qx, const float* qy,
                 k_grad_split<float><<<(unsigned)n, kSplitThreads, 0, st>>>(mv, x, y, z, qs, n, m->axis,
                                                                             (float*)g + 3 * o);
         } else if (prec == GWN_PREC_FP64) {
-            k_grad_batch<double><<<blocks, 256, 0, st>>>(mv, x, y, z, qs, n, m->axis, (double*)g + 3 * o);
+            k_grad_batch<double, false><<<blocks, 256, 0, st>>>(mv, x, y, z, qs, n, m->axis, (double*)g + 3 * o);
+        } else if (m->nb < 512) {
+            k_grad_batch<float, true><<<blocks, 256, 0, st>>>(mv, x, y, z, qs, n, m->axis, (float*)g + 3 * o);
         } else {
-            k_grad_batch<float><<<blocks, 256, 0, st>>>(mv, x, y, z, qs, n, m->axis, (float*)g + 3 * o);
+            k_grad_batch<float, false><<<blocks, 256, 0, st>>>(mv, x, y, z, qs, n, m->axis, (float*)g + 3 * o);
+            GWN_HIP_TRY(hipGetLastError());
+            k_grad_again<<<blocks, 256, 0, st>>>(mv, x, y, z, qs, n, m->axis, (float*)g + 3 * o);
         }
         GWN_HIP_TRY(hipGetLastError());
     }
