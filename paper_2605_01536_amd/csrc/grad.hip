@@ -517,7 +517,7 @@ gwn_status launch_grad_grid(const gwn_mesh_s* m, const GridArgs& ga, T* g, hipSt
     if (s == GWN_OK) {
         const FarView far = far_view(p);
         const long long blocks = (ga.nz + 63) / 64;
-        if (split_columns(ga.nx * ga.ny * blocks, m->nchunk, sizeof(T) == 8)) s = launch_grad_columns<T, 1, true>(m, ga, far, g, st);
+        if (split_gradient(ga.nx * ga.ny, blocks, m->nchunk, sizeof(T) == 8)) s = launch_grad_columns<T, 1, true>(m, ga, far, g, st);
         else if (blocks == 1) s = launch_grad_columns<T, 1, false>(m, ga, far, g, st);
         else s = launch_grad_columns<T, ZB, false>(m, ga, far, g, st);
     }

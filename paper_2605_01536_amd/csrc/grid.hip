@@ -377,7 +377,7 @@ gwn_status launch_columns(const gwn_mesh_s* m, GridArgs ga, const FarView& far, 
     if (zb == 0) zb = m->grid_zb[sizeof(T) == 8 ? GWN_PREC_FP64 : GWN_PREC_FP32];
     const long long blocks = (ga.nz + 63) / 64;
     if (zb == 0) {
-        if (split_columns(ga.nx * ga.ny * blocks, m->nchunk, sizeof(T) == 8)) return launch_grid_zb<T, 1, true>(m, ga, far, cc, w, chi_out, st);
+        if (split_columns(ga.nx * ga.ny, blocks, m->nchunk, sizeof(T) == 8)) return launch_grid_zb<T, 1, true>(m, ga, far, cc, w, chi_out, st);
         zb = blocks >= 8 ? 4 : blocks == 2 || blocks >= 4 ? 2 : 1;
         if (m->nchunk < kFewChunks && blocks == 3) zb = 4;   // the fewest waves
     }
