@@ -11,6 +11,7 @@
 // they come, a few queries per wave or a query per lane (see plan_forms).
 #include <algorithm>
 #include <chrono>
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -299,33 +300,63 @@ void release(gwn_multi_s* p) {
 // triangle 231 us, in order 377; on 320 closed triangles 479 in order, 990 without, 1,107 if the
 // queries are not those that the order was made from).
 //
-// The others' queries lie too far apart for an order.  Crossings by a wave per query until
-// there are queries enough to hide a lane's walk (want_chi_point, over all such meshes: they
-// run side by side).  FP32 sums in groups of queries, 0.13 ns sqrt(edges) a query; by a lane per
-// query 1.2 ps an edge and query, where the plan has work for the 0.07 us per edge that a
-// lane takes (us, groups / lanes: 100 x 8,000 queries on 1,026 edges 3,880 / 2,000 in all, 64 x
-// 8,000 on a loop of 2,002 edges 2,630 / 1,400, 256 x 4,000 on 216 edges 2,370 / 1,250).
+// The others' queries lie too far apart for an order.  Crossings by a wave per query, or by a
+// lane where its longer way is hidden by queries enough, over all such meshes, and no longer
+// for it (us, waves / lanes at 64 k, 256 k and 800 k queries on meshes of 320 closed triangles 87 /
+// 81, 296 / 158, 882 / 416; 5,120 closed 121 / 134, 400 / 243, 1,164 / 649; 1,329 of four open
+// spheres 95 / 195, 287 / 300, 829 / 684; 3,434 of soups 102 / 217, 318 / 393, 904 / 944; 35,000
+// 132 / 331, 384 / 611, 1,090 / 1,379).
+//
+// FP32 sums in groups of queries or by a lane per query, the boundaries of least edges first,
+// as many as the expected time asks for.  A lane takes 0.25 us per edge, and with work
+// enough 1.2 ps per edge and query; a group 3.5 us sqrt(edges), and 0.1 ns sqrt(edges) a query.
+// Groups / lanes, us: 16 k queries on boundaries of 61 edges 43 / 29, of 216 73 / 69, of 1,046
+// 175 / 281, of 3,036 285 / 721, of 10,660 459 / 2,654; 256 k 315 / 115, 440 / 164, 1,100 / 552,
+// 1,913 / 1,366, 2,801 / 3,880.  (Queries in order come before a lane's, the smallest boundaries
+// last, and hide little of a lane's way.)
 std::vector<Form> plan_forms(const std::vector<gwn_mesh_s*>& meshes, const std::vector<long long>& off) {
     const int n = (int)meshes.size();
     const bool order = off[n] <= 0x7fffffffll;   // the permutations hold 32-bit indices
     auto queries = [&](int m) { return off[m + 1] - off[m]; };
-    auto lane = [&](int m) { return 1.2e-12 * (double)meshes[m]->nb; };
-    auto group = [&](int m) { return 0.13e-9 * std::sqrt((double)meshes[m]->nb); };
+    auto edges = [&](int m) { return (double)meshes[m]->nb; };
+    auto lane = [&](int m) { return (double)queries(m) * (0.18e-9 + 1.2e-12 * edges(m)); };
+    auto group = [&](int m) { return (double)queries(m) * (0.5e-9 + 0.1e-9 * std::sqrt(edges(m))); };
     std::vector<Form> f(n);
-    long long loose = 0;    // queries that a lane or a wave walks for
-    double total = 3e-5;    // seconds of the plan's sums
+    std::vector<int> loose;    // whose sums a lane or a group may take
+    long long walked = 0;      // queries that a lane or a wave walks for
+    double lanes = 0.0, groups = 0.0;   // seconds
     for (int m = 0; m < n; ++m) {
         const bool dense = order && queries(m) >= kDenseQueries;
         f[m].chi = meshes[m]->nf < 64 ? kChiTogether : dense ? kChiOrdered : kChiLane;
         f[m].sum = dense && meshes[m]->nb >= 32 ? kSumOrdered : kSumLane;
-        if (f[m].chi == kChiLane) loose += queries(m);
-        total += (double)queries(m) * std::min(lane(m), group(m));
+        if (f[m].chi == kChiLane) walked += queries(m);
+        if (f[m].sum == kSumOrdered) continue;
+        if (meshes[m]->wide_edges()) lanes += lane(m);
+        else if (queries(m) > 0) {
+            loose.push_back(m);
+            groups += group(m);
+        }
     }
     for (int m = 0; m < n; ++m) {
-        if (f[m].chi == kChiLane && want_chi_point(meshes[m], loose)) f[m].chi = kChiPoint;
-        if (f[m].sum == kSumLane && !meshes[m]->wide_edges() && !(lane(m) < group(m) && 0.07e-6 * (double)meshes[m]->nb < total))
-            f[m].sum = kSumGroup;
+        const long long most = meshes[m]->nb == 0 ? 1ll << 16 : meshes[m]->nf < 2048 ? 1ll << 18 : LLONG_MAX;
+        if (f[m].chi == kChiLane && walked <= most) f[m].chi = kChiPoint;
     }
+    std::stable_sort(loose.begin(), loose.end(), [&](int a, int b) { return edges(a) < edges(b); });
+    size_t best = 0;
+    double least = INFINITY;
+    for (size_t k = 0; k <= loose.size(); ++k) {   // the first k by lanes
+        if (k > 0) {
+            lanes += lane(loose[k - 1]);
+            groups -= group(loose[k - 1]);
+        }
+        const double way = k > 0 ? 0.25e-6 * edges(loose[k - 1]) : 0.0;
+        const double t = std::max(lanes, way) + (k < loose.size() ? groups + 3.5e-6 * std::sqrt(edges(loose.back())) : 0.0);
+        if (t < least) {
+            least = t;
+            best = k;
+        }
+    }
+    for (size_t k = best; k < loose.size(); ++k) f[loose[k]].sum = kSumGroup;
     return f;
 }
 

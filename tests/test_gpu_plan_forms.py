@@ -94,3 +94,23 @@ def test_forms(gwn, monkeypatch, sizes, prec, order):
             plan.run()
             torch.cuda.synchronize()
             assert torch.equal(plan.w, w) and torch.equal(chi, c)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_many_unordered_queries(gwn, prec):
+    """enough of them that small and closed meshes' crossings are a lane's; the others' a wave's"""
+    pool = [(_mesh(gwn, s), s) for s in (SOUPS[k]() for k in ("closed", "spheres", "ellipsoids"))]
+    rng = np.random.default_rng(7)
+    sizes = [16383] * 17 + [1]
+    meshes, Q, w, c = [], [], [], []
+    for i, n in enumerate(sizes):
+        m, s = pool[i % 3]
+        q = torch.from_numpy(W.uniform_box(rng, n, s.bbox()[0] - 0.1, s.bbox()[1] + 0.1)).cuda()
+        a, b = gwn.query_batch(m, q, prec=prec, want_chi=True)
+        meshes.append(m), Q.append(q), w.append(a), c.append(b)
+    Q = torch.cat(Q)
+    chi = torch.full((len(Q),), -99, dtype=torch.int32, device="cuda")
+    plan = gwn.MultiPlan(meshes, Q, np.concatenate([[0], np.cumsum(sizes)]), chi_out=chi, prec=prec)
+    plan.run()
+    torch.cuda.synchronize()
+    assert torch.equal(plan.w, torch.cat(w)) and torch.equal(chi, torch.cat(c))
