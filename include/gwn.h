@@ -227,7 +227,9 @@ gwn_status gwn_query_batch_noalloc(gwn_mesh m, const float* qx, const float* qy,
  *   w_out, chi_out        : dims[0]*dims[1]*dims[2] results at (i*ny + j)*nz + k.
  * chi equals gwn_query_batch's at the same points bit for bit; w agrees with it
  * to rounding (the boundary sum of a column is formed in a different order),
- * and is itself deterministic for a given grid.
+ * and is itself deterministic for a given grid.  Under stream capture, or where
+ * the device has no memory for the call's workspace, far edges are summed one by
+ * one and columns walk the BVH: chi is the same, w may differ in its last bits.
  */
 gwn_status gwn_query_grid(gwn_mesh m, const double* origin, const double* spacing, const int64_t* dims,
                           int32_t prec, void* w_out, int32_t* chi_out, void* stream);
@@ -251,7 +253,8 @@ gwn_status gwn_query_crossings(gwn_mesh m, const float* qx, const float* qy, con
  * on the axis).  grad_out: device array of 3 * nq values, (dw/dx, dw/dy, dw/dz)
  * per query, float for GWN_PREC_FP32 and double for GWN_PREC_FP64.  Queries and
  * errors as in gwn_query_batch.  Undefined (may be inf/nan) on the boundary
- * curve and where w is undefined.
+ * curve and where w is undefined.  FP32 sums that leave FP32's range beside the
+ * boundary are taken again in FP64.
  */
 gwn_status gwn_query_gradient(gwn_mesh m, const float* qx, const float* qy, const float* qz, int64_t qstride,
                               int64_t nq, int32_t prec, void* grad_out, void* stream);
@@ -286,8 +289,12 @@ gwn_status gwn_query_direct(gwn_mesh m, const float* qx, const float* qy, const 
  * query tile), orders them (largest estimated cost first by default), and
  * captures one HIP graph: reset of the work counters, crossing counts for every
  * query, and persistent kernels whose waves claim items from a counter.  Meshes
- * with at least 16,384 queries take them in orders made at creation from the
- * query values then (4 or 8 bytes per query).
+ * with at least 16,384 queries (crossings: and 64 triangles; FP32 sums: and 32
+ * boundary edges) take them in orders made at creation from the query values then
+ * (4 or 8 bytes per query; without the memory for them, as they come).  Queries
+ * written after creation give the same bits, some 10% later than if no order had
+ * been made.  Which kernels take a mesh's queries follows from its sizes and the
+ * plan's; the bits do not depend on it.
  * With opts->autotune the candidate schedules (tile size, item order, resident
  * waves, and the best of those with each mesh's queries in Morton order) are
  * timed on the real inputs and the fastest is kept; with

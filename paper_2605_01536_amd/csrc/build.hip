@@ -539,8 +539,8 @@ __global__ void k_emit_loops(const int* __restrict__ efrom, const int* __restric
 
 // ---------------------------------------------------------------- boundary chunks
 // The grid kernels decide per chunk of the boundary whether it is near a block of
-// columns, so a chunk should be compact: loops are taken in Morton order of their
-// first vertex's x, y, and a chunk holds kChunk = 8 chained vertices (7 edges).
+// columns, so a chunk should be compact: loops are taken along a Hilbert curve
+// by their first vertex, and a chunk holds kChunk = 8 chained vertices (7 edges).
 // Fewer vertices per chunk cost more repeated end vertices (8/7 of the vertex work,
 // 4/3 at four), more make the chunks wide: on the 64 loops of the 1.05M-triangle
 // opened spheres a chunk of 16 has 2.1 times the edges near a block that single
@@ -561,7 +561,7 @@ __global__ void k_loop_keys(const BVert* __restrict__ bv, const int* __restrict_
     idx[l] = (int)l;
 }
 
-// per loop, in Morton order: whole chunks (piece[i]), halves (piece[nl + i]) and edges
+// per loop, in that order: whole chunks (piece[i]), halves (piece[nl + i]) and edges
 // (piece[2 nl + i]); one scan makes prefix sums of all three, off
 __global__ void k_loop_pieces(const int* __restrict__ loop_off, const int* __restrict__ order, int64_t nl,
                               int* __restrict__ rank, int* __restrict__ piece) {
@@ -840,10 +840,13 @@ __global__ void k_chunk_boxes(int64_t nchunk, CVert* __restrict__ chain, GVertex
 //
 // Truncation at degree P, with A the area of triangle fans spanning the loops, a the
 // radius and t = a / distance:  at most  A / a^2 (P + 1) t^(P+2) / (1 - t)^2 / 2.  The
-// distances from which a degree is taken are those where that bound is kPoleBound; for
-// degree 10 measured errors there are below 1/200 of it (60 triangles of
-// one orientation on a disc: 5.5e-8 at most at 3 radii, bound 1.3e-5).  The bound scales
-// with the area, so a pile of duplicated triangles only moves dmin out.
+// distances from which a degree is taken are those where that bound is kPoleBound.  Errors
+// there, as parts of the bound at degree 10, 6 and 4 (worst of some hundred points around
+// clusters of 27 edges, series and solid angle in FP64 on the host): triangles of one
+// orientation on a disc 1/57, 1/16, 1/8; random ones 1/24, 1/9, 1/6; all at two opposite
+// ends of the cluster 1/12, 1/3, 1/2, the most found: 2.4e-6, 1.7e-6 and 4.4e-7 of solid
+// angle, in w the 4 pi-th part.  The bound scales with the area, so a pile of duplicated
+// triangles only moves dmin out.
 // For degree kPoles, kPolesMid, kPolesLow: so that FP32 results are nearer to FP64 than the sum
 // of all edges with an arctangent each was (relative: 48 ellipsoid soups 8.3e-8 against 1.2e-7,
 // torus of 63 k edges 1.1e-7 against 3.5e-7; largest 5e-7 against 7e-7).  With 1e-4, 1e-5, 3e-6
@@ -1711,7 +1714,7 @@ gwn_status build_mesh(const float* vx, const float* vy, const float* vz, int64_t
             loop_tail = (int)nb;   // function scope: the copy reads it after this block
             GWN_HIP_TRY(hipMemcpyAsync(m->loop_off + m->nloops, &loop_tail, sizeof(int), hipMemcpyHostToDevice, st));
 
-            // the boundary in chunks, loops in Morton order and in clusters
+            // the boundary in chunks, loops along a Hilbert curve and in clusters
             const int64_t nl = m->nloops;
             const int csize = kLeafEdges;
             const int most = (int)std::min<int64_t>(nl, nb / csize + 1);

@@ -9,7 +9,7 @@
 // whatever its z), the node values are interpolated down the levels, and a sample
 // sums only the chunks near its level-0 block itself.  On the 512^3 grid of the
 // 1.05M-triangle soup that leaves 1.5% of the (sample, edge) pairs, and node values for
-// about as many again: 397 -> 26 ms.
+// about as many again: 397 -> 23.5 ms.
 //
 // Interpolation error.  The terms' singularities lie outside the Bernstein ellipse of
 // parameter kappa + sqrt(kappa^2 + 1) in every axis: 5.2 at kappa = 2.5 (FP32), 6.2 at 3

@@ -18,7 +18,8 @@ struct alignas(16) Node {
     int4 lxy;   // left child  xlo, xhi, ylo, yhi
     int4 rxy;   // right child xlo, xhi, ylo, yhi
     int4 z;     // left zlo, left zhi, right zlo, right zhi
-    int4 link;  // left, right, parent, unused
+    int4 link;  // left, right, parent, and the other end of the leaf range that begins or
+                // ends with the node's own index (k_karras writes it, k_refit reads it)
 };
 
 // Quantised triangle corners in Morton order (w unused).
@@ -40,8 +41,8 @@ struct alignas(32) BVert {
 // The boundary again as chunks of kChunk chained vertices (see k_emit_chain in
 // build.hip): entry e of a chunk leads to entry e + 1 where flags & kChainEdge.
 // A long loop is cut every kChunk - 1 edges, loops (or their ends) of at most
-// three edges share a chunk in pairs; loops follow each other in Morton order, so
-// a chunk is small.  Entries past a piece's end repeat a vertex, without an edge.
+// three edges share a chunk in pairs; loops follow each other along a Hilbert
+// curve, so a chunk is small.  Entries past a piece's end repeat a vertex, without an edge.
 constexpr int kChunk = 8;
 constexpr int kChainEdge = 1, kChainValid = 2;
 constexpr int kChainTri = 4;    // first vertex of a loop of three edges
