@@ -139,6 +139,11 @@ bool want_parts(const gwn_mesh_s* m, int64_t n, int prec);
 
 constexpr int64_t kSharedPoints64 = 96 << 10;
 
+// Up to this many FP32 points on meshes of few, wide edges (which have no groups of points) 16
+// waves share 64 points: us by 4 / 16 waves on 279 edges 500 points 36 / 31, 8 k 43 / 33 (calls one
+// after another, of which the host takes 30), 16 k 194 / 184, 32 k 204 / 199, 64 k 226 / 234.
+constexpr int64_t kManyParts = 16384;
+
 // Crossing counts of few points take a wave per point: a lane's walk is a chain of loads,
 // 65 us for 1,000 points on 1,280 triangles and 238 us on 85 k (9 and 30 with a wave each),
 // until there are points enough to hide it: 33 k points on 85 k triangles 0.68 ms with the

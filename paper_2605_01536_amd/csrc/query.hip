@@ -101,13 +101,13 @@ __global__ __launch_bounds__(kChiBlock) void k_chi_line(MeshView mv, const float
 // sums added in LDS; in FP64 in turn with a chunk each, whose sums the first wave adds in the
 // chunks' order, so that the bits are those of a lane alone.
 template <class T, int PARTS>
-__global__ __launch_bounds__(256) void k_bdry_batch(MeshView mv, const float* __restrict__ qx, const float* __restrict__ qy,
+__global__ __launch_bounds__(PARTS > 4 ? 64 * PARTS : 256) void k_bdry_batch(MeshView mv, const float* __restrict__ qx, const float* __restrict__ qy,
                                                     const float* __restrict__ qz, long long qs, long long nq,
                                                     const int* __restrict__ perm, const int* __restrict__ chi,
                                                     T* __restrict__ w) {
-    static_assert(PARTS == 1 || PARTS == 4, "a workgroup of four waves");
+    static_assert(PARTS == 1 || PARTS == 4 || (PARTS == 16 && sizeof(T) == 4), "256 threads, FP32 also 1,024");
     const int wave = PARTS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const long long j = (long long)blockIdx.x * (256 / PARTS) + (PARTS == 1 ? threadIdx.x : threadIdx.x & 63);
+    const long long j = (long long)blockIdx.x * (PARTS == 1 ? 256 : 64) + (PARTS == 1 ? threadIdx.x : threadIdx.x & 63);
     const long long jj = j < nq ? j : nq - 1;
     // with a traversal order, lane j takes point perm[j]: the lanes of a wave are
     // neighbours, with the same clusters near and far
@@ -303,7 +303,10 @@ gwn_status launch_batch(const gwn_mesh_s* m, const float* qx, const float* qy, c
         if (e == hipSuccess && !closed) {
             if (!few) {
                 const bool parts = want_parts(m, n, kPrec);
-                if (parts)
+                const bool many = sizeof(T) == 4 && parts && m->wide_edges() && n <= kManyParts;
+                if constexpr (sizeof(T) == 4)
+                    if (many) k_bdry_batch<T, 16><<<(unsigned)((n + 63) / 64), 1024, 0, st>>>(mv, x, y, z, qs, n, perm, chi + o, w + o);
+                if (parts && !many)
                     k_bdry_batch<T, 4><<<(unsigned)((n + 63) / 64), 256, 0, st>>>(mv, x, y, z, qs, n, perm, chi + o, w + o);
                 if (!parts)
                     k_bdry_batch<T, 1><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(mv, x, y, z, qs, n, perm, chi + o, w + o);

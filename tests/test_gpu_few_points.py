@@ -44,3 +44,23 @@ def test_bits_of_a_lane_per_point(gwn, monkeypatch, soup):
     monkeypatch.delenv("GWN_SPLIT_BOUNDARY")
     for n in (1, 2, 255, 256, 257, 600):
         assert torch.equal(gwn.query_batch(m, Q[:n]), w[:n]), n
+
+
+# few, wide edges: up to 16,384 points 16 waves share 64, then four, from 2^18 on none
+@pytest.mark.parametrize("soup", ["spheres", "ellipsoids", "more ellipsoids"])
+def test_bits_of_shared_lanes_on_few_edges(gwn, soup):
+    s = {"spheres": lambda: W.opened_spheres(seed=1, n_surf=4, tris_per_surf=400),
+         "ellipsoids": lambda: W.ellipsoid_union(np.random.default_rng(1), 1000, 0.1),
+         "more ellipsoids": lambda: W.ellipsoid_union(np.random.default_rng(4), 1300, 0.1)}[soup]()
+    m = gwn.Mesh(torch.from_numpy(s.V).cuda(), torch.from_numpy(s.F).cuda())
+    rng = np.random.default_rng(3)
+    lo, hi = s.bbox()
+    P = rng.uniform(lo - 0.05, hi + 0.05, (2 ** 18 + 1, 3)).astype(np.float32)
+    P[2::37] *= 60
+    P[3::41, 2] = 300 * rng.choice([-1, 1], len(P[3::41]))
+    Q = torch.from_numpy(P).cuda()
+    w = gwn.query_batch(m, Q)
+    for n in (1, 63, 64, 65, 1063, 16384, 16385):
+        assert torch.equal(gwn.query_batch(m, Q[:n]), w[:n]), n
+        if n <= 1063:
+            assert torch.equal(gwn.query_batch_noalloc(m, Q[:n]), w[:n]), n
