@@ -132,9 +132,9 @@ constexpr int64_t kFewPoints = 256, kDensePoints = 48 << 10, kSinglePoints = 614
 // A point per lane, with four waves to share 64 points' sums.  FP64, ms shared / not (and at
 // first, edge by edge): 63 k edges 16 k points 4.3 / 15.3 (14.5), 66 k 11.7 / 18.9 (20.7), 131 k
 // 17.3 / 19.5; 2,002 edges in a loop 66 k 0.45 / 0.63 (0.61), 131 k 0.65 / 0.64; 61 edges 66 k
-// 0.159 / 0.173 (0.167), 140 k 0.178 / 0.189 (0.184).  FP32, where few chunks to share are not
-// worth the waves' own work: a loop of 2,002 edges 131 k 0.28 / 0.36 (0.32), 216 edges 131 k
-// 0.158 / 0.175, 530 k 0.51 / 0.51, 61 edges 530 k 0.408 / 0.406.
+// 0.159 / 0.173 (0.167), 140 k 0.178 / 0.189 (0.184).  FP32: a loop of 2,002 edges
+// 131 k 0.28 / 0.36 (0.32), 216 edges 131 k 0.158 / 0.175, 600 k with the crossings 0.57 / 0.59, 381
+// edges 420 k 0.74 / 0.80, 1 M 1.55 / 1.62, 61 edges 530 k 0.408 / 0.406.
 bool want_parts(const gwn_mesh_s* m, int64_t n, int prec);
 
 constexpr int64_t kSharedPoints64 = 96 << 10;

@@ -380,7 +380,7 @@ bool want_split(const gwn_mesh_s* m, int64_t n, int prec) {
 
 bool want_parts(const gwn_mesh_s* m, int64_t n, int prec) {
     if (prec == GWN_PREC_FP64) return n <= (m->nchunk < 64 ? 4 * kSharedPoints64 : kSharedPoints64) && m->nchunk >= 8;
-    return n <= (m->nclusters < kFewClusters ? 1 << 18 : kSharedPoints) && m->nchunk >= 8;
+    return n <= kSharedPoints && m->nchunk >= 8;
 }
 
 int64_t max_launch_queries() {

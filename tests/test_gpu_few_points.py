@@ -46,7 +46,7 @@ def test_bits_of_a_lane_per_point(gwn, monkeypatch, soup):
         assert torch.equal(gwn.query_batch(m, Q[:n]), w[:n]), n
 
 
-# few, wide edges: up to 16,384 points 16 waves share 64, then four, from 2^18 on none
+# few, wide edges: up to 16,384 points 16 waves share 64, then four, above 2^20 none
 @pytest.mark.parametrize("soup", ["spheres", "ellipsoids", "more ellipsoids"])
 def test_bits_of_shared_lanes_on_few_edges(gwn, soup):
     s = {"spheres": lambda: W.opened_spheres(seed=1, n_surf=4, tris_per_surf=400),
@@ -55,7 +55,7 @@ def test_bits_of_shared_lanes_on_few_edges(gwn, soup):
     m = gwn.Mesh(torch.from_numpy(s.V).cuda(), torch.from_numpy(s.F).cuda())
     rng = np.random.default_rng(3)
     lo, hi = s.bbox()
-    P = rng.uniform(lo - 0.05, hi + 0.05, (2 ** 18 + 1, 3)).astype(np.float32)
+    P = rng.uniform(lo - 0.05, hi + 0.05, (2 ** 20 + 1, 3)).astype(np.float32)
     P[2::37] *= 60
     P[3::41, 2] = 300 * rng.choice([-1, 1], len(P[3::41]))
     Q = torch.from_numpy(P).cuda()
