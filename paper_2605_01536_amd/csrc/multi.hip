@@ -11,7 +11,6 @@
 // they come, a few queries per wave or a query per lane (see plan_forms).
 #include <algorithm>
 #include <chrono>
-#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -300,9 +299,9 @@ void release(gwn_multi_s* p) {
 // triangle 231 us, in order 377; on 320 closed triangles 479 in order, 990 without, 1,107 if the
 // queries are not those that the order was made from).
 //
-// The others' queries lie too far apart for an order.  Crossings by a wave per query, or by a
-// lane where its longer way is hidden by queries enough, over all such meshes, and no longer
-// for it (us, waves / lanes at 64 k, 256 k and 800 k queries on meshes of 320 closed triangles 87 /
+// The others' queries lie too far apart for an order.  Crossings by a wave per query, or, on
+// closed meshes and on few triangles, by a lane where queries enough, over all such meshes, hide
+// its longer way (us, waves / lanes at 64 k, 256 k and 800 k queries on meshes of 320 closed triangles 87 /
 // 81, 296 / 158, 882 / 416; 5,120 closed 121 / 134, 400 / 243, 1,164 / 649; 1,329 of four open
 // spheres 95 / 195, 287 / 300, 829 / 684; 3,434 of soups 102 / 217, 318 / 393, 904 / 944; 35,000
 // 132 / 331, 384 / 611, 1,090 / 1,379).
@@ -321,15 +320,16 @@ std::vector<Form> plan_forms(const std::vector<gwn_mesh_s*>& meshes, const std::
     auto edges = [&](int m) { return (double)meshes[m]->nb; };
     auto lane = [&](int m) { return (double)queries(m) * (0.18e-9 + 1.2e-12 * edges(m)); };
     auto group = [&](int m) { return (double)queries(m) * (0.5e-9 + 0.1e-9 * std::sqrt(edges(m))); };
+    auto walks = [&](int m) { return meshes[m]->nb == 0 ? 4 : meshes[m]->nf < 2048 ? 1 : 0; };
     std::vector<Form> f(n);
     std::vector<int> loose;    // whose sums a lane or a group may take
-    long long walked = 0;      // queries that a lane or a wave walks for
+    long long walked = 0;      // queries that a lane may walk for, closed meshes' four times
     double lanes = 0.0, groups = 0.0;   // seconds
     for (int m = 0; m < n; ++m) {
         const bool dense = order && queries(m) >= kDenseQueries;
         f[m].chi = meshes[m]->nf < 64 ? kChiTogether : dense ? kChiOrdered : kChiLane;
         f[m].sum = dense && meshes[m]->nb >= 32 ? kSumOrdered : kSumLane;
-        if (f[m].chi == kChiLane) walked += queries(m);
+        if (f[m].chi == kChiLane) walked += walks(m) * queries(m);
         if (f[m].sum == kSumOrdered) continue;
         if (meshes[m]->wide_edges()) lanes += lane(m);
         else if (queries(m) > 0) {
@@ -337,10 +337,8 @@ std::vector<Form> plan_forms(const std::vector<gwn_mesh_s*>& meshes, const std::
             groups += group(m);
         }
     }
-    for (int m = 0; m < n; ++m) {
-        const long long most = meshes[m]->nb == 0 ? 1ll << 16 : meshes[m]->nf < 2048 ? 1ll << 18 : LLONG_MAX;
-        if (f[m].chi == kChiLane && walked <= most) f[m].chi = kChiPoint;
-    }
+    for (int m = 0; m < n; ++m)
+        if (f[m].chi == kChiLane && (walked <= 1 << 18 || walks(m) == 0)) f[m].chi = kChiPoint;
     std::stable_sort(loose.begin(), loose.end(), [&](int a, int b) { return edges(a) < edges(b); });
     size_t best = 0;
     double least = INFINITY;
