@@ -48,3 +48,22 @@ def test_points_and_grids(gwn, prec, tol, axis):
         ref_g = _exact(P.astype(np.float64))
         g = gwn.query_grid_gradient(m, *grid, prec=prec).double().cpu().numpy().reshape(-1, 3)
         assert (np.abs(g - ref_g).max(1) <= tol * np.abs(ref_g).max(1)).all(), s
+
+
+# grids of columns enough for a wave each, one sample or two to a lane: on boundary enough the
+# samples are taken again by a kernel of their own (also cut into launches)
+@pytest.mark.parametrize("dims", [(64, 65, 3), (45, 31, 130)])
+@pytest.mark.parametrize("axis", ["z", "x", "y"])
+@pytest.mark.parametrize("launch", [None, "65536"])
+def test_large_grids(gwn, monkeypatch, dims, axis, launch):
+    if launch:
+        monkeypatch.setenv("GWN_MAX_LAUNCH_QUERIES", launch)
+    far = W.torus_soup(seed=3, n_u=41, n_v=31)
+    U, G = np.concatenate([V, far.V + np.float32(30)]), np.concatenate([F, far.F + len(V)]).astype(np.int32)
+    m = gwn.Mesh(torch.from_numpy(U).cuda(), torch.from_numpy(G).cuda(), axis=axis)
+    assert m.info()["nboundary"] >= 512
+    for s in (1e-6, 1e-21):
+        grid = ((0.0, 0.0, 0.0), (-s, -1.3 * s, -0.8 * s), dims)
+        ref = _exact(W.grid_points(W.GridSpec(*grid)).astype(np.float64))
+        g = gwn.query_grid_gradient(m, *grid, prec="fp32").double().cpu().numpy().reshape(-1, 3)
+        assert (np.abs(g - ref).max(1) <= 1e-6 * np.abs(ref).max(1) + 1e-3).all(), s
