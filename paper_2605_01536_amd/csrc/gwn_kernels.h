@@ -1410,20 +1410,22 @@ constexpr long long kFewWaves = 4096;
 constexpr int kSplitWaves = 8;
 
 // Whether columns of `blocks` blocks of 64 samples are few: up to four waves per SIMD, FP64's w,
-// whose registers leave room for fewer, up to two and a half (three where a lane would take two
-// samples else), and fewer where a wave's share of the chunks does not pay for what every wave of
-// the column repeats: for w the crossings and, FP64, much of the work per vertex.  us split /
-// not: w, 10 chunks 1,024 waves 58 / 33 (FP64 95 / 38), 36 chunks 2,115 waves 60 / 65 (155 /
+// whose registers leave room for fewer, up to two and a half, from three (which would be four) up
+// to three and a half (from two up to three where a lane would take two samples else), and fewer
+// where a wave's share of the chunks does not pay for what every wave of the column repeats:
+// for w the crossings and, FP64, much of the work per vertex.  us split / not: w, 10 chunks 1,024 waves 58 / 33 (FP64 95 / 38), 36 chunks 2,115 waves 60 / 65 (155 /
 // 113), 2,880 in pairs 69 / 84, 70 chunks 2,970 waves 71 / 79 (211 / 156), 150 chunks FP64 2,115
 // waves 346 / 364, 2,970 467 / 411, 2,880 in pairs 450 / 514, 2,500 chunks 2,544 waves 4,538 /
-// 4,762, 2,880 in pairs 5,313 / 6,034, 3,600 6,686 / 6,314; gradient, 10 chunks 576 waves 13 /
+// 4,762, 3,000 5,345 / 4,821, 3,127 5,760 / 6,420, 3,720 6,658 / 6,418, 2,880 in pairs 5,313 /
+// 6,034; gradient, 10 chunks 576 waves 13 /
 // 14 (27 / 17), 1,024 22 / 15 (30 / 17), 36 chunks 2,115 waves 40 / 52 (88 / 100), 2,970 51 / 54
 // (114 / 102), 2,880 in pairs 52 / 74 (113 / 128), 70 chunks 4,032 waves 100 / 104 (214 / 217),
 // 2,500 chunks FP64 4,032 7,990 / 8,801.
 inline bool split_columns(long long columns, long long blocks, int64_t nchunk, bool f64) {
     const bool pairs = blocks == 2 || blocks > 3;
-    const long long most = !f64 ? kFewWaves : pairs ? 3200 : 2500, pays = (f64 ? 24 : 64) * nchunk;
-    return columns * blocks < std::min(most, (f64 ? pairs : blocks > 1) ? pays + pays / 2 : pays);
+    const long long waves = columns * blocks, pays = (f64 ? 24 : 64) * nchunk;
+    const long long most = !f64 ? kFewWaves : pairs ? 3200 : waves <= 3072 ? 2540 : nchunk < 2048 ? 3300 : 3520;
+    return waves < std::min(most, (f64 ? pairs : blocks > 1) ? pays + pays / 2 : pays);
 }
 inline bool split_gradient(long long columns, long long blocks, int64_t nchunk, bool f64) {
     const long long pays = f64 ? 80 * (nchunk - 6) : 100 * (nchunk - 4);
